@@ -1234,10 +1234,21 @@ __device__ __forceinline__ void stage_tables_direct(const SearchArgs &a, double 
     __builtin_amdgcn_s_waitcnt(0);               // the loads count as vector memory operations: all of them have landed
 }
 
-template <int MASK, bool FAST, bool LIMIT = false, bool REGROUP = false, bool LATCAP = false>
+// SUM: how a candidate's energy is added up (ModelConst::energy_sum).  SUM_ORDERED forms it term by term,
+// 6 operations per candidate with the minimum; SUM_FUSED forms the first sum with one fused multiply-add whose
+// product is exact, i.e. with the bits of the two separate roundings; SUM_REGROUPED adds a row and a tiling part.
+// The energy key alone leaves the two addends that all candidates of a (tiling, r) share, the register-file
+// and MAC parts, to the nine minima: adding a constant and rounding keeps the order, so the minimum of the
+// finished sums is the finished sum of the minimum, bit for bit (OUTSIDE).  Per candidate that is addition,
+// multiplication, addition, minimum (4), with SUM_FUSED 3, with SUM_REGROUPED 2.  The kernel is bound by
+// VALU issue, so its time follows these counts: energy key of a 2048 x 768 x 3072 x 768 chain (3.6e9
+// candidates) 0.700 ms with six operations, 0.524 with four, 0.430 with three, 0.335 with two.
+template <int MASK, bool FAST, bool LIMIT = false, int SUM = SUM_ORDERED, bool LATCAP = false>
 __global__ __launch_bounds__(DENSE_THREADS, 4) void k_search_dense(SearchArgs a)
 {
     static_assert(!LATCAP || (MASK == 1 && !LIMIT), "the latency cap goes with the energy key alone");
+    constexpr bool REGROUP = SUM == SUM_REGROUPED;
+    constexpr bool OUTSIDE = !REGROUP && MASK == 1 && !LIMIT;
     __shared__ double tab[DENSE_PAIRS * DENSE_PAIR_F64];
     __shared__ Key wave_best[N_OBJ][DENSE_WAVES];
     __shared__ uint32_t is_last;
@@ -1384,9 +1395,12 @@ __global__ __launch_bounds__(DENSE_THREADS, 4) void k_search_dense(SearchArgs a)
                     en = e_part + gb[c9];
                 } else {
                     double gb_words = dram_words + gb[c9];
-                    en = e_part + a.mc.e_gb * gb_words;
-                    en = en + e_rf_part;
-                    en = en + e_mac_part;
+                    if constexpr (SUM == SUM_FUSED) en = __builtin_fma(a.mc.e_gb, gb_words, e_part);
+                    else en = e_part + a.mc.e_gb * gb_words;
+                    if constexpr (!OUTSIDE) {
+                        en = en + e_rf_part;
+                        en = en + e_mac_part;
+                    }
                     if constexpr (LATCAP) en = fmax(en, too_slow[c9]);
                 }
                 double lat = fmax(l_dram, latc[c9]);
@@ -1469,6 +1483,11 @@ __global__ __launch_bounds__(DENSE_THREADS, 4) void k_search_dense(SearchArgs a)
                     cost_row((x_bs + c_bs) + y_ret, (y_bs + c_bs) + x_ret, (x_da + y_da) + c_da, q * 25u + ab);
                 }
             }
+        }
+
+        if constexpr (OUTSIDE) {
+#pragma unroll
+            for (int c9 = 0; c9 < 9; ++c9) bestE[c9] = (bestE[c9] + e_rf_part) + e_mac_part;
         }
 
         // index row (Sec. VI-A numbering) of the task's row number `code`, combination 0

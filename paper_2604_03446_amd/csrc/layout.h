@@ -90,9 +90,15 @@ struct ModelConst {
     // product and partial sum of the energy is then an exact integer, the order of the additions
     // cannot change a bit of the result, and the search adds one row part and one tiling part.
     uint32_t regroup;
+    // e_gb is a whole number and e_gb * (buffer words of any candidate) stays below 2^53: that product is
+    // exact, and e_gb * words + x rounds once whether it is formed by one fused operation or by two
+    uint32_t gb_product_exact;
     uint32_t pe_rows, pe_cols, g_words, c_softmax;
     uint32_t T, tpad;
 };
+
+// order of the energy additions in k_search_dense
+enum { SUM_ORDERED = 0, SUM_REGROUPED = 1, SUM_FUSED = 2 };
 
 constexpr int N_OBJ = 4;         // energy, latency, latency-then-energy, energy-delay product
 

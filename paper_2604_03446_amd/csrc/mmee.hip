@@ -236,6 +236,8 @@ int make_plan(const mmee_chain *w, const mmee_hw *hw, Plan &p)
                                        (2.0L + (long double)w->c_softmax) * hw->e_mac);
         p.whole_energies = whole(hw->e_dram) && whole(hw->e_gb) && whole(hw->e_rf) && whole(hw->e_mac);
         p.can_regroup = p.whole_energies && worst < 9007199254740992.0L;
+        // buffer words of a candidate: DRAM words + buffer<->RF words <= 14 P
+        mc.gb_product_exact = whole(hw->e_gb) && 14.0L * P * hw->e_gb < 9007199254740992.0L ? 1u : 0u;
     }
     mc.dram_bw = hw->dram_bw; mc.gb_bw = hw->gb_bw;
     // with a power-of-two bandwidth and array count, (B*H/n) * (words*word/bw) is the B*H-scaled
@@ -463,11 +465,15 @@ int ensure_slots(size_t n)
 // order, and any other candidate computes to more than 2^52 in either order.  An optimum below
 // 2^52 pJ therefore is the optimum of the term-by-term sum too, ties included; otherwise the
 // caller repeats the pass with MMEE_SEARCH_ORDERED_SUM.
+constexpr int MASK_ENERGY = 1 << MMEE_OBJ_ENERGY;
 constexpr double REGROUP_PROOF_LIMIT = 4503599627370496.0;   // 2^52
 ModelConst pass_constants(const Plan &p, uint32_t flags, int mask = 8, bool *unproven = nullptr)
 {
     ModelConst mc = p.mc;
-    const bool allowed = p.exact_k && !(flags & MMEE_SEARCH_ORDERED_SUM);
+    // (the regrouped kernels with a latency in the key take the DRAM time as one exact product; the energy
+    // alone has no DRAM time: 2048 x 768 x 3072 x 768 chain, 60 B/cycle, exhaustive: 0.706 ms summed in
+    // order, 0.335 ms regrouped)
+    const bool allowed = (p.exact_k || mask == MASK_ENERGY) && !(flags & MMEE_SEARCH_ORDERED_SUM);
     const bool on_trust = allowed && !p.can_regroup && p.whole_energies && !(mask & 8) && unproven;
     mc.regroup = ((allowed && p.can_regroup) || on_trust) ? 1u : 0u;
     if (unproven) *unproven = on_trust;
@@ -527,24 +533,30 @@ void launch_search_limited(bool exact_k, dim3 grid, const SearchArgs &a)
 template <int MASK>
 void launch_dense_mask(bool exact_k, dim3 grid, const SearchArgs &a)
 {
-    if (a.mc.regroup) hipLaunchKernelGGL((k_search_dense<MASK, true, false, true>), grid, dim3(DENSE_THREADS), 0, S.stream, a);
-    else if (exact_k) hipLaunchKernelGGL((k_search_dense<MASK, true>), grid, dim3(DENSE_THREADS), 0, S.stream, a);
-    else hipLaunchKernelGGL((k_search_dense<MASK, false>), grid, dim3(DENSE_THREADS), 0, S.stream, a);
+    // the energy alone does not look at the DRAM time: exact_k makes no difference to it
+    constexpr bool NO_DRAM_TIME = MASK == MASK_ENERGY;
+    if (a.mc.regroup) hipLaunchKernelGGL((k_search_dense<MASK, true, false, SUM_REGROUPED>), grid, dim3(DENSE_THREADS), 0, S.stream, a);
+    else if (NO_DRAM_TIME && a.mc.gb_product_exact)
+        hipLaunchKernelGGL((k_search_dense<MASK, true, false, NO_DRAM_TIME ? SUM_FUSED : SUM_ORDERED>), grid, dim3(DENSE_THREADS), 0, S.stream, a);
+    else if (NO_DRAM_TIME || exact_k) hipLaunchKernelGGL((k_search_dense<MASK, true>), grid, dim3(DENSE_THREADS), 0, S.stream, a);
+    else hipLaunchKernelGGL((k_search_dense<MASK, NO_DRAM_TIME>), grid, dim3(DENSE_THREADS), 0, S.stream, a);
 }
 
 // second pass of the (latency, energy) key: lowest energy among the candidates within a.lat_cap
 void launch_dense_latcap(bool exact_k, dim3 grid, const SearchArgs &a)
 {
-    if (a.mc.regroup) hipLaunchKernelGGL((k_search_dense<1, true, false, true, true>), grid, dim3(DENSE_THREADS), 0, S.stream, a);
-    else if (exact_k) hipLaunchKernelGGL((k_search_dense<1, true, false, false, true>), grid, dim3(DENSE_THREADS), 0, S.stream, a);
-    else hipLaunchKernelGGL((k_search_dense<1, false, false, false, true>), grid, dim3(DENSE_THREADS), 0, S.stream, a);
+    if (a.mc.regroup) hipLaunchKernelGGL((k_search_dense<1, true, false, SUM_REGROUPED, true>), grid, dim3(DENSE_THREADS), 0, S.stream, a);
+    else if (a.mc.gb_product_exact && exact_k) hipLaunchKernelGGL((k_search_dense<1, true, false, SUM_FUSED, true>), grid, dim3(DENSE_THREADS), 0, S.stream, a);
+    else if (a.mc.gb_product_exact) hipLaunchKernelGGL((k_search_dense<1, false, false, SUM_FUSED, true>), grid, dim3(DENSE_THREADS), 0, S.stream, a);
+    else if (exact_k) hipLaunchKernelGGL((k_search_dense<1, true, false, SUM_ORDERED, true>), grid, dim3(DENSE_THREADS), 0, S.stream, a);
+    else hipLaunchKernelGGL((k_search_dense<1, false, false, SUM_ORDERED, true>), grid, dim3(DENSE_THREADS), 0, S.stream, a);
 }
 
 // first pass of one step of the Pareto walk over the full row set: lowest latency among the candidates
 // with energy below a.e_limit (the second pass is launch_dense_latcap)
 void launch_dense_limited(bool exact_k, dim3 grid, const SearchArgs &a)
 {
-    if (a.mc.regroup) hipLaunchKernelGGL((k_search_dense<2, true, true, true>), grid, dim3(DENSE_THREADS), 0, S.stream, a);
+    if (a.mc.regroup) hipLaunchKernelGGL((k_search_dense<2, true, true, SUM_REGROUPED>), grid, dim3(DENSE_THREADS), 0, S.stream, a);
     else if (exact_k) hipLaunchKernelGGL((k_search_dense<2, true, true>), grid, dim3(DENSE_THREADS), 0, S.stream, a);
     else hipLaunchKernelGGL((k_search_dense<2, false, true>), grid, dim3(DENSE_THREADS), 0, S.stream, a);
 }
