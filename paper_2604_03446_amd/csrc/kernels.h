@@ -31,6 +31,22 @@ __device__ __forceinline__ bool key_less(const Key &a, const Key &b)
     return a.idx < b.idx;
 }
 
+// c_lat * fl(fl(words * word) / dram_bw) without a division: with y = fl(1 / b), two Newton steps on the
+// quotient, each on the remainder that a fused multiply-add leaves, end on the correctly rounded one
+// (Markstein, "Computation of elementary functions on the IBM RISC System/6000 processor", 1990: a quotient
+// within one unit in the last place, corrected once by the remainder times the rounded reciprocal, is the
+// rounded quotient; the first step brings it there).  b is the bandwidth scaled into [1, 2) and c_lat by the
+// inverse power of two, so no intermediate leaves the normal range.  Eight operations where the compiler's
+// division alone takes about fourteen, next to the two divisions this replaces.
+__device__ __forceinline__ double dram_time_general(const ModelConst &mc, double words)
+{
+    const double x = words * mc.word;
+    double q = x * mc.dram_y;
+    q = __builtin_fma(__builtin_fma(-mc.dram_b, q, x), mc.dram_y, q);
+    q = __builtin_fma(__builtin_fma(-mc.dram_b, q, x), mc.dram_y, q);
+    return mc.dram_c * q;
+}
+
 // ---- cross-lane moves for the wave-level argmin (DPP inside a row of 16 lanes,
 // ds_swizzle across rows of a half wave, ds_bpermute across the halves) --------
 template <int STEP>
@@ -1203,9 +1219,13 @@ __global__ __launch_bounds__(SEARCH_THREADS, (popcount4(MASK) >= 3 || (MASK & 4 
 //
 // A block stages one chunk of TC tilings (stage_tables_direct below) and its waves take neighbouring tasks.
 // Persistent blocks, global work counter and grid finish as in k_search; the last chunks are handed
-// out in fifths of tasks (one p_D each) to even out the end.  The host sends single-key passes
-// here: the 18 per-tiling constants, the (D, E) parts and one key's nine minima fit 128 registers
-// (four waves per SIMD), two keys' minima do not.
+// out in fifths of tasks (one p_D each) to even out the end.
+//
+// Registers decide the shape of the row loop.  One key: the 18 per-tiling constants, the (D, E) parts of all
+// five p_D values and nine minima fit 128 registers (four waves per SIMD).  Two keys together hold
+// 18 minima: there one p_D value at a time is kept, and the (A, B) parts are read once per row instead of
+// once per five rows -- three LDS reads (12 cycles of the CU's LDS pipe) against the row's 46 operations
+// (184 cycles of each SIMD).
 constexpr int DENSE_THREADS = 512;           // eight waves, two blocks per CU
 constexpr int DENSE_BLOCKS_PER_CU = 2;
 constexpr int DENSE_WAVES = DENSE_THREADS / 64;
@@ -1222,12 +1242,14 @@ __device__ __forceinline__ uint32_t dense_at(uint32_t e) { return e * (DENSE_PAI
 // LDS write instructions, all of a wave's loads in flight at once.  Columns beyond the last tiling exist
 // in the global table (it is padded to whole chunks and repeats its last tiling there); so does the
 // entry after the last one of an odd count.
-template <int WAVES>
+// RAW: the DRAM terms without the B*H factor in the place of the scaled ones.
+template <int WAVES, bool RAW>
 __device__ __forceinline__ void stage_tables_direct(const SearchArgs &a, double *tab, uint32_t t0, uint32_t wave, uint32_t lane)
 {
     static_assert(NENT + 1 <= NENT_ALL, "the pair of the last entry reads one entry beyond it");
     for (uint32_t pair = wave; pair < (uint32_t)DENSE_PAIRS; pair += WAVES) {
-        const uint32_t e = 2 * pair + (lane >> 5);
+        const uint32_t place = 2 * pair + (lane >> 5);
+        const uint32_t e = RAW && place >= (uint32_t)ENT_DA_AB && place < (uint32_t)NENT ? place + ENT_RAW_DA : place;
         const double *src = a.btab + (uint64_t)e * a.mc.tpad + t0 + 2 * (lane & 31);
         __builtin_amdgcn_global_load_lds(src, tab + pair * DENSE_PAIR_F64, 16, 0, 0);
     }
@@ -1243,12 +1265,18 @@ __device__ __forceinline__ void stage_tables_direct(const SearchArgs &a, double 
 // multiplication, addition, minimum (4), with SUM_FUSED 3, with SUM_REGROUPED 2.  The kernel is bound by
 // VALU issue, so its time follows these counts: energy key of a 2048 x 768 x 3072 x 768 chain (3.6e9
 // candidates) 0.700 ms with six operations, 0.524 with four, 0.430 with three, 0.335 with two.
+//
+// FAST: the DRAM time is one exact multiply of the B*H-scaled traffic (ModelConst::dram_k).  Otherwise the table
+// slice holds the traffic per instance and the time is dram_time_general; a true division here cost
+// 1.2 to 5 times the whole rest of the loop (energy and latency of the chain above at 60 B/cycle: 2.05 ms).
 template <int MASK, bool FAST, bool LIMIT = false, int SUM = SUM_ORDERED, bool LATCAP = false>
 __global__ __launch_bounds__(DENSE_THREADS, 4) void k_search_dense(SearchArgs a)
 {
     static_assert(!LATCAP || (MASK == 1 && !LIMIT), "the latency cap goes with the energy key alone");
     constexpr bool REGROUP = SUM == SUM_REGROUPED;
-    constexpr bool OUTSIDE = !REGROUP && MASK == 1 && !LIMIT;
+    static_assert(!(MASK & 4) && popcount4(MASK) <= 2, "one or two of the scalar keys");
+    constexpr bool OUTSIDE = !REGROUP && (MASK & 1) && !(MASK & 8) && !LIMIT;
+    constexpr uint32_t ROWS_PER_STEP = popcount4(MASK) == 2 ? 1u : 5u;       // p_D values held in registers
     __shared__ double tab[DENSE_PAIRS * DENSE_PAIR_F64];
     __shared__ Key wave_best[N_OBJ][DENSE_WAVES];
     __shared__ uint32_t is_last;
@@ -1258,7 +1286,6 @@ __global__ __launch_bounds__(DENSE_THREADS, 4) void k_search_dense(SearchArgs a)
     // one.  A wave whose values all lie strictly above it cannot hold the optimum and recovers no position.
     __shared__ unsigned long long hint_bits[N_OBJ];
 
-    constexpr bool LAZY = !(MASK & 4);             // the energy bound of LIMIT masks values, which the lazy argmin handles too
     const double inf = pos_inf();
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1293,7 +1320,7 @@ __global__ __launch_bounds__(DENSE_THREADS, 4) void k_search_dense(SearchArgs a)
     while (true) {
         if (threadIdx.x == 0) {
             s_item = upcoming;
-            if constexpr (LAZY) {
+            {
                 // exchange with the launch-wide values read during the previous item: take what is lower there,
                 // hand over what is lower here (no reply awaited)
                 if (a.hints) {
@@ -1313,7 +1340,7 @@ __global__ __launch_bounds__(DENSE_THREADS, 4) void k_search_dense(SearchArgs a)
         if (item >= a.n_items) break;
         if (threadIdx.x == 0) {
             upcoming = gridDim.x + __hip_atomic_fetch_add(a.work_counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if constexpr (LAZY) {
+            {
                 if (a.hints) {
 #pragma unroll
                     for (int o = 0; o < N_OBJ; ++o)
@@ -1327,7 +1354,7 @@ __global__ __launch_bounds__(DENSE_THREADS, 4) void k_search_dense(SearchArgs a)
         else { const uint32_t j = item - a.n_coarse_items; chunk = a.d_ncc + j / a.d_gf; group = j % a.d_gf; }
         const uint32_t t0 = chunk * TC;
         const uint32_t nt = min((uint32_t)TC, a.mc.T - t0);
-        stage_tables_direct<DENSE_WAVES>(a, tab, t0, wave, lane);
+        stage_tables_direct<DENSE_WAVES, !FAST>(a, tab, t0, wave, lane);
         __syncthreads();
 
         const uint32_t per_class = fine ? 25u : 5u;
@@ -1357,27 +1384,24 @@ __global__ __launch_bounds__(DENSE_THREADS, 4) void k_search_dense(SearchArgs a)
 
         // the class row and the task's (D, E) rows: all requested before the first is used
         const uint4 e_c = enc[row0];
-        uint4 e_de5[5];
+        uint4 e_de[ROWS_PER_STEP];
 #pragma unroll
-        for (int q = 0; q < 5; ++q) e_de5[q] = enc[row_de0 + 25u * min((uint32_t)q, npd - 1)];
+        for (uint32_t q = 0; q < ROWS_PER_STEP; ++q) e_de[q] = enc[row_de0 + 25u * min(q, npd - 1)];
         const double c_bs = col[dense_at(sel_of(e_c, 2))], c_da = col[dense_at(sel_of(e_c, 7))];
 
-        double bestE[9], bestL[9], bestLE_l[9], bestLE_e[9], bestP[9];
-        uint32_t codeE[9], codeL[9], codeLE[9], codeP[9];
+        double bestE[9], bestL[9], bestP[9];
 #pragma unroll
-        for (int c9 = 0; c9 < 9; ++c9) {
-            bestE[c9] = bestL[c9] = bestLE_l[c9] = bestLE_e[c9] = bestP[c9] = inf;
-            codeE[c9] = codeL[c9] = codeLE[c9] = codeP[c9] = 0;
-        }
+        for (int c9 = 0; c9 < 9; ++c9) bestE[c9] = bestL[c9] = bestP[c9] = inf;
 
         // one row of this lane's tiling: Eq. (1), (2), (4), the capacity mask, B*H * Eq. (7), then
-        // the nine combinations.  code = the row's place in the task, in index order.
-        auto cost_row = [&](double bs1, double bs2, double dram_words, uint32_t code) {
+        // the nine combinations.
+        auto cost_row = [&](double bs1, double bs2, double traffic) {
             bool ok = fmax(bs1, bs2) <= cap;
+            const double dram_words = FAST ? traffic : traffic * a.mc.BH;
             double e_part = (REGROUP ? a.mc.e_sum : a.mc.e_dram) * dram_words;
             double l_dram;
-            if constexpr (FAST) l_dram = dram_words * a.mc.dram_k;
-            else l_dram = a.mc.dram_bw > 0.0 ? a.mc.c_lat * (((dram_words / a.mc.BH) * a.mc.word) / a.mc.dram_bw) : 0.0;
+            if constexpr (FAST) l_dram = traffic * a.mc.dram_k;
+            else l_dram = dram_time_general(a.mc, traffic);
             if constexpr (LATCAP) ok = ok & (l_dram <= lat_cap);
             if constexpr (MASK == 1) {
                 e_part = ok ? e_part : inf;             // the energy alone: one select, the DRAM time is not needed
@@ -1409,54 +1433,28 @@ __global__ __launch_bounds__(DENSE_THREADS, 4) void k_search_dense(SearchArgs a)
                     en = out_of_range ? inf : en;
                     lat = out_of_range ? inf : lat;
                 }
-                if constexpr (LAZY) {
-                    if constexpr (MASK & 8) bestP[c9] = fmin(bestP[c9], en * lat);
-                    if constexpr (MASK & 1) bestE[c9] = fmin(bestE[c9], en);
-                    if constexpr (MASK & 2) bestL[c9] = fmin(bestL[c9], lat);
-                } else {
-                    if constexpr (MASK & 8) {
-                        double edp = en * lat;
-                        bool lt = edp < bestP[c9];
-                        bestP[c9] = fmin(bestP[c9], edp);
-                        codeP[c9] = lt ? code : codeP[c9];
-                    }
-                    if constexpr (MASK & 1) {
-                        bool lt = en < bestE[c9];
-                        bestE[c9] = fmin(bestE[c9], en);
-                        codeE[c9] = lt ? code : codeE[c9];
-                    }
-                    if constexpr (MASK & 2) {
-                        bool lt = lat < bestL[c9];
-                        bestL[c9] = fmin(bestL[c9], lat);
-                        codeL[c9] = lt ? code : codeL[c9];
-                    }
-                    if constexpr (MASK & 4) {
-                        bool lt = (lat < bestLE_l[c9]) | ((lat == bestLE_l[c9]) & (en < bestLE_e[c9]));
-                        bestLE_l[c9] = lt ? lat : bestLE_l[c9];
-                        bestLE_e[c9] = lt ? en : bestLE_e[c9];
-                        codeLE[c9] = lt ? code : codeLE[c9];
-                    }
-                }
+                if constexpr (MASK & 8) bestP[c9] = fmin(bestP[c9], en * lat);
+                if constexpr (MASK & 1) bestE[c9] = fmin(bestE[c9], en);
+                if constexpr (MASK & 2) bestL[c9] = fmin(bestL[c9], lat);
             }
         };
 
-        if constexpr (LAZY) {
-            // (D, E) parts of the task's p_D values in registers; the (A, B) parts are read one step
-            // ahead of their use and their selectors one step ahead of that
-            double y_ret[5], y_bs[5], y_da[5];
+        // (D, E) parts of up to ROWS_PER_STEP p_D values in registers, the class's C terms riding on them; the
+        // (A, B) parts are read one step ahead of their use and their selectors one step ahead of that
+        for (uint32_t q0 = 0;;) {
+            double y_ret[ROWS_PER_STEP], y_bs[ROWS_PER_STEP], y_da[ROWS_PER_STEP];
 #pragma unroll
-            for (int q = 0; q < 5; ++q) {
-                // the class's C terms ride on the (D, E) parts
-                y_ret[q] = c_bs + col[dense_at(sel_of(e_de5[q], 1))];
-                y_bs[q] = col[dense_at(sel_of(e_de5[q], 3))] + c_bs;
-                y_da[q] = c_da + col[dense_at(sel_of(e_de5[q], 6))];
+            for (uint32_t q = 0; q < ROWS_PER_STEP; ++q) {
+                y_ret[q] = c_bs + col[dense_at(sel_of(e_de[q], 1))];
+                y_bs[q] = col[dense_at(sel_of(e_de[q], 3))] + c_bs;
+                y_da[q] = c_da + col[dense_at(sel_of(e_de[q], 6))];
             }
             double x_bs = col[dense_at(sel_of(e_c, 0))], x_ret = col[dense_at(sel_of(e_c, 4))],
                    x_da = col[dense_at(sel_of(e_c, 5))];                  // row0 is (p_A, p_B) = 0
             uint4 e_ab = enc[row0 + 1];
-            // the loop over (p_A, p_B), for a task of five p_D values or of one: no branch between the rows
-            auto ab_loop = [&](auto five) {
-                constexpr int NPD = decltype(five)::value ? 5 : 1;
+            // the loop over (p_A, p_B), for a whole step of p_D values or for one: no branch between the rows
+            auto ab_loop = [&](auto count) {
+                constexpr int N = decltype(count)::value;
 #pragma unroll 5
                 for (uint32_t ab = 0; ab < 25; ++ab) {
                     const double now_bs = x_bs, now_ret = x_ret, now_da = x_da;
@@ -1465,24 +1463,14 @@ __global__ __launch_bounds__(DENSE_THREADS, 4) void k_search_dense(SearchArgs a)
                     x_da = col[dense_at(sel_of(e_ab, 5))];
                     e_ab = enc[row0 + min(ab + 2, 24u)];
 #pragma unroll
-                    for (int q = 0; q < NPD; ++q) cost_row(now_bs + y_ret[q], y_bs[q] + now_ret, now_da + y_da[q], 0);
+                    for (int q = 0; q < N; ++q) cost_row(now_bs + y_ret[q], y_bs[q] + now_ret, now_da + y_da[q]);
                 }
             };
-            if (npd == 5) ab_loop(std::true_type{});
-            else ab_loop(std::false_type{});
-        } else {
-            // index order (p_D, then (p_A, p_B)): a strict < then keeps the lowest index on ties
-            for (uint32_t q = 0; q < npd; ++q) {
-                const uint4 e_de = enc[row_de0 + 25u * q];
-                const double y_ret = col[dense_at(sel_of(e_de, 1))], y_bs = col[dense_at(sel_of(e_de, 3))],
-                             y_da = col[dense_at(sel_of(e_de, 6))];
-                for (uint32_t ab = 0; ab < 25; ++ab) {
-                    const uint4 e_ab = enc[row0 + ab];
-                    const double x_bs = col[dense_at(sel_of(e_ab, 0))], x_ret = col[dense_at(sel_of(e_ab, 4))],
-                                 x_da = col[dense_at(sel_of(e_ab, 5))];
-                    cost_row((x_bs + c_bs) + y_ret, (y_bs + c_bs) + x_ret, (x_da + y_da) + c_da, q * 25u + ab);
-                }
-            }
+            if (ROWS_PER_STEP == 5 && npd == 5) ab_loop(std::integral_constant<int, ROWS_PER_STEP>{});
+            else ab_loop(std::integral_constant<int, 1>{});
+            if constexpr (ROWS_PER_STEP == 5) break;
+            if (++q0 == npd) break;
+            e_de[0] = enc[row_de0 + 25u * q0];
         }
 
         if constexpr (OUTSIDE) {
@@ -1493,7 +1481,7 @@ __global__ __launch_bounds__(DENSE_THREADS, 4) void k_search_dense(SearchArgs a)
         // index row (Sec. VI-A numbering) of the task's row number `code`, combination 0
         auto index_row_of = [&](uint32_t code) { return index_row_base(row_de0 + 25u * (code / 25u) + code % 25u); };
 
-        if constexpr (LAZY) {
+        {
 #pragma unroll
             for (int o = 0; o < N_OBJ; ++o) {
                 if (!((MASK >> o) & 1)) continue;
@@ -1534,12 +1522,13 @@ __global__ __launch_bounds__(DENSE_THREADS, 4) void k_search_dense(SearchArgs a)
                                   double cda, double cap_t, double gb_t, double latc_t, double slow_t, double rf_t, double mac_t) {
                     const double bs1 = (x_bs + cbs) + y_ret;
                     const double bs2 = y_bs + (cbs + x_ret);
-                    const double dram2 = (x_da + cda) + y_da;
+                    const double traffic2 = (x_da + cda) + y_da;
+                    const double dram2 = FAST ? traffic2 : traffic2 * a.mc.BH;
                     bool ok2 = fmax(bs1, bs2) <= cap_t;
                     double e2 = (REGROUP ? a.mc.e_sum : a.mc.e_dram) * dram2;
                     double l2;
-                    if constexpr (FAST) l2 = dram2 * a.mc.dram_k;
-                    else l2 = a.mc.dram_bw > 0.0 ? a.mc.c_lat * (((dram2 / a.mc.BH) * a.mc.word) / a.mc.dram_bw) : 0.0;
+                    if constexpr (FAST) l2 = traffic2 * a.mc.dram_k;
+                    else l2 = dram_time_general(a.mc, traffic2);
                     if constexpr (LATCAP) ok2 = ok2 & (l2 <= lat_cap);
                     const double over2 = __hiloint2double(ok2 ? 0 : 0x7ff00000, 0);
                     e2 = fmax(e2, over2);
@@ -1613,44 +1602,10 @@ __global__ __launch_bounds__(DENSE_THREADS, 4) void k_search_dense(SearchArgs a)
                     if (wave_v < run_p[o] || idx < run_idx[o]) { run_p[o] = wave_v; run_idx[o] = idx; }
                 }
             }
-            continue;
-        }
-        // eager keys: fold the nine per-combination minima of this lane (ascending combination =
-        // ascending index), reduce over the wave, keep the wave's best
-        Key mine[N_OBJ];
-#pragma unroll
-        for (int o = 0; o < N_OBJ; ++o) { mine[o].p = inf; mine[o].s = 0.0; mine[o].idx = ~0ull; }
-#pragma unroll
-        for (int c9 = 0; c9 < 9; ++c9) {
-            const uint32_t combo_rows = 30000u * (c9 % 3) + 90000u * (c9 / 3);
-            auto idx_of = [&](uint32_t code) { return (uint64_t)(t0 + tl) + (uint64_t)a.mc.T * (index_row_of(code) + combo_rows); };
-            if constexpr (MASK & 1) {
-                if (bestE[c9] < mine[0].p) { mine[0].p = bestE[c9]; mine[0].idx = idx_of(codeE[c9]); }
-            }
-            if constexpr (MASK & 2) {
-                if (bestL[c9] < mine[1].p) { mine[1].p = bestL[c9]; mine[1].idx = idx_of(codeL[c9]); }
-            }
-            if constexpr (MASK & 4) {
-                if (bestLE_l[c9] < mine[2].p || (bestLE_l[c9] == mine[2].p && bestLE_e[c9] < mine[2].s)) {
-                    mine[2].p = bestLE_l[c9];
-                    mine[2].s = bestLE_e[c9];
-                    mine[2].idx = idx_of(codeLE[c9]);
-                }
-            }
-            if constexpr (MASK & 8) {
-                if (bestP[c9] < mine[3].p) { mine[3].p = bestP[c9]; mine[3].idx = idx_of(codeP[c9]); }
-            }
-        }
-#pragma unroll
-        for (int o = 0; o < N_OBJ; ++o) {
-            if (!((MASK >> o) & 1)) continue;
-            if (!(mine[o].p < inf)) { mine[o].s = 0.0; mine[o].idx = ~0ull; }
-            Key k = wave_min(mine[o]);
-            if (lane == 0 && key_less(k, wave_best[o][wave])) wave_best[o][wave] = k;
         }
     }
 
-    if constexpr (LAZY) {
+    {
         if (lane == 0) {
 #pragma unroll
             for (int o = 0; o < N_OBJ; ++o) {

@@ -79,6 +79,8 @@ struct ModelConst {
     double dram_bw, gb_bw;
     double dram_k;      // word / dram_bw / n_arrays when that is exact (powers of two), else unused
     double eval_k;      // word / dram_bw when the bandwidth is a power of two (or 0), else unused
+    double dram_b, dram_y, dram_c;   // general DRAM time (dram_time_general): dram_bw / 2^k in [1, 2), 1 / dram_b rounded once,
+                        // c_lat / 2^k; bandwidth 0: 1, 1, 0
     double gb_k;        // word / gb_bw when the buffer bandwidth is a power of two, else unused
     // 1 / pe_rows, 1 / pe_cols, 1 / (pe_cols * g_words), rounded once: floor((a - 0.5) * 1/b) + 1 is
     // ceil(a / b) for every 1 <= a < 2^32 (a - 0.5 over b stays 0.5 / b away from whole numbers, the two

@@ -249,6 +249,12 @@ int make_plan(const mmee_chain *w, const mmee_hw *hw, Plan &p)
     mc.dram_k = hw->dram_bw > 0.0 ? mc.word / hw->dram_bw / (double)hw->n_arrays : 0.0;
     mc.eval_k = hw->dram_bw > 0.0 ? mc.word / hw->dram_bw : 0.0;
     mc.bw_pow2 = bw_pow2 ? 1u : 0u;
+    mc.dram_b = mc.dram_y = 1.0;
+    if (hw->dram_bw > 0.0) {
+        mc.dram_b = 2.0 * std::frexp(hw->dram_bw, &ex);
+        mc.dram_y = 1.0 / mc.dram_b;
+        mc.dram_c = std::ldexp(mc.c_lat, 1 - ex);
+    }
     mc.pe_rows = hw->pe_rows; mc.pe_cols = hw->pe_cols;
     mc.g_words = hw->rf_bytes / w->word_bytes / 2;
     mc.gb_pow2 = hw->gb_bw > 0.0 && std::frexp(hw->gb_bw, &ex) == 0.5 ? 1u : 0u;
@@ -467,13 +473,13 @@ int ensure_slots(size_t n)
 // caller repeats the pass with MMEE_SEARCH_ORDERED_SUM.
 constexpr int MASK_ENERGY = 1 << MMEE_OBJ_ENERGY;
 constexpr double REGROUP_PROOF_LIMIT = 4503599627370496.0;   // 2^52
-ModelConst pass_constants(const Plan &p, uint32_t flags, int mask = 8, bool *unproven = nullptr)
+ModelConst pass_constants(const Plan &p, uint32_t flags, int mask = 8, bool *unproven = nullptr, bool any_time = false)
 {
     ModelConst mc = p.mc;
-    // (the regrouped kernels with a latency in the key take the DRAM time as one exact product; the energy
-    // alone has no DRAM time: 2048 x 768 x 3072 x 768 chain, 60 B/cycle, exhaustive: 0.706 ms summed in
-    // order, 0.335 ms regrouped)
-    const bool allowed = (p.exact_k || mask == MASK_ENERGY) && !(flags & MMEE_SEARCH_ORDERED_SUM);
+    // (any_time: the kernel regroups whatever the DRAM time needs; the others take the DRAM time as one exact
+    // product where they regroup, and only the energy alone has no DRAM time: 2048 x 768 x 3072 x 768 chain,
+    // 60 B/cycle, exhaustive: 0.706 ms summed in order, 0.335 ms regrouped)
+    const bool allowed = (p.exact_k || any_time || mask == MASK_ENERGY) && !(flags & MMEE_SEARCH_ORDERED_SUM);
     const bool on_trust = allowed && !p.can_regroup && p.whole_energies && !(mask & 8) && unproven;
     mc.regroup = ((allowed && p.can_regroup) || on_trust) ? 1u : 0u;
     if (unproven) *unproven = on_trust;
@@ -530,35 +536,25 @@ void launch_search_limited(bool exact_k, dim3 grid, const SearchArgs &a)
     else hipLaunchKernelGGL((k_search<4, false, true>), grid, dim3(SEARCH_THREADS), 0, S.stream, a);
 }
 
-template <int MASK>
-void launch_dense_mask(bool exact_k, dim3 grid, const SearchArgs &a)
+// One pass of the dense kernel.  MASK: energy, latency, both or the energy-delay product.  LIMIT: only
+// candidates with energy below a.e_limit (first pass of a step of the Pareto walk).  LATCAP: only those with a
+// latency within a.lat_cap (second pass of the (latency, energy) key).
+template <int MASK, bool LIMIT = false, bool LATCAP = false>
+void launch_dense(bool exact_k, dim3 grid, const SearchArgs &a)
 {
-    // the energy alone does not look at the DRAM time: exact_k makes no difference to it
-    constexpr bool NO_DRAM_TIME = MASK == MASK_ENERGY;
-    if (a.mc.regroup) hipLaunchKernelGGL((k_search_dense<MASK, true, false, SUM_REGROUPED>), grid, dim3(DENSE_THREADS), 0, S.stream, a);
-    else if (NO_DRAM_TIME && a.mc.gb_product_exact)
-        hipLaunchKernelGGL((k_search_dense<MASK, true, false, NO_DRAM_TIME ? SUM_FUSED : SUM_ORDERED>), grid, dim3(DENSE_THREADS), 0, S.stream, a);
-    else if (NO_DRAM_TIME || exact_k) hipLaunchKernelGGL((k_search_dense<MASK, true>), grid, dim3(DENSE_THREADS), 0, S.stream, a);
-    else hipLaunchKernelGGL((k_search_dense<MASK, NO_DRAM_TIME>), grid, dim3(DENSE_THREADS), 0, S.stream, a);
-}
-
-// second pass of the (latency, energy) key: lowest energy among the candidates within a.lat_cap
-void launch_dense_latcap(bool exact_k, dim3 grid, const SearchArgs &a)
-{
-    if (a.mc.regroup) hipLaunchKernelGGL((k_search_dense<1, true, false, SUM_REGROUPED, true>), grid, dim3(DENSE_THREADS), 0, S.stream, a);
-    else if (a.mc.gb_product_exact && exact_k) hipLaunchKernelGGL((k_search_dense<1, true, false, SUM_FUSED, true>), grid, dim3(DENSE_THREADS), 0, S.stream, a);
-    else if (a.mc.gb_product_exact) hipLaunchKernelGGL((k_search_dense<1, false, false, SUM_FUSED, true>), grid, dim3(DENSE_THREADS), 0, S.stream, a);
-    else if (exact_k) hipLaunchKernelGGL((k_search_dense<1, true, false, SUM_ORDERED, true>), grid, dim3(DENSE_THREADS), 0, S.stream, a);
-    else hipLaunchKernelGGL((k_search_dense<1, false, false, SUM_ORDERED, true>), grid, dim3(DENSE_THREADS), 0, S.stream, a);
-}
-
-// first pass of one step of the Pareto walk over the full row set: lowest latency among the candidates
-// with energy below a.e_limit (the second pass is launch_dense_latcap)
-void launch_dense_limited(bool exact_k, dim3 grid, const SearchArgs &a)
-{
-    if (a.mc.regroup) hipLaunchKernelGGL((k_search_dense<2, true, true, SUM_REGROUPED>), grid, dim3(DENSE_THREADS), 0, S.stream, a);
-    else if (exact_k) hipLaunchKernelGGL((k_search_dense<2, true, true>), grid, dim3(DENSE_THREADS), 0, S.stream, a);
-    else hipLaunchKernelGGL((k_search_dense<2, false, true>), grid, dim3(DENSE_THREADS), 0, S.stream, a);
+    // keys that do not look at the energy or at the DRAM time need one variant only
+    constexpr bool ENERGY = MASK != (1 << MMEE_OBJ_LATENCY) || LIMIT, TIME = MASK != MASK_ENERGY || LATCAP;
+    auto with = [&](auto fast, auto sum) {
+        hipLaunchKernelGGL((k_search_dense<MASK, decltype(fast)::value, LIMIT, decltype(sum)::value, LATCAP>), grid, dim3(DENSE_THREADS), 0,
+                           S.stream, a);
+    };
+    auto with_sum = [&](auto sum) {
+        if (!TIME || exact_k) with(std::true_type{}, sum);
+        else with(std::integral_constant<bool, !TIME>{}, sum);
+    };
+    if (!ENERGY || a.mc.regroup) with_sum(std::integral_constant<int, SUM_REGROUPED>{});
+    else if (a.mc.gb_product_exact) with_sum(std::integral_constant<int, ENERGY ? SUM_FUSED : SUM_REGROUPED>{});
+    else with_sum(std::integral_constant<int, ENERGY ? SUM_ORDERED : SUM_REGROUPED>{});
 }
 
 // enqueue one pass (tables + search; the final records land in b.final_dev) in the buffers b
@@ -566,10 +562,15 @@ int enqueue_search_in(const Bufs &B, const Plan &p, int mask, uint32_t flags, ui
                       const double *e_limit = nullptr, bool build_tables = true, bool bs_da_step = false,
                       bool *unproven = nullptr)
 {
-    const ModelConst mc = pass_constants(p, flags, bs_da_step ? 8 : mask, unproven);
+    const int which = (flags & MMEE_SEARCH_EXHAUSTIVE) ? 0 : 1;
+    // The full row set goes through the dense kernel (lane = tiling, wave = 125 rows of a class).  Energy, latency
+    // and energy-delay product together would need two of its passes (27 minima do not fit four waves per
+    // SIMD): 1.14 ms for the 2048 x 768 x 3072 x 768 chain, in one pass of k_search 1.01 ms; but where the
+    // DRAM time needs a division k_search takes 2.70 ms and the dense kernel 1.29 ms.
+    const bool dense = which == 0 && !bs_da_step && B.cls_dev && !(mask == 11 && p.exact_k);
+    const ModelConst mc = pass_constants(p, flags, bs_da_step ? 8 : mask, unproven, dense);
     int rc = build_tables ? launch_tilings(p, mc, B, B.dv_dev) : MMEE_OK;
     if (rc) return rc;
-    const int which = (flags & MMEE_SEARCH_EXHAUSTIVE) ? 0 : 1;
     SearchArgs a;
     std::memset(&a, 0, sizeof(a));
     a.enc = B.enc; a.rows = B.rows[which]; a.row_enc = B.row_enc[which];
@@ -608,10 +609,6 @@ int enqueue_search_in(const Bufs &B, const Plan &p, int mask, uint32_t flags, ui
     }
     a.btab = B.btab; a.ctab_s = B.ctab_s; a.ctab_e = B.ctab_e;
     a.mc = mc;
-    // One key over the full row set goes through the dense kernel (lane = tiling, wave = 125 rows of
-    // a class).  With several keys its accumulators no longer fit four waves per SIMD, and the
-    // row-per-lane kernel is the faster one.
-    const bool dense = which == 0 && !bs_da_step && (mask & (mask - 1)) == 0 && B.cls_dev;
     uint64_t n_items;
     if (dense) {
         a.cls = B.cls_dev; a.n_cls = B.n_cls;
@@ -651,31 +648,38 @@ int enqueue_search_in(const Bufs &B, const Plan &p, int mask, uint32_t flags, ui
             // lowest energy among the candidates within the latency found is below it
             SearchArgs first = a, second = a;
             first.final_key_dev = B.key_dev;
-            launch_dense_limited(p.exact_k, grid, first);
+            launch_dense<2, true>(p.exact_k, grid, first);
             second.lat_cap = B.key_dev + 1;
             second.final_out = a.final_out + 2;
-            launch_dense_latcap(p.exact_k, grid, second);
+            launch_dense<1, false, true>(p.exact_k, grid, second);
         } else
             launch_search_limited(p.exact_k, grid, a);
-    } else if (dense && mask == 4) {
-        // The (latency, energy) key over the full row set, as two passes that each cost what a
-        // single scalar key costs: the lowest latency first, then the lowest energy among the
-        // candidates that reach it (a candidate's latency is a maximum of a row part and a
-        // combination part, so the cap applies to the two separately).  The second pass's energy
-        // record lands in the slot of this key.
-        SearchArgs first = a, second = a;
+    } else if (dense) {
+        // The (latency, energy) key over the full row set is two passes that each cost what a single scalar
+        // key costs: the lowest latency first, then the lowest energy among the candidates that reach it (a
+        // candidate's latency is a maximum of a row part and a combination part, so the cap applies to the
+        // two separately).  The second pass's energy record lands in the slot of this key.  The first pass
+        // serves the latency key as well.  Of the scalar keys two go together in one pass (energy and latency of
+        // the 2048 x 768 x 3072 x 768 chain: 0.602 ms, in two passes 0.732), a third takes a pass of its own.
+        const bool lex = mask & 4;
+        const int scalar = (mask & 11) | (lex ? 2 : 0);
+        SearchArgs first = a;
         first.final_key_dev = B.key_dev;
-        launch_dense_mask<2>(p.exact_k, grid, first);
-        second.lat_cap = B.key_dev + 1;
-        second.final_out = a.final_out + 2;
-        launch_dense_latcap(p.exact_k, grid, second);
-    } else if (dense)
-    switch (mask) {
-    case 1: launch_dense_mask<1>(p.exact_k, grid, a); break;
-    case 2: launch_dense_mask<2>(p.exact_k, grid, a); break;
-    case 4: launch_dense_mask<4>(p.exact_k, grid, a); break;
-    case 8: launch_dense_mask<8>(p.exact_k, grid, a); break;
-    default: return MMEE_EINVAL;
+        switch (scalar) {
+        case 1: launch_dense<1>(p.exact_k, grid, first); break;
+        case 2: launch_dense<2>(p.exact_k, grid, first); break;
+        case 8: launch_dense<8>(p.exact_k, grid, first); break;
+        case 9: launch_dense<9>(p.exact_k, grid, first); break;
+        case 10: launch_dense<10>(p.exact_k, grid, first); break;
+        default: launch_dense<3>(p.exact_k, grid, first); break;
+        }
+        if (lex) {
+            SearchArgs second = a;
+            second.lat_cap = B.key_dev + 1;
+            second.final_out = a.final_out + 2;
+            launch_dense<1, false, true>(p.exact_k, grid, second);
+        }
+        if (scalar == 11) launch_dense<8>(p.exact_k, grid, a);
     }
     else
     switch (mask) {

@@ -34,3 +34,19 @@ def test_exhaustive_energy_against_the_oracle(change):
             assert got.best.idx == idx, (change, objective)
             assert got.cost.energy_pj == cost.energy_pj and got.cost.latency_cycles == cost.latency_cycles
         print(change, objective, "ok", flush=True)
+
+
+@pytest.mark.parametrize("change", [dict(), dict(dram_bw=60.0), dict(n_arrays=3, e_dram=137.25), dict(e_gb=5.7, dram_bw=3.7)])
+def test_exhaustive_key_sets_against_the_oracle(change):
+    """Every set of keys: the passes the dense kernel makes of it return each key's own optimum."""
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_2604_03446_amd as M
+    w, h = dict(W, N=18, d=4), dict(H, gb_bytes=300, **change)
+    rc, idx, cost, _, _ = O.search_all(O.workload(w), O.hw(h))
+    assert rc == 0
+    for mask in range(1, 16):
+        keys = [o for o in range(4) if mask >> o & 1]
+        for o, got in zip(keys, M.mmee_search_multi(w, h, keys, M.SEARCH_EXHAUSTIVE)):
+            assert got.best.idx == idx[o], (change, keys, o)
+            assert got.cost.energy_pj == cost[o].energy_pj and got.cost.latency_cycles == cost[o].latency_cycles
