@@ -14,18 +14,15 @@
 // problem) stretch leaves one record per key; k_batch_finish, launched behind the search, reduces a
 // problem's records and writes the winner's full cost record and mapping.
 //
-// Included once by mmee.hip, after kernels.h.
+// Included once by mmee.hip.
 #pragma once
-#include "kernels.h"
+#include "boundary.h"
 
 namespace mmee {
 
 constexpr int BATCH_THREADS = 512;           // two blocks per CU, four waves per SIMD
 constexpr int BATCH_WAVES = BATCH_THREADS / 64;
-constexpr int BATCH_TC = 64;                 // tilings per item = lanes of a wave
 constexpr int BATCH_NCS = 20;                // constants per (tiling, r), as in layout.h
-constexpr int BATCH_MAX_USED = 80;           // table entries the row lists may refer to (the pruned rows use 77)
-constexpr int BATCH_MAX_ROWS = 288;          // rows the lists may hold (the pruned lists hold 270)
 constexpr int BATCH_MAX_SPLIT = 4;           // blocks that may share the rows of one chunk (small launches)
 
 constexpr int BATCH_INLINE_DIVS = 448;       // divisors (all four lists together) of a problem that rides in the kernel arguments
@@ -59,11 +56,6 @@ struct BatchArgs {
     const uint32_t *first_items;             // [n_prob + 1] ascending, for the item -> problem search
     uint32_t n_prob, n_items;
     const uint4 *enc;                        // every encoded row (for the winner's record)
-    // the row lists, one after the other (group by group, ascending row number inside a group)
-    const uint32_t *row_off;                 // [n_rows][8] byte offsets of a row's eight table values in the staged table
-    const uint32_t *row_df;                  // [n_rows] the rows' numbers (levels/order + 15000 * (r + 2 f))
-    const uint32_t *cmap;                    // [NENT] table entry -> its place in the staged table, 0xFFFF when no row refers to it
-    uint32_t n_rows, n_used;
     // A chunk's rows are shared out over `split` work items (1 in a large launch; more when the launch
     // would otherwise leave most of the chip idle), and inside a work item over the waves of the block.
     uint32_t split, split_log2;                 // a power of two
@@ -89,192 +81,6 @@ __device__ __forceinline__ void batch_tables(const BatchArgs &a, const BatchProb
     }
 }
 
-// ---- the boundary side, one value at a time ---------------------------------------------------
-// Every count of the model is an integer below 2^53 (the host refuses workloads where it is not),
-// so products and sums of them are exact in fp64 whatever their order.
-
-struct TilingF {                             // boundary vector of one tiling (Eq. (10)), as fp64
-    double G[4], D[4];
-};
-
-// digit q of tiling t: the intra-tile size x_G and the inter-tile count x_D of dimension q
-__device__ __forceinline__ void tiling_dim(const DivTable &dv, uint32_t t, int q, double &G, double &D)
-{
-    uint32_t radix = 1;
-    for (int k = 0; k < q; ++k) radix *= dv.ndiv[k];
-    const uint32_t g = dv.div[q][(t / radix) % dv.ndiv[q]];
-    G = (double)g;
-    D = (double)(dv.X[q] / g);
-}
-
-__device__ __forceinline__ TilingF tiling_of(const DivTable &dv, uint32_t t)
-{
-    TilingF v;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) tiling_dim(dv, t, q, v.G[q], v.D[q]);
-    return v;
-}
-
-// tile_X * {1, d0, d1, d0 d1}; option 4 = the operand takes no space
-__device__ __forceinline__ double footprint(double tile, double d0, double d1, uint32_t opt)
-{
-    const double v = tile * ((opt & 1) ? d0 : 1.0) * ((opt & 2) ? d1 : 1.0);
-    return opt >= 4 ? 0.0 : v;
-}
-
-// entry `ent` of the per-tiling table (layout.h), bh = B*H for the scaled DRAM terms, 1 for the raw ones
-__device__ __forceinline__ double table_entry(uint32_t ent, const TilingF &v, const double X[4], double bh)
-{
-    const double tA = v.G[DI] * v.G[DK], tB = v.G[DK] * v.G[DL], tC = v.G[DI] * v.G[DL], tD = v.G[DL] * v.G[DJ],
-                 tE = v.G[DI] * v.G[DJ];
-    if (ent < ENT_BS_DE) {                                   // BS_A[a] + BS_B[b]
-        const uint32_t k = ent - ENT_BS_AB;
-        return footprint(tA, v.D[DI], v.D[DK], k & 3) + footprint(tB, v.D[DK], v.D[DL], k >> 2);
-    }
-    if (ent < ENT_RET_DE) {                                  // BS_D[a] + BS_E[b]
-        const uint32_t k = ent - ENT_BS_DE;
-        return footprint(tD, v.D[DL], v.D[DJ], k & 3) + footprint(tE, v.D[DI], v.D[DJ], k >> 2);
-    }
-    if (ent < ENT_RET_AB) {                                  // tau_D BS_D[a] + tau_E BS_E[b]
-        const uint32_t k = ent - ENT_RET_DE;
-        return footprint(tD, v.D[DL], v.D[DJ], k % 5) + footprint(tE, v.D[DI], v.D[DJ], k / 5);
-    }
-    if (ent < ENT_BS_C) {                                    // tau_A BS_A[a] + tau_B BS_B[b]
-        const uint32_t k = ent - ENT_RET_AB;
-        return footprint(tA, v.D[DI], v.D[DK], k % 5) + footprint(tB, v.D[DK], v.D[DL], k / 5);
-    }
-    if (ent < ENT_DA_AB) return footprint(tC, v.D[DI], v.D[DL], ent - ENT_BS_C);
-    if (ent < ENT_DA_DE) {                                   // |A| {1, l_D, j_D, l_D j_D} + |B| {1, i_D, j_D, i_D j_D}
-        const uint32_t k = ent - ENT_DA_AB;
-        return bh * (footprint(X[DI] * X[DK], v.D[DL], v.D[DJ], k & 3) + footprint(X[DK] * X[DL], v.D[DI], v.D[DJ], k >> 2));
-    }
-    if (ent < ENT_DA_C) {                                    // |D| {1, i_D, k_D, i_D k_D} + |E| {1, k_D, l_D, k_D l_D}
-        const uint32_t k = ent - ENT_DA_DE;
-        return bh * (footprint(X[DL] * X[DJ], v.D[DI], v.D[DK], k & 3) + footprint(X[DI] * X[DJ], v.D[DK], v.D[DL], k >> 2));
-    }
-    // unfused C: spilled by Op1, fetched by Op2, plus one softmax pass over S and P; option 4: fused, no traffic
-    const uint32_t c = ent - ENT_DA_C;
-    const double spill = (c & 1) ? v.D[DK] : 1.0, fetch = (c & 2) ? v.D[DJ] : 1.0;
-    return c >= 4 ? 0.0 : bh * (X[DI] * X[DL]) * (spill + fetch + 2.0);
-}
-
-// ceil(a / b) for a whole number 1 <= a < 2^32 held in fp64, given 1 / b rounded once (ModelConst)
-__device__ __forceinline__ double cdiv_f64(double a, double rcp_b) { return __builtin_floor((a - 0.5) * rcp_b) + 1.0; }
-
-// words crossing buffer<->RF and cycles of one tile matmul m x r x n; mode 0 WS, 1 IS, 2 OS
-__device__ __forceinline__ void tile_cost_f64(double m, double r, double n, uint32_t mode, const ModelConst &mc,
-                                              double &words, double &cycles)
-{
-    const double rd = mode == 0 ? r : m;                     // spread over PE rows
-    const double cd = mode == 1 ? r : n;                     // spread over PE columns
-    const double time_dim = mode == 0 ? m : (mode == 1 ? n : r);
-    const double row_folds = cdiv_f64(rd, mc.rcp_rows);
-    words = rd * cd + time_dim * rd * cdiv_f64(cd, mc.rcp_cols_g) + time_dim * cd * row_folds;
-    cycles = row_folds * cdiv_f64(cd, mc.rcp_cols) * time_dim;
-}
-
-// what one stationary combination (s1, s2) and recomputation choice r contribute for one tiling
-struct ComboTerms {
-    double br, cyc, mac, sm;                 // buffer<->RF words, cycles, MACs, softmax elements (per instance)
-    double lat_part;                         // c_lat * max(cycles, buffer<->RF time)
-    double e_rf_part, e_mac_part;
-};
-
-// ... from the two operators' tile costs (words and cycles of one tile matmul each)
-__device__ __forceinline__ ComboTerms combo_terms_from(const TilingF &v, const double X[4], const ModelConst &mc, uint32_t r,
-                                                       double br1, double cy1, double br2, double cy2)
-{
-    ComboTerms o;
-    const double rho = r ? v.D[DJ] : 1.0;                    // producer repeated per j tile (Sec. V-D)
-    const double st1 = rho * v.D[DI] * v.D[DK] * v.D[DL], st2 = v.D[DI] * v.D[DL] * v.D[DJ];
-    o.br = st1 * br1 + st2 * br2;
-    o.cyc = st1 * cy1 + st2 * cy2;
-    o.mac = rho * X[DI] * X[DK] * X[DL] + X[DI] * X[DL] * X[DJ];
-    o.sm = rho * X[DI] * X[DL];
-    // a power-of-two bandwidth: the quotient is the product with one exactly representable constant
-    const double t_gb = mc.gb_pow2 ? o.br * mc.gb_k : (mc.gb_bw > 0.0 ? (o.br * mc.word) / mc.gb_bw : 0.0);
-    o.lat_part = mc.c_lat * fmax(o.cyc, t_gb);
-    o.e_rf_part = mc.e_rf * (mc.BH * 3.0 * o.mac);
-    o.e_mac_part = mc.e_mac * (mc.BH * (o.mac + (double)mc.c_softmax * o.sm));
-    return o;
-}
-
-__device__ __forceinline__ ComboTerms combo_terms(const TilingF &v, const double X[4], const ModelConst &mc, uint32_t r,
-                                                  uint32_t s1, uint32_t s2)
-{
-    double br1, cy1, br2, cy2;
-    tile_cost_f64(v.G[DI], v.G[DK], v.G[DL], s1, mc, br1, cy1);
-    tile_cost_f64(v.G[DI], v.G[DL], v.G[DJ], s2, mc, br2, cy2);
-    return combo_terms_from(v, X, mc, r, br1, cy1, br2, cy2);
-}
-
-// One candidate, complete, from the problem description alone: the winner's cost record (Sec. V-D's
-// order of the energy terms, as eval_candidate).
-__device__ __forceinline__ void eval_candidate_direct(const uint4 *enc, const DivTable &dv, const ModelConst &mc, uint64_t idx,
-                                                      mmee_cost &c)
-{
-    const uint32_t t = (uint32_t)(idx % mc.T), row = (uint32_t)(idx / mc.T);
-    const uint32_t lo = row % 15000;
-    uint32_t hi = row / 15000;
-    const uint32_t r = hi & 1; hi >>= 1;
-    const uint32_t s1 = hi % 3; hi /= 3;
-    const uint32_t s2 = hi % 3, f = hi / 3;
-    const uint4 e = enc[lo + ROWS_PER_GROUP * (r + 2 * f)];
-    if (!(sel_of(e, ROW_FLAGS) & 1)) {
-        c.bs_words = c.da_words = c.br_words = c.mac_total = c.comp_cycles = 0;
-        c.energy_pj = pos_inf(); c.latency_cycles = pos_inf();
-        c.valid = 0; c.reason = 1;
-        return;
-    }
-    const TilingF v = tiling_of(dv, t);
-    const double X[4] = {(double)dv.X[0], (double)dv.X[1], (double)dv.X[2], (double)dv.X[3]};
-    double w[NSEL];
-#pragma unroll
-    for (int k = 0; k < NSEL; ++k) w[k] = table_entry(sel_of(e, k), v, X, 1.0);
-    const ComboTerms ct = combo_terms(v, X, mc, r, s1, s2);
-    const double bs = fmax(w[0] + w[2] + w[1], w[3] + w[2] + w[4]);     // Eq. (1), (2), (4)
-    const double da = w[5] + w[6] + w[7];                                // Eq. (7)
-    c.bs_words = (uint64_t)bs; c.da_words = (uint64_t)da; c.br_words = (uint64_t)ct.br;
-    c.mac_total = (uint64_t)ct.mac; c.comp_cycles = (uint64_t)ct.cyc;
-    if (bs > mc.cap_words) {
-        c.energy_pj = pos_inf(); c.latency_cycles = pos_inf();
-        c.valid = 0; c.reason = 2;
-        return;
-    }
-    double en = mc.e_dram * (mc.BH * da);
-    en = en + mc.e_gb * (mc.BH * (da + ct.br));
-    en = en + ct.e_rf_part;
-    en = en + ct.e_mac_part;
-    double l_dram;
-    if (mc.bw_pow2) l_dram = da * mc.eval_k;
-    else l_dram = (da * mc.word) / mc.dram_bw;
-    c.energy_pj = en;
-    c.latency_cycles = fmax(mc.c_lat * l_dram, ct.lat_part);
-    c.valid = 1; c.reason = 0;
-}
-
-// The table entries of one kind, for this lane's tiling, into the staged table: x[a] + y[b] for every
-// option pair (na x nb of them, entry number first + a + na * b), each at the place cmap gives it.
-template <int NA, int NB>
-__device__ __forceinline__ void stage_pair_sums(double *tab_lane, ConstPtr<uint32_t> cmap, int first, const double (&x)[5],
-                                                const double (&y)[5])
-{
-    // the places are wave-uniform (scalar loads): an entry no row refers to costs a branch, nothing more
-#pragma unroll
-    for (int b = 0; b < NB; ++b)
-#pragma unroll
-        for (int a = 0; a < NA; ++a) {
-            const uint32_t at = cmap[first + a + NA * b];
-            if (at != 0xFFFFu) tab_lane[at * BATCH_TC] = x[a] + y[b];
-        }
-}
-
-// footprints of one operand under its five options (4 = takes no space)
-__device__ __forceinline__ void footprints(double (&o)[5], double tile, double d0, double d1)
-{
-    o[0] = tile; o[1] = tile * d0; o[2] = tile * d1; o[3] = tile * d0 * d1; o[4] = 0.0;
-}
-
 // MASK, FAST, REGROUP as in k_search.  Every block takes a contiguous range of the work items, so
 // that it stays with one problem for many items: a wave keeps its running best (value, index) per key
 // across the items of a problem and recovers a position only where it can matter; one record per
@@ -282,10 +88,10 @@ __device__ __forceinline__ void footprints(double (&o)[5], double tile, double d
 template <int MASK, bool FAST, bool REGROUP>
 __global__ __launch_bounds__(BATCH_THREADS, 4) void k_search_batch(BatchArgs a)
 {
-    __shared__ double tab[BATCH_MAX_USED * BATCH_TC];        // entry-major, lane = tiling: conflict-free as it is
-    __shared__ double cst[2 * BATCH_NCS * BATCH_TC];         // [r][constant][tiling]
-    __shared__ double gd[8 * BATCH_TC];                      // the chunk's boundary vectors: G[0..3], D[0..3] per tiling
-    __shared__ double tc[6 * 2 * BATCH_TC];                  // tile costs: [op * 3 + mode][words, cycles][tiling]
+    __shared__ double tab[KEPT_LINES * PRUNED_TC];        // entry-major, lane = tiling: conflict-free as it is
+    __shared__ double cst[2 * BATCH_NCS * PRUNED_TC];         // [r][constant][tiling]
+    __shared__ double gd[8 * PRUNED_TC];                      // the chunk's boundary vectors: G[0..3], D[0..3] per tiling
+    __shared__ double tc[6 * 2 * PRUNED_TC];                  // tile costs: [op * 3 + mode][words, cycles][tiling]
     __shared__ uint32_t div_lds[4 * MAXDIV];                 // the current problem's divisor lists
     __shared__ Key wave_best[N_OBJ][BATCH_WAVES];
 
@@ -295,8 +101,7 @@ __global__ __launch_bounds__(BATCH_THREADS, 4) void k_search_batch(BatchArgs a)
     // A wave's rows and the table's entry places are the same for all its lanes: both come through
     // the constant address space (scalar loads), a row's eight offsets as one load, one row ahead of use.
     typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
-    ConstPtr<u32x8> row_offs = (ConstPtr<u32x8>)a.row_off;
-    ConstPtr<uint32_t> cmap_c = as_constant(a.cmap);
+    ConstPtr<u32x8> row_offs = (ConstPtr<u32x8>)&kept_dev.off[0][0];
 
     const uint32_t item_lo = blockIdx.x * a.per_block, item_hi = min(item_lo + a.per_block, a.n_items);
     if (item_lo >= item_hi) return;
@@ -313,7 +118,7 @@ __global__ __launch_bounds__(BATCH_THREADS, 4) void k_search_batch(BatchArgs a)
         }
         p = lo;
     }
-    ConstPtr<uint32_t> row_df = as_constant(a.row_df);
+    ConstPtr<uint32_t> row_df = as_constant(kept_dev.number);
     const char *tab_bytes = reinterpret_cast<const char *>(tab) + lane * 8;
 
     // the wave's running best over the items of the current problem
@@ -355,12 +160,12 @@ __global__ __launch_bounds__(BATCH_THREADS, 4) void k_search_batch(BatchArgs a)
         }
         ConstPtr<uint32_t> tail = as_constant(&pr->h.first_item);
         const uint32_t work = item - tail[0];
-        const uint32_t t0 = (work >> a.split_log2) * BATCH_TC;
+        const uint32_t t0 = (work >> a.split_log2) * PRUNED_TC;
         // this wave's piece of one group's rows, within the work item's share of the chunk's rows
         const uint32_t task = (work & (a.split - 1)) * BATCH_WAVES + wave;
         const uint32_t n_rows = a.task_cnt[task], row_lo = a.task_lo[task], r = a.task_g[task] & 1;
         const uint32_t T = mc.T;
-        const uint32_t nt = min((uint32_t)BATCH_TC, T - t0);
+        const uint32_t nt = min((uint32_t)PRUNED_TC, T - t0);
         ConstPtr<uint32_t> dvw = as_constant(pr->h.X);       // X[4], ndiv[4]
         const uint32_t nd0 = dvw[4], nd1 = dvw[5], nd2 = dvw[6], nd3 = dvw[7];
         if (staged_p != p) {
@@ -379,87 +184,36 @@ __global__ __launch_bounds__(BATCH_THREADS, 4) void k_search_batch(BatchArgs a)
             const uint32_t nq = wave == 0 ? nd0 : (wave == 1 ? nd1 : (wave == 2 ? nd2 : nd3));
             const uint32_t list0 = wave == 0 ? 0u : (wave == 1 ? nd0 : (wave == 2 ? nd0 + nd1 : nd0 + nd1 + nd2));
             const uint32_t g = div_lds[list0 + (t / radix) % nq];
-            gd[wave * BATCH_TC + lane] = (double)g;
-            gd[(4 + wave) * BATCH_TC + lane] = (double)(dvw[wave] / g);
+            gd[wave * PRUNED_TC + lane] = (double)g;
+            gd[(4 + wave) * PRUNED_TC + lane] = (double)(dvw[wave] / g);
         }
         __syncthreads();
 
         // ---- build, first half: the six tile costs (one per wave) and the table entries the rows refer to
         TilingF v;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) { v.G[q] = gd[q * BATCH_TC + lane]; v.D[q] = gd[(4 + q) * BATCH_TC + lane]; }
+        for (int q = 0; q < 4; ++q) { v.G[q] = gd[q * PRUNED_TC + lane]; v.D[q] = gd[(4 + q) * PRUNED_TC + lane]; }
         const double X[4] = {(double)dvw[0], (double)dvw[1], (double)dvw[2], (double)dvw[3]};
+        const double size[5] = {X[DI] * X[DK], X[DK] * X[DL], X[DL] * X[DJ], X[DI] * X[DJ], X[DI] * X[DL]};   // A, B, D, E, C
         if (wave < 6) {
             double words, cycles;
             if (wave < 3) tile_cost_f64(v.G[DI], v.G[DK], v.G[DL], wave, mc, words, cycles);
             else tile_cost_f64(v.G[DI], v.G[DL], v.G[DJ], wave - 3, mc, words, cycles);
-            tc[(wave * 2) * BATCH_TC + lane] = words;
-            tc[(wave * 2 + 1) * BATCH_TC + lane] = cycles;
+            tc[(wave * 2) * PRUNED_TC + lane] = words;
+            tc[(wave * 2 + 1) * PRUNED_TC + lane] = cycles;
         }
-        {
-            // one kind of table entry per wave (layout.h); the two waves without a tile cost take the 25-entry kinds
-            double *tab_lane = tab + lane;
-            double x[5], y[5];
-            switch (wave) {
-            case 0:                                           // BS_A[a] + BS_B[b]
-                footprints(x, v.G[DI] * v.G[DK], v.D[DI], v.D[DK]);
-                footprints(y, v.G[DK] * v.G[DL], v.D[DK], v.D[DL]);
-                stage_pair_sums<4, 4>(tab_lane, cmap_c, ENT_BS_AB, x, y);
-                break;
-            case 1:                                           // BS_D[a] + BS_E[b]
-                footprints(x, v.G[DL] * v.G[DJ], v.D[DL], v.D[DJ]);
-                footprints(y, v.G[DI] * v.G[DJ], v.D[DI], v.D[DJ]);
-                stage_pair_sums<4, 4>(tab_lane, cmap_c, ENT_BS_DE, x, y);
-                break;
-            case 6:                                           // tau_D BS_D[a] + tau_E BS_E[b]
-                footprints(x, v.G[DL] * v.G[DJ], v.D[DL], v.D[DJ]);
-                footprints(y, v.G[DI] * v.G[DJ], v.D[DI], v.D[DJ]);
-                stage_pair_sums<5, 5>(tab_lane, cmap_c, ENT_RET_DE, x, y);
-                break;
-            case 7:                                           // tau_A BS_A[a] + tau_B BS_B[b]
-                footprints(x, v.G[DI] * v.G[DK], v.D[DI], v.D[DK]);
-                footprints(y, v.G[DK] * v.G[DL], v.D[DK], v.D[DL]);
-                stage_pair_sums<5, 5>(tab_lane, cmap_c, ENT_RET_AB, x, y);
-                break;
-            case 2: {                                         // BS_C[c]; B*H * DA_C[c]
-                footprints(x, v.G[DI] * v.G[DL], v.D[DI], v.D[DL]);
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const uint32_t at = cmap_c[ENT_BS_C + c];
-                    if (at != 0xFFFFu) tab_lane[at * BATCH_TC] = x[c];
-                }
-#pragma unroll
-                for (int c = 0; c < 5; ++c) {
-                    // unfused C: spilled by Op1, fetched by Op2, one softmax pass over S and P; option 4: fused
-                    const double spill = (c & 1) ? v.D[DK] : 1.0, fetch = (c & 2) ? v.D[DJ] : 1.0;
-                    const uint32_t at = cmap_c[ENT_DA_C + c];
-                    if (at != 0xFFFFu) tab_lane[at * BATCH_TC] = c >= 4 ? 0.0 : mc.BH * (X[DI] * X[DL]) * (spill + fetch + 2.0);
-                }
-                break;
-            }
-            case 3:                                           // B*H * (|A| {1, l_D, j_D, l_D j_D} + |B| {1, i_D, j_D, i_D j_D})
-                footprints(x, mc.BH * (X[DI] * X[DK]), v.D[DL], v.D[DJ]);
-                footprints(y, mc.BH * (X[DK] * X[DL]), v.D[DI], v.D[DJ]);
-                stage_pair_sums<4, 4>(tab_lane, cmap_c, ENT_DA_AB, x, y);
-                break;
-            case 4:                                           // B*H * (|D| {1, i_D, k_D, i_D k_D} + |E| {1, k_D, l_D, k_D l_D})
-                footprints(x, mc.BH * (X[DL] * X[DJ]), v.D[DI], v.D[DK]);
-                footprints(y, mc.BH * (X[DI] * X[DJ]), v.D[DK], v.D[DL]);
-                stage_pair_sums<4, 4>(tab_lane, cmap_c, ENT_DA_DE, x, y);
-                break;
-            default: break;
-            }
-        }
+        // one kind of table entry per wave (layout.h); the two waves without a tile cost take the 25-entry kinds
+        stage_kept(tab + lane, wave, v, size, mc.BH);
         __syncthreads();
         // ---- build, second half: the 18 (recomputation, combination) constant pairs, shared out over the waves
         for (uint32_t job = wave; job < 18; job += BATCH_WAVES) {
             const uint32_t rr = job / 9, c9 = job % 9, s1 = c9 % 3, s2 = c9 / 3;
-            const ComboTerms ct = combo_terms_from(v, X, mc, rr, tc[(s1 * 2) * BATCH_TC + lane], tc[(s1 * 2 + 1) * BATCH_TC + lane],
-                                                   tc[((3 + s2) * 2) * BATCH_TC + lane], tc[((3 + s2) * 2 + 1) * BATCH_TC + lane]);
-            double *cs = cst + rr * BATCH_NCS * BATCH_TC + lane;
-            cs[c9 * BATCH_TC] = REGROUP ? (mc.e_gb * (mc.BH * ct.br) + ct.e_rf_part) + ct.e_mac_part : mc.BH * ct.br;
-            cs[(9 + c9) * BATCH_TC] = ct.lat_part;
-            if (c9 == 0) { cs[18 * BATCH_TC] = ct.e_rf_part; cs[19 * BATCH_TC] = ct.e_mac_part; }
+            const ComboTerms ct = combo_terms_from(v, X, mc, rr, tc[(s1 * 2) * PRUNED_TC + lane], tc[(s1 * 2 + 1) * PRUNED_TC + lane],
+                                                   tc[((3 + s2) * 2) * PRUNED_TC + lane], tc[((3 + s2) * 2 + 1) * PRUNED_TC + lane]);
+            double *cs = cst + rr * BATCH_NCS * PRUNED_TC + lane;
+            cs[c9 * PRUNED_TC] = REGROUP ? (mc.e_gb * (mc.BH * ct.br) + ct.e_rf_part) + ct.e_mac_part : mc.BH * ct.br;
+            cs[(9 + c9) * PRUNED_TC] = ct.lat_part;
+            if (c9 == 0) { cs[18 * PRUNED_TC] = ct.e_rf_part; cs[19 * PRUNED_TC] = ct.e_mac_part; }
         }
         __syncthreads();
 
@@ -467,12 +221,12 @@ __global__ __launch_bounds__(BATCH_THREADS, 4) void k_search_batch(BatchArgs a)
         const double cap = lane < nt ? mc.cap_words : -1.0;  // a lane beyond the chunk never passes the capacity test
         double gb[9], latc[9];
         {
-            const double *cs = cst + r * BATCH_NCS * BATCH_TC + lane;
+            const double *cs = cst + r * BATCH_NCS * PRUNED_TC + lane;
 #pragma unroll
-            for (int c = 0; c < 9; ++c) { gb[c] = cs[c * BATCH_TC]; latc[c] = cs[(9 + c) * BATCH_TC]; }
+            for (int c = 0; c < 9; ++c) { gb[c] = cs[c * PRUNED_TC]; latc[c] = cs[(9 + c) * PRUNED_TC]; }
         }
-        const double e_rf_part = REGROUP ? 0.0 : cst[(r * BATCH_NCS + 18) * BATCH_TC + lane];
-        const double e_mac_part = REGROUP ? 0.0 : cst[(r * BATCH_NCS + 19) * BATCH_TC + lane];
+        const double e_rf_part = REGROUP ? 0.0 : cst[(r * BATCH_NCS + 18) * PRUNED_TC + lane];
+        const double e_mac_part = REGROUP ? 0.0 : cst[(r * BATCH_NCS + 19) * PRUNED_TC + lane];
 
         // Every key is a monotone function of a candidate's DRAM traffic once tiling, recomputation choice
         // and stationary combination are fixed: DRAM energy and DRAM time grow with it, every rounded sum,
@@ -528,7 +282,7 @@ __global__ __launch_bounds__(BATCH_THREADS, 4) void k_search_batch(BatchArgs a)
 
         double min_d = inf;
         {
-            u32x8 off_next = row_offs[min(row_lo, a.n_rows - 1)];
+            u32x8 off_next = row_offs[min(row_lo, KEPT.n - 1)];
 #pragma unroll 4
             for (uint32_t i = 0; i < n_rows; ++i) {
                 const u32x8 off_now = off_next;
@@ -598,7 +352,7 @@ __global__ __launch_bounds__(BATCH_THREADS, 4) void k_search_batch(BatchArgs a)
                 unsigned long long cands = __ballot((kp_u == wave_p) & (ks_u == wave_s));
                 if (n_rows <= 64 && 2u * (uint32_t)__popcll(cands) <= scan) {
                     // Few such tilings: take them one by one with lane = row, all rows of the piece at once.
-                    const uint4 *ro = reinterpret_cast<const uint4 *>(a.row_off) + 2 * (row_lo + min(lane, n_rows - 1));
+                    const uint4 *ro = reinterpret_cast<const uint4 *>(&kept_dev.off[0][0]) + 2 * (row_lo + min(lane, n_rows - 1));
                     const uint4 oa = ro[0], ob = ro[1];
                     const uint32_t off[NSEL] = {oa.x, oa.y, oa.z, oa.w, ob.x, ob.y, ob.z, ob.w};
                     while (cands) {

@@ -9,13 +9,14 @@
 //   k_front_step     online:   one point of the buffer-size / DRAM-access front
 //   k_eval_batch     online:   the same model, one 64-byte record per candidate
 //   k_decode         online:   index -> mapping
-// (k_search_batch and k_batch_finish, the pruned search over many problems per launch: batch.h)
+// (k_search_pruned and k_pruned_finish, the pruned search over one or many problems per launch: pruned.h)
 #pragma once
 #include <hip/hip_runtime.h>
 #include <type_traits>
 #include <math.h>
 #include "../../include/mmee.h"
 #include "layout.h"
+#include "rows.h"
 
 namespace mmee {
 
@@ -132,118 +133,19 @@ __device__ __forceinline__ double uniform_f64(double x)
 // ---------------------------------------------------------------------------
 // offline stage: the query side
 
-// the 24 inter-tile loop orders, outer -> inner, in lexicographic order over i<k<l<j;
-// 2 bits per slot, slot 0 = outermost
-__device__ __forceinline__ uint32_t order_of_rank(uint32_t rank)
-{
-    uint32_t avail = 0xE4;            // nibble list 3,2,1,0 packed 2 bits each: entry e at bits 2e
-    uint32_t packed = 0;
-    uint32_t f = 6, left = 4;
-    for (uint32_t slot = 0; slot < 4; ++slot) {
-        uint32_t pick = rank / f;
-        rank -= pick * f;
-        uint32_t sym = (avail >> (2 * pick)) & 3;
-        packed |= sym << (2 * slot);
-        // delete entry `pick` from the list
-        uint32_t low = avail & ((1u << (2 * pick)) - 1);
-        uint32_t high = (avail >> (2 * pick + 2)) << (2 * pick);
-        avail = low | high;
-        --left;
-        if (left) f /= left;
-    }
-    return packed;
-}
-
-// selector of a DRAM term: which of the two loops an operand does not own multiply its
-// matrix size.  nest_mask: loops of the operand's operator nest; own0/own1: its own dims;
-// n0/n1: the other two dims in table order.
-__device__ __forceinline__ uint32_t dram_selector(const int pos[4], uint32_t nest_mask, uint32_t prefix_mask,
-                                                  int own0, int own1, int n0, int n1, int level)
-{
-    // blocker: innermost own loop outside the buffering level (Sec. V-A)
-    int bpos = 99, bdim = -1;
-    if (pos[own0] >= level) { bpos = pos[own0]; bdim = own0; }
-    if (pos[own1] >= level && pos[own1] < bpos) { bpos = pos[own1]; bdim = own1; }
-    if (bdim < 0) return 0;                                   // whole matrix resident: fetched once
-    uint32_t counted;
-    if (level == 0 && ((prefix_mask >> bdim) & 1)) {
-        counted = prefix_mask;                                // evicted at every operator switch
-    } else {
-        counted = 0;                                          // Scenario 1: blocker and all loops above it
-        for (int q = 0; q < 4; ++q)
-            if (((nest_mask >> q) & 1) && pos[q] >= bpos) counted |= 1u << q;
-    }
-    return ((counted >> n0) & 1) | (((counted >> n1) & 1) << 1);
-}
-
 __global__ void k_build_rows(uint4 *enc, uint32_t *sig)
 {
     uint32_t row = blockIdx.x * blockDim.x + threadIdx.x;
     if (row >= N_DFROWS) return;
     uint32_t x = row;
-    int lvl[5];
-    lvl[OA] = x % 5; x /= 5;
-    lvl[OB] = x % 5; x /= 5;
-    lvl[OD] = x % 5; x /= 5;
-    lvl[OE] = x % 5; x /= 5;
-    lvl[OC] = 0;
-    uint32_t rank = x % 24; x /= 24;
-    uint32_t r = x & 1, f = x >> 1;
-
-    uint32_t ord = order_of_rank(rank);
-    int pos[4];
-    for (int slot = 0; slot < 4; ++slot) pos[(ord >> (2 * slot)) & 3] = 3 - slot;
-
-    // loops iterated by both operators lead the nest (Sec. IV-B); the rest splits per operator
-    uint32_t shared_mask = (1u << DI) | (1u << DL) | (r ? (1u << DJ) : 0u);
-    uint32_t prefix_mask = 0;
-    for (int slot = 0; slot < 4; ++slot) {
-        uint32_t q = (ord >> (2 * slot)) & 3;
-        if (!((shared_mask >> q) & 1)) break;
-        prefix_mask |= 1u << q;
-    }
-    uint32_t nest1 = prefix_mask | (1u << DI) | (1u << DK) | (1u << DL);
-    uint32_t nest2 = prefix_mask | (1u << DI) | (1u << DL) | (1u << DJ);
-
-    const int own[5][2] = {{DI, DK}, {DK, DL}, {DI, DL}, {DL, DJ}, {DI, DJ}};
-    uint32_t bs_sel[5];
-    for (int X = 0; X < 5; ++X) {
-        if (X == OC) continue;
-        bs_sel[X] = (uint32_t)(pos[own[X][0]] < lvl[X]) | ((uint32_t)(pos[own[X][1]] < lvl[X]) << 1);
-    }
-    // C holds every tile the producer finishes before the consumer starts (fused), else one tile
-    bs_sel[OC] = f ? ((uint32_t)!((prefix_mask >> DI) & 1) | ((uint32_t)!((prefix_mask >> DL) & 1) << 1)) : 0u;
-    // retained operands (buffered at an inter-tile loop) also occupy the other operator's buffer
-    const int ret[4] = {OA, OB, OD, OE};
-    uint32_t tau_bits = 0, ret_sel[4];
-    for (int y = 0; y < 4; ++y) {
-        bool tau = lvl[ret[y]] >= 1;
-        tau_bits |= (uint32_t)tau << y;
-        ret_sel[y] = tau ? bs_sel[ret[y]] : 4u;
-    }
-    uint32_t da_sel[4];
-    da_sel[0] = dram_selector(pos, nest1, prefix_mask, DI, DK, DL, DJ, lvl[OA]);
-    da_sel[1] = dram_selector(pos, nest1, prefix_mask, DK, DL, DI, DJ, lvl[OB]);
-    da_sel[2] = dram_selector(pos, nest2, prefix_mask, DL, DJ, DI, DK, lvl[OD]);
-    da_sel[3] = dram_selector(pos, nest2, prefix_mask, DI, DJ, DK, DL, lvl[OE]);
-    uint32_t dac_sel = 0, dac_opt = 4;                        // fused: DA_C = 0 (Sec. V-C)
-    if (!f) {
-        uint32_t out_k = dram_selector(pos, nest1, prefix_mask, DI, DL, DK, DJ, 0) & 1;
-        uint32_t in_j = (dram_selector(pos, nest2, prefix_mask, DI, DL, DK, DJ, 0) >> 1) & 1;
-        dac_sel = dac_opt = out_k | (in_j << 1);
-    }
-    // recomputation must revisit C tiles (j outside k) and needs an on-chip C
-    bool valid = !(r && (!f || pos[DK] > pos[DJ]));
+    int lvl[4];
+    for (int y = 0; y < 4; ++y) { lvl[y] = x % 5; x /= 5; }
+    const uint32_t rank = x % 24; x /= 24;
+    const uint32_t r = x & 1, f = x >> 1;
+    const RowTerms t = row_terms(rank, r, f, lvl);
     uint8_t sel[16];
-    sel[0] = (uint8_t)(ENT_BS_AB + bs_sel[OA] + 4 * bs_sel[OB]);
-    sel[1] = (uint8_t)(ENT_RET_DE + ret_sel[2] + 5 * ret_sel[3]);
-    sel[2] = (uint8_t)(ENT_BS_C + bs_sel[OC]);
-    sel[3] = (uint8_t)(ENT_BS_DE + bs_sel[OD] + 4 * bs_sel[OE]);
-    sel[4] = (uint8_t)(ENT_RET_AB + ret_sel[0] + 5 * ret_sel[1]);
-    sel[5] = (uint8_t)(ENT_DA_AB + da_sel[0] + 4 * da_sel[1]);
-    sel[6] = (uint8_t)(ENT_DA_DE + da_sel[2] + 4 * da_sel[3]);
-    sel[7] = (uint8_t)(ENT_DA_C + dac_opt);
-    sel[ROW_FLAGS] = (uint8_t)((valid ? 1u : 0u) | (r << 1) | (f << 2));
+    for (int k = 0; k < NSEL; ++k) sel[k] = (uint8_t)row_entry(t, k);
+    sel[ROW_FLAGS] = (uint8_t)((t.valid ? 1u : 0u) | (r << 1) | (f << 2));
     for (int k = ROW_FLAGS + 1; k < 16; ++k) sel[k] = 0;
 
     uint4 packed;
@@ -253,14 +155,7 @@ __global__ void k_build_rows(uint4 *enc, uint32_t *sig)
     packed.w = sel[12] | (sel[13] << 8) | (sel[14] << 16) | ((uint32_t)sel[15] << 24);
     enc[row] = packed;
 
-    // symbolic signature: one bit per optional factor of every term; a row whose bits are a
-    // subset of another's is no larger in any term, for every tiling (all factors are >= 1)
-    uint32_t s = 0;
-    for (int X = 0; X < 5; ++X) s |= bs_sel[X] << (2 * X);
-    s |= tau_bits << 10;
-    for (int y = 0; y < 4; ++y) s |= da_sel[y] << (14 + 2 * y);
-    s |= dac_sel << 22;
-    sig[row] = valid ? s : 0xFFFFFFFFu;
+    sig[row] = t.valid ? row_signature(t) : 0xFFFFFFFFu;
 }
 
 // Eq. (12) in a form that also protects index ties: row v goes if some row u of its group with a
@@ -1686,6 +1581,13 @@ __global__ void k_clear_words(uint32_t *words, uint32_t n)
 {
     const uint32_t a = blockIdx.x * blockDim.x + threadIdx.x;
     if (a < n) words[a] = 0;
+}
+
+// words[0 .. n) = value
+__global__ void k_fill_words64(unsigned long long *words, uint64_t n, unsigned long long value)
+{
+    const uint64_t a = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (a < n) words[a] = value;
 }
 
 // the search's final record -> an mmee_result in the caller's device buffer

@@ -82,6 +82,7 @@ struct ModelConst {
     double dram_b, dram_y, dram_c;   // general DRAM time (dram_time_general): dram_bw / 2^k in [1, 2), 1 / dram_b rounded once,
                         // c_lat / 2^k; bandwidth 0: 1, 1, 0
     double gb_k;        // word / gb_bw when the buffer bandwidth is a power of two, else unused
+    double gb_b, gb_y, gb_scale;     // the same for the buffer bandwidth, 2^-k apart from c_lat (combo_time); bandwidth 0: 1, 1, 0
     // 1 / pe_rows, 1 / pe_cols, 1 / (pe_cols * g_words), rounded once: floor((a - 0.5) * 1/b) + 1 is
     // ceil(a / b) for every 1 <= a < 2^32 (a - 0.5 over b stays 0.5 / b away from whole numbers, the two
     // roundings move it by less than that)

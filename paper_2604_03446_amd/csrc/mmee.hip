@@ -4,6 +4,7 @@
 // Every number the calls return is produced by the kernels in kernels.h.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <chrono>
 #include <cmath>
 #include <cstdio>
@@ -14,6 +15,7 @@
 
 #include "kernels.h"
 #include "batch.h"
+#include "pruned.h"
 
 // ---- fixed scratch of the entry point that allocates nothing (mmee_search_noalloc) ------------
 // One array per GPU, held from the moment the library is loaded until the process ends.  In host
@@ -100,9 +102,13 @@ struct State {
     Key *item_keys = nullptr;
     size_t item_cap = 0;
     uint32_t task_lo[BATCH_WAVES] = {}, task_cnt[BATCH_WAVES] = {}, task_g[BATCH_WAVES] = {};
-    uint32_t *batch_row_off = nullptr, *batch_row_df = nullptr, *batch_cmap = nullptr;
-    uint32_t batch_rows = 0, batch_n_used = 0;
-    bool batch_ok = false;      // the surviving rows fit the batched kernel's fixed LDS layout
+    // pruned search of many problems on one shape: problem descriptions (pinned staging + device copy), the lowest
+    // published values per result slot
+    unsigned char *desc_host = nullptr, *desc_dev = nullptr;
+    size_t desc_cap = 0;
+    void *block_records = nullptr;              // what the blocks of a pruned search leave for the reduction
+    size_t block_records_cap = 0;
+    unsigned long long *pruned_hints = nullptr;
 } S;
 
 // The device buffers one search pass works in.  The allocating entry points fill this from the
@@ -259,6 +265,12 @@ int make_plan(const mmee_chain *w, const mmee_hw *hw, Plan &p)
     mc.g_words = hw->rf_bytes / w->word_bytes / 2;
     mc.gb_pow2 = hw->gb_bw > 0.0 && std::frexp(hw->gb_bw, &ex) == 0.5 ? 1u : 0u;
     mc.gb_k = mc.gb_pow2 ? mc.word / hw->gb_bw : 0.0;
+    mc.gb_b = mc.gb_y = 1.0;
+    if (hw->gb_bw > 0.0) {
+        mc.gb_b = 2.0 * std::frexp(hw->gb_bw, &ex);
+        mc.gb_y = 1.0 / mc.gb_b;
+        mc.gb_scale = std::ldexp(1.0, 1 - ex);
+    }
     mc.rcp_rows = 1.0 / (double)mc.pe_rows;
     mc.rcp_cols = 1.0 / (double)mc.pe_cols;
     mc.rcp_cols_g = 1.0 / ((double)mc.pe_cols * (double)mc.g_words);
@@ -269,6 +281,24 @@ int make_plan(const mmee_chain *w, const mmee_hw *hw, Plan &p)
 }
 
 // ---- device state ------------------------------------------------------------
+
+// The pruned search has the kept rows compiled in (rows.h); they must be the ones the device's offline stage found.
+int check_kept_rows(const uint32_t *rows_dev, const uint32_t (&counts)[4])
+{
+    const uint32_t group_of[LEAST_CLASSES] = {0, 2, 3};      // class (r, f) -> g = r + 2 f
+    bool same = counts[1] == 0;
+    for (int c = 0; same && c < LEAST_CLASSES; ++c) {
+        const uint32_t g = group_of[c], n = KEPT.rows[c];
+        uint32_t rows[KEPT_ALL];
+        same = counts[g] == n;
+        if (!same) break;
+        HIP_TRY(hipMemcpy(rows, rows_dev + (size_t)g * ROWS_PER_GROUP, sizeof(uint32_t) * n, hipMemcpyDeviceToHost));
+        same = std::memcmp(rows, KEPT.number + KEPT.first[c], sizeof(uint32_t) * n) == 0;
+    }
+    if (same) return MMEE_OK;
+    std::snprintf(g_last_error, sizeof(g_last_error), "the offline stage's rows are not the compiled ones");
+    return MMEE_EDEVICE;
+}
 
 int ensure_ready()
 {
@@ -352,45 +382,8 @@ int ensure_ready()
         S.n_cls = (uint32_t)cls.size();
     }
     {
-        // Batched search over the surviving rows.  The rows refer to a subset of the table entries only:
-        // the kernel stages just those, and a row becomes the eight byte offsets of its values in that
-        // compact table.  Lists follow each other group by group.
-        std::vector<uint4> rows;
-        std::vector<uint32_t> group_first(N_GROUPS + 1, 0);
-        for (uint32_t g = 0; g < N_GROUPS; ++g) {
-            const uint32_t n = S.counts[1][g];
-            group_first[g] = (uint32_t)rows.size();
-            if (!n) continue;
-            rows.resize(rows.size() + n);
-            HIP_TRY(hipMemcpy(rows.data() + group_first[g], S.row_enc[1] + (size_t)g * ROWS_PER_GROUP, sizeof(uint4) * n,
-                              hipMemcpyDeviceToHost));
-        }
-        group_first[N_GROUPS] = (uint32_t)rows.size();
-        auto sel_at = [](const uint4 &e, int k) { const uint32_t w = k < 4 ? e.x : e.y; return (w >> (8 * (k & 3))) & 0xFFu; };
-        std::vector<int> compact(NENT, -1);
-        std::vector<uint32_t> used;
-        for (const uint4 &e : rows)
-            for (int k = 0; k < NSEL; ++k) compact[sel_at(e, k)] = 0;
-        for (uint32_t ent = 0; ent < (uint32_t)NENT; ++ent)
-            if (compact[ent] == 0) { compact[ent] = (int)used.size(); used.push_back(ent); }
-        S.batch_rows = (uint32_t)rows.size();
-        S.batch_n_used = (uint32_t)used.size();
-        S.batch_ok = !rows.empty() && rows.size() <= BATCH_MAX_ROWS && used.size() <= BATCH_MAX_USED;
-        if (S.batch_ok) {
-            std::vector<uint32_t> off(rows.size() * 8), df(rows.size());
-            for (size_t i = 0; i < rows.size(); ++i) {
-                for (int k = 0; k < NSEL; ++k) off[i * 8 + k] = (uint32_t)compact[sel_at(rows[i], k)] * BATCH_TC * 8u;
-                df[i] = rows[i].w;
-            }
-            HIP_TRY(hipMalloc(&S.batch_row_off, sizeof(uint32_t) * off.size()));
-            HIP_TRY(hipMalloc(&S.batch_row_df, sizeof(uint32_t) * df.size()));
-            std::vector<uint32_t> cmap(NENT);
-            for (int ent = 0; ent < NENT; ++ent) cmap[ent] = compact[ent] < 0 ? 0xFFFFu : (uint32_t)compact[ent];
-            HIP_TRY(hipMalloc(&S.batch_cmap, sizeof(uint32_t) * NENT));
-            HIP_TRY(hipMemcpy(S.batch_row_off, off.data(), sizeof(uint32_t) * off.size(), hipMemcpyHostToDevice));
-            HIP_TRY(hipMemcpy(S.batch_row_df, df.data(), sizeof(uint32_t) * df.size(), hipMemcpyHostToDevice));
-            HIP_TRY(hipMemcpy(S.batch_cmap, cmap.data(), sizeof(uint32_t) * NENT, hipMemcpyHostToDevice));
-        }
+        const int rc = check_kept_rows(S.rows[1], S.counts[1]);
+        if (rc) return rc;
         // share the rows of each group out over the waves of a block, every wave a contiguous piece of
         // one group's list (rows of one group share r and f)
         uint32_t waves[N_GROUPS] = {0, 0, 0, 0}, taken = 0;
@@ -406,13 +399,15 @@ int ensure_ready()
             if (worst == N_GROUPS || most <= 1) break;
             ++waves[worst]; ++taken;
         }
-        uint32_t wv = 0;
-        for (uint32_t g = 0; g < N_GROUPS; ++g)
+        uint32_t wv = 0, group_first = 0;
+        for (uint32_t g = 0; g < N_GROUPS; ++g) {
             for (uint32_t k = 0; k < waves[g]; ++k, ++wv) {
                 const uint32_t n = S.counts[1][g], lo = (uint32_t)((uint64_t)n * k / waves[g]),
                                hi = (uint32_t)((uint64_t)n * (k + 1) / waves[g]);
-                S.task_lo[wv] = group_first[g] + lo; S.task_cnt[wv] = hi - lo; S.task_g[wv] = g;
+                S.task_lo[wv] = group_first + lo; S.task_cnt[wv] = hi - lo; S.task_g[wv] = g;
             }
+            group_first += S.counts[1][g];
+        }
         for (; wv < BATCH_WAVES; ++wv) { S.task_lo[wv] = 0; S.task_cnt[wv] = 0; S.task_g[wv] = 0; }
     }
     S.ready = true;
@@ -446,11 +441,16 @@ int ensure_slots(size_t n)
     if (n <= S.slots) return MMEE_OK;
     if (S.final_host) {
         HIP_TRY(hipStreamSynchronize(S.stream));
-        (void)hipFree(S.dv_dev);
+        (void)hipFree(S.dv_dev); (void)hipFree(S.pruned_hints);
         (void)hipHostFree(S.final_host);
     }
-    S.slots = 0; S.final_host = nullptr; S.final_map = nullptr; S.dv_dev = nullptr;
+    S.slots = 0; S.final_host = nullptr; S.final_map = nullptr; S.dv_dev = nullptr; S.pruned_hints = nullptr;
     HIP_TRY(hipMalloc(&S.dv_dev, sizeof(DivTable) * n));
+    // +inf until a launch lowers them; the launch's finish puts +inf back
+    HIP_TRY(hipMalloc(&S.pruned_hints, sizeof(unsigned long long) * N_OBJ * n));
+    hipLaunchKernelGGL(k_fill_words64, dim3((uint32_t)((N_OBJ * n + 255) / 256)), dim3(256), 0, S.stream, S.pruned_hints, N_OBJ * (uint64_t)n,
+                       INF_BITS);
+    HIP_TRY(hipGetLastError());
     HIP_TRY(hipHostMalloc(&S.final_host, sizeof(FinalRecord) * N_OBJ * n, hipHostMallocMapped));
     HIP_TRY(hipHostGetDevicePointer(reinterpret_cast<void **>(&S.final_map), S.final_host, 0));
     while (S.events.size() < 2 * n) {
@@ -784,7 +784,7 @@ int enqueue_batches(std::vector<BatchEntry> &entries, uint32_t flags, size_t ev_
             if (c.mask == e.mask && c.fast == fast && c.regroup == regroup) v = &c;
         if (!v) { variants.push_back(Variant{e.mask, fast, regroup, {}, 0, 1}); v = &variants.back(); }
         v->members.push_back(k);
-        v->items += (e.plan->T + BATCH_TC - 1) / BATCH_TC;
+        v->items += (e.plan->T + PRUNED_TC - 1) / PRUNED_TC;
     }
     for (Variant &v : variants) {
         // a launch with few chunks leaves most of the chip idle: let several blocks share a chunk's rows
@@ -796,7 +796,7 @@ int enqueue_batches(std::vector<BatchEntry> &entries, uint32_t flags, size_t ev_
     auto fill_head = [&](BatchProblemHead &h, uint32_t *list, const BatchEntry &e, uint32_t first_item, uint32_t split) {
         h.mc = e.mc;
         h.first_item = first_item;
-        h.n_work = (uint32_t)((e.plan->T + BATCH_TC - 1) / BATCH_TC) * split;
+        h.n_work = (uint32_t)((e.plan->T + PRUNED_TC - 1) / PRUNED_TC) * split;
         h.slot = (uint32_t)e.slot;
         h.pad_ = 0;
         uint32_t at = 0;
@@ -861,8 +861,6 @@ int enqueue_batches(std::vector<BatchEntry> &entries, uint32_t flags, size_t ev_
         }
         a.n_prob = (uint32_t)L.n_prob; a.n_items = (uint32_t)L.n_items;
         a.enc = S.enc;
-        a.row_off = S.batch_row_off; a.row_df = S.batch_row_df; a.cmap = S.batch_cmap;
-        a.n_rows = S.batch_rows; a.n_used = S.batch_n_used;
         // every wave's piece of its group's list, cut once more into one sub-piece per row share
         a.split = v.split;
         for (a.split_log2 = 0; (1u << a.split_log2) < v.split; ++a.split_log2) {}
@@ -891,6 +889,256 @@ int enqueue_batches(std::vector<BatchEntry> &entries, uint32_t flags, size_t ev_
     HIP_TRY(hipEventRecord(S.events[2 * ev_slot + 1], S.stream));
     return MMEE_OK;
 }
+
+// ---- pruned search ---------------------------------------------------------------------------
+
+static_assert(sizeof(PrunedArgs) <= 4096, "kernel arguments are limited to 4 KiB");
+
+// One problem of a pruned search, as the host sees it.
+struct PrunedEntry {
+    const Plan *plan;
+    int mask;
+    uint32_t slot;          // result slot: its N_OBJ final records
+};
+
+// Where one launch of the pruned search works; the allocating entry points fill it from State.
+struct PrunedBufs {
+    const uint4 *enc;
+    unsigned long long *hints;
+    FinalRecord *final_out;
+};
+
+DigitConst digit_constants(const DivTable &dv)
+{
+    DigitConst d;
+    double radix = 1.0;
+    for (int q = 0; q < 4; ++q) {
+        d.rcp_radix[q] = 1.0 / radix;
+        d.rcp_n[q] = 1.0 / (double)dv.ndiv[q];
+        radix *= (double)dv.ndiv[q];
+    }
+    return d;
+}
+
+// extents and operand sizes (A, B, D, E, C) as fp64; exact: all counts of a problem are below 2^53
+void shape_constants(const DivTable &dv, double (&extent)[4], double (&size)[5])
+{
+    for (int q = 0; q < 4; ++q) extent[q] = (double)dv.X[q];
+    size[0] = extent[DI] * extent[DK]; size[1] = extent[DK] * extent[DL]; size[2] = extent[DL] * extent[DJ];
+    size[3] = extent[DI] * extent[DJ]; size[4] = extent[DI] * extent[DL];
+}
+
+uint32_t list_length(const DivTable &dv) { return dv.ndiv[0] + dv.ndiv[1] + dv.ndiv[2] + dv.ndiv[3]; }
+void pack_lists(const DivTable &dv, uint32_t *list)
+{
+    for (int q = 0; q < 4; ++q) {
+        std::memcpy(list, dv.div[q], sizeof(uint32_t) * dv.ndiv[q]);
+        list += dv.ndiv[q];
+    }
+}
+
+// Groups of problems with one shape, laid out as the kernel reads them.
+struct PrunedLayout {
+    std::vector<unsigned char> desc;
+    uint32_t n_groups = 0, n_members = 0, members_off = 0, n_items = 0, stride = 0;
+};
+
+// entries[order[k]], k in [lo, hi): the groups of one launch
+struct PrunedSlice { uint32_t lo, hi, n_caps; };
+
+bool same_shape(const Plan &a, const Plan &b)
+{
+    // (extents and divisor counts settle the divisor lists: two modes with equal counts list the same divisors)
+    return std::memcmp(a.dv.X, b.dv.X, sizeof(a.dv.X)) == 0 && std::memcmp(a.dv.ndiv, b.dv.ndiv, sizeof(a.dv.ndiv)) == 0;
+}
+
+// Whether to share the row side among problems of a shape.  Per chunk of 64 tilings k_search_batch takes about 6500 wave
+// instructions per problem, k_search_pruned 3000 per four capacities and 800 per problem; below four problems a
+// shape it does not pay, and small launches are quicker in k_search_batch (pruned.h).
+bool worth_sharing(const std::vector<PrunedEntry> &entries);
+
+// Problems of one shape become groups of at most PRUNED_MEMBERS, by ascending capacity.
+void pruned_slices(const std::vector<PrunedEntry> &entries, std::vector<uint32_t> &order, std::vector<PrunedSlice> &slices)
+{
+    // shapes in order of first appearance, through a small open-addressed table
+    std::vector<uint32_t> head, shape_of(entries.size()), count;
+    size_t cap = 16;
+    while (cap < 2 * entries.size()) cap *= 2;
+    std::vector<uint32_t> table(cap, 0xFFFFFFFFu);
+    for (uint32_t k = 0; k < entries.size(); ++k) {
+        const DivTable &dv = entries[k].plan->dv;
+        uint64_t h = 0x9E3779B97F4A7C15ull;
+        for (int q = 0; q < 4; ++q) h = (h ^ (dv.X[q] + ((uint64_t)dv.ndiv[q] << 32))) * 0xBF58476D1CE4E5B9ull;
+        size_t at = (h >> 32) & (cap - 1);
+        while (table[at] != 0xFFFFFFFFu && !same_shape(*entries[head[table[at]]].plan, *entries[k].plan)) at = (at + 1) & (cap - 1);
+        if (table[at] == 0xFFFFFFFFu) { table[at] = (uint32_t)head.size(); head.push_back(k); count.push_back(0); }
+        shape_of[k] = table[at];
+        ++count[shape_of[k]];
+    }
+    std::vector<uint32_t> at(head.size() + 1, 0);
+    for (size_t g = 0; g < head.size(); ++g) at[g + 1] = at[g] + count[g];
+    order.resize(entries.size());
+    std::vector<uint32_t> next(at.begin(), at.end() - 1);
+    for (uint32_t k = 0; k < entries.size(); ++k) order[next[shape_of[k]]++] = k;
+    auto cap_of = [&](uint32_t k) { return entries[order[k]].plan->mc.cap_words; };
+    slices.clear();
+    for (size_t g = 0; g < head.size(); ++g) {
+        std::sort(order.begin() + at[g], order.begin() + at[g + 1], [&](uint32_t a, uint32_t b) {
+            const double ca = entries[a].plan->mc.cap_words, cb = entries[b].plan->mc.cap_words;
+            return ca != cb ? ca < cb : a < b;
+        });
+        for (uint32_t lo = at[g]; lo < at[g + 1]; lo += PRUNED_MEMBERS) {
+            PrunedSlice sl{lo, std::min<uint32_t>(lo + PRUNED_MEMBERS, at[g + 1]), 1};
+            for (uint32_t k = lo + 1; k < sl.hi; ++k) sl.n_caps += cap_of(k) != cap_of(k - 1);
+            slices.push_back(sl);
+        }
+    }
+}
+
+bool worth_sharing(const std::vector<PrunedEntry> &entries)
+{
+    if (entries.size() < 4) return false;
+    std::vector<uint32_t> order;
+    std::vector<PrunedSlice> slices;
+    pruned_slices(entries, order, slices);
+    return entries.size() >= 4 * slices.size();
+}
+
+void pruned_layout(const std::vector<PrunedEntry> &entries, const std::vector<uint32_t> &order, const std::vector<PrunedSlice> &slices,
+                   PrunedLayout &out)
+{
+    auto up16 = [](size_t x) { return (x + 15) & ~(size_t)15; };
+    size_t n_members = 0, n_caps = 0, n_list = 0;
+    out.stride = 0;
+    for (const PrunedSlice &sl : slices) {
+        const DivTable &dv = entries[order[sl.lo]].plan->dv;
+        n_members += sl.hi - sl.lo;
+        n_caps += sl.n_caps;
+        n_list += list_length(dv);
+        out.stride = std::max(out.stride, sl.hi - sl.lo);
+    }
+    const size_t members_off = up16(sizeof(PrunedGroup) * slices.size());
+    size_t caps_off = up16(members_off + sizeof(PrunedMember) * n_members), list_off = up16(caps_off + sizeof(double) * n_caps);
+    out.desc.resize(up16(list_off + sizeof(uint32_t) * n_list));
+    out.n_groups = (uint32_t)slices.size();
+    out.n_members = (uint32_t)n_members;
+    out.members_off = (uint32_t)members_off;
+    unsigned char *base = out.desc.data();
+    PrunedGroup *groups = reinterpret_cast<PrunedGroup *>(base);
+    PrunedMember *members = reinterpret_cast<PrunedMember *>(base + members_off);
+    uint32_t item = 0, member = 0;
+    for (size_t g = 0; g < slices.size(); ++g) {
+        const PrunedSlice &sl = slices[g];
+        const Plan &p = *entries[order[sl.lo]].plan;
+        PrunedGroup G;
+        std::memset(&G, 0, sizeof(G));
+        G.first_item = item;
+        G.n_items = (uint32_t)((p.T + PRUNED_TC - 1) / PRUNED_TC);
+        G.member0 = member;
+        G.n_members = sl.hi - sl.lo;
+        G.n_caps = sl.n_caps;
+        G.caps_off = (uint32_t)caps_off;
+        G.T = (uint32_t)p.T;
+        G.list_off = (uint32_t)list_off;
+        double *caps = reinterpret_cast<double *>(base + caps_off);
+        uint32_t cap = 0;
+        for (uint32_t k = sl.lo; k < sl.hi; ++k) {
+            const PrunedEntry &e = entries[order[k]];
+            if (k == sl.lo) caps[0] = e.plan->mc.cap_words;
+            else if (e.plan->mc.cap_words != caps[cap]) caps[++cap] = e.plan->mc.cap_words;
+            PrunedMember &m = members[member++];
+            m.mc = e.plan->mc;
+            m.slot = e.slot; m.cap = cap; m.mask = (uint32_t)e.mask; m.group = (uint32_t)g;
+        }
+        uint32_t *list = reinterpret_cast<uint32_t *>(base + list_off);
+        for (int q = 0; q < 4; ++q) {
+            G.X[q] = p.dv.X[q];
+            G.ndiv[q] = p.dv.ndiv[q];
+        }
+        G.dg = digit_constants(p.dv);
+        shape_constants(p.dv, G.extent, G.size);
+        pack_lists(p.dv, list);
+        list += list_length(p.dv);
+        caps_off += sizeof(double) * sl.n_caps;
+        list_off = (size_t)(reinterpret_cast<unsigned char *>(list) - base);
+        item += G.n_items;
+        groups[g] = G;
+    }
+    out.n_items = item;
+}
+
+// Launch the search and its finish.  desc_dev: the layout's descriptions in device memory; null: they fit the
+// kernel arguments.
+int launch_pruned(const PrunedBufs &B, const PrunedLayout &l, const unsigned char *desc_dev, Key *keys)
+{
+    static PrunedArgs a;                       // (callers hold g_lock)
+    std::memset(&a, 0, offsetof(PrunedArgs, inl));
+    a.desc = desc_dev;
+    if (!desc_dev) {
+        if (l.desc.size() > sizeof(a.inl)) return MMEE_EINVAL;
+        std::memcpy(a.inl, l.desc.data(), l.desc.size());
+    }
+    a.n_groups = l.n_groups; a.n_items = l.n_items;
+    a.members_off = l.members_off; a.n_members = l.n_members; a.stride = l.stride;
+    a.enc = B.enc; a.keys = keys; a.hints = B.hints; a.final_out = B.final_out;
+    hipLaunchKernelGGL(k_search_pruned, dim3(l.n_items), dim3(PRUNED_THREADS), 0, S.stream, a);
+    hipLaunchKernelGGL(k_pruned_finish, dim3(l.n_members), dim3(256), 0, S.stream, a);
+    HIP_TRY(hipGetLastError());
+    return MMEE_OK;
+}
+
+int ensure_desc(size_t bytes)
+{
+    if (bytes <= S.desc_cap) return MMEE_OK;
+    if (S.desc_host) { HIP_TRY(hipStreamSynchronize(S.stream)); (void)hipHostFree(S.desc_host); (void)hipFree(S.desc_dev); }
+    S.desc_host = nullptr; S.desc_dev = nullptr; S.desc_cap = 0;
+    const size_t cap = std::max<size_t>(bytes * 2, 1 << 16);
+    HIP_TRY(hipHostMalloc(&S.desc_host, cap, hipHostMallocDefault));
+    HIP_TRY(hipMalloc(&S.desc_dev, cap));
+    S.desc_cap = cap;
+    return MMEE_OK;
+}
+
+int ensure_block_records(size_t bytes)
+{
+    if (bytes <= S.block_records_cap) return MMEE_OK;
+    if (S.block_records) { HIP_TRY(hipStreamSynchronize(S.stream)); (void)hipFree(S.block_records); }
+    S.block_records = nullptr; S.block_records_cap = 0;
+    const size_t cap = std::max<size_t>(bytes + bytes / 2, 1 << 20);
+    HIP_TRY(hipMalloc(&S.block_records, cap));
+    S.block_records_cap = cap;
+    return MMEE_OK;
+}
+
+// Enqueue pruned searches.  Events of slot `ev_slot` bracket it all.
+int enqueue_pruned(const std::vector<PrunedEntry> &entries, size_t ev_slot)
+{
+    if (entries.empty()) return MMEE_OK;
+    std::vector<uint32_t> order;
+    std::vector<PrunedSlice> slices;
+    pruned_slices(entries, order, slices);
+    uint64_t items = 0;
+    for (const PrunedSlice &sl : slices) items += (entries[order[sl.lo]].plan->T + PRUNED_TC - 1) / PRUNED_TC;
+    if (items > 0x7fffffffull) return MMEE_EINVAL;
+    PrunedLayout l;
+    pruned_layout(entries, order, slices, l);
+    const bool inside = l.desc.size() <= (size_t)PRUNED_INLINE;
+    int rc = inside ? MMEE_OK : ensure_desc(l.desc.size());
+    if (!rc) rc = ensure_block_records((size_t)l.n_items * l.stride * N_OBJ * sizeof(Key));
+    if (rc) return rc;
+    HIP_TRY(hipEventRecord(S.events[2 * ev_slot], S.stream));
+    if (!inside) {
+        std::memcpy(S.desc_host, l.desc.data(), l.desc.size());
+        HIP_TRY(hipMemcpyAsync(S.desc_dev, S.desc_host, l.desc.size(), hipMemcpyHostToDevice, S.stream));
+    }
+    const PrunedBufs B = {S.enc, S.pruned_hints, S.final_map};
+    rc = launch_pruned(B, l, inside ? nullptr : S.desc_dev, static_cast<Key *>(S.block_records));
+    if (rc) return rc;
+    HIP_TRY(hipEventRecord(S.events[2 * ev_slot + 1], S.stream));
+    return MMEE_OK;
+}
+
+uint64_t kept_row_count() { return (uint64_t)S.counts[1][0] + S.counts[1][1] + S.counts[1][2] + S.counts[1][3]; }
 
 int unpack_result(const Plan &p, size_t slot, int objective, uint64_t evaluated, double seconds, double ksec,
                   mmee_result *out)
@@ -1136,7 +1384,7 @@ int mmee_chain_search_many(const mmee_chain *w, const mmee_hw *hw, const int *ob
     // group neighbouring entries that describe the same problem into one pass
     struct Pass {
         uint32_t first, n; int mask; Plan plan; int rc; uint64_t evaluated; bool unproven;
-        bool batched = false; size_t ev_slot = 0;
+        size_t ev_slot = 0;
     };
     std::vector<Pass> passes;
     std::vector<int> codes(count, MMEE_OK);
@@ -1159,17 +1407,29 @@ int mmee_chain_search_many(const mmee_chain *w, const mmee_hw *hw, const int *ob
     }
     rc = ensure_slots(passes.size());
     if (rc) return rc;
-    // Pruned searches whose key set the batched kernel is built for share launches; everything else
-    // (the full row set, other key sets) goes problem by problem.  `round_flags` adds
-    // MMEE_SEARCH_ORDERED_SUM on the second round, which repeats what the first could not prove.
+    // Pruned searches share launches: problems on few shapes the tables and the row side too (enqueue_pruned), others
+    // the launch only (enqueue_batches), where the kernel is built for their key set.  Everything else goes
+    // problem by problem.  `round_flags` adds MMEE_SEARCH_ORDERED_SUM on the second round, which repeats what the
+    // first could not prove.
     auto run_round = [&](uint32_t round_flags, bool only_unproven) -> int {
+        std::vector<PrunedEntry> shared;
         std::vector<BatchEntry> batch;
         std::vector<size_t> batch_pass;
+        auto takes_part = [&](const Pass &ps) { return ps.rc == MMEE_OK && (!only_unproven || ps.unproven); };
+        if (!(round_flags & MMEE_SEARCH_EXHAUSTIVE)) {
+            for (size_t s = 0; s < passes.size(); ++s)
+                if (takes_part(passes[s])) shared.push_back(PrunedEntry{&passes[s].plan, passes[s].mask, (uint32_t)s});
+            if (!worth_sharing(shared)) shared.clear();
+        }
         for (size_t s = 0; s < passes.size(); ++s) {
             Pass &ps = passes[s];
-            if (ps.rc != MMEE_OK || (only_unproven && !ps.unproven)) continue;
-            ps.batched = S.batch_ok && !(round_flags & MMEE_SEARCH_EXHAUSTIVE) && batch_mask(ps.mask);
-            if (ps.batched) {
+            if (!takes_part(ps)) continue;
+            ps.ev_slot = s;
+            if (!shared.empty()) {
+                ps.ev_slot = shared[0].slot;
+                ps.evaluated = kept_row_count() * ps.plan.T * 9ull;
+                ps.unproven = false;
+            } else if (!(round_flags & MMEE_SEARCH_EXHAUSTIVE) && batch_mask(ps.mask)) {
                 BatchEntry e;
                 e.plan = &ps.plan; e.mask = ps.mask; e.slot = s; e.unproven = false; e.evaluated = 0;
                 batch.push_back(e);
@@ -1180,6 +1440,10 @@ int mmee_chain_search_many(const mmee_chain *w, const mmee_hw *hw, const int *ob
                                        only_unproven ? nullptr : &unproven);
                 ps.unproven = unproven;
             }
+        }
+        if (!shared.empty()) {
+            const int src = enqueue_pruned(shared, shared[0].slot);
+            for (const PrunedEntry &e : shared) passes[e.slot].rc = src;
         }
         if (!batch.empty()) {
             int brc = enqueue_batches(batch, round_flags, batch_pass[0]);
@@ -1223,8 +1487,7 @@ int mmee_chain_search_many(const mmee_chain *w, const mmee_hw *hw, const int *ob
     for (size_t s = 0; s < passes.size(); ++s) {
         Pass &ps = passes[s];
         float ms = 0.f;
-        // a batched pass reports the device time of the launches it shared
-        const size_t ev = ps.batched ? ps.ev_slot : s;
+        const size_t ev = ps.ev_slot;                        // a pass reports the device time of the launches it shared
         if (ps.rc == MMEE_OK) (void)hipEventElapsedTime(&ms, S.events[2 * ev], S.events[2 * ev + 1]);
         for (uint32_t a = ps.first; a < ps.first + ps.n; ++a) {
             int code = codes[a] ? codes[a] : ps.rc;
@@ -1478,7 +1741,8 @@ void mmee_shutdown(void)
     if (S.final_host) (void)hipHostFree(S.final_host);
     if (S.batch_host) (void)hipHostFree(S.batch_host);
     (void)hipFree(S.batch_dev); (void)hipFree(S.item_keys);
-    (void)hipFree(S.batch_row_off); (void)hipFree(S.batch_row_df); (void)hipFree(S.batch_cmap);
+    if (S.desc_host) (void)hipHostFree(S.desc_host);
+    (void)hipFree(S.desc_dev); (void)hipFree(S.block_records); (void)hipFree(S.pruned_hints);
     for (hipEvent_t e : S.events) (void)hipEventDestroy(e);
     hipStream_t keep = S.stream;
     S = State();

@@ -1,0 +1,695 @@
+// The pruned search (Sec. VI-B) of many problems on few shapes, as a sweep over accelerators asks for it.
+//
+// For a fixed tiling, recomputation choice r and stationary combination every key is a monotone function of a
+// candidate's DRAM traffic: DRAM energy and DRAM time grow with it, every rounded sum, product and maximum they
+// pass through keeps the order, and the capacity test does not look at the combination.  Of the rows that fit,
+// the one with the least traffic therefore has the least cost under every combination and every key, bit for bit
+// the value that costing row by row gives.  (Rounding may give rows with more traffic the same cost: positions
+// are recovered by comparing costs, not traffic.)  So the search is, per tiling,
+//   1. the least traffic of each (r, f) class under the buffer capacity -- a matter of the workload's shape
+//      and the capacity alone, shared by every accelerator that is searched on that shape;
+//   2. the nine combinations on top of it, per accelerator.
+//
+// k_search_batch (batch.h) does both per problem and is bound by step 1: eight table values per row and tiling
+// from LDS, 270 rows, 32 LDS cycles each.  Here step 1 is done once per shape and distinct capacity, and without a
+// table: the rows are known at compile time (rows.h: 181 suffice), so they are straight-line code on one tiling per
+// lane, the operands' footprints and traffic options are registers, shared sums are formed once, and a row is
+// about four vector operations and three per capacity.
+//
+// A work item is (shape, chunk of 64 tilings), lane = tiling, one block.  The block decodes the chunk, its waves take
+// the classes under four capacities each (step 1), then the accelerators one wave each (step 2).  Positions: each
+// wave publishes its values, takes the launch-wide lowest ones back, and only a value that nothing published beats is
+// followed up: the lowest class (f, combination, r), then the first row, then the first tiling that reach it.  Each
+// item leaves one record per problem and key for k_pruned_finish.
+//
+// 64 accelerators x 8 attention shapes x 2 keys: 1.63 ms in k_search_batch, 0.28 ms here.  Bound by step 2's vector
+// issue (about 800 instructions per problem and chunk) at half the issue rate: two blocks per CU, reductions
+// across lanes between short stretches of arithmetic.  What k_search_batch keeps: calls whose problems share
+// little, where this kernel's step 1 would be done for one accelerator at a time, and it costs two launches of
+// more code (a single 1764-tiling problem: 17 us against 11).
+//
+// Included once by mmee.hip.
+#pragma once
+#include "boundary.h"
+
+namespace mmee {
+
+constexpr int PRUNED_THREADS = 512;          // two blocks per CU, four waves per SIMD
+constexpr int PRUNED_WAVES = PRUNED_THREADS / 64;
+constexpr int PRUNED_MEMBERS = 64;           // problems of one group at most
+constexpr int PRUNED_CAPS = 4;               // capacities one wave carries through a class's rows
+constexpr int PRUNED_ROUND = 16;             // capacities per round of a shared chunk
+constexpr int PRUNED_INLINE = 3000;          // bytes of problem descriptions that ride in the kernel arguments
+
+typedef ConstPtr<unsigned char> ConstBytes;
+
+// A group: problems with one shape and tiling mode.  Offsets are bytes from the start of the descriptions.
+struct PrunedGroup {
+    uint32_t first_item, n_items;            // its work items, one block each
+    uint32_t member0, n_members;             // its problems, by ascending capacity
+    uint32_t n_caps, caps_off;               // the distinct capacities, words, ascending (fp64)
+    uint32_t T, list_off;                    // tilings; the four divisor lists one after the other
+    uint32_t X[4], ndiv[4];                  // extents and divisor counts of i, k, l, j
+    DigitConst dg;
+    double extent[4], size[5];               // the extents, and the words of A, B, D, E, C: as fp64 they reach the kernel
+                                             // in scalar registers, where converting the integers would take vector ones
+};
+
+struct PrunedMember {
+    ModelConst mc;
+    uint32_t slot;                           // where its N_OBJ final records and hints are
+    uint32_t cap;                            // number of its capacity in the group's list
+    uint32_t mask;                           // keys asked for
+    uint32_t group;
+};
+
+struct PrunedArgs {
+    const unsigned char *desc;               // descriptions in device memory; null: in `inl`
+    uint32_t n_groups, n_items;
+    uint32_t members_off, n_members;
+    uint32_t stride;                         // problems the largest group holds: records per item
+    const uint4 *enc;                        // every encoded row (for the winner's record)
+    Key *keys;                               // [n_items][stride][N_OBJ]
+    unsigned long long *hints;               // [slot][N_OBJ] lowest value published so far (bit pattern); +inf between launches
+    FinalRecord *final_out;                  // [slot][N_OBJ]
+    alignas(16) unsigned char inl[PRUNED_INLINE];
+};
+
+__device__ __forceinline__ ConstBytes pruned_desc(const PrunedArgs &a)
+{
+    if (a.desc) return as_constant(a.desc);
+    return (ConstBytes)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(PrunedArgs, inl);
+}
+template <class T>
+__device__ __forceinline__ T read_const(ConstBytes p)        // wave-uniform: scalar loads
+{
+    static_assert(sizeof(T) % 4 == 0, "whole words");
+    uint32_t buf[sizeof(T) / 4];
+#pragma unroll
+    for (uint32_t k = 0; k < sizeof(T) / 4; ++k) buf[k] = ((ConstPtr<uint32_t>)p)[k];
+    T out;
+    __builtin_memcpy(&out, buf, sizeof(T));
+    return out;
+}
+
+// ---- step 1: the least traffic of a class ------------------------------------------------------
+
+// no row fits: larger than any traffic (below 2^53), still finite whatever its low word holds
+__device__ __forceinline__ double nothing_fits() { return __hiloint2double(0x7fe00000, 0); }
+constexpr double FITS_BELOW = 1e300;
+
+// every option of every term, for one tiling (the unused ones cost nothing once inlined)
+struct TermOptions {
+    double bs[4][4], c[4];                   // buffer sizes of A, B, D, E; of C
+    double da[4][4], dac[4];                 // DRAM words of A, B, D, E; of an unfused C
+};
+
+__device__ __forceinline__ TermOptions term_options(const TilingF &v, const double (&size)[5])
+{
+    TermOptions o;
+    const int own[4][2] = {{DI, DK}, {DK, DL}, {DL, DJ}, {DI, DJ}}, other[4][2] = {{DL, DJ}, {DI, DJ}, {DI, DK}, {DK, DL}};
+    auto fill = [](double (&out)[4], double base, double f0, double f1) {
+        out[0] = base; out[1] = base * f0; out[2] = base * f1; out[3] = out[1] * f1;
+    };
+#pragma unroll
+    for (int y = 0; y < 4; ++y) {
+        fill(o.bs[y], v.G[own[y][0]] * v.G[own[y][1]], v.D[own[y][0]], v.D[own[y][1]]);
+        fill(o.da[y], size[y], v.D[other[y][0]], v.D[other[y][1]]);
+    }
+    fill(o.c, v.G[DI] * v.G[DL], v.D[DI], v.D[DL]);
+#pragma unroll
+    for (int y = 0; y < 4; ++y) o.bs[y][3] = size[y];       // the whole matrix: uniform
+    o.c[3] = size[4];
+    const double whole = size[4];            // spilled by Op1, fetched by Op2, one softmax pass over S and P
+    o.dac[0] = whole * 4.0;
+    o.dac[1] = whole * (v.D[DK] + 3.0);
+    o.dac[2] = whole * (v.D[DJ] + 3.0);
+    o.dac[3] = whole * (v.D[DK] + v.D[DJ] + 2.0);
+    return o;
+}
+
+// Row I of class CLS under K capacities: Eq. (1), (2), (4), the mask, Eq. (7), the running minima.  All of it is
+// exact integers, so the association is free: sums that rows share are written alike and formed once.
+template <int CLS, int I, int K>
+__device__ __forceinline__ void least_row(const TermOptions &o, const double (&cap)[K], double (&least)[K])
+{
+    constexpr RowTerms R = LEAST[CLS].row[I];
+    double bs1 = (o.bs[0][R.bs[0]] + o.bs[1][R.bs[1]]) + o.c[R.c];
+    double bs2 = (o.bs[2][R.bs[2]] + o.bs[3][R.bs[3]]);
+    constexpr uint32_t DE = R.tau >> 2, AB = R.tau & 3;
+    if constexpr (DE == 3) bs1 = bs1 + (o.bs[2][R.bs[2]] + o.bs[3][R.bs[3]]);
+    else if constexpr (DE) bs1 = bs1 + o.bs[DE == 1 ? 2 : 3][R.bs[DE == 1 ? 2 : 3]];
+    if constexpr (AB == 0) bs2 = bs2 + o.c[R.c];
+    else if constexpr (AB == 3) bs2 = bs2 + ((o.bs[0][R.bs[0]] + o.bs[1][R.bs[1]]) + o.c[R.c]);
+    else bs2 = bs2 + (o.bs[AB - 1][R.bs[AB - 1]] + o.c[R.c]);
+    double da = o.da[0][R.da[0]] + o.da[1][R.da[1]];
+    if constexpr (R.dac != 4) da = da + o.dac[R.dac & 3];
+    da = da + (o.da[2][R.da[2]] + o.da[3][R.da[3]]);
+    const double bs = fmax(bs1, bs2);
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const bool fits = bs <= cap[k];
+        least[k] = fmin(least[k], __hiloint2double(fits ? __double2hiint(da) : 0x7fe00000, __double2loint(da)));
+    }
+}
+
+// rows [LO, LO + N) of a class
+template <int CLS, int LO, int K, int... I>
+__device__ __forceinline__ void least_rows_of(const TermOptions &o, const double (&cap)[K], double (&least)[K],
+                                              std::integer_sequence<int, I...>)
+{
+    (least_row<CLS, LO + I, K>(o, cap, least), ...);
+}
+
+constexpr int LEAST_RUN = 14;                // rows between two marks
+
+// Rows [LO, HI) of a class, a run at a time.  Options and sums are shared within a run only: without the mark
+// between runs (nothing but an opaque copy of the tiling) the compiler keeps every option and sum of a class for
+// its last use and spills hundreds of registers.
+template <int CLS, int LO, int HI, int K>
+__device__ __forceinline__ void least_runs(TilingF v, const double (&size)[5], const double (&cap)[K], double (&least)[K])
+{
+    constexpr int RUNS = (HI - LO + LEAST_RUN - 1) / LEAST_RUN, N = (HI - LO + RUNS - 1) / RUNS;
+    {
+        const TermOptions o = term_options(v, size);
+        least_rows_of<CLS, LO, K>(o, cap, least, std::make_integer_sequence<int, N>{});
+    }
+    if constexpr (RUNS > 1) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) { asm("" : "+v"(v.G[q])); asm("" : "+v"(v.D[q])); }
+        least_runs<CLS, LO + N, HI, K>(v, size, cap, least);
+    }
+}
+
+// piece PART of PARTS of a class's rows
+template <int CLS, int PART, int PARTS, int K>
+__device__ __forceinline__ void least_traffic(const TilingF &v, const double (&size)[5], const double (&cap)[K], double (&least)[K])
+{
+    constexpr int LO = LEAST[CLS].n * PART / PARTS, HI = LEAST[CLS].n * (PART + 1) / PARTS;
+#pragma unroll
+    for (int k = 0; k < K; ++k) least[k] = nothing_fits();
+    least_runs<CLS, LO, HI, K>(v, size, cap, least);
+}
+
+// one capacity: the 181 rows in eight pieces of 20 to 26, one per wave
+constexpr int PIECE_CLASS[PRUNED_WAVES] = {0, 0, 0, 1, 1, 2, 2, 2};
+
+// ---- step 2: an accelerator's costs on top of it -----------------------------------------------
+
+// What the two operators contribute per (r, stationary mode): words and cycles over all their tile stages.
+struct StageTerms {
+    double br1[2][3], cy1[2][3], br2[3], cy2[3];
+    double e_rf[2], e_mac[2];
+};
+
+__device__ __forceinline__ StageTerms stage_terms(const TilingF &v, const double (&X)[4], const ModelConst &mc)
+{
+    StageTerms t;
+    const double st1 = v.D[DI] * v.D[DK] * v.D[DL], st2 = v.D[DI] * v.D[DL] * v.D[DJ];
+#pragma unroll
+    for (uint32_t s = 0; s < 3; ++s) {
+        double words, cycles;
+        tile_cost_f64(v.G[DI], v.G[DK], v.G[DL], s, mc, words, cycles);
+        t.br1[0][s] = st1 * words; t.cy1[0][s] = st1 * cycles;
+        t.br1[1][s] = v.D[DJ] * t.br1[0][s]; t.cy1[1][s] = v.D[DJ] * t.cy1[0][s];
+        tile_cost_f64(v.G[DI], v.G[DL], v.G[DJ], s, mc, words, cycles);
+        t.br2[s] = st2 * words; t.cy2[s] = st2 * cycles;
+    }
+    const double m1 = X[DI] * X[DK] * X[DL], m2 = X[DI] * X[DL] * X[DJ], s1 = X[DI] * X[DL];
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        const double rho = r ? v.D[DJ] : 1.0;                // producer repeated per j tile (Sec. V-D)
+        const double mac = rho * m1 + m2;
+        t.e_rf[r] = mc.e_rf * (mc.BH * 3.0 * mac);
+        t.e_mac[r] = mc.e_mac * (mc.BH * (mac + (double)mc.c_softmax * (rho * s1)));
+    }
+    return t;
+}
+
+// max(compute cycles, buffer<->RF time) of combination s1 + 3 s2, without the factor c_lat: a minimum of such times times
+// c_lat is the minimum of the products, bit for bit.  POW2: the buffer bandwidth is a power of two, gb1 and gb2 are the
+// two operators' shares of the time (br1, br2 times one exact constant).
+template <bool POW2>
+__device__ __forceinline__ double combo_time(const StageTerms &t, const double (&gb1)[2][3], const double (&gb2)[3], const ModelConst &mc, int r, int c)
+{
+    const double cyc = t.cy1[r][c % 3] + t.cy2[c / 3];
+    if constexpr (POW2) return fmax(cyc, gb1[r][c % 3] + gb2[c / 3]);
+    else return fmax(cyc, buffer_time_general(mc, t.br1[r][c % 3] + t.br2[c / 3]));
+}
+
+// the row side of a candidate's costs, from its traffic; +inf both when no row fits
+struct RowSide { double words, e_part, time; };
+__device__ __forceinline__ RowSide row_side(const ModelConst &mc, double least)
+{
+    RowSide rs;
+    const bool fits = least < FITS_BELOW;
+    const double d = fits ? least : 0.0, over = fits ? 0.0 : pos_inf();
+    rs.words = mc.BH * d;
+    rs.e_part = fmax(mc.e_dram * rs.words, over);
+    rs.time = fmax(dram_time_general(mc, d), over);
+    return rs;
+}
+__device__ __forceinline__ double energy_of(const ModelConst &mc, const RowSide &rs, double br, double e_rf, double e_mac)
+{
+    double en = rs.e_part + mc.e_gb * (rs.words + mc.BH * br);
+    en = en + e_rf;
+    return en + e_mac;
+}
+
+// energy and latency of combination c under every class, from the classes' row sides.  Class numbers go up with the
+// index: f, then the combination, then r (f = 0: the combination; f = 1: 9 + 2 * combination + r).  One combination
+// per call, in loops that are not unrolled: nine of them side by side do not fit the registers.
+template <class Use>
+__device__ __forceinline__ void each_class(const TilingF &v, const double (&X)[4], const ModelConst &mc, const RowSide (&rs)[LEAST_CLASSES],
+                                           uint32_t c, Use &&use)
+{
+    double br1, cy1, br2, cy2;
+    tile_cost_f64(v.G[DI], v.G[DK], v.G[DL], c % 3, mc, br1, cy1);
+    tile_cost_f64(v.G[DI], v.G[DL], v.G[DJ], c / 3, mc, br2, cy2);
+#pragma unroll
+    for (uint32_t r = 0; r < 2; ++r) {
+        const ComboTerms ct = combo_terms_from(v, X, mc, r, br1, cy1, br2, cy2);
+#pragma unroll
+        for (uint32_t g = r ? 2 : 0; g < (r ? 3u : 2u); ++g)
+            use(g == 0 ? c : 9u + 2u * c + r, energy_of(mc, rs[g], ct.br, ct.e_rf_part, ct.e_mac_part), fmax(rs[g].time, ct.lat_part));
+    }
+}
+
+// key o of a candidate as a (primary, secondary) pair; the secondary is 0 for the scalar keys
+__device__ __forceinline__ void key_values(uint32_t o, double en, double lat, double &kp, double &ks)
+{
+    kp = o == MMEE_OBJ_ENERGY ? en : (o == MMEE_OBJ_EDP ? en * lat : lat);
+    ks = o == MMEE_OBJ_LATENCY_THEN_ENERGY ? en : 0.0;
+}
+
+// a wave's best of one key: value, lowest class that reaches it, and the tilings (lanes) that do in that class
+struct ClassBest {
+    double p, s;
+    uint32_t code;                            // 0xFFFFFFFF: nothing feasible
+    unsigned long long lanes;
+};
+
+__device__ __forceinline__ void class_of_code(uint32_t code, uint32_t &cls, uint32_t &combo)
+{
+    cls = code < 9 ? 0u : 1u + ((code - 9) & 1);
+    combo = code < 9 ? code : (code - 9) / 2;
+}
+
+// The first row (index order) of class b.code in which one of the tilings `b.lanes` reaches (b.p, b.s), at its lowest
+// such tiling: together the lowest index that does.  Rows are costed with the staged table; `offs` are their
+// offsets into it (KeptRows::off, in LDS or device memory).  The row's place in the class list and the
+// tiling's lane; row 0xFFFFFFFF: none.
+struct Found { uint32_t row, lane; };
+template <class Off4>
+__device__ __forceinline__ Found first_row(const double *tab, Off4 offs, const ComboTerms &ct, const ModelConst &mc, uint32_t nt, uint32_t o,
+                                           const ClassBest &b, uint32_t row_lo, uint32_t n_rows)
+{
+    typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
+    const uint32_t lane = threadIdx.x & 63;
+    Found f = {0xFFFFFFFFu, 0};
+    unsigned long long cands = b.lanes;
+    // does the row with these offsets reach the value for the tiling in column `col`?
+    auto reaches = [&](const char *col, const uint32_t (&off)[NSEL], double cap, double br, double time, double rf, double mac) {
+        double w[NSEL];
+#pragma unroll
+        for (int k = 0; k < NSEL; ++k) w[k] = *reinterpret_cast<const double *>(col + off[k]);
+        const bool ok = fmax(w[0] + w[2] + w[1], w[3] + w[2] + w[4]) <= cap;      // Eq. (1), (2), (4)
+        const RowSide rr = row_side(mc, ok ? w[5] + w[6] + w[7] : nothing_fits());  // Eq. (7)
+        double kp, ks;
+        key_values(o, energy_of(mc, rr, br, rf, mac), fmax(rr.time, time), kp, ks);
+        return kp == b.p && ks == b.s;
+    };
+    if (2u * (uint32_t)__popcll(cands) <= n_rows) {
+        // few tilings: one by one with lane = row, 64 rows of the class at a time
+        while (cands && f.row != 0) {
+            const uint32_t l = __builtin_amdgcn_readfirstlane((uint32_t)__ffsll((long long)cands) - 1u);
+            cands &= cands - 1;
+            const char *col = reinterpret_cast<const char *>(tab) + l * 8;
+            const double br_l = lane_value_f64(ct.br, l), time_l = lane_value_f64(ct.lat_part, l);
+            const double rf_l = lane_value_f64(ct.e_rf_part, l), mac_l = lane_value_f64(ct.e_mac_part, l);
+#pragma unroll 1
+            for (uint32_t i0 = 0; i0 < n_rows && i0 < f.row; i0 += 64) {
+                const uint32_t i = row_lo + min(i0 + lane, n_rows - 1);
+                const uint4 oa = offs(2 * i), ob = offs(2 * i + 1);
+                const uint32_t off[NSEL] = {oa.x, oa.y, oa.z, oa.w, ob.x, ob.y, ob.z, ob.w};
+                const unsigned long long hits = __ballot(reaches(col, off, mc.cap_words, br_l, time_l, rf_l, mac_l) && i0 + lane < n_rows);
+                if (!hits) continue;
+                const uint32_t at = i0 + (uint32_t)__ffsll((long long)hits) - 1u;
+                if (at < f.row) { f.row = at; f.lane = l; }  // ascending tilings: the lower one stays on equal rows
+                break;
+            }
+        }
+    } else {
+        // many: all at once, row by row; the first rows reach it where the cost hangs on something else than traffic
+        const double cap = lane < nt ? mc.cap_words : -1.0;
+        const char *col = reinterpret_cast<const char *>(tab) + lane * 8;
+        ConstPtr<u32x8> list = (ConstPtr<u32x8>)(&kept_dev.off[row_lo][0]);
+        u32x8 next = list[0];
+#pragma unroll 1
+        for (uint32_t i = 0; i < n_rows; ++i) {
+            const uint32_t off[NSEL] = {next[0], next[1], next[2], next[3], next[4], next[5], next[6], next[7]};
+            next = list[min(i + 1, n_rows - 1)];
+            const unsigned long long hits = __ballot(reaches(col, off, cap, ct.br, ct.lat_part, ct.e_rf_part, ct.e_mac_part));
+            if (!hits) continue;
+            f.row = i;
+            f.lane = (uint32_t)__ffsll((long long)hits) - 1u;
+            break;
+        }
+    }
+    return f;
+}
+
+// where a class's rows are in the lists
+__device__ __forceinline__ void rows_of_class(uint32_t cls, uint32_t &first, uint32_t &n)
+{
+    first = cls == 0 ? KEPT.first[0] : (cls == 1 ? KEPT.first[1] : KEPT.first[2]);
+    n = cls == 0 ? KEPT.rows[0] : (cls == 1 ? KEPT.rows[1] : KEPT.rows[2]);
+}
+
+// the lowest index a candidate of class `code` in the chunk at t0 can have
+__device__ __forceinline__ uint64_t lowest_index(const ModelConst &mc, uint32_t t0, uint32_t code)
+{
+    uint32_t cls, combo;
+    class_of_code(code, cls, combo);
+    const uint32_t row = cls == 0 ? KEPT.number[KEPT.first[0]] : (cls == 1 ? KEPT.number[KEPT.first[1]] : KEPT.number[KEPT.first[2]]);
+    return (uint64_t)t0 + (uint64_t)mc.T * (index_row_base(row) + 30000u * (combo % 3) + 90000u * (combo / 3));
+}
+
+// ---- many problems: chunks of a shape, shared by its accelerators -------------------------------
+// Capacities are taken PRUNED_CAPS at a time by a wave and PRUNED_ROUND at a time by a block: a row then costs four
+// operations plus three per capacity.
+__global__ __launch_bounds__(PRUNED_THREADS, 4) void k_search_pruned(PrunedArgs a)
+{
+    __shared__ double tab[KEPT_LINES * PRUNED_TC];           // recovery: entry-major, lane = tiling: conflict-free as it is
+    __shared__ double gd[8 * PRUNED_TC];                     // the chunk's boundary vectors: G[0..3], D[0..3] per tiling
+    __shared__ double least[PRUNED_ROUND * LEAST_CLASSES][PRUNED_TC];
+    __shared__ uint32_t div_lds[4 * MAXDIV];                 // the group's divisor lists
+    // per problem of the group and key, only touched by wave (member mod 8): the value, its class and tilings
+    __shared__ Key best[PRUNED_MEMBERS][N_OBJ];
+    __shared__ unsigned long long lanes_of[PRUNED_MEMBERS][N_OBJ];
+    __shared__ uint32_t code_of[PRUNED_MEMBERS][N_OBJ];
+
+    const double inf = pos_inf();
+    const uint32_t lane = threadIdx.x & 63;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t item = blockIdx.x;
+    ConstBytes desc = pruned_desc(a);
+    // the item's group: the last one whose first item is not beyond it
+    uint32_t gi;
+    {
+        uint32_t lo = 0, hi = a.n_groups;
+        while (hi - lo > 1) {
+            const uint32_t mid = (lo + hi) >> 1;
+            if (((ConstPtr<uint32_t>)(desc + mid * sizeof(PrunedGroup)))[0] <= item) lo = mid; else hi = mid;
+        }
+        gi = lo;
+    }
+    const PrunedGroup G = read_const<PrunedGroup>(desc + gi * sizeof(PrunedGroup));
+    ConstBytes members = desc + a.members_off + G.member0 * sizeof(PrunedMember);
+    ConstF64 caps = (ConstF64)(desc + G.caps_off);
+    {
+        ConstPtr<uint32_t> lists = (ConstPtr<uint32_t>)(desc + G.list_off);
+        for (uint32_t k = threadIdx.x; k < G.ndiv[0] + G.ndiv[1] + G.ndiv[2] + G.ndiv[3]; k += PRUNED_THREADS) div_lds[k] = lists[k];
+    }
+    const double (&X)[4] = G.extent;
+    __syncthreads();
+
+    const uint32_t t0 = (item - G.first_item) * PRUNED_TC, nt = min((uint32_t)PRUNED_TC, G.T - t0);
+    // ---- decode: dimension q of every tiling of the chunk by wave q (beyond the chunk: its last
+    // tiling once more, masked out below)
+    if (wave < 4) {
+        // (by scalar loads at wave's own offset: indexed as an array the description would move to scratch memory)
+        ConstBytes Gp = desc + gi * sizeof(PrunedGroup);
+        auto f64_at = [&](size_t off) { return ((ConstF64)(Gp + off))[wave]; };
+        const double extent = f64_at(offsetof(PrunedGroup, extent));
+        const uint32_t list0 = (wave > 0 ? G.ndiv[0] : 0u) + (wave > 1 ? G.ndiv[1] : 0u) + (wave > 2 ? G.ndiv[2] : 0u);
+        const uint32_t digit = digit_of(t0 + min(lane, nt - 1), f64_at(offsetof(PrunedGroup, dg) + offsetof(DigitConst, rcp_radix)),
+                                        f64_at(offsetof(PrunedGroup, dg) + offsetof(DigitConst, rcp_n)),
+                                        ((ConstPtr<uint32_t>)(Gp + offsetof(PrunedGroup, ndiv)))[wave]);
+        const double g = (double)div_lds[list0 + digit];
+        gd[wave * PRUNED_TC + lane] = g;
+        gd[(4 + wave) * PRUNED_TC + lane] = whole_quotient(extent, g);
+    }
+    __syncthreads();
+    // Read again by every part, and by every problem of step 2: kept in registers, the tiling and the products that
+    // problems share would spill what a problem needs (2.5 GB of scratch traffic per sweep, 0.47 ms).
+    auto this_tiling = [&]() {
+        TilingF v;
+        uint32_t l = lane;
+        asm volatile("" : "+v"(l));
+#pragma unroll
+        for (int q = 0; q < 4; ++q) { v.G[q] = gd[q * PRUNED_TC + l]; v.D[q] = gd[(4 + q) * PRUNED_TC + l]; }
+        return v;
+    };
+    // ---- the table that the recovery of positions reads
+    stage_kept(tab + lane, wave, this_tiling(), G.size, 1.0);
+
+    // members are sorted by capacity: a round's members follow those of the round before
+    uint32_t m_lo = 0;
+#pragma unroll 1
+    for (uint32_t cap0 = 0; cap0 < G.n_caps; cap0 += PRUNED_ROUND) {
+        // ---- step 1.  Waves 0-3: class 2 (77 rows) under four capacities each; waves 4-7: classes 0 and 1 (65 + 39)
+        {
+            const uint32_t first = cap0 + (wave & 3) * PRUNED_CAPS;
+            if (first < G.n_caps) {
+                const TilingF v = this_tiling();
+                double cap[PRUNED_CAPS], l[PRUNED_CAPS];
+#pragma unroll
+                for (uint32_t k = 0; k < PRUNED_CAPS; ++k) cap[k] = caps[min(first + k, G.n_caps - 1)];
+                auto keep = [&](uint32_t cls) {
+#pragma unroll
+                    for (uint32_t k = 0; k < PRUNED_CAPS; ++k) least[((wave & 3) * PRUNED_CAPS + k) * LEAST_CLASSES + cls][lane] = l[k];
+                };
+                if (wave < 4) {
+                    least_traffic<2, 0, 1>(v, G.size, cap, l);
+                    keep(2);
+                } else {
+                    least_traffic<0, 0, 1>(v, G.size, cap, l);
+                    keep(0);
+                    least_traffic<1, 0, 1>(v, G.size, cap, l);
+                    keep(1);
+                }
+            }
+        }
+        __syncthreads();
+        uint32_t m_hi = m_lo;
+        while (m_hi < G.n_members &&
+               ((ConstPtr<uint32_t>)(members + m_hi * sizeof(PrunedMember) + offsetof(PrunedMember, cap)))[0] < cap0 + PRUNED_ROUND)
+            ++m_hi;
+
+        // ---- step 2.  This wave's problems: wave, wave + 8, ..., at most eight.  Lane 4 m + o looks after key o of the
+        // m-th: it holds what has been published of it when the step begins; a value above that needs no class.
+        const uint32_t m_first = m_lo + wave;
+        const uint32_t my_j = m_first + (lane / N_OBJ) * PRUNED_WAVES;
+        const bool my_key = lane < (PRUNED_MEMBERS / PRUNED_WAVES) * N_OBJ && my_j < m_hi;
+        unsigned long long *my_hint = a.hints;
+        double seen = inf;
+        if (my_key) {
+            my_hint += (uint64_t)((ConstPtr<uint32_t>)(members + my_j * sizeof(PrunedMember) + offsetof(PrunedMember, slot)))[0] * N_OBJ + lane % N_OBJ;
+            seen = __longlong_as_double((long long)__hip_atomic_load(my_hint, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        }
+#pragma unroll 1
+        for (uint32_t j = m_first, m = 0; j < m_hi; j += PRUNED_WAVES, ++m) {
+            const PrunedMember mb = read_const<PrunedMember>(members + j * sizeof(PrunedMember));
+            const ModelConst &mc = mb.mc;
+            RowSide rs[LEAST_CLASSES];
+#pragma unroll
+            for (uint32_t g = 0; g < LEAST_CLASSES; ++g) {
+                const double d = least[(mb.cap - cap0) * LEAST_CLASSES + g][lane];
+                rs[g] = row_side(mc, lane < nt ? d : nothing_fits());
+            }
+            auto keep = [&](uint32_t o, double p, double s, uint32_t code, bool reached) {
+                const uint32_t low = __builtin_amdgcn_readfirstlane(wave_min_u32(reached ? code : 0xFFFFFFFFu));
+                const unsigned long long who = __ballot(reached && code == low);
+                if (lane == 0) {
+                    best[j][o].p = p; best[j][o].s = s; best[j][o].idx = ~0ull;
+                    lanes_of[j][o] = who;
+                    code_of[j][o] = low;
+                }
+            };
+            auto beaten = [&](uint32_t o, double p) {
+                const double s = lane_value_f64(seen, m * N_OBJ + o);
+                if (p < inf && !(p > s)) return false;
+                if (lane == 0) { best[j][o].p = inf; best[j][o].s = 0.0; best[j][o].idx = ~0ull; }
+                return true;
+            };
+            if (mb.mask & 1) {
+                const StageTerms t = stage_terms(this_tiling(), X, mc);
+                // the energy grows with the buffer<->RF words: the least of them decides
+                const double br2 = fmin(fmin(t.br2[0], t.br2[1]), t.br2[2]);
+                double val = inf;
+#pragma unroll
+                for (int g = 0; g < LEAST_CLASSES; ++g) {
+                    const int r = g == 2;
+                    const double br = fmin(fmin(t.br1[r][0], t.br1[r][1]), t.br1[r][2]) + br2;
+                    val = fmin(val, energy_of(mc, rs[g], br, t.e_rf[r], t.e_mac[r]));
+                }
+                const double p = uniform_f64(wave_min_f64(val));
+                // (its class is looked for below, where it matters: rarely)
+                if (!beaten(0, p) && lane == 0) { best[j][0].p = p; best[j][0].s = 0.0; best[j][0].idx = ~0ull; }
+            }
+            if (mb.mask & 2) {
+                const StageTerms t = stage_terms(this_tiling(), X, mc);   // (once more: kept across the energy it spills)
+                auto latency = [&](auto pow2) {
+                    constexpr bool POW2 = decltype(pow2)::value;
+                    double gb1[2][3], gb2[3], fastest[2] = {inf, inf};
+#pragma unroll
+                    for (int s = 0; s < 3; ++s) { gb1[0][s] = t.br1[0][s] * mc.gb_k; gb1[1][s] = t.br1[1][s] * mc.gb_k; gb2[s] = t.br2[s] * mc.gb_k; }
+#pragma unroll
+                    for (int r = 0; r < 2; ++r) {
+#pragma unroll
+                        for (int c = 0; c < 9; ++c) fastest[r] = fmin(fastest[r], combo_time<POW2>(t, gb1, gb2, mc, r, c));
+                        fastest[r] = mc.c_lat * fastest[r];
+                    }
+                    const double val = fmin(fmin(fmax(rs[0].time, fastest[0]), fmax(rs[1].time, fastest[0])), fmax(rs[2].time, fastest[1]));
+                    const double p = uniform_f64(wave_min_f64(val));
+                    if (!beaten(1, p)) {
+                        // no candidate is below p: one has it if neither of its two parts exceeds it
+                        // (descending codes: the last one met is the lowest)
+                        uint32_t low[2] = {9, 9};
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int r = 0; r < 2; ++r)
+#pragma unroll
+                            for (int c = 8; c >= 0; --c) low[r] = mc.c_lat * combo_time<POW2>(t, gb1, gb2, mc, r, c) <= p ? (uint32_t)c : low[r];
+                        uint32_t code = rs[2].time <= p && low[1] < 9 ? 10u + 2u * low[1] : 0xFFFFFFFFu;
+                        code = rs[1].time <= p && low[0] < 9 ? min(code, 9u + 2u * low[0]) : code;
+                        code = rs[0].time <= p && low[0] < 9 ? low[0] : code;
+                        keep(1, p, 0.0, code, val == p);
+                    }
+                };
+                if (mc.gb_pow2) latency(std::true_type{});
+                else latency(std::false_type{});
+            }
+            // the other two keys: candidate by candidate, one key at a time
+#pragma unroll 1
+            for (uint32_t o = 2; o < N_OBJ; ++o) {
+                if (!((mb.mask >> o) & 1)) continue;
+                const TilingF v = this_tiling();
+                double mine_p = inf, mine_s = inf;
+                uint32_t code = 0xFFFFFFFFu;
+#pragma unroll 1
+                for (uint32_t c = 0; c < 9; ++c)
+                    each_class(v, X, mc, rs, c, [&](uint32_t cls_code, double en, double lat) {
+                        double kp, ks;
+                        key_values(o, en, lat, kp, ks);
+                        const bool same = kp == mine_p && ks == mine_s, lower = kp < mine_p || (kp == mine_p && ks < mine_s);
+                        mine_p = lower ? kp : mine_p;
+                        mine_s = lower ? ks : mine_s;
+                        code = lower || (same && cls_code < code) ? cls_code : code;
+                    });
+                const double p = uniform_f64(wave_min_f64(mine_p));
+                if (beaten(o, p)) continue;
+                const double sec = o == MMEE_OBJ_LATENCY_THEN_ENERGY ? uniform_f64(wave_min_f64(mine_p == p ? mine_s : inf)) : 0.0;
+                keep(o, p, sec, code, mine_p == p && mine_s == sec);
+            }
+            if (lane < N_OBJ && !((mb.mask >> lane) & 1)) { best[j][lane].p = inf; best[j][lane].s = 0.0; best[j][lane].idx = ~0ull; }
+        }
+        // ---- publish, all of the wave's values at once; what something lower was published for is dropped here
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        bool up = false;
+        if (my_key && best[my_j][lane % N_OBJ].p < inf) {
+            const unsigned long long bits = (unsigned long long)__double_as_longlong(best[my_j][lane % N_OBJ].p);
+            up = bits <= __hip_atomic_fetch_min(my_hint, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (!up) best[my_j][lane % N_OBJ].p = inf;
+        }
+        unsigned long long follow = __ballot(up);
+        // ---- positions of the others
+        while (follow) {
+            const uint32_t which = __builtin_amdgcn_readfirstlane((uint32_t)__ffsll((long long)follow) - 1u);
+            follow &= follow - 1;
+            const uint32_t j = m_first + (which / N_OBJ) * PRUNED_WAVES, o = which % N_OBJ;
+            const PrunedMember mb = read_const<PrunedMember>(members + j * sizeof(PrunedMember));
+            ClassBest b;
+            b.p = uniform_f64(best[j][o].p); b.s = uniform_f64(best[j][o].s);
+            b.code = __builtin_amdgcn_readfirstlane(code_of[j][o]);
+            const unsigned long long who = lanes_of[j][o];
+            b.lanes = ((unsigned long long)__builtin_amdgcn_readfirstlane((uint32_t)(who >> 32)) << 32) | __builtin_amdgcn_readfirstlane((uint32_t)who);
+            if (o == MMEE_OBJ_ENERGY) {
+                // the lowest class in which one of these tilings has it
+                RowSide rs[LEAST_CLASSES];
+#pragma unroll
+                for (uint32_t g = 0; g < LEAST_CLASSES; ++g) {
+                    const double d = least[(mb.cap - cap0) * LEAST_CLASSES + g][lane];
+                    rs[g] = row_side(mb.mc, lane < nt ? d : nothing_fits());
+                }
+                const TilingF v = this_tiling();
+                uint32_t code = 0xFFFFFFFFu;
+#pragma unroll 1
+                for (uint32_t c = 0; c < 9; ++c)
+                    each_class(v, X, mb.mc, rs, c, [&](uint32_t cls_code, double en, double) { code = en == b.p ? min(code, cls_code) : code; });
+                b.code = __builtin_amdgcn_readfirstlane(wave_min_u32(code));
+                b.lanes = __ballot(code == b.code);
+            }
+            uint32_t cls, combo, row_lo, n_rows;
+            class_of_code(b.code, cls, combo);
+            rows_of_class(cls, row_lo, n_rows);
+            const ComboTerms ct = combo_terms(this_tiling(), X, mb.mc, cls == 2u, combo % 3, combo / 3);
+            const uint4 *offs = reinterpret_cast<const uint4 *>(&kept_dev.off[0][0]);
+            const Found f = first_row(tab, [&](uint32_t i) { return offs[i]; }, ct, mb.mc, nt, o, b, row_lo, n_rows);
+            if (lane == 0) {
+                if (f.row == 0xFFFFFFFFu) best[j][o].p = inf;        // cannot happen: the value came from here
+                else {
+                    const uint32_t row = index_row_base(kept_dev.number[row_lo + f.row]) + 30000u * (combo % 3) + 90000u * (combo / 3);
+                    best[j][o].idx = (uint64_t)t0 + f.lane + (uint64_t)G.T * row;
+                }
+            }
+        }
+        m_lo = m_hi;
+        __syncthreads();                                      // the round's minima are free again
+    }
+    // ---- the item's records
+    for (uint32_t k = threadIdx.x; k < G.n_members * N_OBJ; k += PRUNED_THREADS)
+        a.keys[((uint64_t)item * a.stride + k / N_OBJ) * N_OBJ + k % N_OBJ] = best[k / N_OBJ][k % N_OBJ];
+}
+
+// After the search: one block per problem reduces the problem's records, one per item of its group, and writes the
+// winner's full cost record and mapping.
+__global__ __launch_bounds__(256) void k_pruned_finish(PrunedArgs a)
+{
+    __shared__ Key wave_best[N_OBJ][4];
+    __shared__ DivTable dv_s;
+    const double inf = pos_inf();
+    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    ConstBytes desc = pruned_desc(a);
+    const PrunedMember mb = read_const<PrunedMember>(desc + a.members_off + blockIdx.x * sizeof(PrunedMember));
+    const PrunedGroup G = read_const<PrunedGroup>(desc + mb.group * sizeof(PrunedGroup));
+    {
+        // the packed lists back into the table form the decoding helpers take
+        ConstPtr<uint32_t> list = (ConstPtr<uint32_t>)(desc + G.list_off);
+        uint32_t first = 0;
+        for (int q = 0; q < 4; ++q) {
+            for (uint32_t k = threadIdx.x; k < G.ndiv[q]; k += 256) dv_s.div[q][k] = list[first + k];
+            first += G.ndiv[q];
+        }
+        if (threadIdx.x < 4) { dv_s.X[threadIdx.x] = G.X[threadIdx.x]; dv_s.ndiv[threadIdx.x] = G.ndiv[threadIdx.x]; }
+    }
+    const uint32_t member = blockIdx.x - G.member0;
+#pragma unroll
+    for (int o = 0; o < N_OBJ; ++o) {
+        if (!((mb.mask >> o) & 1)) continue;
+        Key k; k.p = inf; k.s = 0.0; k.idx = ~0ull;
+        for (uint32_t b = threadIdx.x; b < G.n_items; b += 256) {
+            const Key c = a.keys[((uint64_t)(G.first_item + b) * a.stride + member) * N_OBJ + o];
+            if (key_less(c, k)) k = c;
+        }
+        k = wave_min(k);
+        if (lane == 0) wave_best[o][wave] = k;
+    }
+    __syncthreads();
+    if (threadIdx.x < N_OBJ) a.hints[(uint64_t)mb.slot * N_OBJ + threadIdx.x] = INF_BITS;     // for the next launch
+    if (threadIdx.x < N_OBJ && ((mb.mask >> threadIdx.x) & 1)) {
+        const int o = threadIdx.x;
+        Key k = wave_best[o][0];
+        for (int wv = 1; wv < 4; ++wv)
+            if (key_less(wave_best[o][wv], k)) k = wave_best[o][wv];
+        mmee_result res;
+        winner_record(a.enc, dv_s, mb.mc, k, res);
+        write_record(a.final_out + (uint64_t)mb.slot * N_OBJ + o, k, res);
+    }
+}
+
+}  // namespace mmee

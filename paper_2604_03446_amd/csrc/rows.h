@@ -1,0 +1,270 @@
+// What a row of the query side -- loop order, buffering levels, recomputation choice r, fusion f -- stands for,
+// and the rows that can hold the least DRAM traffic.
+//
+// row_terms is the single statement of the row side of the model: k_build_rows encodes every row with it at run
+// time, and least_rows lists at compile time, per (r, f), the rows that are needed to know the least DRAM traffic
+// of a tiling under a buffer capacity.  Both use only symbols (which inter-tile loops multiply which term).
+#pragma once
+#include <stdint.h>
+#include "layout.h"
+
+namespace mmee {
+
+// the 24 inter-tile loop orders, outer -> inner, in lexicographic order over i<k<l<j;
+// 2 bits per slot, slot 0 = outermost
+constexpr uint32_t order_of_rank(uint32_t rank)
+{
+    uint32_t avail = 0xE4;            // nibble list 3,2,1,0 packed 2 bits each: entry e at bits 2e
+    uint32_t packed = 0;
+    uint32_t f = 6, left = 4;
+    for (uint32_t slot = 0; slot < 4; ++slot) {
+        const uint32_t pick = rank / f;
+        rank -= pick * f;
+        const uint32_t sym = (avail >> (2 * pick)) & 3;
+        packed |= sym << (2 * slot);
+        // delete entry `pick` from the list
+        const uint32_t low = avail & ((1u << (2 * pick)) - 1);
+        const uint32_t high = (avail >> (2 * pick + 2)) << (2 * pick);
+        avail = low | high;
+        --left;
+        if (left) f /= left;
+    }
+    return packed;
+}
+
+// selector of a DRAM term: which of the two loops an operand does not own multiply its
+// matrix size.  nest_mask: loops of the operand's operator nest; own0/own1: its own dims;
+// n0/n1: the other two dims in table order.
+constexpr uint32_t dram_selector(const int (&pos)[4], uint32_t nest_mask, uint32_t prefix_mask, int own0, int own1, int n0, int n1,
+                                 int level)
+{
+    // blocker: innermost own loop outside the buffering level (Sec. V-A)
+    int bpos = 99, bdim = -1;
+    if (pos[own0] >= level) { bpos = pos[own0]; bdim = own0; }
+    if (pos[own1] >= level && pos[own1] < bpos) { bpos = pos[own1]; bdim = own1; }
+    if (bdim < 0) return 0;                                   // whole matrix resident: fetched once
+    uint32_t counted = 0;
+    if (level == 0 && ((prefix_mask >> bdim) & 1)) {
+        counted = prefix_mask;                                // evicted at every operator switch
+    } else {
+        for (int q = 0; q < 4; ++q)                           // Scenario 1: blocker and all loops above it
+            if (((nest_mask >> q) & 1) && pos[q] >= bpos) counted |= 1u << q;
+    }
+    return ((counted >> n0) & 1) | (((counted >> n1) & 1) << 1);
+}
+
+// The optional factors of every term, as option numbers (layout.h).  Operands in the order A, B, D, E.
+struct RowTerms {
+    uint32_t bs[4];              // buffer size options
+    uint32_t tau;                // bit per operand: retained across operator switches
+    uint32_t c;                  // buffer size option of C
+    uint32_t da[4];              // DRAM options
+    uint32_t dac;                // DRAM option of C, 4 = fused: none
+    bool valid;                  // denotes a dataflow
+};
+
+constexpr RowTerms row_terms(uint32_t rank, uint32_t r, uint32_t f, const int (&lvl)[4])
+{
+    RowTerms t{};
+    const uint32_t ord = order_of_rank(rank);
+    int pos[4] = {0, 0, 0, 0};
+    for (int slot = 0; slot < 4; ++slot) pos[(ord >> (2 * slot)) & 3] = 3 - slot;
+    // loops iterated by both operators lead the nest (Sec. IV-B); the rest splits per operator
+    const uint32_t shared_mask = (1u << DI) | (1u << DL) | (r ? (1u << DJ) : 0u);
+    uint32_t prefix_mask = 0;
+    for (int slot = 0; slot < 4; ++slot) {
+        const uint32_t q = (ord >> (2 * slot)) & 3;
+        if (!((shared_mask >> q) & 1)) break;
+        prefix_mask |= 1u << q;
+    }
+    const uint32_t nest1 = prefix_mask | (1u << DI) | (1u << DK) | (1u << DL);
+    const uint32_t nest2 = prefix_mask | (1u << DI) | (1u << DL) | (1u << DJ);
+    const int own[4][2] = {{DI, DK}, {DK, DL}, {DL, DJ}, {DI, DJ}}, other[4][2] = {{DL, DJ}, {DI, DJ}, {DI, DK}, {DK, DL}};
+    for (int y = 0; y < 4; ++y) {
+        t.bs[y] = (uint32_t)(pos[own[y][0]] < lvl[y]) | ((uint32_t)(pos[own[y][1]] < lvl[y]) << 1);
+        // retained operands (buffered at an inter-tile loop) also occupy the other operator's buffer
+        t.tau |= (uint32_t)(lvl[y] >= 1) << y;
+        t.da[y] = dram_selector(pos, y < 2 ? nest1 : nest2, prefix_mask, own[y][0], own[y][1], other[y][0], other[y][1], lvl[y]);
+    }
+    // C holds every tile the producer finishes before the consumer starts (fused), else one tile
+    t.c = f ? ((uint32_t)!((prefix_mask >> DI) & 1) | ((uint32_t)!((prefix_mask >> DL) & 1) << 1)) : 0u;
+    t.dac = 4;                                                // fused: DA_C = 0 (Sec. V-C)
+    if (!f) {
+        const uint32_t out_k = dram_selector(pos, nest1, prefix_mask, DI, DL, DK, DJ, 0) & 1;
+        const uint32_t in_j = (dram_selector(pos, nest2, prefix_mask, DI, DL, DK, DJ, 0) >> 1) & 1;
+        t.dac = out_k | (in_j << 1);
+    }
+    // recomputation must revisit C tiles (j outside k) and needs an on-chip C
+    t.valid = !(r && (!f || pos[DK] > pos[DJ]));
+    return t;
+}
+
+// symbolic signature: one bit per optional factor of every term; a row whose bits are a
+// subset of another's is no larger in any term, for every tiling (all factors are >= 1)
+constexpr uint32_t row_signature(const RowTerms &t)
+{
+    uint32_t s = t.bs[0] | (t.bs[1] << 2) | (t.c << 4) | (t.bs[2] << 6) | (t.bs[3] << 8) | (t.tau << 10);
+    for (int y = 0; y < 4; ++y) s |= t.da[y] << (14 + 2 * y);
+    return s | ((t.dac & 3u) << 22);
+}
+
+// ---- the rows that the least traffic needs -----------------------------------------------------
+// Within one (r, f) a row that another one does not exceed in any term never has less traffic, nor fits where
+// the other does not.  Unlike the offline stage's list, which must keep the lowest index among equals, the order
+// of the rows plays no part here: 65, 39 and 77 rows remain of the 86, 74 and 110 that stage keeps.
+constexpr int LEAST_CLASSES = 3;                              // (r, f) = (0, 0), (0, 1), (1, 1), in index order
+constexpr int LEAST_MAX = 80;
+struct LeastRows {
+    int n;
+    RowTerms row[LEAST_MAX];
+};
+
+constexpr uint32_t least_sort_key(const RowTerms &t)          // rows that share C's and A, B's terms side by side
+{
+    return (t.c << 20) | (t.dac << 16) | (t.bs[0] << 14) | (t.bs[1] << 12) | ((t.tau & 3u) << 10) | (t.da[0] << 8) | (t.da[1] << 6);
+}
+
+constexpr LeastRows least_rows(uint32_t r, uint32_t f)
+{
+    LeastRows out{};
+    uint32_t sig[LEAST_MAX] = {};
+    for (uint32_t rank = 0; rank < 24; ++rank) {
+        int lvl[4] = {0, 0, 0, 0};
+        if (!row_terms(rank, r, f, lvl).valid) continue;
+        // per operand, the levels whose options differ from the level below
+        int list[4][5] = {}, count[4] = {0, 0, 0, 0};
+        for (int y = 0; y < 4; ++y) {
+            RowTerms last{};
+            for (int p = 0; p < 5; ++p) {
+                int l[4] = {0, 0, 0, 0};
+                l[y] = p;
+                const RowTerms t = row_terms(rank, r, f, l);
+                if (p == 0 || t.bs[y] != last.bs[y] || t.da[y] != last.da[y] || t.tau != last.tau) list[y][count[y]++] = p;
+                last = t;
+            }
+        }
+        for (int e = 0; e < count[3]; ++e)
+            for (int d = 0; d < count[2]; ++d)
+                for (int b = 0; b < count[1]; ++b)
+                    for (int a = 0; a < count[0]; ++a) {
+                        const int l[4] = {list[0][a], list[1][b], list[2][d], list[3][e]};
+                        const RowTerms t = row_terms(rank, r, f, l);
+                        const uint32_t s = row_signature(t);
+                        bool covered = false;
+                        for (int k = 0; k < out.n && !covered; ++k) covered = (sig[k] & ~s) == 0;
+                        if (covered) continue;
+                        int n = 0;                            // drop what the new row covers
+                        for (int k = 0; k < out.n; ++k)
+                            if ((s & ~sig[k]) != 0) { sig[n] = sig[k]; out.row[n] = out.row[k]; ++n; }
+                        sig[n] = s;
+                        out.row[n] = t;
+                        out.n = n + 1;
+                    }
+    }
+    for (int i = 1; i < out.n; ++i)                           // insertion sort
+        for (int k = i; k > 0 && least_sort_key(out.row[k]) < least_sort_key(out.row[k - 1]); --k) {
+            const RowTerms t = out.row[k];
+            out.row[k] = out.row[k - 1];
+            out.row[k - 1] = t;
+        }
+    return out;
+}
+
+// ---- the rows that the offline stage keeps, at compile time ---------------------------------------
+// Eq. (12) as k_prune_rows applies it: a row goes if a row of its class with a lower number covers it.  A level
+// whose options are those of the level below is always covered by it, and covering is transitive, so only
+// the distinct levels are walked, in index order, against the rows kept so far.  The library compares the list with
+// the device's when it starts.
+constexpr int KEPT_MAX = 112;
+struct KeptClass {
+    int n;
+    RowTerms row[KEPT_MAX];
+    uint16_t number[KEPT_MAX];               // within its group: levels/order
+};
+
+constexpr KeptClass kept_class(uint32_t r, uint32_t f)
+{
+    KeptClass out{};
+    uint32_t sig[KEPT_MAX] = {};
+    for (uint32_t rank = 0; rank < 24; ++rank) {
+        int lvl[4] = {0, 0, 0, 0};
+        if (!row_terms(rank, r, f, lvl).valid) continue;
+        int list[4][5] = {}, count[4] = {0, 0, 0, 0};
+        for (int y = 0; y < 4; ++y) {
+            RowTerms last{};
+            for (int p = 0; p < 5; ++p) {
+                int l[4] = {0, 0, 0, 0};
+                l[y] = p;
+                const RowTerms t = row_terms(rank, r, f, l);
+                if (p == 0 || t.bs[y] != last.bs[y] || t.da[y] != last.da[y] || t.tau != last.tau) list[y][count[y]++] = p;
+                last = t;
+            }
+        }
+        for (int e = 0; e < count[3]; ++e)
+            for (int d = 0; d < count[2]; ++d)
+                for (int b = 0; b < count[1]; ++b)
+                    for (int a = 0; a < count[0]; ++a) {
+                        const int l[4] = {list[0][a], list[1][b], list[2][d], list[3][e]};
+                        const RowTerms t = row_terms(rank, r, f, l);
+                        const uint32_t s = row_signature(t);
+                        bool covered = false;
+                        for (int k = 0; k < out.n && !covered; ++k) covered = (sig[k] & ~s) == 0;
+                        if (covered) continue;
+                        sig[out.n] = s;
+                        out.row[out.n] = t;
+                        out.number[out.n] = (uint16_t)(l[0] + 5 * l[1] + 25 * l[2] + 125 * l[3] + 625 * rank);
+                        ++out.n;
+                    }
+    }
+    return out;
+}
+
+// the eight table entries of a row (layout.h)
+constexpr uint32_t row_entry(const RowTerms &t, int k)
+{
+    uint32_t ret[4] = {0, 0, 0, 0};
+    for (int y = 0; y < 4; ++y) ret[y] = (t.tau >> y) & 1 ? t.bs[y] : 4u;
+    const uint32_t e[NSEL] = {ENT_BS_AB + t.bs[0] + 4 * t.bs[1], ENT_RET_DE + ret[2] + 5 * ret[3], ENT_BS_C + t.c,
+                              ENT_BS_DE + t.bs[2] + 4 * t.bs[3], ENT_RET_AB + ret[0] + 5 * ret[1], ENT_DA_AB + t.da[0] + 4 * t.da[1],
+                              ENT_DA_DE + t.da[2] + 4 * t.da[3], ENT_DA_C + t.dac};
+    return e[k];
+}
+
+// All kept rows, class after class, and the compact table they refer to: 77 of the 123 entries, one line of
+// KEPT_LINE bytes (64 tilings) each.
+constexpr int KEPT_ALL = 270, KEPT_LINE = 64 * 8;
+struct alignas(32) KeptRows {
+    uint32_t off[KEPT_ALL][NSEL];            // a row's entries, as byte offsets of their lines
+    uint32_t first[LEAST_CLASSES], rows[LEAST_CLASSES];
+    uint32_t n, used;
+    uint32_t number[KEPT_ALL];               // levels/order + 15000 * (r + 2 f)
+    uint32_t place[NENT];                    // table entry -> its line in the compact table, NENT: no row refers to it
+};
+constexpr KeptRows kept_rows()
+{
+    KeptRows k{};
+    for (int e = 0; e < NENT; ++e) k.place[e] = NENT;
+    for (int c = 0; c < LEAST_CLASSES; ++c) {
+        const KeptClass cls = kept_class(c == 2 ? 1u : 0u, c == 0 ? 0u : 1u);
+        k.first[c] = k.n;
+        k.rows[c] = (uint32_t)cls.n;
+        for (int i = 0; i < cls.n; ++i, ++k.n) {
+            k.number[k.n] = cls.number[i] + ROWS_PER_GROUP * (c == 0 ? 0u : (c == 1 ? 2u : 3u));
+            for (int q = 0; q < NSEL; ++q) {
+                k.off[k.n][q] = row_entry(cls.row[i], q);
+                k.place[k.off[k.n][q]] = 0;
+            }
+        }
+    }
+    for (int e = 0; e < NENT; ++e)
+        if (k.place[e] == 0) k.place[e] = k.used++;
+    for (uint32_t i = 0; i < k.n; ++i)
+        for (int q = 0; q < NSEL; ++q) k.off[i][q] = k.place[k.off[i][q]] * KEPT_LINE;
+    return k;
+}
+constexpr KeptRows KEPT = kept_rows();
+static_assert(KEPT.n == KEPT_ALL, "the arrays are sized for the kept rows");
+
+constexpr LeastRows LEAST[LEAST_CLASSES] = {least_rows(0, 0), least_rows(0, 1), least_rows(1, 1)};
+
+}  // namespace mmee

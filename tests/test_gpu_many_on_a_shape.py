@@ -1,0 +1,56 @@
+"""Many accelerators on few shapes in one call (k_search_pruned: shared row side, capacities in rounds of
+sixteen, groups of at most 64 problems) against one call per problem, which takes another kernel.  Every key set;
+fewer tilings than a chunk, whole chunks and a remainder; one capacity for all, more capacities than a round,
+more problems than a group; capacities nothing fits; bandwidths, array counts and energies of every kind."""
+import random
+
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def M():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_2604_03446_amd as mod
+    return mod
+
+
+SHAPES = [dict(N=2, d=3, tiling_mode=1), dict(N=60, d=10, tiling_mode=1), dict(N=64, d=32, tiling_mode=0), dict(N=36, d=75, tiling_mode=1)]
+
+
+def accelerators(rng, n, caps):
+    return [dict(pe_rows=rng.choice([1, 3, 8, 16]), pe_cols=rng.choice([2, 7, 8, 32]), n_arrays=rng.choice([1, 1, 2, 3]),
+                 rf_bytes=rng.choice([8, 64, 96]), gb_bytes=caps[k % len(caps)], e_dram=rng.choice([200.0, rng.uniform(100, 300), 0.0]),
+                 e_gb=rng.choice([6.0, 5.7]), e_rf=rng.choice([1.0, 0.0]), e_mac=1.0, dram_bw=rng.choice([64.0, 60.0, 0.0]),
+                 gb_bw=rng.choice([256.0, 100.0, 0.0])) for k in range(n)]
+
+
+@pytest.mark.parametrize("n,n_caps", [(8, 1), (9, 5), (17, 16), (40, 17), (64, 64), (70, 70)])
+def test_same_results_as_one_call_per_problem(M, n, n_caps):
+    rng = random.Random(1000 * n + n_caps)
+    caps = [4] + [rng.randrange(100, 60000) for _ in range(n_caps - 1)] if n_caps > 1 else [4000]
+    points = []
+    for shape in rng.sample(SHAPES, 2):
+        w = dict(B=1, H=rng.choice([1, 3]), word_bytes=2, c_softmax=10, **shape)
+        for k, h in enumerate(accelerators(rng, n, caps)):
+            mask = (k % 15) + 1
+            points += [(w, h, o) for o in range(4) if mask >> o & 1]
+    results, codes = M.mmee_search_many(points, M.SEARCH_PRUNED)
+    infeasible = 0
+    for (w, h, o), r, code in zip(points, results, codes):
+        want_code, want = M.mmee_search_ex(w, h, o, M.SEARCH_PRUNED, allow_infeasible=True)
+        assert code == want_code, (w, h, o)
+        infeasible += code != 0
+        if code:
+            assert r.cost.valid == 0
+            continue
+        assert r.best.idx == want.best.idx, (w, h, o)
+        assert bytes(r.cost) == bytes(want.cost) and bytes(r.best) == bytes(want.best), (w, h, o)
+        assert r.evaluated == want.evaluated and r.space == want.space
+    if n_caps > 1:
+        assert 0 < infeasible < len(points)
+    # once more: nothing of a call is left for the next
+    again, codes2 = M.mmee_search_many(points, M.SEARCH_PRUNED)
+    assert list(codes2) == list(codes) and [r.best.idx for r in again] == [r.best.idx for r in results]
