@@ -53,7 +53,7 @@ TRAFFIC_SOURCE = {"k_search_dense_long": "profiles/k_search_dense_long.md", "k_s
 def kernel_sources_digest():
     import hashlib
     h = hashlib.sha256()
-    for f in ("layout.h", "rows.h", "kernels.h", "boundary.h", "batch.h", "pruned.h", "mmee.hip"):
+    for f in ("layout.h", "rows.h", "kernels.h", "boundary.h", "batch.h", "pruned.h", "fronts.h", "mmee.hip"):
         with open(os.path.join(ROOT, "paper_2604_03446_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()

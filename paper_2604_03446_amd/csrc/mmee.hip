@@ -16,6 +16,7 @@
 #include "kernels.h"
 #include "batch.h"
 #include "pruned.h"
+#include "fronts.h"
 
 // ---- fixed scratch of the entry point that allocates nothing (mmee_search_noalloc) ------------
 // One array per GPU, held from the moment the library is loaded until the process ends.  In host
@@ -106,6 +107,11 @@ struct State {
     // published values per result slot
     unsigned char *desc_host = nullptr, *desc_dev = nullptr;
     size_t desc_cap = 0;
+    // fronts over the kept rows: the chunks' points and their counters, the front's records and their number (pinned)
+    Key *front_points = nullptr, *front_lists = nullptr;
+    uint32_t *front_counts = nullptr;
+    FinalRecord *front_host = nullptr, *front_map = nullptr;     // [FRONT_POINTS], host address / device address
+    uint32_t *front_n_host = nullptr, *front_n_map = nullptr;
     void *block_records = nullptr;              // what the blocks of a pruned search leave for the reduction
     size_t block_records_cap = 0;
     unsigned long long *pruned_hints = nullptr;
@@ -1140,10 +1146,8 @@ int enqueue_pruned(const std::vector<PrunedEntry> &entries, size_t ev_slot)
 
 uint64_t kept_row_count() { return (uint64_t)S.counts[1][0] + S.counts[1][1] + S.counts[1][2] + S.counts[1][3]; }
 
-int unpack_result(const Plan &p, size_t slot, int objective, uint64_t evaluated, double seconds, double ksec,
-                  mmee_result *out)
+int unpack_record(const Plan &p, const FinalRecord &fr, uint64_t evaluated, double seconds, double ksec, mmee_result *out)
 {
-    const FinalRecord &fr = S.final_host[N_OBJ * slot + objective];
     std::memset(out, 0, sizeof(*out));
     std::memcpy(&out->cost, fr.cost, sizeof(mmee_cost));
     std::memcpy(&out->best, fr.map, sizeof(mmee_mapping));
@@ -1152,6 +1156,53 @@ int unpack_result(const Plan &p, size_t slot, int objective, uint64_t evaluated,
     out->seconds = seconds;
     out->kernel_seconds = ksec;
     if (!(fr.key.p < INFINITY)) { out->cost.valid = 0; return MMEE_ENOFEASIBLE; }
+    return MMEE_OK;
+}
+
+int unpack_result(const Plan &p, size_t slot, int objective, uint64_t evaluated, double seconds, double ksec,
+                  mmee_result *out)
+{
+    return unpack_record(p, S.final_host[N_OBJ * slot + objective], evaluated, seconds, ksec, out);
+}
+
+// ---- fronts over the kept rows ---------------------------------------------------------------
+
+static_assert(sizeof(FrontArgs) <= 4096, "kernel arguments are limited to 4 KiB");
+
+// The front in three launches; its records land in S.front_host, their number in *S.front_n_host (TOO_MANY: something
+// outgrew its room, walk the front).  Events of slot 0 bracket it.
+int enqueue_front(const Plan &p, bool bs_da, uint32_t capacity)
+{
+    if (!S.front_n_host) {
+        HIP_TRY(hipMalloc(&S.front_points, sizeof(Key) * FRONT_BLOCKS * FRONT_WAVE));
+        HIP_TRY(hipMalloc(&S.front_lists, sizeof(Key) * FRONT_LISTS * FRONT_LIST));
+        HIP_TRY(hipMalloc(&S.front_counts, sizeof(uint32_t) * (FRONT_BLOCKS + FRONT_LISTS)));
+        HIP_TRY(hipHostMalloc(&S.front_host, sizeof(FinalRecord) * FRONT_POINTS, hipHostMallocMapped));
+        HIP_TRY(hipHostGetDevicePointer(reinterpret_cast<void **>(&S.front_map), S.front_host, 0));
+        HIP_TRY(hipHostMalloc(&S.front_n_host, sizeof(uint32_t), hipHostMallocMapped));
+        HIP_TRY(hipHostGetDevicePointer(reinterpret_cast<void **>(&S.front_n_map), S.front_n_host, 0));
+    }
+    FrontArgs a;
+    std::memset(&a, 0, sizeof(a));
+    a.mc = p.mc;
+    a.dg = digit_constants(p.dv);
+    shape_constants(p.dv, a.extent, a.size);
+    for (int q = 0; q < 4; ++q) { a.X[q] = p.dv.X[q]; a.ndiv[q] = p.dv.ndiv[q]; }
+    if (list_length(p.dv) > FRONT_DIVS) return MMEE_EINVAL;
+    pack_lists(p.dv, a.list);
+    a.capacity = std::min<uint32_t>(capacity, FRONT_POINTS);
+    a.points = S.front_points; a.lists = S.front_lists; a.counts = S.front_counts; a.enc = S.enc;
+    a.n_blocks = (uint32_t)((p.T + PRUNED_TC - 1) / PRUNED_TC) * (bs_da ? FRONT_SPLIT : 1);
+    a.n_lists = (a.n_blocks + FRONT_FAN - 1) / FRONT_FAN;
+    a.out = S.front_map; a.n_out = S.front_n_map;
+    HIP_TRY(hipEventRecord(S.events[0], S.stream));
+    const dim3 grid(a.n_blocks);
+    if (bs_da) hipLaunchKernelGGL(k_front_points<true>, grid, dim3(PRUNED_THREADS), 0, S.stream, a);
+    else hipLaunchKernelGGL(k_front_points<false>, grid, dim3(PRUNED_THREADS), 0, S.stream, a);
+    hipLaunchKernelGGL(k_front_merge<false>, dim3(a.n_lists), dim3(MERGE_THREADS), 0, S.stream, a);
+    hipLaunchKernelGGL(k_front_merge<true>, dim3(1), dim3(MERGE_THREADS), 0, S.stream, a);
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(hipEventRecord(S.events[1], S.stream));
     return MMEE_OK;
 }
 
@@ -1516,7 +1567,8 @@ int mmee_chain_search_multi(const mmee_chain *w, const mmee_hw *hw, const int *o
     return mmee_chain_search_many(ws, hs, objectives, n_obj, flags, out, nullptr);
 }
 
-// Walk along a front.  Energy-latency (Sec. VII-E): by ascending latency, each step the
+// A front.  Over the kept rows of a problem that is not too large, in three launches (fronts.h); else a walk along it.
+// Energy-latency (Sec. VII-E): by ascending latency, each step the
 // latency-then-energy optimum among the candidates whose energy is strictly below the previous
 // point's.  Buffer size / DRAM access (Sec. VII-C): by ascending buffer size, each step the
 // (size, traffic)-smallest dataflow whose traffic is strictly below the previous point's.
@@ -1535,6 +1587,23 @@ static int walk_front(const mmee_chain *w, const mmee_hw *hw, bool bs_da, uint32
     if (rc) return rc;
     rc = ensure_slots(1);
     if (rc) return rc;
+    if (!(flags & MMEE_SEARCH_EXHAUSTIVE) && (p.T + PRUNED_TC - 1) / PRUNED_TC <= FRONT_CHUNKS) {
+        rc = enqueue_front(p, bs_da, capacity);
+        if (rc) return rc;
+        HIP_TRY(hipStreamSynchronize(S.stream));
+        const uint32_t n = *S.front_n_host;
+        if (n != TOO_MANY) {
+            float ms = 0.f;
+            (void)hipEventElapsedTime(&ms, S.events[0], S.events[1]);
+            const bool fits = n <= capacity;
+            // counted as the walk counts: one pass over the candidates per point, and the one that finds nothing more
+            const uint64_t formed = fits ? kept_row_count() * p.T * (bs_da ? 1ull : 9ull) * ((uint64_t)n + 1) : 0;
+            const double seconds = fits ? now_seconds() - t_start : 0.0;
+            *n_points = std::min(n, capacity);
+            for (uint32_t k = 0; k < *n_points; ++k) (void)unpack_record(p, S.front_host[k], formed, seconds, fits ? ms * 1e-3 : 0.0, out + k);
+            return !fits ? MMEE_EOVERFLOW : (n ? MMEE_OK : MMEE_ENOFEASIBLE);
+        }
+    }
     double limit = INFINITY, ksec = 0.0;
     uint64_t evaluated = 0;
     for (uint32_t k = 0;; ++k) {
@@ -1742,6 +1811,9 @@ void mmee_shutdown(void)
     if (S.batch_host) (void)hipHostFree(S.batch_host);
     (void)hipFree(S.batch_dev); (void)hipFree(S.item_keys);
     if (S.desc_host) (void)hipHostFree(S.desc_host);
+    (void)hipFree(S.front_points); (void)hipFree(S.front_lists); (void)hipFree(S.front_counts);
+    if (S.front_host) (void)hipHostFree(S.front_host);
+    if (S.front_n_host) (void)hipHostFree(S.front_n_host);
     (void)hipFree(S.desc_dev); (void)hipFree(S.block_records); (void)hipFree(S.pruned_hints);
     for (hipEvent_t e : S.events) (void)hipEventDestroy(e);
     hipStream_t keep = S.stream;
