@@ -65,6 +65,8 @@ struct BatchArgs {
     Key *item_keys;                          // [n_items][N_OBJ]; written at the first item of every (block, problem) stretch
     uint32_t per_block;                      // items per block of the search launch (the finish kernel needs it)
     FinalRecord *final_out;                  // [result slot][N_OBJ]
+    mmee_result *packed;                     // not null: the launch's one key of its one problem goes here, as a result record
+    uint64_t space, evaluated;               // ... with these
     BatchInline inl;                         // inl.on: the launch's only problem is here, prob and first_items are unused
 };
 
@@ -481,24 +483,13 @@ __global__ __launch_bounds__(256) void k_batch_finish(BatchArgs a)
         Key k = wave_best[o][0];
         for (int wv = 1; wv < 4; ++wv)
             if (key_less(wave_best[o][wv], k)) k = wave_best[o][wv];
-        FinalRecord *fr = a.final_out + (uint64_t)head_s.slot * N_OBJ + o;
-        fr->key = k;
-        mmee_cost c;
-        mmee_mapping m;
-        if (k.p < inf) {
-            eval_candidate_direct(a.enc, dv_s, head_s.mc, k.idx, c);
-            decode_candidate(dv_s, head_s.mc.T, k.idx, m);
-        } else {
-            c.bs_words = c.da_words = c.br_words = c.mac_total = c.comp_cycles = 0;
-            c.energy_pj = inf; c.latency_cycles = inf; c.valid = 0; c.reason = 0;
-            for (int q = 0; q < 4; ++q) { m.xG[q] = m.xD[q] = 0; m.order[q] = m.level[q] = 0; }
-            m.idx = ~0ull; m.recompute = m.stat1 = m.stat2 = m.fused = 0;
-        }
-        const uint64_t *cs = reinterpret_cast<const uint64_t *>(&c);
-        for (int q = 0; q < 8; ++q) fr->cost[q] = cs[q];
-        uint64_t mbuf[7] = {0, 0, 0, 0, 0, 0, 0};
-        __builtin_memcpy(mbuf, &m, sizeof(mmee_mapping));
-        for (int q = 0; q < 7; ++q) fr->map[q] = mbuf[q];
+        mmee_result res;
+        winner_record(a.enc, dv_s, head_s.mc, k, res);
+        if (a.packed) {
+            res.space = a.space; res.evaluated = a.evaluated;
+            *a.packed = res;
+        } else
+            write_record(a.final_out + (uint64_t)head_s.slot * N_OBJ + o, k, res);
     }
 }
 

@@ -97,12 +97,11 @@ struct State {
     size_t eval_cap = 0;
     uint32_t resident_blocks = 512;
     // batched search over the pruned rows: problem descriptors (pinned staging + device copy), one record
-    // per work item and objective; the split of the row lists over the waves of a block
+    // per work item and objective
     unsigned char *batch_host = nullptr, *batch_dev = nullptr;
     size_t batch_blob_cap = 0;
     Key *item_keys = nullptr;
     size_t item_cap = 0;
-    uint32_t task_lo[BATCH_WAVES] = {}, task_cnt[BATCH_WAVES] = {}, task_g[BATCH_WAVES] = {};
     // pruned search of many problems on one shape: problem descriptions (pinned staging + device copy), the lowest
     // published values per result slot
     unsigned char *desc_host = nullptr, *desc_dev = nullptr;
@@ -390,31 +389,6 @@ int ensure_ready()
     {
         const int rc = check_kept_rows(S.rows[1], S.counts[1]);
         if (rc) return rc;
-        // share the rows of each group out over the waves of a block, every wave a contiguous piece of
-        // one group's list (rows of one group share r and f)
-        uint32_t waves[N_GROUPS] = {0, 0, 0, 0}, taken = 0;
-        for (uint32_t g = 0; g < N_GROUPS; ++g)
-            if (S.counts[1][g]) { waves[g] = 1; ++taken; }
-        while (taken < BATCH_WAVES) {
-            uint32_t worst = N_GROUPS, most = 0;
-            for (uint32_t g = 0; g < N_GROUPS; ++g) {
-                if (!waves[g]) continue;
-                const uint32_t per = (S.counts[1][g] + waves[g] - 1) / waves[g];
-                if (per > most) { most = per; worst = g; }
-            }
-            if (worst == N_GROUPS || most <= 1) break;
-            ++waves[worst]; ++taken;
-        }
-        uint32_t wv = 0, group_first = 0;
-        for (uint32_t g = 0; g < N_GROUPS; ++g) {
-            for (uint32_t k = 0; k < waves[g]; ++k, ++wv) {
-                const uint32_t n = S.counts[1][g], lo = (uint32_t)((uint64_t)n * k / waves[g]),
-                               hi = (uint32_t)((uint64_t)n * (k + 1) / waves[g]);
-                S.task_lo[wv] = group_first + lo; S.task_cnt[wv] = hi - lo; S.task_g[wv] = g;
-            }
-            group_first += S.counts[1][g];
-        }
-        for (; wv < BATCH_WAVES; ++wv) { S.task_lo[wv] = 0; S.task_cnt[wv] = 0; S.task_g[wv] = 0; }
     }
     S.ready = true;
     return MMEE_OK;
@@ -723,12 +697,104 @@ int enqueue_search(const Plan &p, int mask, uint32_t flags, size_t slot, uint64_
     return enqueue_search_in(b, p, mask, flags, evaluated, e_limit, build_tables, bs_da_step, unproven);
 }
 
+uint32_t list_length(const DivTable &dv) { return dv.ndiv[0] + dv.ndiv[1] + dv.ndiv[2] + dv.ndiv[3]; }
+void pack_lists(const DivTable &dv, uint32_t *list)
+{
+    for (int q = 0; q < 4; ++q) {
+        std::memcpy(list, dv.div[q], sizeof(uint32_t) * dv.ndiv[q]);
+        list += dv.ndiv[q];
+    }
+}
+
 static_assert(sizeof(BatchArgs) <= 4096, "kernel arguments are limited to 4 KiB");
 
 // ---- batched search over the pruned rows -----------------------------------------------------
 
 // masks the batched kernel is built for; other key sets take the per-problem kernels
 bool batch_mask(int mask) { return mask == 1 || mask == 2 || mask == 3 || mask == 4 || mask == 8; }
+
+template <int MASK>
+void launch_batch_mask(bool fast, bool regroup, dim3 grid, const BatchArgs &a)
+{
+    if (regroup) hipLaunchKernelGGL((k_search_batch<MASK, true, true>), grid, dim3(BATCH_THREADS), 0, S.stream, a);
+    else if (fast) hipLaunchKernelGGL((k_search_batch<MASK, true, false>), grid, dim3(BATCH_THREADS), 0, S.stream, a);
+    else hipLaunchKernelGGL((k_search_batch<MASK, false, false>), grid, dim3(BATCH_THREADS), 0, S.stream, a);
+    // the problems' records are complete when the search kernel has ended: one block per problem finishes
+    hipLaunchKernelGGL((k_batch_finish<MASK>), dim3(a.n_prob), dim3(256), 0, S.stream, a);
+}
+
+// The kept rows shared out over the waves of a block, every wave a contiguous piece of one class's list (rows of a
+// class share r and f).
+struct BatchTasks { uint32_t lo[BATCH_WAVES], cnt[BATCH_WAVES], g[BATCH_WAVES]; };
+const BatchTasks &batch_tasks()
+{
+    static const BatchTasks tasks = [] {
+        BatchTasks t;
+        uint32_t waves[LEAST_CLASSES] = {1, 1, 1}, wv = 0;
+        const uint32_t group_of[LEAST_CLASSES] = {0, 2, 3};  // class (r, f) -> g = r + 2 f
+        for (int taken = LEAST_CLASSES; taken < BATCH_WAVES; ++taken) {
+            int most = 0;
+            for (int c = 1; c < LEAST_CLASSES; ++c)
+                if ((KEPT.rows[c] + waves[c] - 1) / waves[c] > (KEPT.rows[most] + waves[most] - 1) / waves[most]) most = c;
+            ++waves[most];
+        }
+        for (int c = 0; c < LEAST_CLASSES; ++c)
+            for (uint32_t k = 0; k < waves[c]; ++k, ++wv) {
+                const uint32_t n = KEPT.rows[c], lo = n * k / waves[c], hi = n * (k + 1) / waves[c];
+                t.lo[wv] = KEPT.first[c] + lo; t.cnt[wv] = hi - lo; t.g[wv] = group_of[c];
+            }
+        return t;
+    }();
+    return tasks;
+}
+
+// every wave's piece of its class's list, cut once more into one sub-piece per row share
+void set_batch_tasks(BatchArgs &a, uint32_t split)
+{
+    const BatchTasks &t = batch_tasks();
+    a.split = split;
+    for (a.split_log2 = 0; (1u << a.split_log2) < split; ++a.split_log2) {}
+    for (uint32_t sh = 0; sh < split; ++sh)
+        for (int wv = 0; wv < BATCH_WAVES; ++wv) {
+            const uint32_t n = t.cnt[wv], lo = n * sh / split, hi = n * (sh + 1) / split;
+            a.task_lo[sh * BATCH_WAVES + wv] = t.lo[wv] + lo;
+            a.task_cnt[sh * BATCH_WAVES + wv] = hi - lo;
+            a.task_g[sh * BATCH_WAVES + wv] = t.g[wv];
+        }
+}
+
+// a launch with few chunks leaves most of the chip idle: let several blocks share a chunk's rows
+uint32_t batch_split(uint64_t chunks, uint32_t resident_blocks)
+{
+    uint32_t split = 1;
+    while (split < BATCH_MAX_SPLIT && chunks * split * 2 <= resident_blocks) split *= 2;
+    return split;
+}
+
+void fill_batch_head(BatchProblemHead &h, uint32_t *list, const Plan &p, const ModelConst &mc, uint32_t slot, uint32_t first_item, uint32_t split)
+{
+    h.mc = mc;
+    h.first_item = first_item;
+    h.n_work = (uint32_t)((p.T + PRUNED_TC - 1) / PRUNED_TC) * split;
+    h.slot = slot;
+    h.pad_ = 0;
+    for (int q = 0; q < 4; ++q) { h.X[q] = p.dv.X[q]; h.ndiv[q] = p.dv.ndiv[q]; }
+    pack_lists(p.dv, list);
+}
+
+int launch_batch(int mask, bool fast, bool regroup, dim3 grid, const BatchArgs &a)
+{
+    switch (mask) {
+    case 1: launch_batch_mask<1>(fast, regroup, grid, a); break;
+    case 2: launch_batch_mask<2>(fast, regroup, grid, a); break;
+    case 3: launch_batch_mask<3>(fast, regroup, grid, a); break;
+    case 4: launch_batch_mask<4>(fast, regroup, grid, a); break;
+    case 8: launch_batch_mask<8>(fast, regroup, grid, a); break;
+    default: return MMEE_EINVAL;
+    }
+    HIP_TRY(hipGetLastError());
+    return MMEE_OK;
+}
 
 int ensure_batch(size_t blob_bytes, size_t n_items)
 {
@@ -748,16 +814,6 @@ int ensure_batch(size_t blob_bytes, size_t n_items)
         S.item_cap = cap;
     }
     return MMEE_OK;
-}
-
-template <int MASK>
-void launch_batch_mask(bool fast, bool regroup, dim3 grid, const BatchArgs &a)
-{
-    if (regroup) hipLaunchKernelGGL((k_search_batch<MASK, true, true>), grid, dim3(BATCH_THREADS), 0, S.stream, a);
-    else if (fast) hipLaunchKernelGGL((k_search_batch<MASK, true, false>), grid, dim3(BATCH_THREADS), 0, S.stream, a);
-    else hipLaunchKernelGGL((k_search_batch<MASK, false, false>), grid, dim3(BATCH_THREADS), 0, S.stream, a);
-    // the problems' records are complete when the search kernel has ended: one block per problem finishes
-    hipLaunchKernelGGL((k_batch_finish<MASK>), dim3(a.n_prob), dim3(256), 0, S.stream, a);
 }
 
 // One problem of a batched launch, as the host sees it.
@@ -793,30 +849,18 @@ int enqueue_batches(std::vector<BatchEntry> &entries, uint32_t flags, size_t ev_
         v->items += (e.plan->T + PRUNED_TC - 1) / PRUNED_TC;
     }
     for (Variant &v : variants) {
-        // a launch with few chunks leaves most of the chip idle: let several blocks share a chunk's rows
-        while (v.split < BATCH_MAX_SPLIT && v.items * v.split * 2 <= S.resident_blocks) v.split *= 2;
+        v.split = batch_split(v.items, S.resident_blocks);
         v.items *= v.split;
         total_items += v.items;
     }
     if (total_items > 0x7fffffffull) return MMEE_EINVAL;
     auto fill_head = [&](BatchProblemHead &h, uint32_t *list, const BatchEntry &e, uint32_t first_item, uint32_t split) {
-        h.mc = e.mc;
-        h.first_item = first_item;
-        h.n_work = (uint32_t)((e.plan->T + PRUNED_TC - 1) / PRUNED_TC) * split;
-        h.slot = (uint32_t)e.slot;
-        h.pad_ = 0;
-        uint32_t at = 0;
-        for (int q = 0; q < 4; ++q) {
-            h.X[q] = e.plan->dv.X[q];
-            h.ndiv[q] = e.plan->dv.ndiv[q];
-            for (uint32_t k = 0; k < h.ndiv[q]; ++k) list[at++] = e.plan->dv.div[q][k];
-        }
+        fill_batch_head(h, list, *e.plan, e.mc, (uint32_t)e.slot, first_item, split);
     };
-    auto list_len = [](const Plan &pl) { return pl.dv.ndiv[0] + pl.dv.ndiv[1] + pl.dv.ndiv[2] + pl.dv.ndiv[3]; };
     // A variant with one problem whose divisor lists fit carries it in the kernel arguments; the others'
     // descriptors go through one blob: per variant its problem descriptors, then its first-item table.
     auto rides_in_arguments = [&](const Variant &v) {
-        return v.members.size() == 1 && list_len(*entries[v.members[0]].plan) <= (uint32_t)BATCH_INLINE_DIVS;
+        return v.members.size() == 1 && list_length(entries[v.members[0]].plan->dv) <= (uint32_t)BATCH_INLINE_DIVS;
     };
     size_t blob = 0;
     for (const Variant &v : variants)
@@ -867,31 +911,15 @@ int enqueue_batches(std::vector<BatchEntry> &entries, uint32_t flags, size_t ev_
         }
         a.n_prob = (uint32_t)L.n_prob; a.n_items = (uint32_t)L.n_items;
         a.enc = S.enc;
-        // every wave's piece of its group's list, cut once more into one sub-piece per row share
-        a.split = v.split;
-        for (a.split_log2 = 0; (1u << a.split_log2) < v.split; ++a.split_log2) {}
-        for (uint32_t sh = 0; sh < v.split; ++sh)
-            for (int wv = 0; wv < BATCH_WAVES; ++wv) {
-                const uint32_t n = S.task_cnt[wv], lo = n * sh / v.split, hi = n * (sh + 1) / v.split;
-                a.task_lo[sh * BATCH_WAVES + wv] = S.task_lo[wv] + lo;
-                a.task_cnt[sh * BATCH_WAVES + wv] = hi - lo;
-                a.task_g[sh * BATCH_WAVES + wv] = S.task_g[wv];
-            }
+        set_batch_tasks(a, v.split);
         a.item_keys = S.item_keys + N_OBJ * L.item0;
         a.final_out = S.final_map;
         // persistent blocks, two per CU, each with a contiguous range of the items
         dim3 grid((uint32_t)std::min<uint64_t>(L.n_items, (uint64_t)S.resident_blocks));
         a.per_block = (uint32_t)((L.n_items + grid.x - 1) / grid.x);
-        switch (v.mask) {
-        case 1: launch_batch_mask<1>(v.fast, v.regroup, grid, a); break;
-        case 2: launch_batch_mask<2>(v.fast, v.regroup, grid, a); break;
-        case 3: launch_batch_mask<3>(v.fast, v.regroup, grid, a); break;
-        case 4: launch_batch_mask<4>(v.fast, v.regroup, grid, a); break;
-        case 8: launch_batch_mask<8>(v.fast, v.regroup, grid, a); break;
-        default: return MMEE_EINVAL;
-        }
+        rc = launch_batch(v.mask, v.fast, v.regroup, grid, a);
+        if (rc) return rc;
     }
-    HIP_TRY(hipGetLastError());
     HIP_TRY(hipEventRecord(S.events[2 * ev_slot + 1], S.stream));
     return MMEE_OK;
 }
@@ -932,15 +960,6 @@ void shape_constants(const DivTable &dv, double (&extent)[4], double (&size)[5])
     for (int q = 0; q < 4; ++q) extent[q] = (double)dv.X[q];
     size[0] = extent[DI] * extent[DK]; size[1] = extent[DK] * extent[DL]; size[2] = extent[DL] * extent[DJ];
     size[3] = extent[DI] * extent[DJ]; size[4] = extent[DI] * extent[DL];
-}
-
-uint32_t list_length(const DivTable &dv) { return dv.ndiv[0] + dv.ndiv[1] + dv.ndiv[2] + dv.ndiv[3]; }
-void pack_lists(const DivTable &dv, uint32_t *list)
-{
-    for (int q = 0; q < 4; ++q) {
-        std::memcpy(list, dv.div[q], sizeof(uint32_t) * dv.ndiv[q]);
-        list += dv.ndiv[q];
-    }
 }
 
 // Groups of problems with one shape, laid out as the kernel reads them.
@@ -1269,6 +1288,8 @@ int noalloc_setup(int dev, NoAllocDevice *&out)
     HIP_TRY(hipMemcpyAsync(h, counts, sizeof(h), hipMemcpyDeviceToHost, S.stream));
     HIP_TRY(hipStreamSynchronize(S.stream));
     for (int g = 0; g < 4; ++g) { d.counts[0][g] = h[g]; d.counts[1][g] = h[4 + g]; }
+    const int rc = check_kept_rows(rows1, d.counts[1]);
+    if (rc) return rc;
     d.built = true;
     return MMEE_OK;
 }
@@ -1785,6 +1806,28 @@ int mmee_search_noalloc(const mmee_workload *w, const mmee_hw *hw, int objective
     b.final_dev = reinterpret_cast<FinalRecord *>(q + noalloc::OFF_FINAL);
     b.dv_dev = reinterpret_cast<DivTable *>(q + noalloc::OFF_DV);
     b.resident_blocks = d->resident_blocks;
+    if (!(flags & MMEE_SEARCH_EXHAUSTIVE)) {
+        // The kept rows: no tables, no counters to clear, the finish writes the result record; 16384 tilings have at most
+        // 240 + 68 + 1 + 1 divisors and 512 items.
+        BatchArgs a;
+        std::memset(&a, 0, sizeof(a));
+        const uint32_t chunks = (uint32_t)((p.T + PRUNED_TC - 1) / PRUNED_TC), split = batch_split(chunks, b.resident_blocks);
+        if (list_length(p.dv) > (uint32_t)BATCH_INLINE_DIVS || chunks * split > noalloc::MAX_BLOCKS) return MMEE_ETOOBIG;
+        // the regrouped energy sum only where it is provably exact: nothing is read back to check it
+        const ModelConst mc = pass_constants(p, flags, 1 << objective);
+        fill_batch_head(a.inl.h, a.inl.list, p, mc, 0, 0, split);
+        a.inl.firsts[0] = 0; a.inl.firsts[1] = a.inl.h.n_work;
+        a.inl.on = 1;
+        a.n_prob = 1; a.n_items = a.inl.h.n_work;
+        a.enc = b.enc;
+        set_batch_tasks(a, split);
+        a.item_keys = b.partials;
+        a.packed = out_dev; a.space = p.space;
+        a.evaluated = ((uint64_t)d->counts[1][0] + d->counts[1][1] + d->counts[1][2] + d->counts[1][3]) * p.T * 9ull;
+        const dim3 grid(std::min(a.n_items, b.resident_blocks));
+        a.per_block = (a.n_items + grid.x - 1) / grid.x;
+        return launch_batch(1 << objective, p.exact_k, mc.regroup != 0, grid, a);
+    }
     // the finish ticket and the work counter must start at zero whatever the last call left
     hipLaunchKernelGGL(k_clear_words, dim3(1), dim3(64), 0, S.stream, b.ticket, 2u);
     uint64_t evaluated = 0;
