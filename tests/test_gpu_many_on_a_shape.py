@@ -54,3 +54,19 @@ def test_same_results_as_one_call_per_problem(M, n, n_caps):
     # once more: nothing of a call is left for the next
     again, codes2 = M.mmee_search_many(points, M.SEARCH_PRUNED)
     assert list(codes2) == list(codes) and [r.best.idx for r in again] == [r.best.idx for r in results]
+
+
+@pytest.mark.parametrize("n", [1, 255, 257, 4096, 4097])
+def test_decode_of_short_and_long_lists(M, n):
+    """Lists up to 4096 indices are read and written in pinned host memory, longer ones on the device."""
+    import oracle as O
+    w, h = dict(B=1, H=2, N=60, d=10, word_bytes=2, tiling_mode=1, c_softmax=10), accelerators(random.Random(n), 1, [4000])[0]
+    space = M.mmee_space_size(w, h)
+    idx = [random.Random(n + k).randrange(space) for k in range(n)]
+    got = M.mmee_decode(w, h, idx)
+    assert [m.idx for m in got] == idx
+    for k in sorted({0, n // 2, n - 1, min(n - 1, 255), min(n - 1, 256)}):
+        want, _, _ = O.evaluate(O.workload(w), O.hw(h), idx[k])
+        for fld in ("xG", "xD", "order", "level"):
+            assert list(getattr(got[k], fld)) == list(getattr(want, fld)), (n, k, fld)
+        assert (got[k].recompute, got[k].stat1, got[k].stat2, got[k].fused) == (want.recompute, want.stat1, want.stat2, want.fused)
