@@ -17,6 +17,7 @@
 #include "batch.h"
 #include "pruned.h"
 #include "fronts.h"
+#include "pinned.h"
 
 // ---- fixed scratch of the entry point that allocates nothing (mmee_search_noalloc) ------------
 // One array per GPU, held from the moment the library is loaded until the process ends.  In host
@@ -96,7 +97,7 @@ struct State {
     void *eval_dev = nullptr;
     size_t eval_cap = 0;
     // short index lists of mmee_decode and their mappings: pinned host memory the kernel reads and writes directly
-    unsigned char *decode_host = nullptr, *decode_map = nullptr;
+    Pinned decode;
     uint32_t resident_blocks = 512;
     // batched search over the pruned rows: problem descriptors (pinned staging + device copy), one record
     // per work item and objective
@@ -108,11 +109,11 @@ struct State {
     // published values per result slot
     unsigned char *desc_host = nullptr, *desc_dev = nullptr;
     size_t desc_cap = 0;
-    // fronts over the kept rows: the chunks' points and their counters, the front's records and their number (pinned)
+    // fronts over the kept rows: the chunks' points and their counters; FRONT_POINTS records of the front and their
+    // number (pinned)
     Key *front_points = nullptr, *front_lists = nullptr;
     uint32_t *front_counts = nullptr;
-    FinalRecord *front_host = nullptr, *front_map = nullptr;     // [FRONT_POINTS], host address / device address
-    uint32_t *front_n_host = nullptr, *front_n_map = nullptr;
+    Pinned front;
     void *block_records = nullptr;              // what the blocks of a pruned search leave for the reduction
     size_t block_records_cap = 0;
     unsigned long long *pruned_hints = nullptr;
@@ -396,6 +397,19 @@ int ensure_ready()
     return MMEE_OK;
 }
 
+struct HipPinned {
+    hipError_t success = hipSuccess;
+    hipError_t alloc(unsigned char **host, size_t bytes) const
+    {
+        return hipHostMalloc(reinterpret_cast<void **>(host), bytes, hipHostMallocMapped);
+    }
+    hipError_t address(unsigned char **map, unsigned char *host) const
+    {
+        return hipHostGetDevicePointer(reinterpret_cast<void **>(map), host, 0);
+    }
+    hipError_t release(unsigned char *host) const { return hipHostFree(host); }
+};
+
 int ensure_tilings(uint64_t tpad)
 {
     if (tpad <= S.tiling_cap) return MMEE_OK;
@@ -421,10 +435,10 @@ int ensure_partials(size_t nblocks)
 int ensure_slots(size_t n)
 {
     if (n <= S.slots) return MMEE_OK;
-    if (S.final_host) {
+    if (S.dv_dev) {
         HIP_TRY(hipStreamSynchronize(S.stream));
         (void)hipFree(S.dv_dev); (void)hipFree(S.pruned_hints);
-        (void)hipHostFree(S.final_host);
+        if (S.final_host) (void)hipHostFree(S.final_host);
     }
     S.slots = 0; S.final_host = nullptr; S.final_map = nullptr; S.dv_dev = nullptr; S.pruned_hints = nullptr;
     HIP_TRY(hipMalloc(&S.dv_dev, sizeof(DivTable) * n));
@@ -1190,19 +1204,16 @@ int unpack_result(const Plan &p, size_t slot, int objective, uint64_t evaluated,
 
 static_assert(sizeof(FrontArgs) <= 4096, "kernel arguments are limited to 4 KiB");
 
-// The front in three launches; its records land in S.front_host, their number in *S.front_n_host (TOO_MANY: something
-// outgrew its room, walk the front).  Events of slot 0 bracket it.
+constexpr size_t FRONT_N_AT = sizeof(FinalRecord) * FRONT_POINTS;     // where S.front has the number of its records
+
+// The front in three launches; its records and their number land in S.front (TOO_MANY: something outgrew its room,
+// walk the front).  Events of slot 0 bracket it.
 int enqueue_front(const Plan &p, bool bs_da, uint32_t capacity)
 {
-    if (!S.front_n_host) {
-        HIP_TRY(hipMalloc(&S.front_points, sizeof(Key) * FRONT_BLOCKS * FRONT_WAVE));
-        HIP_TRY(hipMalloc(&S.front_lists, sizeof(Key) * FRONT_LISTS * FRONT_LIST));
-        HIP_TRY(hipMalloc(&S.front_counts, sizeof(uint32_t) * (FRONT_BLOCKS + FRONT_LISTS)));
-        HIP_TRY(hipHostMalloc(&S.front_host, sizeof(FinalRecord) * FRONT_POINTS, hipHostMallocMapped));
-        HIP_TRY(hipHostGetDevicePointer(reinterpret_cast<void **>(&S.front_map), S.front_host, 0));
-        HIP_TRY(hipHostMalloc(&S.front_n_host, sizeof(uint32_t), hipHostMallocMapped));
-        HIP_TRY(hipHostGetDevicePointer(reinterpret_cast<void **>(&S.front_n_map), S.front_n_host, 0));
-    }
+    if (!S.front_points) HIP_TRY(hipMalloc(&S.front_points, sizeof(Key) * FRONT_BLOCKS * FRONT_WAVE));
+    if (!S.front_lists) HIP_TRY(hipMalloc(&S.front_lists, sizeof(Key) * FRONT_LISTS * FRONT_LIST));
+    if (!S.front_counts) HIP_TRY(hipMalloc(&S.front_counts, sizeof(uint32_t) * (FRONT_BLOCKS + FRONT_LISTS)));
+    HIP_TRY(ensure_pinned(HipPinned{}, S.front, FRONT_N_AT + sizeof(uint32_t)));
     FrontArgs a;
     std::memset(&a, 0, sizeof(a));
     a.mc = p.mc;
@@ -1215,7 +1226,8 @@ int enqueue_front(const Plan &p, bool bs_da, uint32_t capacity)
     a.points = S.front_points; a.lists = S.front_lists; a.counts = S.front_counts; a.enc = S.enc;
     a.n_blocks = (uint32_t)((p.T + PRUNED_TC - 1) / PRUNED_TC) * (bs_da ? FRONT_SPLIT : 1);
     a.n_lists = (a.n_blocks + FRONT_FAN - 1) / FRONT_FAN;
-    a.out = S.front_map; a.n_out = S.front_n_map;
+    a.out = reinterpret_cast<FinalRecord *>(S.front.map);
+    a.n_out = reinterpret_cast<uint32_t *>(S.front.map + FRONT_N_AT);
     HIP_TRY(hipEventRecord(S.events[0], S.stream));
     const dim3 grid(a.n_blocks);
     if (bs_da) hipLaunchKernelGGL(k_front_points<true>, grid, dim3(PRUNED_THREADS), 0, S.stream, a);
@@ -1369,17 +1381,14 @@ int mmee_chain_decode(const mmee_chain *w, const mmee_hw *hw, const uint64_t *id
     if (rc) return rc;
     if (n <= DECODE_SHORT) {
         // (two allocations, two copies and two frees were 17 us more per call of sixteen indices)
-        if (!S.decode_host) {
-            HIP_TRY(hipHostMalloc(&S.decode_host, (sizeof(mmee_mapping) + sizeof(uint64_t)) * DECODE_SHORT, hipHostMallocMapped));
-            HIP_TRY(hipHostGetDevicePointer(reinterpret_cast<void **>(&S.decode_map), S.decode_host, 0));
-        }
+        HIP_TRY(ensure_pinned(HipPinned{}, S.decode, (sizeof(mmee_mapping) + sizeof(uint64_t)) * DECODE_SHORT));
         constexpr size_t OUT = sizeof(uint64_t) * DECODE_SHORT;
-        std::memcpy(S.decode_host, idx, sizeof(uint64_t) * n);
+        std::memcpy(S.decode.host, idx, sizeof(uint64_t) * n);
         hipLaunchKernelGGL(k_decode, dim3((uint32_t)((n + 255) / 256)), dim3(256), 0, S.stream, p.dv, p.mc.T,
-                           reinterpret_cast<const uint64_t *>(S.decode_map), n, reinterpret_cast<mmee_mapping *>(S.decode_map + OUT));
+                           reinterpret_cast<const uint64_t *>(S.decode.map), n, reinterpret_cast<mmee_mapping *>(S.decode.map + OUT));
         HIP_TRY(hipGetLastError());
         HIP_TRY(hipStreamSynchronize(S.stream));
-        std::memcpy(out, S.decode_host + OUT, sizeof(mmee_mapping) * n);
+        std::memcpy(out, S.decode.host + OUT, sizeof(mmee_mapping) * n);
         return MMEE_OK;
     }
     uint64_t *d_idx = nullptr;
@@ -1631,7 +1640,8 @@ static int walk_front(const mmee_chain *w, const mmee_hw *hw, bool bs_da, uint32
         rc = enqueue_front(p, bs_da, capacity);
         if (rc) return rc;
         HIP_TRY(hipStreamSynchronize(S.stream));
-        const uint32_t n = *S.front_n_host;
+        const FinalRecord *records = reinterpret_cast<const FinalRecord *>(S.front.host);
+        const uint32_t n = *reinterpret_cast<const uint32_t *>(S.front.host + FRONT_N_AT);
         if (n != TOO_MANY) {
             float ms = 0.f;
             (void)hipEventElapsedTime(&ms, S.events[0], S.events[1]);
@@ -1640,7 +1650,7 @@ static int walk_front(const mmee_chain *w, const mmee_hw *hw, bool bs_da, uint32
             const uint64_t formed = fits ? kept_row_count() * p.T * (bs_da ? 1ull : 9ull) * ((uint64_t)n + 1) : 0;
             const double seconds = fits ? now_seconds() - t_start : 0.0;
             *n_points = std::min(n, capacity);
-            for (uint32_t k = 0; k < *n_points; ++k) (void)unpack_record(p, S.front_host[k], formed, seconds, fits ? ms * 1e-3 : 0.0, out + k);
+            for (uint32_t k = 0; k < *n_points; ++k) (void)unpack_record(p, records[k], formed, seconds, fits ? ms * 1e-3 : 0.0, out + k);
             return !fits ? MMEE_EOVERFLOW : (n ? MMEE_OK : MMEE_ENOFEASIBLE);
         }
     }
@@ -1873,10 +1883,9 @@ void mmee_shutdown(void)
     if (S.batch_host) (void)hipHostFree(S.batch_host);
     (void)hipFree(S.batch_dev); (void)hipFree(S.item_keys);
     if (S.desc_host) (void)hipHostFree(S.desc_host);
-    if (S.decode_host) (void)hipHostFree(S.decode_host);
+    if (S.decode.host) (void)hipHostFree(S.decode.host);
     (void)hipFree(S.front_points); (void)hipFree(S.front_lists); (void)hipFree(S.front_counts);
-    if (S.front_host) (void)hipHostFree(S.front_host);
-    if (S.front_n_host) (void)hipHostFree(S.front_n_host);
+    if (S.front.host) (void)hipHostFree(S.front.host);
     (void)hipFree(S.desc_dev); (void)hipFree(S.block_records); (void)hipFree(S.pruned_hints);
     for (hipEvent_t e : S.events) (void)hipEventDestroy(e);
     hipStream_t keep = S.stream;
