@@ -66,6 +66,7 @@ namespace {
 
 char g_last_error[512] = "";
 std::mutex g_lock;
+uint64_t g_front_walks = 0;         // fronts walked point by point so far
 
 struct State {
     bool ready = false;
@@ -1206,12 +1207,12 @@ static_assert(sizeof(FrontArgs) <= 4096, "kernel arguments are limited to 4 KiB"
 
 constexpr size_t FRONT_N_AT = sizeof(FinalRecord) * FRONT_POINTS;     // where S.front has the number of its records
 
-// The front in three launches; its records and their number land in S.front (TOO_MANY: something outgrew its room,
+// The front in three launches (two where the blocks are few); its records and their number land in S.front (TOO_MANY: something outgrew its room,
 // walk the front).  Events of slot 0 bracket it.
 int enqueue_front(const Plan &p, bool bs_da, uint32_t capacity)
 {
-    if (!S.front_points) HIP_TRY(hipMalloc(&S.front_points, sizeof(Key) * FRONT_BLOCKS * FRONT_WAVE));
-    if (!S.front_lists) HIP_TRY(hipMalloc(&S.front_lists, sizeof(Key) * FRONT_LISTS * FRONT_LIST));
+    if (!S.front_points) HIP_TRY(hipMalloc(&S.front_points, sizeof(Key) * FRONT_BLOCKS * FRONT_BLOCK));
+    if (!S.front_lists) HIP_TRY(hipMalloc(&S.front_lists, sizeof(Key) * FRONT_LISTS * FRONT_POINTS));
     if (!S.front_counts) HIP_TRY(hipMalloc(&S.front_counts, sizeof(uint32_t) * (FRONT_BLOCKS + FRONT_LISTS)));
     HIP_TRY(ensure_pinned(HipPinned{}, S.front, FRONT_N_AT + sizeof(uint32_t)));
     FrontArgs a;
@@ -1226,13 +1227,14 @@ int enqueue_front(const Plan &p, bool bs_da, uint32_t capacity)
     a.points = S.front_points; a.lists = S.front_lists; a.counts = S.front_counts; a.enc = S.enc;
     a.n_blocks = (uint32_t)((p.T + PRUNED_TC - 1) / PRUNED_TC) * (bs_da ? FRONT_SPLIT : 1);
     a.n_lists = (a.n_blocks + FRONT_FAN - 1) / FRONT_FAN;
+    a.one_merge = a.n_blocks <= FRONT_FAN;
     a.out = reinterpret_cast<FinalRecord *>(S.front.map);
     a.n_out = reinterpret_cast<uint32_t *>(S.front.map + FRONT_N_AT);
     HIP_TRY(hipEventRecord(S.events[0], S.stream));
     const dim3 grid(a.n_blocks);
     if (bs_da) hipLaunchKernelGGL(k_front_points<true>, grid, dim3(PRUNED_THREADS), 0, S.stream, a);
     else hipLaunchKernelGGL(k_front_points<false>, grid, dim3(PRUNED_THREADS), 0, S.stream, a);
-    hipLaunchKernelGGL(k_front_merge<false>, dim3(a.n_lists), dim3(MERGE_THREADS), 0, S.stream, a);
+    if (!a.one_merge) hipLaunchKernelGGL(k_front_merge<false>, dim3(a.n_lists), dim3(MERGE_THREADS), 0, S.stream, a);
     hipLaunchKernelGGL(k_front_merge<true>, dim3(1), dim3(MERGE_THREADS), 0, S.stream, a);
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipEventRecord(S.events[1], S.stream));
@@ -1654,6 +1656,7 @@ static int walk_front(const mmee_chain *w, const mmee_hw *hw, bool bs_da, uint32
             return !fits ? MMEE_EOVERFLOW : (n ? MMEE_OK : MMEE_ENOFEASIBLE);
         }
     }
+    ++g_front_walks;
     double limit = INFINITY, ksec = 0.0;
     uint64_t evaluated = 0;
     for (uint32_t k = 0;; ++k) {
@@ -1688,6 +1691,13 @@ static int walk_front(const mmee_chain *w, const mmee_hw *hw, bool bs_da, uint32
         out[k].evaluated = evaluated; out[k].seconds = seconds; out[k].kernel_seconds = ksec;
     }
     return *n_points ? MMEE_OK : MMEE_ENOFEASIBLE;
+}
+
+// Not part of the interface: which way the fronts took, for tests.
+uint64_t mmee_front_walks(void)
+{
+    std::lock_guard<std::mutex> guard(g_lock);
+    return g_front_walks;
 }
 
 int mmee_chain_pareto(const mmee_chain *w, const mmee_hw *hw, uint32_t flags, mmee_result *out, uint32_t capacity,
