@@ -982,7 +982,8 @@ void shape_constants(const DivTable &dv, double (&extent)[4], double (&size)[5])
 // Groups of problems with one shape, laid out as the kernel reads them.
 struct PrunedLayout {
     std::vector<unsigned char> desc;
-    uint32_t n_groups = 0, n_members = 0, members_off = 0, n_items = 0, stride = 0;
+    uint32_t n_groups = 0, n_members = 0, members_off = 0, n_items = 0;
+    uint64_t n_keys = 0;    // records of all its items
 };
 
 // entries[order[k]], k in [lo, hi): the groups of one launch
@@ -1051,13 +1052,11 @@ void pruned_layout(const std::vector<PrunedEntry> &entries, const std::vector<ui
 {
     auto up16 = [](size_t x) { return (x + 15) & ~(size_t)15; };
     size_t n_members = 0, n_caps = 0, n_list = 0;
-    out.stride = 0;
     for (const PrunedSlice &sl : slices) {
         const DivTable &dv = entries[order[sl.lo]].plan->dv;
         n_members += sl.hi - sl.lo;
         n_caps += sl.n_caps;
         n_list += list_length(dv);
-        out.stride = std::max(out.stride, sl.hi - sl.lo);
     }
     const size_t members_off = up16(sizeof(PrunedGroup) * slices.size());
     size_t caps_off = up16(members_off + sizeof(PrunedMember) * n_members), list_off = up16(caps_off + sizeof(double) * n_caps);
@@ -1081,6 +1080,8 @@ void pruned_layout(const std::vector<PrunedEntry> &entries, const std::vector<ui
         G.n_caps = sl.n_caps;
         G.caps_off = (uint32_t)caps_off;
         G.T = (uint32_t)p.T;
+        G.key0 = out.n_keys;
+        out.n_keys += (uint64_t)G.n_items * G.n_members * N_OBJ;
         G.list_off = (uint32_t)list_off;
         double *caps = reinterpret_cast<double *>(base + caps_off);
         uint32_t cap = 0;
@@ -1121,7 +1122,7 @@ int launch_pruned(const PrunedBufs &B, const PrunedLayout &l, const unsigned cha
         std::memcpy(a.inl, l.desc.data(), l.desc.size());
     }
     a.n_groups = l.n_groups; a.n_items = l.n_items;
-    a.members_off = l.members_off; a.n_members = l.n_members; a.stride = l.stride;
+    a.members_off = l.members_off; a.n_members = l.n_members;
     a.enc = B.enc; a.keys = keys; a.hints = B.hints; a.final_out = B.final_out;
     hipLaunchKernelGGL(k_search_pruned, dim3(l.n_items), dim3(PRUNED_THREADS), 0, S.stream, a);
     hipLaunchKernelGGL(k_pruned_finish, dim3(l.n_members), dim3(256), 0, S.stream, a);
@@ -1166,7 +1167,7 @@ int enqueue_pruned(const std::vector<PrunedEntry> &entries, size_t ev_slot)
     pruned_layout(entries, order, slices, l);
     const bool inside = l.desc.size() <= (size_t)PRUNED_INLINE;
     int rc = inside ? MMEE_OK : ensure_desc(l.desc.size());
-    if (!rc) rc = ensure_block_records((size_t)l.n_items * l.stride * N_OBJ * sizeof(Key));
+    if (!rc) rc = ensure_block_records((size_t)l.n_keys * sizeof(Key));
     if (rc) return rc;
     HIP_TRY(hipEventRecord(S.events[2 * ev_slot], S.stream));
     if (!inside) {

@@ -49,6 +49,7 @@ struct PrunedGroup {
     uint32_t member0, n_members;             // its problems, by ascending capacity
     uint32_t n_caps, caps_off;               // the distinct capacities, words, ascending (fp64)
     uint32_t T, list_off;                    // tilings; the four divisor lists one after the other
+    uint64_t key0;                           // its records in PrunedArgs::keys: [n_items][n_members][N_OBJ]
     uint32_t X[4], ndiv[4];                  // extents and divisor counts of i, k, l, j
     DigitConst dg;
     double extent[4], size[5];               // the extents, and the words of A, B, D, E, C: as fp64 they reach the kernel
@@ -67,9 +68,8 @@ struct PrunedArgs {
     const unsigned char *desc;               // descriptions in device memory; null: in `inl`
     uint32_t n_groups, n_items;
     uint32_t members_off, n_members;
-    uint32_t stride;                         // problems the largest group holds: records per item
     const uint4 *enc;                        // every encoded row (for the winner's record)
-    Key *keys;                               // [n_items][stride][N_OBJ]
+    Key *keys;                               // the items' records, group after group
     unsigned long long *hints;               // [slot][N_OBJ] lowest value published so far (bit pattern); +inf between launches
     FinalRecord *final_out;                  // [slot][N_OBJ]
     alignas(16) unsigned char inl[PRUNED_INLINE];
@@ -643,7 +643,7 @@ __global__ __launch_bounds__(PRUNED_THREADS, 4) void k_search_pruned(PrunedArgs 
     }
     // ---- the item's records
     for (uint32_t k = threadIdx.x; k < G.n_members * N_OBJ; k += PRUNED_THREADS)
-        a.keys[((uint64_t)item * a.stride + k / N_OBJ) * N_OBJ + k % N_OBJ] = best[k / N_OBJ][k % N_OBJ];
+        a.keys[G.key0 + (uint64_t)(item - G.first_item) * (G.n_members * N_OBJ) + k] = best[k / N_OBJ][k % N_OBJ];
 }
 
 // After the search: one block per problem reduces the problem's records, one per item of its group, and writes the
@@ -673,7 +673,7 @@ __global__ __launch_bounds__(256) void k_pruned_finish(PrunedArgs a)
         if (!((mb.mask >> o) & 1)) continue;
         Key k; k.p = inf; k.s = 0.0; k.idx = ~0ull;
         for (uint32_t b = threadIdx.x; b < G.n_items; b += 256) {
-            const Key c = a.keys[((uint64_t)(G.first_item + b) * a.stride + member) * N_OBJ + o];
+            const Key c = a.keys[G.key0 + ((uint64_t)b * G.n_members + member) * N_OBJ + o];
             if (key_less(c, k)) k = c;
         }
         k = wave_min(k);

@@ -70,3 +70,25 @@ def test_decode_of_short_and_long_lists(M, n):
         for fld in ("xG", "xD", "order", "level"):
             assert list(getattr(got[k], fld)) == list(getattr(want, fld)), (n, k, fld)
         assert (got[k].recompute, got[k].stat1, got[k].stat2, got[k].fused) == (want.recompute, want.stat1, want.stat2, want.fused)
+
+
+def test_records_of_a_shape_take_room_for_its_own_problems(M):
+    """One shape of sixty-four problems beside one of many tilings and four problems: what the call keeps on the device
+    goes by each shape's own number of problems (4 MB of records here; 62 MB if all were sized for the largest)."""
+    import torch
+    rng = random.Random(3)
+    small = dict(batch=1, I=8, K=2, L=8, J=2, word_bytes=2, tiling_mode=0, c_softmax=0)
+    large = dict(batch=1, I=5040, K=720, L=360, J=48, word_bytes=2, tiling_mode=1, c_softmax=0)      # 60 * 30 * 24 * 10 = 432000 tilings
+    sizes = [(small, 64), (dict(small, batch=2), 64), (large, 4)]
+    points = [(c, h, 0) for c, n in sizes for h in accelerators(rng, n, [4000, 40000])]
+    M.mmee_shutdown()
+    M.mmee_chain_search_many(points[:2], M.SEARCH_PRUNED)        # the offline stage and the small buffers
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    results, codes = M.mmee_chain_search_many(points, M.SEARCH_PRUNED)
+    taken = free - torch.cuda.mem_get_info()[0]
+    assert taken < 48 << 20, taken
+    for (c, h, o), r, code in zip(points, results, codes):
+        assert code == 0
+        want = M.mmee_chain_search_multi(c, h, [o], M.SEARCH_PRUNED)[0]
+        assert bytes(r.cost) == bytes(want.cost) and r.best.idx == want.best.idx
