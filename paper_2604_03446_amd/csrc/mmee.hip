@@ -995,11 +995,6 @@ bool same_shape(const Plan &a, const Plan &b)
     return std::memcmp(a.dv.X, b.dv.X, sizeof(a.dv.X)) == 0 && std::memcmp(a.dv.ndiv, b.dv.ndiv, sizeof(a.dv.ndiv)) == 0;
 }
 
-// Whether to share the row side among problems of a shape.  Per chunk of 64 tilings k_search_batch takes about 6500 wave
-// instructions per problem, k_search_pruned 3000 per four capacities and 800 per problem; below four problems a
-// shape it does not pay, and small launches are quicker in k_search_batch (pruned.h).
-bool worth_sharing(const std::vector<PrunedEntry> &entries);
-
 // Problems of one shape become groups of at most PRUNED_MEMBERS, by ascending capacity.
 void pruned_slices(const std::vector<PrunedEntry> &entries, std::vector<uint32_t> &order, std::vector<PrunedSlice> &slices)
 {
@@ -1038,13 +1033,81 @@ void pruned_slices(const std::vector<PrunedEntry> &entries, std::vector<uint32_t
     }
 }
 
-bool worth_sharing(const std::vector<PrunedEntry> &entries)
+// Of a call's groups, those that k_search_pruned takes; the others stay with k_search_batch, or, with a key set that it
+// is not built for, get a pass of their own.
+//
+// A block of k_search_batch takes a chunk of one problem, 512 at a time on the chip; a block of k_search_pruned takes
+// a chunk of all problems of a group, its waves an eighth of them each, one after the other: with few
+// chunks that chain is longer than what the row side costs per problem.  So the ways are estimated, in microseconds per
+// call apart from what the host does per problem either way (0.44): all in batches; groups of four problems or more
+// shared and the rest in batches (two sets of copies and launches that wait for each other: 110); all shared.
+// Fitted to 1650 calls of 1 to 640 problems on 1 to 40 shapes of 1 to 324 chunks, one key set a call: the choice costs
+// 1 % over the better way on average, 3 % or more over k_search_batch in 18 calls (at most 15 %), 3 % or more over
+// k_search_pruned in 58 (at most 17 %).  Sharing from four problems a group on whatever their size cost up to 208 %
+// (64 problems of 77 chunks, (latency, energy) key: 254 us, 192 in k_search_batch; 64 of one chunk, energy: 118 and 68),
+// never sharing up to 270 % (64 problems of 324 chunks, energy: 475 us, 126 shared).  A pass of its own costs 33 us
+// a problem of one chunk and 105 us at 324 chunks (energy, latency and energy-delay product).
+void keep_shared(const std::vector<PrunedEntry> &entries, const std::vector<uint32_t> &order, std::vector<PrunedSlice> &slices)
 {
-    if (entries.size() < 4) return false;
-    std::vector<uint32_t> order;
-    std::vector<PrunedSlice> slices;
-    pruned_slices(entries, order, slices);
-    return entries.size() >= 4 * slices.size();
+    struct Batches {                         // chunks, and kinds of kernel: each is a launch of its own
+        double items = 0.0;
+        uint64_t kinds = 0;
+        void add(const PrunedEntry &e, double chunks)
+        {
+            items += chunks;
+            kinds |= 1ull << (e.mask * 4 + (e.plan->exact_k ? 2 : 0) + (e.plan->can_regroup ? 1 : 0));
+        }
+        double us() const
+        {
+            const double rounds = items / 512.0;
+            return items == 0.0 ? 0.0 : 21.0 + 20.0 * __builtin_popcountll(kinds) + 15.0 * std::min(1.0, rounds) + 10.5 * std::max(0.0, rounds - 1.0);
+        }
+    };
+    struct Shared {                          // bytes of descriptions, the longest block, all blocks 512 at a time
+        size_t bytes = 0;
+        double longest = 0.0, work = 0.0;
+        void add(size_t members, double chunks, double block_us)
+        {
+            bytes += sizeof(PrunedGroup) + members * sizeof(PrunedMember);
+            longest = std::max(longest, block_us);
+            work += 1.12 / 512.0 * chunks * block_us;
+        }
+        // (descriptions beyond the kernel arguments are copied)
+        double us() const { return 9.5 + (bytes > (size_t)PRUNED_INLINE ? 10.5 : 0.0) + std::max(longest, work); }
+    };
+    auto key_us = [](int mask) {             // one problem after the other
+        return ((mask & 3) == 3 ? 6.0 : ((mask & 3) ? 5.0 : 0.0)) + ((mask & 4) ? 14.0 : 0.0) + ((mask & 8) ? 9.5 : 0.0);
+    };
+    Batches all, rest;
+    Shared large, every;
+    double alone_us = 0.0, rest_alone_us = 0.0;
+    auto is_large = [](const PrunedSlice &sl) { return sl.hi - sl.lo >= 4; };
+    for (const PrunedSlice &sl : slices) {
+        const double chunks = std::ceil((double)entries[order[sl.lo]].plan->T / PRUNED_TC);
+        const uint32_t members = sl.hi - sl.lo;
+        double keys = 0.0;
+        for (uint32_t k = sl.lo; k < sl.hi; ++k) {
+            const PrunedEntry &e = entries[order[k]];
+            keys += key_us(e.mask);
+            if (!batch_mask(e.mask)) {
+                alone_us += 33.0 + 0.22 * chunks;
+                if (!is_large(sl)) rest_alone_us += 33.0 + 0.22 * chunks;
+                continue;
+            }
+            all.add(e, chunks);
+            if (!is_large(sl)) rest.add(e, chunks);
+        }
+        // (another round of capacities: the rows once more)
+        const double block_us = 24.0 + 12.0 * ((sl.n_caps - 1) / PRUNED_ROUND) + keys / members * std::ceil(members / 8.0);
+        every.add(members, chunks, block_us);
+        if (is_large(sl)) large.add(members, chunks, block_us);
+    }
+    // (85: the 110, less what the synchronisation adds to either part; 1.15: a lone problem's blocks are short of waves in step 2)
+    const double batched_us = all.us() + alone_us, every_us = every.us() * (rest.items > 0.0 ? 1.15 : 1.0);
+    const double mixed_us = large.bytes && rest.items > 0.0 ? large.us() + rest.us() + rest_alone_us + 85.0 : INFINITY;
+    const bool none_large = !large.bytes && alone_us == 0.0;
+    if (none_large || batched_us <= std::min(every_us, mixed_us)) slices.clear();
+    else if (mixed_us < every_us) slices.erase(std::remove_if(slices.begin(), slices.end(), [&](const PrunedSlice &sl) { return !is_large(sl); }), slices.end());
 }
 
 void pruned_layout(const std::vector<PrunedEntry> &entries, const std::vector<uint32_t> &order, const std::vector<PrunedSlice> &slices,
@@ -1153,13 +1216,10 @@ int ensure_block_records(size_t bytes)
     return MMEE_OK;
 }
 
-// Enqueue pruned searches.  Events of slot `ev_slot` bracket it all.
-int enqueue_pruned(const std::vector<PrunedEntry> &entries, size_t ev_slot)
+// Enqueue the pruned searches of these groups.  Events of slot `ev_slot` bracket it all.
+int enqueue_pruned(const std::vector<PrunedEntry> &entries, const std::vector<uint32_t> &order, const std::vector<PrunedSlice> &slices,
+                   size_t ev_slot)
 {
-    if (entries.empty()) return MMEE_OK;
-    std::vector<uint32_t> order;
-    std::vector<PrunedSlice> slices;
-    pruned_slices(entries, order, slices);
     uint64_t items = 0;
     for (const PrunedSlice &sl : slices) items += (entries[order[sl.lo]].plan->T + PRUNED_TC - 1) / PRUNED_TC;
     if (items > 0x7fffffffull) return MMEE_EINVAL;
@@ -1515,21 +1575,29 @@ int mmee_chain_search_many(const mmee_chain *w, const mmee_hw *hw, const int *ob
     // problem by problem.  `round_flags` adds MMEE_SEARCH_ORDERED_SUM on the second round, which repeats what the
     // first could not prove.
     auto run_round = [&](uint32_t round_flags, bool only_unproven) -> int {
-        std::vector<PrunedEntry> shared;
+        std::vector<PrunedEntry> pruned;
+        std::vector<uint32_t> order;
+        std::vector<PrunedSlice> slices;                     // the groups that share more than launches
+        std::vector<char> in_slice(passes.size(), 0);
+        size_t slice_ev = 0;
         std::vector<BatchEntry> batch;
         std::vector<size_t> batch_pass;
         auto takes_part = [&](const Pass &ps) { return ps.rc == MMEE_OK && (!only_unproven || ps.unproven); };
-        if (!(round_flags & MMEE_SEARCH_EXHAUSTIVE)) {
+        if (!(round_flags & MMEE_SEARCH_EXHAUSTIVE) && passes.size() > 1) {
             for (size_t s = 0; s < passes.size(); ++s)
-                if (takes_part(passes[s])) shared.push_back(PrunedEntry{&passes[s].plan, passes[s].mask, (uint32_t)s});
-            if (!worth_sharing(shared)) shared.clear();
+                if (takes_part(passes[s])) pruned.push_back(PrunedEntry{&passes[s].plan, passes[s].mask, (uint32_t)s});
+            pruned_slices(pruned, order, slices);
+            keep_shared(pruned, order, slices);
+            for (const PrunedSlice &sl : slices)
+                for (uint32_t k = sl.lo; k < sl.hi; ++k) in_slice[pruned[order[k]].slot] = 1;
+            if (!slices.empty()) slice_ev = pruned[order[slices[0].lo]].slot;
         }
         for (size_t s = 0; s < passes.size(); ++s) {
             Pass &ps = passes[s];
             if (!takes_part(ps)) continue;
             ps.ev_slot = s;
-            if (!shared.empty()) {
-                ps.ev_slot = shared[0].slot;
+            if (in_slice[s]) {
+                ps.ev_slot = slice_ev;
                 ps.evaluated = kept_row_count() * ps.plan.T * 9ull;
                 ps.unproven = false;
             } else if (!(round_flags & MMEE_SEARCH_EXHAUSTIVE) && batch_mask(ps.mask)) {
@@ -1544,9 +1612,10 @@ int mmee_chain_search_many(const mmee_chain *w, const mmee_hw *hw, const int *ob
                 ps.unproven = unproven;
             }
         }
-        if (!shared.empty()) {
-            const int src = enqueue_pruned(shared, shared[0].slot);
-            for (const PrunedEntry &e : shared) passes[e.slot].rc = src;
+        if (!slices.empty()) {
+            const int src = enqueue_pruned(pruned, order, slices, slice_ev);
+            for (size_t s = 0; s < passes.size(); ++s)
+                if (in_slice[s]) passes[s].rc = src;
         }
         if (!batch.empty()) {
             int brc = enqueue_batches(batch, round_flags, batch_pass[0]);

@@ -92,3 +92,21 @@ def test_records_of_a_shape_take_room_for_its_own_problems(M):
         assert code == 0
         want = M.mmee_chain_search_multi(c, h, [o], M.SEARCH_PRUNED)[0]
         assert bytes(r.cost) == bytes(want.cost) and r.best.idx == want.best.idx
+
+
+def test_shapes_of_many_problems_share_beside_single_ones(M):
+    """Sixty-four problems on one shape of 324 chunks beside forty shapes with one problem each: the call takes the former through
+    the kernel that shares the row side and the latter through the batched one, each with the device time of its launches."""
+    rng = random.Random(11)
+    shape = dict(batch=1, I=2048, K=2048, L=2048, J=2048, word_bytes=2, tiling_mode=0, c_softmax=0)
+    h = accelerators(rng, 64, [20000, 60000, 500000])
+    many = [(shape, dict(k, gb_bytes=k["gb_bytes"] + 2 * n), o) for n, k in enumerate(h) for o in (0, 1)]
+    single = [(dict(shape, K=64 * (2 * q + 1)), accelerators(rng, 1, [100000])[0], 0) for q in range(40)]
+    points = many + single
+    results, codes = M.mmee_chain_search_many(points, M.SEARCH_PRUNED)
+    assert not any(codes)
+    times = [{r.kernel_seconds for r in results[a:b]} for a, b in ((0, len(many)), (len(many), len(points)))]
+    assert all(len(t) == 1 for t in times) and times[0] != times[1]
+    for (c, h, o), r in zip(points, results):
+        want = M.mmee_chain_search_multi(c, h, [o], M.SEARCH_PRUNED)[0]
+        assert bytes(r.cost) == bytes(want.cost) and bytes(r.best) == bytes(want.best) and r.evaluated == want.evaluated, (c, h, o)
