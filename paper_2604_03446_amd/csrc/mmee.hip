@@ -554,18 +554,50 @@ void launch_dense(bool exact_k, dim3 grid, const SearchArgs &a)
     else with_sum(std::integral_constant<int, ENERGY ? SUM_ORDERED : SUM_REGROUPED>{});
 }
 
+// The fewest tilings at which the dense kernel takes these keys over the full row set.  One key always went there.  For
+// several it needs one pass for two scalar keys and one more for the (latency, energy) key and for a third scalar
+// key, k_search one pass for all; but with the lanes on rows k_search divides once per candidate where the DRAM time
+// is not one exact product, and keeps a code beside every minimum.  A problem of few chunks leaves the dense kernel's
+// blocks without work (188 items a chunk, 512 blocks), and each of its passes costs some 20 us at least.
+// Measured on 30 shapes of 1 to 14400 tilings for every key set and both kinds of bandwidth, the energy
+// regrouped, with its first sum fused and in order; k_search / dense, us:
+//   energy and latency, regrouped      T = 16: 41 / 50    900: 112 / 142    2800: 176 / 190    4900: 347 / 330    14400: x 0.92
+//   energy and latency, fused          T = 16: 43 / 50    144: x 1.25       900: x 0.98        4900: x 0.73
+//   energy and product, in order       T = 16: 44 / 56    900: 154 / 189    4900: 544 / 551    14400: x 0.99
+//   all four, regrouped                T = 1: 51 / 97     400: 185 / 212    900: 342 / 319     4900: 1395 / 813
+//   all four, bandwidth 60             T = 1: 56 / 99     144: 154 / 176    400: 259 / 214     4900: 2224 / 933
+//   three scalar keys, bandwidth 60    T = 16: 56 / 76    400: 174 / 158    4900: 1301 / 701
+// Energy, latency and energy-delay product with an exact DRAM time: 1.01 ms in k_search, 1.14 dense for 10692 tilings.
+// Near a bound the two differ by a few per cent (three and four chunks, two rounds of blocks: up to 8).
+uint32_t dense_from(int mask, bool exact_k, const ModelConst &mc)
+{
+    constexpr uint32_t NEVER = 0xFFFFFFFFu;
+    struct Row { int mask; uint32_t exact[3], division[2]; };        // exact: regrouped, fused, in order; division: regrouped, not
+    static const Row rows[] = {
+        {3, {3000, 224, 1100}, {8, 8}},        {9, {4500, 2500, 8000}, {16, 32}},     {10, {4500, 2500, 8000}, {16, 32}},
+        {11, {NEVER, NEVER, NEVER}, {224, 512}}, {5, {512, 400, 448}, {32, 32}},      {6, {352, 352, 352}, {32, 32}},
+        {7, {224, 224, 224}, {32, 32}},        {12, {512, 576, 1000}, {32, 224}},     {13, {1150, 1150, 1500}, {352, 448}},
+        {14, {352, 352, 352}, {32, 32}},       {15, {850, 850, 850}, {224, 352}},
+    };
+    for (const Row &r : rows)
+        if (r.mask == mask) return exact_k ? r.exact[mc.regroup ? 0 : (mc.gb_product_exact ? 1 : 2)] : r.division[mc.regroup ? 0 : 1];
+    return 0;
+}
+
 // enqueue one pass (tables + search; the final records land in b.final_dev) in the buffers b
 int enqueue_search_in(const Bufs &B, const Plan &p, int mask, uint32_t flags, uint64_t *evaluated,
                       const double *e_limit = nullptr, bool build_tables = true, bool bs_da_step = false,
                       bool *unproven = nullptr)
 {
     const int which = (flags & MMEE_SEARCH_EXHAUSTIVE) ? 0 : 1;
-    // The full row set goes through the dense kernel (lane = tiling, wave = 125 rows of a class).  Energy, latency
-    // and energy-delay product together would need two of its passes (27 minima do not fit four waves per
-    // SIMD): 1.14 ms for the 2048 x 768 x 3072 x 768 chain, in one pass of k_search 1.01 ms; but where the
-    // DRAM time needs a division k_search takes 2.70 ms and the dense kernel 1.29 ms.
-    const bool dense = which == 0 && !bs_da_step && B.cls_dev && !(mask == 11 && p.exact_k);
-    const ModelConst mc = pass_constants(p, flags, bs_da_step ? 8 : mask, unproven, dense);
+    // the full row set goes through the dense kernel (lane = tiling, wave = 125 rows of a class), several keys on few
+    // tilings excepted
+    bool dense = which == 0 && !bs_da_step && B.cls_dev;
+    ModelConst mc = pass_constants(p, flags, bs_da_step ? 8 : mask, unproven, dense);
+    if (dense && p.T < dense_from(mask, p.exact_k, mc)) {
+        dense = false;
+        mc = pass_constants(p, flags, mask, unproven);
+    }
     int rc = build_tables ? launch_tilings(p, mc, B, B.dv_dev) : MMEE_OK;
     if (rc) return rc;
     SearchArgs a;
