@@ -235,8 +235,8 @@ int mmee_chain_front_bs_da(const mmee_chain *c, const mmee_hw *hw, uint32_t flag
  *             MMEE_OK and the record carries cost.valid = 0 (nothing is read back to tell).
  *   flags     as for mmee_search_ex; the regrouped energy sum is used only where it is exact
  *             beforehand (mmee_energy_regrouped), never on trust.
- * The first call on a device runs the offline stage into the array and reads eight counters back
- * (one synchronisation, still no allocation): make it outside any capture.  All calls on one GPU
+ * The first call on a device runs the offline stage into the array and reads its counts and row
+ * numbers back (one synchronisation of that stream, still no allocation): make it outside any capture.  All calls on one GPU
  * share that GPU's array, which keeps the last call's contents; what must start at zero is cleared
  * by a kernel at the start of each call.  Calls that overlap on one GPU (different streams, or
  * the same stream replayed while an earlier launch still runs) race; so does this call against

@@ -291,19 +291,21 @@ int make_plan(const mmee_chain *w, const mmee_hw *hw, Plan &p)
 
 // ---- device state ------------------------------------------------------------
 
-// The pruned search has the kept rows compiled in (rows.h); they must be the ones the device's offline stage found.
-int check_kept_rows(const uint32_t *rows_dev, const uint32_t (&counts)[4])
+// What the device's offline stage found, back to the host: on the library's stream, with one synchronisation.  The pruned
+// searches have the kept rows compiled in (rows.h); they must be the ones found.
+int read_offline(const uint32_t *counts_dev, const uint32_t *kept, uint32_t (&counts)[2][4])
 {
     const uint32_t group_of[LEAST_CLASSES] = {0, 2, 3};      // class (r, f) -> g = r + 2 f
-    bool same = counts[1] == 0;
-    for (int c = 0; same && c < LEAST_CLASSES; ++c) {
-        const uint32_t g = group_of[c], n = KEPT.rows[c];
-        uint32_t rows[KEPT_ALL];
-        same = counts[g] == n;
-        if (!same) break;
-        HIP_TRY(hipMemcpy(rows, rows_dev + (size_t)g * ROWS_PER_GROUP, sizeof(uint32_t) * n, hipMemcpyDeviceToHost));
-        same = std::memcmp(rows, KEPT.number + KEPT.first[c], sizeof(uint32_t) * n) == 0;
-    }
+    uint32_t h[8], rows[KEPT_ALL];
+    HIP_TRY(hipMemcpyAsync(h, counts_dev, sizeof(h), hipMemcpyDeviceToHost, S.stream));
+    for (int c = 0; c < LEAST_CLASSES; ++c)
+        HIP_TRY(hipMemcpyAsync(rows + KEPT.first[c], kept + (size_t)group_of[c] * ROWS_PER_GROUP, sizeof(uint32_t) * KEPT.rows[c],
+                               hipMemcpyDeviceToHost, S.stream));
+    HIP_TRY(hipStreamSynchronize(S.stream));
+    for (int g = 0; g < 4; ++g) { counts[0][g] = h[g]; counts[1][g] = h[4 + g]; }
+    bool same = counts[1][1] == 0;
+    for (int c = 0; c < LEAST_CLASSES; ++c)
+        same = same && counts[1][group_of[c]] == KEPT.rows[c] && std::memcmp(rows + KEPT.first[c], KEPT.number + KEPT.first[c], sizeof(uint32_t) * KEPT.rows[c]) == 0;
     if (same) return MMEE_OK;
     std::snprintf(g_last_error, sizeof(g_last_error), "the offline stage's rows are not the compiled ones");
     return MMEE_EDEVICE;
@@ -361,10 +363,10 @@ int ensure_ready()
                        S.row_enc[0], S.row_enc[1],
                        S.counts_dev);
     HIP_TRY(hipGetLastError());
-    uint32_t h[8];
-    HIP_TRY(hipMemcpyAsync(h, S.counts_dev, sizeof(h), hipMemcpyDeviceToHost, S.stream));
-    HIP_TRY(hipStreamSynchronize(S.stream));
-    for (int g = 0; g < 4; ++g) { S.counts[0][g] = h[g]; S.counts[1][g] = h[4 + g]; }
+    {
+        const int rc = read_offline(S.counts_dev, S.rows[1], S.counts);
+        if (rc) return rc;
+    }
     {
         // whether a row denotes a dataflow depends on (order, r, f) only: list those classes
         std::vector<uint8_t> flags(N_DFROWS);
@@ -389,10 +391,6 @@ int ensure_ready()
         HIP_TRY(hipMalloc(&S.cls_dev, sizeof(uint32_t) * 96));
         HIP_TRY(hipMemcpy(S.cls_dev, cls.data(), sizeof(uint32_t) * cls.size(), hipMemcpyHostToDevice));
         S.n_cls = (uint32_t)cls.size();
-    }
-    {
-        const int rc = check_kept_rows(S.rows[1], S.counts[1]);
-        if (rc) return rc;
     }
     S.ready = true;
     return MMEE_OK;
@@ -1358,7 +1356,7 @@ struct NoAllocDevice {
 } g_noalloc[NOALLOC_MAX_DEVICES];
 
 // First call on a device: the address of that device's array, then the offline stage (row encoding,
-// pruning, compaction) into it and its eight counts back to the host.  Nothing is allocated.
+// pruning, compaction) into it; its eight counts and the kept rows' numbers come back to the host.  Nothing is allocated.
 int noalloc_setup(int dev, NoAllocDevice *&out)
 {
     if (dev < 0 || dev >= NOALLOC_MAX_DEVICES) return MMEE_EINVAL;
@@ -1393,11 +1391,7 @@ int noalloc_setup(int dev, NoAllocDevice *&out)
     hipLaunchKernelGGL(k_prune_rows, dim3((ROWS_PER_GROUP + 255) / 256, N_GROUPS), dim3(256), 0, S.stream, sig, flags);
     hipLaunchKernelGGL(k_compact_rows, dim3(8), dim3(1024), 0, S.stream, flags, enc, rows0, rows1, renc0, renc1, counts);
     HIP_TRY(hipGetLastError());
-    uint32_t h[8];
-    HIP_TRY(hipMemcpyAsync(h, counts, sizeof(h), hipMemcpyDeviceToHost, S.stream));
-    HIP_TRY(hipStreamSynchronize(S.stream));
-    for (int g = 0; g < 4; ++g) { d.counts[0][g] = h[g]; d.counts[1][g] = h[4 + g]; }
-    const int rc = check_kept_rows(rows1, d.counts[1]);
+    const int rc = read_offline(counts, rows1, d.counts);
     if (rc) return rc;
     d.built = true;
     return MMEE_OK;

@@ -69,3 +69,44 @@ def test_noalloc_infeasible_and_too_big(M):
     # and the scratch still serves the next call
     assert_same(run_noalloc(M, cfg["workload"], cfg["hw"], M.OBJ_EDP, M.SEARCH_PRUNED),
                 M.mmee_search_ex(cfg["workload"], cfg["hw"], M.OBJ_EDP, M.SEARCH_PRUNED), "after refusal")
+
+
+SETUP = r"""
+import os, sys, time
+sys.path.insert(0, %r)
+import torch
+import paper_2604_03446_amd as M
+from inputs import CONFIGS
+w, h = CONFIGS["tiny"]["workload"], CONFIGS["tiny"]["hw"]
+M.mmee_offline_stats()                                   # the library is loaded, its kernels too
+out = torch.zeros(38, dtype=torch.int32, device="cuda")
+side = torch.cuda.Stream()
+torch.cuda._sleep(1000)
+torch.cuda.synchronize()
+t = time.perf_counter(); torch.cuda._sleep(20000000); torch.cuda.synchronize()
+cycles = int(0.6 / (time.perf_counter() - t) * 20000000)
+M.mmee_set_stream(side.cuda_stream)
+torch.cuda._sleep(cycles)                                # the null stream is busy for 0.6 s
+t = time.perf_counter()
+M.mmee_search_noalloc(w, h, M.OBJ_ENERGY, M.SEARCH_PRUNED, out.data_ptr())
+took = time.perf_counter() - t
+torch.cuda.synchronize()
+whole = time.perf_counter() - t
+M.mmee_set_stream(None)
+want = M.mmee_search_ex(w, h, M.OBJ_ENERGY)
+assert out[:2].cpu().numpy().view("uint64")[0] == want.best.idx
+print("RESULT", took, whole)
+"""
+
+
+def test_first_call_waits_for_nothing_but_its_own_stream():
+    """The set-up of the fixed scratch reads its counts and rows back on the library's stream: it does not stand in line
+    behind what the caller has on the null stream."""
+    import os
+    import subprocess
+    import sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    p = subprocess.run([sys.executable, "-c", SETUP % root], capture_output=True, text=True, timeout=100)
+    assert p.returncode == 0, p.stderr[-2000:]
+    took, whole = map(float, [ln for ln in p.stdout.splitlines() if ln.startswith("RESULT")][0].split()[1:])
+    assert whole > 0.3 and took < 0.5 * whole, (took, whole)
