@@ -402,8 +402,7 @@ __global__ __launch_bounds__(PRUNED_THREADS, BS_DA ? 2 : 4) void k_front_points(
             class_of_code(b.code, cls, combo);
             rows_of_class(cls, row_lo, n_rows);
             const ComboTerms ct = combo_terms(v, a.extent, mc, cls == 2u, combo % 3, combo / 3);
-            const uint4 *offs = reinterpret_cast<const uint4 *>(&kept_dev.off[0][0]);
-            const Found f = first_row(tab, [&](uint32_t q) { return offs[q]; }, ct, mc, nt, (uint32_t)MMEE_OBJ_LATENCY_THEN_ENERGY, b, row_lo, n_rows);
+            const Found f = first_row(tab, ct, mc, nt, (uint32_t)MMEE_OBJ_LATENCY_THEN_ENERGY, b, row_lo, n_rows);
             const uint32_t row = index_row_base(as_constant(kept_dev.number)[row_lo + min(f.row, n_rows - 1)]) + 30000u * (combo % 3) + 90000u * (combo / 3);
             k.idx = (uint64_t)t0 + f.lane + (uint64_t)mc.T * row;
             if (lane == 0) out[place - 1] = k;

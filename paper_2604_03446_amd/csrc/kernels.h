@@ -5,11 +5,12 @@
 //   k_compact_rows   offline:  ballot + prefix compaction of surviving rows
 //   k_build_tilings  online:   tiling id -> boundaries -> per-tiling tables (the boundary-matrix side)
 //   k_search         online:   contraction, capacity mask, energy/latency, hierarchical argmin (lane = row)
-//   k_search_dense   online:   the same for one key over the full row set (lane = tiling)
+//   k_search_dense   online:   the same for one or two keys over the full row set (lane = tiling)
 //   k_front_step     online:   one point of the buffer-size / DRAM-access front
 //   k_eval_batch     online:   the same model, one 64-byte record per candidate
 //   k_decode         online:   index -> mapping
-// (k_search_pruned and k_pruned_finish, the pruned search over one or many problems per launch: pruned.h)
+// The searches over the surviving rows: k_search_batch, k_batch_finish (batch.h), and for many problems of one shape
+// k_search_pruned, k_pruned_finish (pruned.h).  Both fronts over them: k_front_points, k_front_merge (fronts.h).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <type_traits>
@@ -1151,7 +1152,7 @@ __device__ __forceinline__ void stage_tables_direct(const SearchArgs &a, double 
     __builtin_amdgcn_s_waitcnt(0);               // the loads count as vector memory operations: all of them have landed
 }
 
-// SUM: how a candidate's energy is added up (ModelConst::energy_sum).  SUM_ORDERED forms it term by term,
+// SUM: how a candidate's energy is added up (ModelConst::regroup and gb_product_exact decide).  SUM_ORDERED forms it term by term,
 // 6 operations per candidate with the minimum; SUM_FUSED forms the first sum with one fused multiply-add whose
 // product is exact, i.e. with the bits of the two separate roundings; SUM_REGROUPED adds a row and a tiling part.
 // The energy key alone leaves the two addends that all candidates of a (tiling, r) share, the register-file

@@ -982,13 +982,6 @@ struct PrunedEntry {
     uint32_t slot;          // result slot: its N_OBJ final records
 };
 
-// Where one launch of the pruned search works; the allocating entry points fill it from State.
-struct PrunedBufs {
-    const uint4 *enc;
-    unsigned long long *hints;
-    FinalRecord *final_out;
-};
-
 DigitConst digit_constants(const DivTable &dv)
 {
     DigitConst d;
@@ -1205,7 +1198,7 @@ void pruned_layout(const std::vector<PrunedEntry> &entries, const std::vector<ui
 
 // Launch the search and its finish.  desc_dev: the layout's descriptions in device memory; null: they fit the
 // kernel arguments.
-int launch_pruned(const PrunedBufs &B, const PrunedLayout &l, const unsigned char *desc_dev, Key *keys)
+int launch_pruned(const PrunedLayout &l, const unsigned char *desc_dev, Key *keys)
 {
     static PrunedArgs a;                       // (callers hold g_lock)
     std::memset(&a, 0, offsetof(PrunedArgs, inl));
@@ -1215,8 +1208,8 @@ int launch_pruned(const PrunedBufs &B, const PrunedLayout &l, const unsigned cha
         std::memcpy(a.inl, l.desc.data(), l.desc.size());
     }
     a.n_groups = l.n_groups; a.n_items = l.n_items;
-    a.members_off = l.members_off; a.n_members = l.n_members;
-    a.enc = B.enc; a.keys = keys; a.hints = B.hints; a.final_out = B.final_out;
+    a.members_off = l.members_off;
+    a.enc = S.enc; a.keys = keys; a.hints = S.pruned_hints; a.final_out = S.final_map;
     hipLaunchKernelGGL(k_search_pruned, dim3(l.n_items), dim3(PRUNED_THREADS), 0, S.stream, a);
     hipLaunchKernelGGL(k_pruned_finish, dim3(l.n_members), dim3(256), 0, S.stream, a);
     HIP_TRY(hipGetLastError());
@@ -1264,8 +1257,7 @@ int enqueue_pruned(const std::vector<PrunedEntry> &entries, const std::vector<ui
         std::memcpy(S.desc_host, l.desc.data(), l.desc.size());
         HIP_TRY(hipMemcpyAsync(S.desc_dev, S.desc_host, l.desc.size(), hipMemcpyHostToDevice, S.stream));
     }
-    const PrunedBufs B = {S.enc, S.pruned_hints, S.final_map};
-    rc = launch_pruned(B, l, inside ? nullptr : S.desc_dev, static_cast<Key *>(S.block_records));
+    rc = launch_pruned(l, inside ? nullptr : S.desc_dev, static_cast<Key *>(S.block_records));
     if (rc) return rc;
     HIP_TRY(hipEventRecord(S.events[2 * ev_slot + 1], S.stream));
     return MMEE_OK;

@@ -67,7 +67,7 @@ struct PrunedMember {
 struct PrunedArgs {
     const unsigned char *desc;               // descriptions in device memory; null: in `inl`
     uint32_t n_groups, n_items;
-    uint32_t members_off, n_members;
+    uint32_t members_off;
     const uint4 *enc;                        // every encoded row (for the winner's record)
     Key *keys;                               // the items' records, group after group
     unsigned long long *hints;               // [slot][N_OBJ] lowest value published so far (bit pattern); +inf between launches
@@ -192,9 +192,6 @@ __device__ __forceinline__ void least_traffic(const TilingF &v, const double (&s
     least_runs<CLS, LO, HI, K>(v, size, cap, least);
 }
 
-// one capacity: the 181 rows in eight pieces of 20 to 26, one per wave
-constexpr int PIECE_CLASS[PRUNED_WAVES] = {0, 0, 0, 1, 1, 2, 2, 2};
-
 // ---- step 2: an accelerator's costs on top of it -----------------------------------------------
 
 // What the two operators contribute per (r, stationary mode): words and cycles over all their tile stages.
@@ -297,14 +294,13 @@ __device__ __forceinline__ void class_of_code(uint32_t code, uint32_t &cls, uint
 }
 
 // The first row (index order) of class b.code in which one of the tilings `b.lanes` reaches (b.p, b.s), at its lowest
-// such tiling: together the lowest index that does.  Rows are costed with the staged table; `offs` are their
-// offsets into it (KeptRows::off, in LDS or device memory).  The row's place in the class list and the
-// tiling's lane; row 0xFFFFFFFF: none.
+// such tiling: together the lowest index that does.  Rows are costed with the staged table.  The row's place in the
+// class list and the tiling's lane; row 0xFFFFFFFF: none.
 struct Found { uint32_t row, lane; };
-template <class Off4>
-__device__ __forceinline__ Found first_row(const double *tab, Off4 offs, const ComboTerms &ct, const ModelConst &mc, uint32_t nt, uint32_t o,
+__device__ __forceinline__ Found first_row(const double *tab, const ComboTerms &ct, const ModelConst &mc, uint32_t nt, uint32_t o,
                                            const ClassBest &b, uint32_t row_lo, uint32_t n_rows)
 {
+    const uint4 *offs = reinterpret_cast<const uint4 *>(&kept_dev.off[0][0]);
     typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
     const uint32_t lane = threadIdx.x & 63;
     Found f = {0xFFFFFFFFu, 0};
@@ -331,7 +327,7 @@ __device__ __forceinline__ Found first_row(const double *tab, Off4 offs, const C
 #pragma unroll 1
             for (uint32_t i0 = 0; i0 < n_rows && i0 < f.row; i0 += 64) {
                 const uint32_t i = row_lo + min(i0 + lane, n_rows - 1);
-                const uint4 oa = offs(2 * i), ob = offs(2 * i + 1);
+                const uint4 oa = offs[2 * i], ob = offs[2 * i + 1];
                 const uint32_t off[NSEL] = {oa.x, oa.y, oa.z, oa.w, ob.x, ob.y, ob.z, ob.w};
                 const unsigned long long hits = __ballot(reaches(col, off, mc.cap_words, br_l, time_l, rf_l, mac_l) && i0 + lane < n_rows);
                 if (!hits) continue;
@@ -365,15 +361,6 @@ __device__ __forceinline__ void rows_of_class(uint32_t cls, uint32_t &first, uin
 {
     first = cls == 0 ? KEPT.first[0] : (cls == 1 ? KEPT.first[1] : KEPT.first[2]);
     n = cls == 0 ? KEPT.rows[0] : (cls == 1 ? KEPT.rows[1] : KEPT.rows[2]);
-}
-
-// the lowest index a candidate of class `code` in the chunk at t0 can have
-__device__ __forceinline__ uint64_t lowest_index(const ModelConst &mc, uint32_t t0, uint32_t code)
-{
-    uint32_t cls, combo;
-    class_of_code(code, cls, combo);
-    const uint32_t row = cls == 0 ? KEPT.number[KEPT.first[0]] : (cls == 1 ? KEPT.number[KEPT.first[1]] : KEPT.number[KEPT.first[2]]);
-    return (uint64_t)t0 + (uint64_t)mc.T * (index_row_base(row) + 30000u * (combo % 3) + 90000u * (combo / 3));
 }
 
 // ---- many problems: chunks of a shape, shared by its accelerators -------------------------------
@@ -628,8 +615,7 @@ __global__ __launch_bounds__(PRUNED_THREADS, 4) void k_search_pruned(PrunedArgs 
             class_of_code(b.code, cls, combo);
             rows_of_class(cls, row_lo, n_rows);
             const ComboTerms ct = combo_terms(this_tiling(), X, mb.mc, cls == 2u, combo % 3, combo / 3);
-            const uint4 *offs = reinterpret_cast<const uint4 *>(&kept_dev.off[0][0]);
-            const Found f = first_row(tab, [&](uint32_t i) { return offs[i]; }, ct, mb.mc, nt, o, b, row_lo, n_rows);
+            const Found f = first_row(tab, ct, mb.mc, nt, o, b, row_lo, n_rows);
             if (lane == 0) {
                 if (f.row == 0xFFFFFFFFu) best[j][o].p = inf;        // cannot happen: the value came from here
                 else {
