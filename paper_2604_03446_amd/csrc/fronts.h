@@ -177,18 +177,22 @@ template <int THREADS, uint32_t ROOM>
 __device__ __forceinline__ void close_up(Key *points, const uint32_t *keep, uint32_t N)
 {
     constexpr uint32_t MAX_PER = ROOM / THREADS;
-    Key k[MAX_PER];
+    double p[MAX_PER], s[MAX_PER];           // (one array per field: an array of keys would live in scratch memory)
+    uint64_t idx[MAX_PER];
     uint32_t to[MAX_PER];
 #pragma unroll
     for (uint32_t q = 0; q < MAX_PER; ++q) {
-        const uint32_t i = threadIdx.x + q * THREADS;
-        to[q] = 0;
-        if (i < N && keep[i] != (i ? keep[i - 1] : 0u)) { to[q] = keep[i]; k[q] = points[i]; }
+        const uint32_t i = min(threadIdx.x + q * THREADS, N - 1);
+        to[q] = threadIdx.x + q * THREADS < N && keep[i] != (i ? keep[i - 1] : 0u) ? keep[i] : 0u;
+        p[q] = points[i].p; s[q] = points[i].s; idx[q] = points[i].idx;
     }
     __syncthreads();
 #pragma unroll
     for (uint32_t q = 0; q < MAX_PER; ++q)
-        if (to[q]) points[to[q] - 1] = k[q];
+        if (to[q]) {
+            Key &k = points[to[q] - 1];
+            k.p = p[q]; k.s = s[q]; k.idx = idx[q];
+        }
     __syncthreads();
 }
 
