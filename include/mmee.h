@@ -149,10 +149,12 @@ enum {
  * times 540000.  Pure host arithmetic. */
 int mmee_space_size(const mmee_workload *w, const mmee_hw *hw, uint64_t *out);
 
-/* *out = 1 when the regrouped energy sum (see MMEE_SEARCH_ORDERED_SUM) is exact for every candidate
- * of (workload, hw) and these flags allow it: whole-number energies per access, total energy of any
- * candidate (Sec. V-D) below 2^53, and a power-of-two DRAM bandwidth and array count; else 0.  Pure
- * host arithmetic. */
+/* *out = 1 when every search of (workload, hw) under these flags adds the energy regrouped (see
+ * MMEE_SEARCH_ORDERED_SUM) and the sum is exact for every candidate beforehand: whole-number energies per
+ * access, total energy of any candidate (Sec. V-D) below 2^53, and a power-of-two DRAM bandwidth and
+ * array count; else 0.  With another bandwidth or array count only some searches regroup (the energy
+ * key alone, and those of the full row set that take one or two keys per pass).  Results have the
+ * same bits either way.  Pure host arithmetic. */
 int mmee_energy_regrouped(const mmee_workload *w, const mmee_hw *hw, uint32_t flags, int *out);
 
 /* On-device mixed-radix decode of n candidate indices (host arrays in and out): index -> loop
@@ -181,10 +183,13 @@ int mmee_search_multi(const mmee_workload *w, const mmee_hw *hw, const int *obje
 /* A helper for sweeps over hardware designs and sequence lengths (Sec. VII-I, Table IV; Sec. VII-H):
  * count independent searches (arrays of count workloads, hws, objectives, results) enqueued
  * back to back on one stream with a single synchronisation at the end.  Neighbouring entries
- * with identical workload and hw share one pass.  Pruned passes for one key, or for energy and
- * latency together, share kernel launches across problems (one per kind of pass present); the
- * other passes run problem by problem.  mmee_result::kernel_seconds of a pass that shared
- * launches is the device time of all the launches it shared.  Returns the first non-zero
+ * with identical workload and hw share one pass.  Pruned passes of problems on the same shape may
+ * share the part of the search that hangs on the shape and the buffer capacity, whatever their keys; else
+ * pruned passes for one key, or for energy and latency together, share kernel launches across
+ * problems (one per kind of pass present).  Which way costs less is estimated per call from the
+ * numbers of shapes, problems and tilings.  The remaining passes run problem by problem.
+ * mmee_result::kernel_seconds of a pass that shared launches is the device time of all the
+ * launches it shared.  Returns the first non-zero
  * per-entry code (per-entry codes are stored in rc[i] when rc is not null). */
 int mmee_search_many(const mmee_workload *w, const mmee_hw *hw, const int *objectives,
                      uint32_t count, uint32_t flags, mmee_result *out, int *rc);
@@ -192,8 +197,10 @@ int mmee_search_many(const mmee_workload *w, const mmee_hw *hw, const int *objec
 /* Energy-latency Pareto front (Sec. VI-A, Sec. VII-E): the feasible candidates that no other
  * candidate beats in both metrics; among candidates with identical (energy, latency) the lowest
  * index stands for all.  out receives at most `capacity` points by ascending latency (descending
- * energy), *n_points their number.  Each point costs one pass over the space.  Returns
- * MMEE_EOVERFLOW (with the first `capacity` points stored) when the front is longer. */
+ * energy), *n_points their number.  Over the surviving rows of a problem of at most 32768 tilings the
+ * front comes out of one pass over the space; otherwise each point costs a pass.  `evaluated` counts
+ * a pass per point and one that finds nothing more, either way.  Returns MMEE_EOVERFLOW (with the
+ * first `capacity` points stored) when the front is longer. */
 int mmee_pareto(const mmee_workload *w, const mmee_hw *hw, uint32_t flags, mmee_result *out,
                 uint32_t capacity, uint32_t *n_points);
 
@@ -256,8 +263,10 @@ int mmee_offline_stats(mmee_row_stats *out);
 int mmee_offline_rows(uint32_t group, uint32_t which, uint32_t *rows_out, uint32_t capacity, uint32_t *n_rows);
 
 /* Environment: MMEE_RESIDENT_BLOCKS=<even number>, read at the first call, lowers the number of
- * persistent blocks the search kernels are launched with (default: two per compute unit).  It
- * changes how the work is split and in which order partial results meet, never a result. */
+ * persistent blocks that searches of the full row set, pruned searches of few problems on a shape and
+ * walked fronts are launched with (default: two per compute unit).  It changes how the work is split
+ * and in which order partial results meet, never a result.  Problems that share their shape's part
+ * and fronts over the surviving rows take one block per 64 tilings and do not look at it. */
 
 /* Use this HIP stream (a hipStream_t passed as void*) for all later launches; NULL = default. */
 int mmee_set_stream(void *hip_stream);

@@ -1,7 +1,10 @@
 """The argmin must not depend on how the work is split over blocks or in which order the partial
 results meet (minimum with ties resolved by index inside the key).  The library sizes its
 persistent grids from the chip; MMEE_RESIDENT_BLOCKS overrides that once per process, so every
-grid size runs in a process of its own and reports the candidates it found."""
+grid size runs in a process of its own and reports the candidates it found.  Searches of the full row
+set, pruned searches of few problems on a shape and fronts walked over the full row set have such
+grids; what takes one block per chunk instead (many problems on a shape, fronts over the surviving
+rows) is run along with them, and its order of events is varied in test_gpu_many_on_a_shape."""
 import json
 import os
 import subprocess
@@ -25,18 +28,20 @@ for name in ("tiny", "bert", "long"):
         res = M.mmee_search_multi(cfg["workload"], cfg["hw"], [0, 1, 2, 3], flags)
         out["%%s/%%d" %% (name, flags)] = [r.best.idx for r in res]
         out["%%s/%%d/single" %% (name, flags)] = [M.mmee_search_ex(cfg["workload"], cfg["hw"], o, flags).best.idx for o in range(4)]
-pts = sweep_points()[:96]
-res, codes = M.mmee_search_many(pts, M.SEARCH_PRUNED)
-out["sweep"] = [r.best.idx for r in res]
+pts = sweep_points()
+for name, some in (("one shape", pts[:96]), ("three problems a shape", [p for s in range(8) for p in pts[128 * s:128 * s + 6]])):
+    res, codes = M.mmee_search_many(some, M.SEARCH_PRUNED)
+    out["sweep, " + name] = [r.best.idx for r in res]
 cases = random_small_cases(24, 0x61D5)
 pts = [(w, h, o) for k, (w, h) in enumerate(cases) for o in ((0, 1), (2,), (3,))[k %% 3]]
 for flags in (M.SEARCH_PRUNED, M.SEARCH_EXHAUSTIVE):
     res, codes = M.mmee_search_many(pts, flags)
     out["small/%%d" %% flags] = [(r.best.idx if c == 0 else -1) for r, c in zip(res, codes)]
-code, fr = M.mmee_pareto(CONFIGS["bert"]["workload"], CONFIGS["bert"]["hw"])
-out["front"] = [code] + [r.best.idx for r in fr]
-code, fr = M.mmee_front_bs_da(CONFIGS["tiny"]["workload"], CONFIGS["tiny"]["hw"])
-out["front_bs_da"] = [code] + [r.best.idx for r in fr]
+for flags in (M.SEARCH_PRUNED, M.SEARCH_EXHAUSTIVE):
+    code, fr = M.mmee_pareto(CONFIGS["bert"]["workload"], CONFIGS["bert"]["hw"], flags)
+    out["front/%%d" %% flags] = [code] + [r.best.idx for r in fr]
+    code, fr = M.mmee_front_bs_da(CONFIGS["tiny"]["workload"], CONFIGS["tiny"]["hw"], flags)
+    out["front_bs_da/%%d" %% flags] = [code] + [r.best.idx for r in fr]
 print("RESULT " + json.dumps(out))
 """ % (ROOT, os.path.join(ROOT, "tests"))
 

@@ -110,3 +110,26 @@ def test_shapes_of_many_problems_share_beside_single_ones(M):
     for (c, h, o), r in zip(points, results):
         want = M.mmee_chain_search_multi(c, h, [o], M.SEARCH_PRUNED)[0]
         assert bytes(r.cost) == bytes(want.cost) and bytes(r.best) == bytes(want.best) and r.evaluated == want.evaluated, (c, h, o)
+
+
+def test_order_of_the_problems_does_not_matter(M):
+    """Waves drop what a lower published value beats, so which positions are recovered hangs on who publishes first:
+    the same problems in other orders (other places in their group, other waves), and the same call again and again, with
+    accelerators whose optima many tilings reach."""
+    rng = random.Random(23)
+    points = []
+    for c in (dict(batch=2, I=512, K=64, L=512, J=64, word_bytes=2, tiling_mode=0, c_softmax=10),
+              dict(batch=1, I=360, K=48, L=360, J=48, word_bytes=2, tiling_mode=1, c_softmax=10)):
+        for n, h in enumerate(accelerators(rng, 40, [20000, 50000, 400000])):
+            h = dict(h, gb_bytes=h["gb_bytes"] + 64 * n, **(dict(dram_bw=0.0, gb_bw=0.0) if n % 4 == 0 else {}))
+            points += [(c, h, o) for o in ((0, 1), (2,), (3, 1), (0, 1, 2, 3))[n % 4]]
+    want, codes = M.mmee_chain_search_many(points, M.SEARCH_PRUNED)
+    assert not any(codes)
+    single = [M.mmee_chain_search_multi(c, h, [o], M.SEARCH_PRUNED)[0] for c, h, o in points]
+    assert [bytes(r.best) + bytes(r.cost) for r in want] == [bytes(r.best) + bytes(r.cost) for r in single]
+    for turn in range(8):
+        order = list(range(len(points)))
+        if turn >= 4:
+            rng.shuffle(order)
+        got, _ = M.mmee_chain_search_many([points[k] for k in order], M.SEARCH_PRUNED)
+        assert all(bytes(r.best) + bytes(r.cost) == bytes(want[k].best) + bytes(want[k].cost) for k, r in zip(order, got)), turn
