@@ -8,8 +8,8 @@
 // touches HBM.  Lane = tiling, wave = a contiguous piece of one group's row list, so a row's table
 // offsets are wave-uniform and the per-tiling constants of the nine stationary combinations sit in
 // registers for the whole item.  Only the table entries that the rows refer to are staged (77 of 123
-// for the pruned rows), which lets two 512-thread blocks share a CU; a row's offsets into the staged
-// table and the entries' places in it reach the waves as scalar loads.  A block takes a contiguous range
+// for the pruned rows), which lets two 512-thread blocks share a CU; the entries' places in the staged
+// table are known at compile time (rows.h), a row's offsets reach the waves as scalar loads.  A block takes a contiguous range
 // of items, waves carry their best (value, index) across the items of a problem, and each (block,
 // problem) stretch leaves one record per key; k_batch_finish, launched behind the search, reduces a
 // problem's records and writes the winner's full cost record and mapping.

@@ -22,11 +22,13 @@
 // followed up: the lowest class (f, combination, r), then the first row, then the first tiling that reach it.  Each
 // item leaves one record per problem and key for k_pruned_finish.
 //
-// 64 accelerators x 8 attention shapes x 2 keys: 1.63 ms in k_search_batch, 0.28 ms here.  Bound by step 2's vector
-// issue (about 800 instructions per problem and chunk) at half the issue rate: two blocks per CU, reductions
-// across lanes between short stretches of arithmetic.  What k_search_batch keeps: calls whose problems share
-// little, where this kernel's step 1 would be done for one accelerator at a time, and it costs two launches of
-// more code (a single 1764-tiling problem: 17 us against 11).
+// 64 accelerators x 8 attention shapes x 2 keys: 1.63 ms in k_search_batch, 0.29 ms here.  Bound by step 2's vector
+// issue (900 wave instructions per problem and chunk, step 1's share included) at 46 % of the issue rate: two blocks
+// per CU, reductions across lanes between short stretches of arithmetic.  128 registers do not hold it: 101 are
+// spilled (368 bytes of scratch per lane), 178 MB written and 110 MB read per such call where the records are 6.7 MB.
+// What k_search_batch keeps (keep_shared): calls whose problems share little, where this kernel's step 1 would be
+// done for one accelerator at a time, and small ones, where a block's chain of problems is long against the
+// chip's other blocks, and two launches of more code count (a single 1764-tiling problem: 17 us against 11).
 //
 // Included once by mmee.hip.
 #pragma once
@@ -420,7 +422,7 @@ __global__ __launch_bounds__(PRUNED_THREADS, 4) void k_search_pruned(PrunedArgs 
     }
     __syncthreads();
     // Read again by every part, and by every problem of step 2: kept in registers, the tiling and the products that
-    // problems share would spill what a problem needs (2.5 GB of scratch traffic per sweep, 0.47 ms).
+    // problems share would spill what a problem needs (2.5 GB of scratch traffic per sweep, 0.47 ms; 0.3 GB as it is).
     auto this_tiling = [&]() {
         TilingF v;
         uint32_t l = lane;
