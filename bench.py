@@ -26,34 +26,32 @@ sys.path.insert(0, ROOT)
 # the model's additions, multiplications, maxima and comparisons round one by one, so each
 # lane-operation is one operation.)
 ALU_PEAK_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
-# fp64-width operations the model needs per candidate.
-# One key (energy) over the full row set, k_search_dense.  Shared by the nine candidates of a
-# (row, tiling) pair: one addition each for Eq. (1) and Eq. (2) (pair sums come from the tables),
-# max + compare for Eq. (4) and the capacity, one addition for Eq. (7), one product, select + max for
-# the mask = 8.  Per candidate, energy regrouped (every term an exact integer): one addition and the
-# running minimum = 2; summed term by term: buffer words, e_gb product, three additions, minimum = 6.
-OPS_DENSE_ENERGY = {True: 2 + 8 / 9, False: 6 + 8 / 9}
-# Two keys (energy and latency) in one pass, k_search: 12 shared (as above plus the second addition of
-# Eq. (1), (2), (7) that the row-per-lane kernel cannot fold, the latency product and its mask), and per
-# candidate one addition, the latency max and two minima = 4 (8 term by term).
-OPS_TWO_KEYS = {True: 4 + 12 / 9, False: 8 + 12 / 9}
+# fp64-width operations the model needs per candidate of k_search_dense over the full row set, by how the energy is
+# added up.  Shared by the nine candidates of a (row, tiling) pair: one addition each for Eq. (1) and Eq. (2) (pair
+# sums come from the tables), max + compare for Eq. (4) and the capacity, one addition for Eq. (7), one product,
+# select + max for the mask = 8; with the latency its product and the max of its mask = 10.
+# Per candidate, energy: regrouped (every term an exact integer) one addition and the running minimum = 2; in order,
+# with the first sum as one fused operation (its product is exact): buffer words, fused sum, minimum = 3 (the two
+# addends that all candidates of a tiling share go to the minima).  The latency adds a max and its minimum.
+OPS_ENERGY = {"regrouped": 2 + 8 / 9, "fused": 3 + 8 / 9}
+OPS_ENERGY_LATENCY = {"regrouped": 4 + 10 / 9, "fused": 5 + 10 / 9}
 HBM_PEAK_GBS = 8000.0
 
 # HBM bytes per launch from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (summaries under profiles/), scaled by
 # what the same counters read for a 1 GiB device-to-device copy (x2.0 and x1.0).  Valid only for the kernel
 # sources they were taken with: any change to the sources turns "traffic" into null.
-COUNTERS_TAKEN_WITH = "74cedcfbae3e9edf44926a0a0e7caf7f4cb45343d2735171fe7d2f1858ba838b"
-TRAFFIC = {"k_search_dense_long": (2 * 58521.384 + 384.183) * 1024.0,      # FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0, KiB per dispatch
-           "k_search_bert": (2 * 26597.313 + 325.094) * 1024.0,
-           "k_eval_batch": (2 * 20242.527 + 4194995.589) * 1024.0}
-TRAFFIC_SOURCE = {"k_search_dense_long": "profiles/k_search_dense_long.md", "k_search_bert": "profiles/k_search_bert_exhaustive.md",
+COUNTERS_TAKEN_WITH = "43eb4655dfcf6374f1fb81d29d2639223de6128cf99b533713783ed93c658e01"
+TRAFFIC = {"k_search_dense_long": (2 * 58614.0 + 384.0) * 1024.0,      # FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0, KiB per dispatch
+           "k_search_dense_bert": (2 * 24279.0 + 2352.0) * 1024.0,
+           "k_eval_batch": (2 * 20241.0 + 4195148.0) * 1024.0}
+TRAFFIC_SOURCE = {"k_search_dense_long": "profiles/k_search_dense_long.md", "k_search_dense_bert": "profiles/k_search_dense_bert.md",
                   "k_eval_batch": "profiles/k_eval_batch_bert.md"}
 
 
 def kernel_sources_digest():
     import hashlib
     h = hashlib.sha256()
-    for f in ("layout.h", "rows.h", "kernels.h", "boundary.h", "batch.h", "pruned.h", "fronts.h", "mmee.hip"):
+    for f in ("layout.h", "rows.h", "kernels.h", "boundary.h", "batch.h", "pruned.h", "fronts.h", "pinned.h", "mmee.hip"):
         with open(os.path.join(ROOT, "paper_2604_03446_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()
@@ -82,7 +80,7 @@ def main():
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--profile-only", action="store_true",
                     help="run the timed steps only (for rocprofv3): no oracle, no extra legs")
-    ap.add_argument("--profile-leg", choices=["long", "bert", "sweep", "eval"], default="long",
+    ap.add_argument("--profile-leg", choices=["long", "bert", "sweep", "fronts", "eval"], default="long",
                     help="with --profile-only: which leg the timed steps run")
     args = ap.parse_args()
     if args.gpus != 1:
@@ -144,6 +142,10 @@ def main():
             timed_search(CONFIGS["bert"], [M.OBJ_ENERGY, M.OBJ_LATENCY], M.SEARCH_EXHAUSTIVE, args.steps, args.warmup)
         elif args.profile_leg == "sweep":
             sweep_leg(M.SEARCH_PRUNED, max(1, args.steps), args.warmup)
+        elif args.profile_leg == "fronts":
+            for _ in range(args.warmup + args.steps):
+                M.mmee_front_bs_da(CONFIGS["bert"]["workload"], CONFIGS["bert"]["hw"])
+                M.mmee_pareto(CONFIGS["bert"]["workload"], CONFIGS["bert"]["hw"])
         else:
             cfg = CONFIGS["bert"]
             buf = torch.empty((1 << 26) * 8, dtype=torch.int64, device="cuda")
@@ -163,7 +165,7 @@ def main():
     # beyond the size bound of the a-priori proof the search still starts regrouped and checks the outcome
     whole = all(float(cfg["hw"][k]).is_integer() for k in ("e_dram", "e_gb", "e_rf", "e_mac"))
     regrouped = M.mmee_energy_regrouped(cfg["workload"], cfg["hw"], M.SEARCH_EXHAUSTIVE) or whole
-    ops = OPS_DENSE_ENERGY[regrouped]
+    ops = OPS_ENERGY["regrouped" if regrouped else "fused"]
     step_s, kernel_s, stream_s, res = timed_search(cfg, objectives, M.SEARCH_EXHAUSTIVE, args.steps, args.warmup)
     evaluated = res[0].evaluated
     traffic, traffic_src = traffic_of("k_search_dense_long")
@@ -185,20 +187,21 @@ def main():
     out["roofline"]["frac"] = out["roofline"]["achieved"] / out["roofline"]["peak"]
 
     if not args.profile_only:
-        # the BERT-like configuration, its two objectives in one pass (k_search, lane = row)
+        # the BERT-like configuration, its two objectives in one pass
         bert = CONFIGS["bert"]
         two = [M.OBJ_ENERGY, M.OBJ_LATENCY]
         legs = {}
         for name, flags in (("regrouped", M.SEARCH_EXHAUSTIVE), ("ordered_sum", M.SEARCH_EXHAUSTIVE | M.SEARCH_ORDERED_SUM)):
             s_, k_, _, r_ = timed_search(bert, two, flags, 50, 5)
             reg = name == "regrouped" and M.mmee_energy_regrouped(bert["workload"], bert["hw"], flags)
-            ach = OPS_TWO_KEYS[reg] * r_[0].evaluated / k_ / 1e12
+            ops_two = OPS_ENERGY_LATENCY["regrouped" if reg else "fused"]
+            ach = ops_two * r_[0].evaluated / k_ / 1e12
             legs[name] = {"value": r_[0].evaluated / s_, "unit": "candidates/s", "ms_per_step": s_ * 1e3,
                           "search_kernel_ms": k_ * 1e3, "candidates_costed_per_step": r_[0].evaluated,
                           "roofline": {"bound": "alu", "achieved": ach, "peak": ALU_PEAK_TOPS, "unit": "Tlane-op/s",
-                                       "frac": ach / ALU_PEAK_TOPS, "ops_per_candidate": OPS_TWO_KEYS[reg],
-                                       "kernel": "k_search<energy+latency%s>" % (", regrouped energy sum" if reg else "")}}
-        t_, src_ = traffic_of("k_search_bert")
+                                       "frac": ach / ALU_PEAK_TOPS, "ops_per_candidate": ops_two,
+                                       "kernel": "k_search_dense<energy+latency%s>" % (", regrouped energy sum" if reg else "")}}
+        t_, src_ = traffic_of("k_search_dense_bert")
         legs["regrouped"]["roofline"].update(traffic=t_, traffic_source=src_)
         out["bert"] = {"workload": "bert: " + describe(bert), **legs}
 
@@ -240,7 +243,7 @@ def main():
             chains[name] = {"pruned_ms": dt_p * 1e3, "exhaustive_ms": dt_x * 1e3, "exhaustive_candidates": rx[0].evaluated,
                             "exhaustive_candidates_per_s": rx[0].evaluated / dt_x}
         beyond["chains_energy"] = chains
-        # both fronts of bert (Sec. VII-E, VII-C): one pass per front point
+        # both fronts of bert (Sec. VII-E, VII-C): over the surviving rows in three launches, exhaustively one or two passes per point
         for key, fn in (("front_energy_latency", M.mmee_pareto), ("front_bs_da", M.mmee_front_bs_da)):
             dt_p, (code_p, pts_p) = wall(lambda: fn(bert["workload"], bert["hw"], M.SEARCH_PRUNED), 5)
             dt_x, (code_x, pts_x) = wall(lambda: fn(bert["workload"], bert["hw"], M.SEARCH_EXHAUSTIVE), 2, 1)
