@@ -1064,12 +1064,13 @@ void pruned_slices(const std::vector<PrunedEntry> &entries, std::vector<uint32_t
 // chunks that chain is longer than what the row side costs per problem.  So the ways are estimated, in microseconds per
 // call apart from what the host does per problem either way (0.44): all in batches; groups of four problems or more
 // shared and the rest in batches (two sets of copies and launches that wait for each other: 110); all shared.
-// Fitted to 1650 calls of 1 to 640 problems on 1 to 40 shapes of 1 to 324 chunks, one key set a call: the choice costs
-// 1 % over the better way on average, 3 % or more over k_search_batch in 18 calls (at most 15 %), 3 % or more over
-// k_search_pruned in 58 (at most 17 %).  Sharing from four problems a group on whatever their size cost up to 208 %
-// (64 problems of 77 chunks, (latency, energy) key: 254 us, 192 in k_search_batch; 64 of one chunk, energy: 118 and 68),
-// never sharing up to 270 % (64 problems of 324 chunks, energy: 475 us, 126 shared).  A pass of its own costs 33 us
-// a problem of one chunk and 105 us at 324 chunks (energy, latency and energy-delay product).
+// Fitted to 3200 calls of 1 to 640 problems on 1 to 40 shapes of 1 to 324 chunks with 1 to 64 capacities, one key set a
+// call: the choice costs 1 % over the better way on average; 10 % or more over k_search_batch in 15 calls (64 problems
+// on each of two shapes of 28 chunks, 16 capacities, latency: 180 us in batches, 274 shared), 10 % or more over sharing from
+// four problems a group on in 16 (64 of 77 chunks with 64 capacities, energy: 146 us shared, 178 in batches).
+// Sharing from four problems a group on whatever their size cost up to 208 % (64 problems of one chunk, energy: 118
+// us, 68 in batches), never sharing up to 270 % (64 problems of 324 chunks, energy: 475 us, 126 shared).  A pass of its
+// own costs 33 us a problem of one chunk and 105 us at 324 chunks (energy, latency and energy-delay product).
 void keep_shared(const std::vector<PrunedEntry> &entries, const std::vector<uint32_t> &order, std::vector<PrunedSlice> &slices)
 {
     struct Batches {                         // chunks, and kinds of kernel: each is a launch of its own
@@ -1089,18 +1090,21 @@ void keep_shared(const std::vector<PrunedEntry> &entries, const std::vector<uint
     struct Shared {                          // bytes of descriptions, the longest block, all blocks 512 at a time
         size_t bytes = 0;
         double longest = 0.0, work = 0.0;
-        void add(size_t members, double chunks, double block_us)
+        // wait_us: what the block's waves wait for memory and for each other, hidden where other blocks follow
+        void add(size_t members, double chunks, double block_us, double wait_us)
         {
             bytes += sizeof(PrunedGroup) + members * sizeof(PrunedMember);
-            longest = std::max(longest, block_us);
-            work += 1.12 / 512.0 * chunks * block_us;
+            longest = std::max(longest, block_us + wait_us);
+            work += 1.2 / 512.0 * chunks * block_us;
         }
         // (descriptions beyond the kernel arguments are copied)
-        double us() const { return 9.5 + (bytes > (size_t)PRUNED_INLINE ? 10.5 : 0.0) + std::max(longest, work); }
+        double us() const { return 10.0 + (bytes > (size_t)PRUNED_INLINE ? 10.0 : 0.0) + std::max(longest, work); }
     };
-    auto key_us = [](int mask) {             // one problem after the other
-        return ((mask & 3) == 3 ? 6.0 : ((mask & 3) ? 5.0 : 0.0)) + ((mask & 4) ? 14.0 : 0.0) + ((mask & 8) ? 9.5 : 0.0);
+    // one problem after the other: per problem, and what it waits
+    auto key_us = [](int mask) {
+        return ((mask & 3) == 3 ? 7.6 : ((mask & 1) ? 6.4 : ((mask & 2) ? 4.6 : 0.0))) + ((mask & 4) ? 15.3 : 0.0) + ((mask & 8) ? 6.6 : 0.0);
     };
+    auto key_wait_us = [](int mask) { return ((mask & 2) ? 2.9 : ((mask & 1) ? 1.0 : 0.0)) + ((mask & 4) ? 3.4 : 0.0) + ((mask & 8) ? 0.7 : 0.0); };
     Batches all, rest;
     Shared large, every;
     double alone_us = 0.0, rest_alone_us = 0.0;
@@ -1108,10 +1112,11 @@ void keep_shared(const std::vector<PrunedEntry> &entries, const std::vector<uint
     for (const PrunedSlice &sl : slices) {
         const double chunks = std::ceil((double)entries[order[sl.lo]].plan->T / PRUNED_TC);
         const uint32_t members = sl.hi - sl.lo;
-        double keys = 0.0;
+        double keys = 0.0, waits = 0.0;
         for (uint32_t k = sl.lo; k < sl.hi; ++k) {
             const PrunedEntry &e = entries[order[k]];
             keys += key_us(e.mask);
+            waits += key_wait_us(e.mask);
             if (!batch_mask(e.mask)) {
                 alone_us += 33.0 + 0.22 * chunks;
                 if (!is_large(sl)) rest_alone_us += 33.0 + 0.22 * chunks;
@@ -1121,9 +1126,10 @@ void keep_shared(const std::vector<PrunedEntry> &entries, const std::vector<uint
             if (!is_large(sl)) rest.add(e, chunks);
         }
         // (another round of capacities: the rows once more)
-        const double block_us = 24.0 + 12.0 * ((sl.n_caps - 1) / PRUNED_ROUND) + keys / members * std::ceil(members / 8.0);
-        every.add(members, chunks, block_us);
-        if (is_large(sl)) large.add(members, chunks, block_us);
+        const double turns = std::ceil(members / 8.0) / members;
+        const double block_us = 20.0 + 16.0 * ((sl.n_caps - 1) / PRUNED_ROUND) + keys * turns;
+        every.add(members, chunks, block_us, waits * turns);
+        if (is_large(sl)) large.add(members, chunks, block_us, waits * turns);
     }
     // (85: the 110, less what the synchronisation adds to either part; 1.15: a lone problem's blocks are short of waves in step 2)
     const double batched_us = all.us() + alone_us, every_us = every.us() * (rest.items > 0.0 ? 1.15 : 1.0);
