@@ -27,14 +27,15 @@ sys.path.insert(0, ROOT)
 # lane-operation is one operation.)
 ALU_PEAK_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
 # fp64-width operations the model needs per candidate of k_search_dense over the full row set, by how the energy is
-# added up.  Shared by the nine candidates of a (row, tiling) pair: one addition each for Eq. (1) and Eq. (2) (pair
-# sums come from the tables), max + compare for Eq. (4) and the capacity, one addition for Eq. (7), one product,
-# select + max for the mask = 8; with the latency its product and the max of its mask = 10.
+# added up.  Shared by the nine candidates of a (row, tiling) pair: two comparisons for Eq. (1), (2), (4) and the
+# capacity (what the row's (D, E) part leaves of it is formed once per five and more rows), one addition for Eq. (7)
+# or its energy = 3; in order the product with the DRAM energy as well = 4; with the latency both products = 5.  (Rows that
+# no tiling of a wave fits are counted like the others.)
 # Per candidate, energy: regrouped (every term an exact integer) one addition and the running minimum = 2; in order,
 # with the first sum as one fused operation (its product is exact): buffer words, fused sum, minimum = 3 (the two
 # addends that all candidates of a tiling share go to the minima).  The latency adds a max and its minimum.
-OPS_ENERGY = {"regrouped": 2 + 8 / 9, "fused": 3 + 8 / 9}
-OPS_ENERGY_LATENCY = {"regrouped": 4 + 10 / 9, "fused": 5 + 10 / 9}
+OPS_ENERGY = {"regrouped": 2 + 3 / 9, "fused": 3 + 4 / 9}
+OPS_ENERGY_LATENCY = {"regrouped": 4 + 5 / 9, "fused": 5 + 5 / 9}
 HBM_PEAK_GBS = 8000.0
 
 # HBM bytes per launch from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (summaries under profiles/), scaled by

@@ -122,7 +122,8 @@ enum {
 
 enum {
     MMEE_SEARCH_PRUNED = 0,             /* offline symbolic pruning on (the paper's method) */
-    MMEE_SEARCH_EXHAUSTIVE = 1,         /* cost every candidate that denotes a dataflow     */
+    MMEE_SEARCH_EXHAUSTIVE = 1,         /* cost every candidate that denotes a dataflow (one that
+                                           exceeds the buffer capacity costs +inf)          */
     /* When the four energies per access are whole numbers and the largest possible total stays
      * below 2^53, every term of the energy is an exact integer and the search adds a (row, tiling)
      * part and a (tiling, stationary modes) part per candidate; the result has the same bits as

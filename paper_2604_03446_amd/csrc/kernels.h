@@ -1107,11 +1107,16 @@ __global__ __launch_bounds__(SEARCH_THREADS, (popcount4(MASK) >= 3 || (MASK & 4 
 // The rows of one (order, r, f) class are the 5^4 buffering levels, and the selectors split: those of
 // A and B (buffer, retained, DRAM) depend on (p_A, p_B) only, those of D and E on (p_D, p_E) only,
 // those of C on the class (k_build_rows).  So here a lane is a tiling, a wave takes the 125 rows of a
-// (class, p_E) task, all selectors are wave-uniform, and a row's three sums are formed from an
-// (A, B) part shared by five rows and a (D, E) part held in registers: 3 + 3/5 LDS reads and
-// 10 + 3/5 operations per (row, tiling) before the nine combinations, whose per-tiling constants
-// are lane registers for the whole task.  All of these sums are exact integers below 2^53 (the
-// host refuses a workload where they are not), so their association is free.
+// (class, p_E) task, all selectors are wave-uniform, and a row is an (A, B) part shared by five rows next to a
+// (D, E) part held in registers.  All of these sums are exact integers below 2^53 (the host refuses workloads where
+// they are not), so their association is free, and a row needs no footprint of its own: it fits if the (A, B)
+// part does not exceed what the (D, E) part and C leave of the capacity, two comparisons.  Its energy (regrouped) or its
+// DRAM time is one addition of the two parts' shares.  A row over capacity costs +inf, whatever the combination: its
+// lanes are masked out of the nine combinations, and a wave none of whose tilings the row fits passes over them.
+// Per (row, tiling) 3 operations before the nine combinations, whose per-tiling constants are lane registers for
+// the whole task, and 3/5 LDS reads.  With both footprints summed, their maximum, and the mask as selects it was 8
+// operations: 12544-tiling attention layer (8192 x 128, buffer 8 MiB), energy, 0.393 ms in the kernel, now 0.317; 10692-tiling
+// chain (2048 x 768 x 3072 x 768) with a buffer that everything fits 0.351 and 0.328, with one of 1 MiB 0.373 and 0.201.
 //
 // A block stages one chunk of TC tilings (stage_tables_direct below) and its waves take neighbouring tasks.
 // Persistent blocks, global work counter and grid finish as in k_search; the last chunks are handed
@@ -1119,9 +1124,11 @@ __global__ __launch_bounds__(SEARCH_THREADS, (popcount4(MASK) >= 3 || (MASK & 4 
 //
 // Registers decide the shape of the row loop.  One key: the 18 per-tiling constants, the (D, E) parts of all
 // five p_D values and nine minima fit 128 registers (four waves per SIMD).  Two keys together hold
-// 18 minima: there one p_D value at a time is kept, and the (A, B) parts are read once per row instead of
-// once per five rows -- three LDS reads (12 cycles of the CU's LDS pipe) against the row's 46 operations
-// (184 cycles of each SIMD).
+// 18 minima: there one p_D value at a time is kept, the (A, B) parts are read once per row instead of
+// once per five rows -- three LDS reads (12 cycles of the CU's LDS pipe) against the row's 41 operations
+// (164 cycles of each SIMD) -- and the parts' traffic is added before it is weighed, one operation less than two shares
+// per row.  Two p_D values at a time spill: energy and latency of a 4900-tiling layer 0.355 ms, 0.264 with one (0.307
+// with footprints and selects).
 constexpr int DENSE_THREADS = 512;           // eight waves, two blocks per CU
 constexpr int DENSE_BLOCKS_PER_CU = 2;
 constexpr int DENSE_WAVES = DENSE_THREADS / 64;
@@ -1160,11 +1167,11 @@ __device__ __forceinline__ void stage_tables_direct(const SearchArgs &a, double 
 // finished sums is the finished sum of the minimum, bit for bit (OUTSIDE).  Per candidate that is addition,
 // multiplication, addition, minimum (4), with SUM_FUSED 3, with SUM_REGROUPED 2.  The kernel is bound by
 // VALU issue, so its time follows these counts: energy key of a 2048 x 768 x 3072 x 768 chain (3.6e9
-// candidates) 0.700 ms with six operations, 0.524 with four, 0.430 with three, 0.335 with two.
+// candidates, a buffer that everything fits) 0.503 ms with four operations, 0.417 with three, 0.328 with two.
 //
 // FAST: the DRAM time is one exact multiply of the B*H-scaled traffic (ModelConst::dram_k).  Otherwise the table
 // slice holds the traffic per instance and the time is dram_time_general; a true division here cost
-// 1.2 to 5 times the whole rest of the loop (energy and latency of the chain above at 60 B/cycle: 2.05 ms).
+// 1.2 to 5 times the whole rest of the loop (energy and latency of the chain above at 60 B/cycle: 2.05 ms, now 0.67).
 template <int MASK, bool FAST, bool LIMIT = false, int SUM = SUM_ORDERED, bool LATCAP = false>
 __global__ __launch_bounds__(DENSE_THREADS, 4) void k_search_dense(SearchArgs a)
 {
@@ -1172,6 +1179,11 @@ __global__ __launch_bounds__(DENSE_THREADS, 4) void k_search_dense(SearchArgs a)
     constexpr bool REGROUP = SUM == SUM_REGROUPED;
     static_assert(!(MASK & 4) && popcount4(MASK) <= 2, "one or two of the scalar keys");
     constexpr bool OUTSIDE = !REGROUP && (MASK & 1) && !(MASK & 8) && !LIMIT;
+    constexpr bool ENERGY = MASK != (1 << MMEE_OBJ_LATENCY) || LIMIT, TIME = MASK != (1 << MMEE_OBJ_ENERGY) || LATCAP;
+    // what a row's costs need of its traffic: a sum of the two parts' energies, of their times, the traffic itself
+    constexpr bool TWO = popcount4(MASK) == 2;
+    constexpr bool E_SUMS = ENERGY && REGROUP && !TWO, L_SUMS = TIME && FAST && !TWO;
+    constexpr bool WORDS = (ENERGY && !E_SUMS) || (TIME && !L_SUMS);
     constexpr uint32_t ROWS_PER_STEP = popcount4(MASK) == 2 ? 1u : 5u;       // p_D values held in registers
     __shared__ double tab[DENSE_PAIRS * DENSE_PAIR_F64];
     __shared__ Key wave_best[N_OBJ][DENSE_WAVES];
@@ -1206,6 +1218,13 @@ __global__ __launch_bounds__(DENSE_THREADS, 4) void k_search_dense(SearchArgs a)
     };
     const EncTable enc = {(ConstPtr<u32x4>)a.enc};
     ConstPtr<uint32_t> cls_list = as_constant(a.cls);
+    // Regrouped, the DRAM side of the energy is whole numbers throughout, and with FAST the DRAM time is a whole number
+    // times one power of two: both are sums of an (A, B) and a (D, E) part, formed once per part.
+    auto words_energy = [&](double words) { return FAST ? a.mc.e_sum * words : a.mc.e_sum * (words * a.mc.BH); };
+    // A row fits if neither operator's footprint exceeds the capacity: what the (D, E) part and C leave of it is formed
+    // once per task, a row compares its (A, B) part with that.  (Whole numbers below 2^53 throughout: exact.)
+    struct AbPart { double bs, ret, da, e, l; };
+    struct DePart { double room_bs, room_ret, da, e, l; };
     // LATCAP: the second pass of the (latency, energy) key over the full row set.  The first pass found
     // the lowest latency; a candidate's latency max(l_dram, constant) stays within it exactly when both
     // parts do, so the cap masks rows and combinations separately and the pass costs what an
@@ -1289,31 +1308,30 @@ __global__ __launch_bounds__(DENSE_THREADS, 4) void k_search_dense(SearchArgs a)
 #pragma unroll
         for (int c9 = 0; c9 < 9; ++c9) bestE[c9] = bestL[c9] = bestP[c9] = inf;
 
-        // one row of this lane's tiling: Eq. (1), (2), (4), the capacity mask, B*H * Eq. (7), then
-        // the nine combinations.
-        auto cost_row = [&](double bs1, double bs2, double traffic) {
-            bool ok = fmax(bs1, bs2) <= cap;
-            const double dram_words = FAST ? traffic : traffic * a.mc.BH;
-            double e_part = (REGROUP ? a.mc.e_sum : a.mc.e_dram) * dram_words;
-            double l_dram;
-            if constexpr (FAST) l_dram = traffic * a.mc.dram_k;
-            else l_dram = dram_time_general(a.mc, traffic);
-            if constexpr (LATCAP) ok = ok & (l_dram <= lat_cap);
-            if constexpr (MASK == 1) {
-                e_part = ok ? e_part : inf;             // the energy alone: one select, the DRAM time is not needed
-            } else {
-                const double over = __hiloint2double(ok ? 0 : 0x7ff00000, 0);
-                e_part = fmax(e_part, over);
-                l_dram = fmax(l_dram, over);
-                pin(l_dram);
+        // one row of this lane's tiling that fits: B*H * Eq. (7), then the nine combinations
+        auto cost_row = [&](const AbPart &x, const DePart &y) {
+            double e_part = 0.0, l_dram = 0.0, dram_words = 0.0;
+            if constexpr (E_SUMS) e_part = x.e + y.e;
+            if constexpr (L_SUMS) l_dram = x.l + y.l;
+            if constexpr (WORDS) {
+                const double traffic = x.da + y.da;
+                if constexpr (ENERGY && REGROUP) {
+                    if constexpr (!E_SUMS) e_part = words_energy(traffic);
+                } else if constexpr (ENERGY) {
+                    dram_words = FAST ? traffic : traffic * a.mc.BH;
+                    e_part = a.mc.e_dram * dram_words;
+                }
+                if constexpr (TIME && !L_SUMS) l_dram = FAST ? traffic * a.mc.dram_k : dram_time_general(a.mc, traffic);
             }
-            pin(e_part);
+            if constexpr (LATCAP) {
+                if (!(l_dram <= lat_cap)) return;
+            }
 #pragma unroll
             for (int c9 = 0; c9 < 9; ++c9) {
-                double en;
-                if constexpr (REGROUP) {
+                double en = 0.0;
+                if constexpr (ENERGY && REGROUP) {
                     en = e_part + gb[c9];
-                } else {
+                } else if constexpr (ENERGY) {
                     double gb_words = dram_words + gb[c9];
                     if constexpr (SUM == SUM_FUSED) en = __builtin_fma(a.mc.e_gb, gb_words, e_part);
                     else en = e_part + a.mc.e_gb * gb_words;
@@ -1338,35 +1356,42 @@ __global__ __launch_bounds__(DENSE_THREADS, 4) void k_search_dense(SearchArgs a)
         // (D, E) parts of up to ROWS_PER_STEP p_D values in registers, the class's C terms riding on them; the
         // (A, B) parts are read one step ahead of their use and their selectors one step ahead of that
         for (uint32_t q0 = 0;;) {
-            double y_ret[ROWS_PER_STEP], y_bs[ROWS_PER_STEP], y_da[ROWS_PER_STEP];
+            DePart y[ROWS_PER_STEP];
 #pragma unroll
             for (uint32_t q = 0; q < ROWS_PER_STEP; ++q) {
-                y_ret[q] = c_bs + col[dense_at(sel_of(e_de[q], 1))];
-                y_bs[q] = col[dense_at(sel_of(e_de[q], 3))] + c_bs;
-                y_da[q] = c_da + col[dense_at(sel_of(e_de[q], 6))];
+                y[q].room_bs = cap - (c_bs + col[dense_at(sel_of(e_de[q], 1))]);
+                y[q].room_ret = cap - (col[dense_at(sel_of(e_de[q], 3))] + c_bs);
+                y[q].da = c_da + col[dense_at(sel_of(e_de[q], 6))];
+                if constexpr (E_SUMS) y[q].e = words_energy(y[q].da);
+                if constexpr (L_SUMS) y[q].l = y[q].da * a.mc.dram_k;
             }
             double x_bs = col[dense_at(sel_of(e_c, 0))], x_ret = col[dense_at(sel_of(e_c, 4))],
                    x_da = col[dense_at(sel_of(e_c, 5))];                  // row0 is (p_A, p_B) = 0
             uint4 e_ab = enc[row0 + 1];
-            // the loop over (p_A, p_B), for a whole step of p_D values or for one: no branch between the rows
+            // the loop over (p_A, p_B), for a whole step of p_D values or for one
             auto ab_loop = [&](auto count) {
                 constexpr int N = decltype(count)::value;
 #pragma unroll 5
                 for (uint32_t ab = 0; ab < 25; ++ab) {
-                    const double now_bs = x_bs, now_ret = x_ret, now_da = x_da;
+                    AbPart x;
+                    x.bs = x_bs; x.ret = x_ret; x.da = x_da;
+                    if constexpr (E_SUMS) { x.e = words_energy(x_da); pin(x.e); }
+                    if constexpr (L_SUMS) { x.l = x_da * a.mc.dram_k; pin(x.l); }
                     x_bs = col[dense_at(sel_of(e_ab, 0))];
                     x_ret = col[dense_at(sel_of(e_ab, 4))];
                     x_da = col[dense_at(sel_of(e_ab, 5))];
                     e_ab = enc[row0 + min(ab + 2, 24u)];
 #pragma unroll
-                    for (int q = 0; q < N; ++q) cost_row(now_bs + y_ret[q], y_bs[q] + now_ret, now_da + y_da[q]);
+                    for (int q = 0; q < N; ++q)
+                        if ((x.bs <= y[q].room_bs) & (x.ret <= y[q].room_ret)) cost_row(x, y[q]);
                 }
             };
-            if (ROWS_PER_STEP == 5 && npd == 5) ab_loop(std::integral_constant<int, ROWS_PER_STEP>{});
+            if (q0 + ROWS_PER_STEP <= npd) ab_loop(std::integral_constant<int, ROWS_PER_STEP>{});
             else ab_loop(std::integral_constant<int, 1>{});
-            if constexpr (ROWS_PER_STEP == 5) break;
-            if (++q0 == npd) break;
-            e_de[0] = enc[row_de0 + 25u * q0];
+            q0 += ROWS_PER_STEP;
+            if (ROWS_PER_STEP == 5 || q0 >= npd) break;
+#pragma unroll
+            for (uint32_t q = 0; q < ROWS_PER_STEP; ++q) e_de[q] = enc[row_de0 + 25u * min(q0 + q, npd - 1)];
         }
 
         if constexpr (OUTSIDE) {
@@ -1418,10 +1443,11 @@ __global__ __launch_bounds__(DENSE_THREADS, 4) void k_search_dense(SearchArgs a)
                                   double cda, double cap_t, double gb_t, double latc_t, double slow_t, double rf_t, double mac_t) {
                     const double bs1 = (x_bs + cbs) + y_ret;
                     const double bs2 = y_bs + (cbs + x_ret);
-                    const double traffic2 = (x_da + cda) + y_da;
+                    const double traffic2 = x_da + (cda + y_da);
                     const double dram2 = FAST ? traffic2 : traffic2 * a.mc.BH;
                     bool ok2 = fmax(bs1, bs2) <= cap_t;
-                    double e2 = (REGROUP ? a.mc.e_sum : a.mc.e_dram) * dram2;
+                    // (regrouped: the very sum of the loop, also where a total taken on trust is not exact)
+                    double e2 = !REGROUP ? a.mc.e_dram * dram2 : (E_SUMS ? words_energy(x_da) + words_energy(cda + y_da) : words_energy(traffic2));
                     double l2;
                     if constexpr (FAST) l2 = traffic2 * a.mc.dram_k;
                     else l2 = dram_time_general(a.mc, traffic2);
