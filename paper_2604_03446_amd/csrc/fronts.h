@@ -1,21 +1,29 @@
-// Both fronts over the kept rows in three launches.
+// Both fronts over the kept rows in two launches.
 //
 // Walking a front point by point (a pass over every candidate, a synchronisation, the next bound) costs a pass and a
 // host round trip per point: 23 passes of 26 us and as much again on the host for the 22 points of a 4900-tiling
 // problem.  Here k_front_points takes every candidate once: a block per chunk of 64 tilings, lane = tiling, each
 // wave with its share of the rows (buffer size / DRAM access) or of the combinations on top of the least
-// traffic per class (energy / latency: only those can lie on the front, see pruned.h).  A wave walks its own front
-// in registers, the block sorts its waves' points and drops what another one covers; k_front_merge does the same
-// for FRONT_FAN blocks' points, and once more for what these leave, and writes the points' full records.
-// Short chains decide (a few dozen chunks, one wave per SIMD): a single merge of all chunks' points (some two
-// thousand) took 65 us, in two levels it takes 54; with FRONT_FAN blocks or fewer the second merge has nothing to add
-// and is left out (one tiling: 61 us, 49 without it).  22 points of a 4900-tiling problem: a call of 0.89 ms walked,
-// 0.14 here; energy and latency of 17424 tilings 0.38 ms walked, 0.09 here.
+// traffic per class (energy / latency: only those can lie on the front, see pruned.h).
 //
-// Room.  How many points a wave or a block has is a matter of the extents' divisors: over 600 shapes of attention layers
-// and GEMM chains at most 91 in a wave, 431 in the waves of a block, 118 in its front, 2917 in all lists (counted
+// Nearly all of them lie far behind the front, and a look at a coarse staircase shows it.  The first metric's range is cut
+// into FRONT_STEPS steps; per step the least second metric of any candidate, first of the block, then of the whole
+// launch (atomic minima in memory that every block publishes to and reads back).  A candidate whose second metric is no lower
+// than the least of the steps below its own is covered, whoever has that least, and goes; which blocks have published
+// by then changes only how much goes at once.  What is left of a wave, a handful, is walked in registers: a
+// wave's own front; the block drops what another of its waves covers and appends the rest to one list.  k_front_merge,
+// one block, looks at the staircase again, complete by now, settles what passes pair by pair, and writes the records.
+//
+// Short chains decide (a few dozen chunks, one wave per SIMD).  With walks of everything (30 to 60 points a wave, 1 us
+// each), a bitonic sort per block and two levels of merges that sorted thousands of points, the 22 points of a
+// 4900-tiling problem took 65 + 27 + 26 us in three launches (a call of 134 us; walked 890), energy and latency of 17424 tilings
+// 34 + 16 + 22 (87 us; walked 380).  Now 30 + 12 us
+// (call 64) and 28 + 10 (54).
+//
+// Room.  How many points a wave or a block has is a matter of the extents' divisors: without the staircase, over 600 shapes of
+// attention layers and GEMM chains at most 91 in a wave, 431 in the waves of a block, 118 in its front, 2917 in all blocks' (counted
 // on the CPU); over 4200 chains of highly composite extents 339, 1213, 355 and 29481.  So the waves of a block
-// share one pool, a block whose waves do not fit it merges them one by one, and a merge takes its lists in as many
+// share one pool, a block whose waves do not fit it merges them one by one, and the merge takes the list in as many
 // turns as it has room for.  Problems of more than FRONT_CHUNKS chunks are walked, and what outgrows FRONT_BLOCK or
 // FRONT_POINTS all the same.
 //
@@ -31,9 +39,8 @@ constexpr uint32_t FRONT_SPLIT = 2;          // blocks that share a chunk's rows
 constexpr uint32_t FRONT_BLOCKS = FRONT_CHUNKS * FRONT_SPLIT;
 constexpr uint32_t FRONT_POOL_BS_DA = 1024, FRONT_POOL_EL = 512;     // points the waves of a block may have together
 constexpr uint32_t FRONT_BLOCK = 512;        // points the front of a block may have
-constexpr uint32_t FRONT_FAN = 16;           // blocks whose points one block merges
-constexpr uint32_t FRONT_LISTS = FRONT_BLOCKS / FRONT_FAN;
-constexpr uint32_t FRONT_POINTS = 4096;      // points a merge sorts at a time in LDS, and the most a list or the front may have
+constexpr uint32_t FRONT_POINTS = 4096;      // points the merge takes at a time in LDS, and the most the front may have
+constexpr uint32_t FRONT_STEPS = 512;        // steps of the staircase: one per thread of a block
 constexpr uint32_t FRONT_DIVS = 512;         // divisors of a problem of FRONT_CHUNKS chunks: 240 + 136 + 1 + 1 at most
 constexpr uint32_t TOO_MANY = 0xFFFFFFFFu;
 constexpr int FRONT_ROWS = (KEPT_ALL + FRONT_SPLIT * PRUNED_WAVES - 1) / (FRONT_SPLIT * PRUNED_WAVES);     // rows per wave
@@ -44,11 +51,11 @@ struct FrontArgs {
     double extent[4], size[5];
     uint32_t X[4], ndiv[4];
     uint32_t capacity;                       // records the caller has room for
-    uint32_t one_merge;                      // not 0: there are at most FRONT_FAN blocks, the last merge takes their points as they are
-    uint32_t n_blocks, n_lists;
-    Key *points;                             // [FRONT_BLOCKS][FRONT_BLOCK] the blocks' fronts
-    Key *lists;                              // [FRONT_LISTS][FRONT_POINTS] those of FRONT_FAN blocks each
-    uint32_t *counts;                        // [FRONT_BLOCKS], then [FRONT_LISTS]: their points; TOO_MANY: outgrew its room
+    uint32_t step_shift;                     // a value's step: the upper word of its fp64, shifted, less step0, held to
+    int32_t step0;                           // 0 .. FRONT_STEPS - 1 (goes up with the value, whatever these two are)
+    Key *points;                             // [FRONT_BLOCKS * FRONT_BLOCK] the blocks' fronts, block after block as they end
+    unsigned long long *stairs;              // [FRONT_STEPS] least second metric per step (bit patterns), +inf between calls
+    uint32_t *counts;                        // [0] points in the list; [1] not 0: a block's front outgrew FRONT_BLOCK; 0 between calls
     const uint4 *enc;
     FinalRecord *out;                        // [capacity], ascending
     uint32_t *n_out;                         // points of the front; TOO_MANY: walk it
@@ -60,6 +67,64 @@ __device__ __forceinline__ Key no_point()
     Key k;
     k.p = pos_inf(); k.s = 0.0; k.idx = ~0ull;
     return k;
+}
+
+// ---- the staircase
+
+__device__ __forceinline__ uint32_t step_of(const FrontArgs &a, double p)
+{
+    const int b = (int)((uint32_t)__double2hiint(p) >> a.step_shift) - a.step0;
+    return (uint32_t)min(max(b, 0), (int)FRONT_STEPS - 1);
+}
+
+// below[b] = the least of own over the steps below b; own: step threadIdx.x's, for the first FRONT_STEPS threads.  Ends with a
+// barrier.
+__device__ __forceinline__ void steps_below(double own, double *below, double (&wave_least)[FRONT_STEPS / 64])
+{
+    const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    double least = own;                                      // of this step and those before it in the wave
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const double v = __shfl_up(least, d);
+        least = lane >= (uint32_t)d ? fmin(least, v) : least;
+    }
+    if (wave < FRONT_STEPS / 64 && lane == 63) wave_least[wave] = least;
+    __syncthreads();
+    double before = __shfl_up(least, 1);
+    before = lane ? before : pos_inf();
+#pragma unroll
+    for (uint32_t w = 0; w < FRONT_STEPS / 64; ++w) before = w < wave ? fmin(before, wave_least[w]) : before;
+    if (threadIdx.x < FRONT_STEPS) below[threadIdx.x] = before;
+    __syncthreads();
+}
+
+// The block's candidates against its own and the launch's staircase: the S of what is covered becomes +inf.
+template <int K>
+__device__ __forceinline__ void drop_covered(const FrontArgs &a, const double (&P)[K], double (&S)[K], unsigned long long *steps,
+                                             double (&wave_least)[FRONT_STEPS / 64])
+{
+    static_assert(FRONT_STEPS == PRUNED_THREADS, "a step per thread");
+    steps[threadIdx.x] = INF_BITS;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        // (a look first: most candidates lower nothing, and minima on one address take turns)
+        unsigned long long *at = steps + step_of(a, P[k]);
+        const unsigned long long bits = (unsigned long long)__double_as_longlong(S[k]);
+        if (bits < __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))
+            (void)__hip_atomic_fetch_min(at, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    __syncthreads();
+    const unsigned long long mine = steps[threadIdx.x];
+    unsigned long long all = __hip_atomic_load(a.stairs + threadIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (mine < all) {
+        (void)__hip_atomic_fetch_min(a.stairs + threadIdx.x, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        all = mine;
+    }
+    double *below = reinterpret_cast<double *>(steps);       // (each thread has taken its entry)
+    steps_below(__longlong_as_double((long long)all), below, wave_least);
+#pragma unroll
+    for (int k = 0; k < K; ++k) S[k] = S[k] < below[step_of(a, P[k])] ? S[k] : pos_inf();
 }
 
 // The front of a wave's candidates into the block's pool: per lane K pairs (P, S) with wave-uniform ids that go up with
@@ -74,7 +139,9 @@ __device__ __forceinline__ void wave_front(const double (&P)[K], const double (&
     const uint32_t lane = threadIdx.x & 63;
     double limit = inf;
     for (;;) {
-        // (asked for ahead of the reductions: the answer is there when they are)
+        // (asked for ahead of the reductions: the answer is there when they are; the wave meets first, or the compiler may
+        // join lane 0's branch at the end of a turn with this one and send the other lanes round without it)
+        __builtin_amdgcn_wave_barrier();
         uint32_t place = 0;
         if (lane == 0) place = __hip_atomic_fetch_add(filled, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         double bp = inf, bs = inf;
@@ -172,6 +239,38 @@ __device__ __forceinline__ uint32_t front_of(Key *points, double *low, uint32_t 
     return block_front<THREADS, ROOM>(points, low, keep, N);
 }
 
+// The front of points[0 .. n), n <= THREADS, to the front of the array, in any order; its size.  Pair by pair: a point goes if
+// one before it (Key order) has no larger s.  Every point's comparisons are shared out over PARTS threads.
+// 256 points and fewer in some 2 us where the sort and the two scans take 13: their barriers are one after the other.
+template <int THREADS>
+__device__ __forceinline__ uint32_t front_by_pairs(Key *points, uint32_t *gone, uint32_t *left, uint32_t n)
+{
+    __syncthreads();
+    if (threadIdx.x < n) gone[threadIdx.x] = 0;
+    if (threadIdx.x == 0) *left = 0;
+    __syncthreads();
+    uint32_t parts = 1;                                      // (uniform)
+    while (parts < 16 && n * parts * 2 <= THREADS) parts *= 2;
+    const uint32_t i = threadIdx.x / parts;
+    if (i < n) {
+        const Key me = points[i];
+        bool covered = !(me.p < pos_inf());
+        for (uint32_t j = threadIdx.x % parts; j < n; j += parts) {
+            const Key k = points[j];
+            covered |= k.s <= me.s && key_less(k, me);
+        }
+        if (covered) gone[i] = 1;
+    }
+    __syncthreads();
+    Key me = no_point();
+    const bool stays = threadIdx.x < n && !gone[threadIdx.x];
+    if (stays) me = points[threadIdx.x];
+    __syncthreads();
+    if (stays) points[__hip_atomic_fetch_add(left, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)] = me;
+    __syncthreads();
+    return *left;
+}
+
 // the points that keep counts to the front of the array
 template <int THREADS, uint32_t ROOM>
 __device__ __forceinline__ void close_up(Key *points, const uint32_t *keep, uint32_t N)
@@ -207,13 +306,13 @@ __global__ __launch_bounds__(PRUNED_THREADS, BS_DA ? 2 : 4) void k_front_points(
     __shared__ uint32_t div_lds[FRONT_DIVS];
     __shared__ Key points[POOL];
     __shared__ unsigned long long lanes[BS_DA ? 1 : POOL];
-    __shared__ double low_own[BS_DA ? 1 : POOL];
     __shared__ uint32_t keep_own[BS_DA ? 1 : POOL];
-    __shared__ uint32_t filled;
-    __shared__ double end_s[PRUNED_WAVES], end_p[PRUNED_WAVES];
+    __shared__ unsigned long long steps[FRONT_STEPS];
+    __shared__ double wave_least[FRONT_STEPS / 64];
+    __shared__ uint32_t filled, n_left, list_at;
     // (buffer size / DRAM access: the table has been read when the points are sorted, and two blocks fit a CU)
     static_assert(POOL + POOL / 2 <= KEPT_LINES * PRUNED_TC, "the scans fit the table's room");
-    double *low = BS_DA ? tab : low_own;
+    [[maybe_unused]] double *low = tab;                      // (sorts: buffer size / DRAM access only)
     uint32_t *keep = BS_DA ? reinterpret_cast<uint32_t *>(tab + POOL) : keep_own;
 
     const double inf = pos_inf();
@@ -242,7 +341,7 @@ __global__ __launch_bounds__(PRUNED_THREADS, BS_DA ? 2 : 4) void k_front_points(
     for (int q = 0; q < 4; ++q) { v.G[q] = gd[q * PRUNED_TC + lane]; v.D[q] = gd[(4 + q) * PRUNED_TC + lane]; }
     stage_kept(tab + lane, wave, v, a.size, 1.0);
 
-    uint32_t m, N;                                           // points of the block's front, entries they are found among
+    uint32_t m, N;                                           // points of the block's front, entries sorted
     if constexpr (BS_DA) {
         __syncthreads();
         // every dataflow, the capacity plays no part; neither metric depends on the stationary modes
@@ -263,30 +362,7 @@ __global__ __launch_bounds__(PRUNED_THREADS, BS_DA ? 2 : 4) void k_front_points(
             id[k] = i;                                       // list places go up with the index
             if (k % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // (all rows' reads at once would not fit the registers)
         }
-        // What the candidate with the least traffic in the block covers goes before the walk: with one or two long
-        // extents that is nearly everything (a block of the 240 tilings of a 720720 x 1 x 1 x 1 chain: 67 points in one
-        // of its waves, 2 in its front; the call 133 us, 91 us walked point by point, 54 us with this).
-        {
-            double es = inf, ep = inf;
-#pragma unroll
-            for (int k = 0; k < FRONT_ROWS; ++k) {
-                const bool better = (S[k] < es) | ((S[k] == es) & (P[k] < ep));
-                es = better ? S[k] : es;
-                ep = better ? P[k] : ep;
-            }
-            const double s = wave_min_f64(es), p = wave_min_f64(es == s ? ep : inf);
-            if (lane == 0) { end_s[wave] = s; end_p[wave] = p; }
-            __syncthreads();
-            es = end_s[0]; ep = end_p[0];
-#pragma unroll
-            for (int w = 1; w < PRUNED_WAVES; ++w) {
-                const bool better = (end_s[w] < es) | ((end_s[w] == es) & (end_p[w] < ep));
-                es = better ? end_s[w] : es;
-                ep = better ? end_p[w] : ep;
-            }
-#pragma unroll
-            for (int k = 0; k < FRONT_ROWS; ++k) S[k] = (P[k] >= ep) & (S[k] > es) ? inf : S[k];
-        }
+        drop_covered(a, P, S, steps, wave_least);
         // index so far: the row's place, then its lowest tiling
         auto mine = [&]() {
             wave_front(P, S, id, points, &filled, POOL, [&](uint32_t place, double p, double s, uint32_t row, unsigned long long who) {
@@ -296,8 +372,11 @@ __global__ __launch_bounds__(PRUNED_THREADS, BS_DA ? 2 : 4) void k_front_points(
         };
         mine();
         __syncthreads();
-        if (filled <= POOL) {
+        if (filled <= PRUNED_THREADS) {
+            m = front_by_pairs<PRUNED_THREADS>(points, keep, &n_left, filled);
+        } else if (filled <= POOL) {
             m = front_of<PRUNED_THREADS, POOL>(points, low, keep, filled, N);
+            close_up<PRUNED_THREADS, POOL>(points, keep, N);
         } else {
             // more than the pool holds (two long extents with hundreds of divisors): one wave after the other, each
             // beside the front of those before it
@@ -311,8 +390,8 @@ __global__ __launch_bounds__(PRUNED_THREADS, BS_DA ? 2 : 4) void k_front_points(
                 const uint32_t n = filled;
                 if (n > POOL) { m = TOO_MANY; break; }
                 m = front_of<PRUNED_THREADS, POOL>(points, low, keep, n, N);
-                if (turn == PRUNED_WAVES - 1) break;
                 close_up<PRUNED_THREADS, POOL>(points, keep, N);
+                if (turn == PRUNED_WAVES - 1) break;
             }
         }
     } else {
@@ -368,33 +447,32 @@ __global__ __launch_bounds__(PRUNED_THREADS, BS_DA ? 2 : 4) void k_front_points(
                 P[k] = swap ? P[k - 1] : p; S[k] = swap ? S[k - 1] : s; id[k] = swap ? id[k - 1] : x;
                 P[k - 1] = swap ? p : P[k - 1]; S[k - 1] = swap ? s : S[k - 1]; id[k - 1] = swap ? x : id[k - 1];
             }
+        drop_covered(a, P, S, steps, wave_least);
         // index so far: the class, then where the lanes are
         wave_front(P, S, id, points, &filled, POOL, [&](uint32_t place, double p, double s, uint32_t code, unsigned long long who) {
             points[place].p = p; points[place].s = s; points[place].idx = ((uint64_t)code << 32) | place;
             lanes[place] = who;
         });
         __syncthreads();
-        m = filled <= POOL ? front_of<PRUNED_THREADS, POOL>(points, low, keep, filled, N) : TOO_MANY;
+        static_assert(BS_DA || POOL <= (uint32_t)PRUNED_THREADS, "a point per thread");
+        m = filled <= POOL ? front_by_pairs<PRUNED_THREADS>(points, keep, &n_left, filled) : TOO_MANY;
     }
-    const bool fits = m <= FRONT_BLOCK;
-    if (threadIdx.x == 0) a.counts[blockIdx.x] = fits ? m : TOO_MANY;
-    if (!fits) return;
-    Key *out = a.points + (uint64_t)blockIdx.x * FRONT_BLOCK;
+    // the block's front, in any order, behind those of the blocks that ended before
+    if (threadIdx.x == 0) {
+        if (m <= FRONT_BLOCK) list_at = __hip_atomic_fetch_add(a.counts, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        else __hip_atomic_store(a.counts + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (m > FRONT_BLOCK) return;
+    __syncthreads();
+    Key *out = a.points + list_at;
     if constexpr (BS_DA) {
-        for (uint32_t i = threadIdx.x; i < N; i += PRUNED_THREADS) {
-            const uint32_t place = keep[i];
-            if (place == (i ? keep[i - 1] : 0u)) continue;
+        for (uint32_t i = threadIdx.x; i < m; i += PRUNED_THREADS) {
             Key k = points[i];
             k.idx = (uint64_t)t0 + (uint32_t)k.idx + (uint64_t)mc.T * index_row_base(kept_dev.number[k.idx >> 32]);
-            out[place - 1] = k;
+            out[i] = k;
         }
     } else {
-        for (uint32_t i = wave; i < N; i += PRUNED_WAVES) {
-            const uint32_t place = __builtin_amdgcn_readfirstlane(keep[i]);
-            if (place == (i ? __builtin_amdgcn_readfirstlane(keep[i - 1]) : 0u)) {
-                if (place == m) break;                       // no more points behind this one
-                continue;
-            }
+        for (uint32_t i = wave; i < m; i += PRUNED_WAVES) {
             Key k = points[i];
             const uint32_t slot = __builtin_amdgcn_readfirstlane((uint32_t)k.idx);
             const unsigned long long who = lanes[slot];
@@ -409,30 +487,73 @@ __global__ __launch_bounds__(PRUNED_THREADS, BS_DA ? 2 : 4) void k_front_points(
             const Found f = first_row(tab, ct, mc, nt, (uint32_t)MMEE_OBJ_LATENCY_THEN_ENERGY, b, row_lo, n_rows);
             const uint32_t row = index_row_base(as_constant(kept_dev.number)[row_lo + min(f.row, n_rows - 1)]) + 30000u * (combo % 3) + 90000u * (combo / 3);
             k.idx = (uint64_t)t0 + f.lane + (uint64_t)mc.T * row;
-            if (lane == 0) out[place - 1] = k;
+            if (lane == 0) out[i] = k;
         }
     }
 }
 
 constexpr int MERGE_THREADS = 1024;
 
-// LAST: the lists of all blocks of the launch before (or the blocks' points themselves, if they are few) into the front's
-// records; else FRONT_FAN blocks' points into a list.
-// As many lists as there is room for at a time, beside the front of those before.
-template <bool LAST>
+// Of points[0 .. n) what a step's corner -- its least s, there the least p, there the least index -- covers goes, the rest
+// to the front of the array, in any order; their number.  least: the s.  Steps are narrow: hardly anything but the
+// front and what many candidates share is left (600 x 64: 27854 points of all blocks, 2292 behind no other step's, 115 after this).
+__device__ __forceinline__ uint32_t drop_behind_corners(const FrontArgs &a, Key *points, uint32_t n, const double *least,
+                                                        unsigned long long *corner_p, unsigned long long *corner_idx, uint32_t *filled)
+{
+    if (threadIdx.x < FRONT_STEPS) { corner_p[threadIdx.x] = INF_BITS; corner_idx[threadIdx.x] = ~0ull; }
+    if (threadIdx.x == 0) *filled = 0;
+    __syncthreads();
+    constexpr uint32_t PER = FRONT_POINTS / MERGE_THREADS;
+    Key k[PER];
+    uint32_t step[PER];
+#pragma unroll
+    for (uint32_t q = 0; q < PER; ++q) {
+        const uint32_t i = q * MERGE_THREADS + threadIdx.x;
+        k[q] = no_point();
+        if (i < n) k[q] = points[i];
+        step[q] = step_of(a, k[q].p);
+        if (i < n && k[q].s == least[step[q]])
+            (void)__hip_atomic_fetch_min(corner_p + step[q], (unsigned long long)__double_as_longlong(k[q].p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t q = 0; q < PER; ++q)
+        if (q * MERGE_THREADS + threadIdx.x < n && k[q].s == least[step[q]] && (unsigned long long)__double_as_longlong(k[q].p) == corner_p[step[q]])
+            (void)__hip_atomic_fetch_min(corner_idx + step[q], (unsigned long long)k[q].idx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __syncthreads();
+#pragma unroll
+    for (uint32_t q = 0; q < PER; ++q) {
+        if (q * MERGE_THREADS + threadIdx.x >= n) continue;
+        Key c;
+        c.p = __longlong_as_double((long long)corner_p[step[q]]); c.s = least[step[q]]; c.idx = corner_idx[step[q]];
+        if (!(c.s <= k[q].s && key_less(c, k[q])))
+            points[__hip_atomic_fetch_add(filled, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)] = k[q];
+    }
+    __syncthreads();
+    const uint32_t left = *filled;
+    __syncthreads();
+    return left;
+}
+
+// The blocks' points into the front's records.  Counters and staircase are left as the next call needs them.
 __global__ __launch_bounds__(MERGE_THREADS) void k_front_merge(FrontArgs a)
 {
     __shared__ Key points[FRONT_POINTS];
     __shared__ double low[FRONT_POINTS];
     __shared__ uint32_t keep[FRONT_POINTS];
     __shared__ DivTable dv_s;
-    const bool lists = LAST && !a.one_merge;
-    const uint32_t source_room = lists ? FRONT_POINTS : FRONT_BLOCK, first = LAST ? 0u : blockIdx.x * FRONT_FAN;
-    const uint32_t n_sources = lists ? a.n_lists : min(FRONT_FAN, a.n_blocks - first);
-    const Key *from = lists ? a.lists : a.points + (uint64_t)first * FRONT_BLOCK;
-    ConstPtr<uint32_t> counts = as_constant(a.counts + (lists ? FRONT_BLOCKS : first));
-    uint32_t *n_out = LAST ? a.n_out : a.counts + FRONT_BLOCKS + blockIdx.x;
-    if constexpr (LAST) {
+    __shared__ double wave_least[FRONT_STEPS / 64];
+    __shared__ uint32_t filled, n_left;
+    // the staircase, until the first sort: the least below each step, in each step, and each step's corner
+    static_assert(4 * FRONT_STEPS <= FRONT_POINTS, "they fit");
+    double *below = low, *least = low + FRONT_STEPS;
+    unsigned long long *corner_p = reinterpret_cast<unsigned long long *>(low + 2 * FRONT_STEPS), *corner_idx = corner_p + FRONT_STEPS;
+    const uint32_t lane = threadIdx.x & 63;
+    const uint32_t n_list = a.counts[0];
+    bool fits = a.counts[1] == 0;
+    double own = pos_inf();
+    if (threadIdx.x < FRONT_STEPS) own = __longlong_as_double((long long)a.stairs[threadIdx.x]);
+    {
         uint32_t at = 0;
         for (int q = 0; q < 4; ++q) {
             for (uint32_t k = threadIdx.x; k < a.ndiv[q]; k += MERGE_THREADS) dv_s.div[q][k] = a.list[at + k];
@@ -440,38 +561,71 @@ __global__ __launch_bounds__(MERGE_THREADS) void k_front_merge(FrontArgs a)
         }
         if (threadIdx.x < 4) { dv_s.X[threadIdx.x] = a.X[threadIdx.x]; dv_s.ndiv[threadIdx.x] = a.ndiv[threadIdx.x]; }
     }
-    uint32_t m, N, have = 0, q = 0;
-    for (;;) {
-        const uint32_t before = q;
-        bool fits = true;
-        for (; q < n_sources; ++q) {
-            const uint32_t n = counts[q];                    // the same for all threads: so are the branches
-            fits = n <= source_room;
-            if (!fits || have + n > FRONT_POINTS) break;
-            for (uint32_t i = threadIdx.x; i < n; i += MERGE_THREADS) points[have + i] = from[(uint64_t)q * source_room + i];
-            have += n;
+    if (threadIdx.x == 0) filled = 0;
+    if (threadIdx.x < FRONT_STEPS) least[threadIdx.x] = own;
+    steps_below(own, below, wave_least);                     // (its barriers: everybody has read counters and staircase)
+    if (threadIdx.x < FRONT_STEPS) a.stairs[threadIdx.x] = INF_BITS;
+    if (threadIdx.x < 2) a.counts[threadIdx.x] = 0;
+
+    uint32_t n = 0;                                          // points in LDS
+    bool sorted = false;
+    for (uint32_t at = 0; fits && at < n_list;) {
+        const uint32_t upto = min(n_list, at + (FRONT_POINTS - n));
+        constexpr uint32_t AHEAD = 4;                        // points a thread has under way
+        for (uint32_t i0 = at; i0 < upto; i0 += AHEAD * MERGE_THREADS) {
+            Key k[AHEAD];
+#pragma unroll
+            for (uint32_t q = 0; q < AHEAD; ++q) {
+                const uint32_t i = i0 + q * MERGE_THREADS + threadIdx.x;
+                k[q] = a.points[min(i, upto - 1)];
+                if (i >= upto) k[q].p = pos_inf();
+            }
+#pragma unroll
+            for (uint32_t q = 0; q < AHEAD; ++q) {
+                // (once the room of the staircase has served a sort, the sort drops what it would have dropped)
+                const bool stays = k[q].p < pos_inf() && (sorted || k[q].s < below[step_of(a, k[q].p)]);
+                const unsigned long long who = __ballot(stays);
+                if (!who) continue;
+                uint32_t place = 0;
+                if (lane == 0) place = __hip_atomic_fetch_add(&filled, (uint32_t)__popcll(who), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                place = __builtin_amdgcn_readfirstlane(place) + (uint32_t)__popcll(who & ((1ull << lane) - 1));
+                if (stays) points[place] = k[q];
+            }
         }
-        if (!fits || q == before) {
-            if (threadIdx.x == 0) *n_out = TOO_MANY;
-            return;
+        at = upto;
+        __syncthreads();
+        n = filled;
+        __syncthreads();                                     // (everybody has read it)
+        if (at < n_list && n <= FRONT_POINTS / 2) continue;
+        if (!sorted) n = drop_behind_corners(a, points, n, least, corner_p, corner_idx, &filled);
+        if (n > (at < n_list ? FRONT_POINTS / 2 : (uint32_t)MERGE_THREADS)) {
+            uint32_t N;
+            const uint32_t m = front_of<MERGE_THREADS, FRONT_POINTS>(points, low, keep, n, N);
+            close_up<MERGE_THREADS, FRONT_POINTS>(points, keep, N);
+            sorted = true;
+            n = m;
+            if (threadIdx.x == 0) filled = n;
+            __syncthreads();
         }
-        m = front_of<MERGE_THREADS, FRONT_POINTS>(points, low, keep, have, N);
-        if (q == n_sources) break;
-        close_up<MERGE_THREADS, FRONT_POINTS>(points, keep, N);
-        have = m;
+        fits = at == n_list || n < FRONT_POINTS;
     }
-    for (uint32_t i = threadIdx.x; i < N; i += MERGE_THREADS) {
-        const uint32_t place = keep[i];
-        if (place == (i ? keep[i - 1] : 0u)) continue;
-        if constexpr (LAST) {
-            if (place > a.capacity) continue;
-            mmee_result res;
-            winner_record(a.enc, dv_s, a.mc, points[i], res);
-            write_record(a.out + place - 1, points[i], res);
-        } else
-            a.lists[(uint64_t)blockIdx.x * FRONT_POINTS + place - 1] = points[i];
+    if (!fits) {
+        if (threadIdx.x == 0) *a.n_out = TOO_MANY;
+        return;
     }
-    if (threadIdx.x == 0) *n_out = m;
+    if (n <= MERGE_THREADS) n = front_by_pairs<MERGE_THREADS>(points, keep, &n_left, n);
+    for (uint32_t i = threadIdx.x; i < n; i += MERGE_THREADS) {
+        const Key me = points[i];
+        uint32_t place = 0;                                  // along the front p goes up
+        if (n <= MERGE_THREADS)
+            for (uint32_t j = 0; j < n; ++j) place += points[j].p < me.p;
+        else place = i;
+        if (place >= a.capacity) continue;
+        mmee_result res;
+        winner_record(a.enc, dv_s, a.mc, me, res);
+        write_record(a.out + place, me, res);
+    }
+    if (threadIdx.x == 0) *a.n_out = n;
 }
 
 }  // namespace mmee

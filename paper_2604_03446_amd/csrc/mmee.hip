@@ -110,10 +110,12 @@ struct State {
     // published values per result slot
     unsigned char *desc_host = nullptr, *desc_dev = nullptr;
     size_t desc_cap = 0;
-    // fronts over the kept rows: the chunks' points and their counters; FRONT_POINTS records of the front and their
+    // fronts over the kept rows: the blocks' points, the staircase and the counters; FRONT_POINTS records of the front and their
     // number (pinned)
-    Key *front_points = nullptr, *front_lists = nullptr;
+    Key *front_points = nullptr;
+    unsigned long long *front_stairs = nullptr;
     uint32_t *front_counts = nullptr;
+    bool front_clean = false;                   // staircase and counters are as a call must find them
     Pinned front;
     void *block_records = nullptr;              // what the blocks of a pruned search leave for the reduction
     size_t block_records_cap = 0;
@@ -1296,13 +1298,13 @@ static_assert(sizeof(FrontArgs) <= 4096, "kernel arguments are limited to 4 KiB"
 
 constexpr size_t FRONT_N_AT = sizeof(FinalRecord) * FRONT_POINTS;     // where S.front has the number of its records
 
-// The front in three launches (two where the blocks are few); its records and their number land in S.front (TOO_MANY: something outgrew its room,
+// The front in two launches; its records and their number land in S.front (TOO_MANY: something outgrew its room,
 // walk the front).  Events of slot 0 bracket it.
 int enqueue_front(const Plan &p, bool bs_da, uint32_t capacity)
 {
     if (!S.front_points) HIP_TRY(hipMalloc(&S.front_points, sizeof(Key) * FRONT_BLOCKS * FRONT_BLOCK));
-    if (!S.front_lists) HIP_TRY(hipMalloc(&S.front_lists, sizeof(Key) * FRONT_LISTS * FRONT_POINTS));
-    if (!S.front_counts) HIP_TRY(hipMalloc(&S.front_counts, sizeof(uint32_t) * (FRONT_BLOCKS + FRONT_LISTS)));
+    if (!S.front_stairs) HIP_TRY(hipMalloc(&S.front_stairs, sizeof(unsigned long long) * FRONT_STEPS));
+    if (!S.front_counts) HIP_TRY(hipMalloc(&S.front_counts, sizeof(uint32_t) * 2));
     HIP_TRY(ensure_pinned(HipPinned{}, S.front, FRONT_N_AT + sizeof(uint32_t)));
     FrontArgs a;
     std::memset(&a, 0, sizeof(a));
@@ -1313,19 +1315,43 @@ int enqueue_front(const Plan &p, bool bs_da, uint32_t capacity)
     if (list_length(p.dv) > FRONT_DIVS) return MMEE_EINVAL;
     pack_lists(p.dv, a.list);
     a.capacity = std::min<uint32_t>(capacity, FRONT_POINTS);
-    a.points = S.front_points; a.lists = S.front_lists; a.counts = S.front_counts; a.enc = S.enc;
-    a.n_blocks = (uint32_t)((p.T + PRUNED_TC - 1) / PRUNED_TC) * (bs_da ? FRONT_SPLIT : 1);
-    a.n_lists = (a.n_blocks + FRONT_FAN - 1) / FRONT_FAN;
-    a.one_merge = a.n_blocks <= FRONT_FAN;
+    a.points = S.front_points; a.stairs = S.front_stairs; a.counts = S.front_counts; a.enc = S.enc;
     a.out = reinterpret_cast<FinalRecord *>(S.front.map);
     a.n_out = reinterpret_cast<uint32_t *>(S.front.map + FRONT_N_AT);
+    // The staircase's steps.  Values of equal upper bits share one: how fine it is decides what a look at it spares,
+    // not what the front is.  Buffer sizes lie between 1 and twice all five matrices: as many steps to a factor of
+    // two as there is room for.  Latencies worth having lie within a few factors of two above what arithmetic and DRAM ask for
+    // at the least: 64 steps to each of eight.
+    double lowest = 1.0;
+    uint32_t fine = 6;
+    if (bs_da) {
+        const double most = 2.0 * (a.size[0] + a.size[1] + a.size[2] + a.size[3] + a.size[4]);
+        for (fine = 9; fine && ((uint64_t)(std::ilogb(most) + 1) << fine) > FRONT_STEPS; --fine) {}
+    } else {
+        const double cycles = (a.extent[DI] * a.extent[DK] * a.extent[DL] + a.extent[DI] * a.extent[DL] * a.extent[DJ]) /
+                              ((double)p.mc.pe_rows * (double)p.mc.pe_cols);
+        const double fetch = p.mc.dram_bw > 0.0 ? (a.size[0] + a.size[1] + a.size[2] + a.size[3]) * p.mc.word / p.mc.dram_bw : 0.0;
+        lowest = 0.999 * p.mc.c_lat * std::max(cycles, fetch);
+    }
+    a.step_shift = 20 - fine;
+    {
+        uint64_t bits;
+        std::memcpy(&bits, &lowest, sizeof(bits));
+        a.step0 = (int32_t)((uint32_t)(bits >> 32) >> a.step_shift);
+    }
+    const uint32_t n_blocks = (uint32_t)((p.T + PRUNED_TC - 1) / PRUNED_TC) * (bs_da ? FRONT_SPLIT : 1);
     HIP_TRY(hipEventRecord(S.events[0], S.stream));
-    const dim3 grid(a.n_blocks);
-    if (bs_da) hipLaunchKernelGGL(k_front_points<true>, grid, dim3(PRUNED_THREADS), 0, S.stream, a);
-    else hipLaunchKernelGGL(k_front_points<false>, grid, dim3(PRUNED_THREADS), 0, S.stream, a);
-    if (!a.one_merge) hipLaunchKernelGGL(k_front_merge<false>, dim3(a.n_lists), dim3(MERGE_THREADS), 0, S.stream, a);
-    hipLaunchKernelGGL(k_front_merge<true>, dim3(1), dim3(MERGE_THREADS), 0, S.stream, a);
+    if (!S.front_clean) {
+        hipLaunchKernelGGL(k_fill_words64, dim3((FRONT_STEPS + 255) / 256), dim3(256), 0, S.stream, S.front_stairs, (uint64_t)FRONT_STEPS, INF_BITS);
+        hipLaunchKernelGGL(k_clear_words, dim3(1), dim3(64), 0, S.stream, S.front_counts, 2u);
+    }
+    S.front_clean = false;                     // (until both launches are in the stream: the merge cleans up)
+    if (bs_da) hipLaunchKernelGGL(k_front_points<true>, dim3(n_blocks), dim3(PRUNED_THREADS), 0, S.stream, a);
+    else hipLaunchKernelGGL(k_front_points<false>, dim3(n_blocks), dim3(PRUNED_THREADS), 0, S.stream, a);
     HIP_TRY(hipGetLastError());
+    hipLaunchKernelGGL(k_front_merge, dim3(1), dim3(MERGE_THREADS), 0, S.stream, a);
+    HIP_TRY(hipGetLastError());
+    S.front_clean = true;
     HIP_TRY(hipEventRecord(S.events[1], S.stream));
     return MMEE_OK;
 }
@@ -1712,7 +1738,7 @@ int mmee_chain_search_multi(const mmee_chain *w, const mmee_hw *hw, const int *o
     return mmee_chain_search_many(ws, hs, objectives, n_obj, flags, out, nullptr);
 }
 
-// A front.  Over the kept rows of a problem that is not too large, in three launches (fronts.h); else a walk along it.
+// A front.  Over the kept rows of a problem that is not too large, in two launches (fronts.h); else a walk along it.
 // Energy-latency (Sec. VII-E): by ascending latency, each step the
 // latency-then-energy optimum among the candidates whose energy is strictly below the previous
 // point's.  Buffer size / DRAM access (Sec. VII-C): by ascending buffer size, each step the
@@ -1988,7 +2014,7 @@ void mmee_shutdown(void)
     (void)hipFree(S.batch_dev); (void)hipFree(S.item_keys);
     if (S.desc_host) (void)hipHostFree(S.desc_host);
     if (S.decode.host) (void)hipHostFree(S.decode.host);
-    (void)hipFree(S.front_points); (void)hipFree(S.front_lists); (void)hipFree(S.front_counts);
+    (void)hipFree(S.front_points); (void)hipFree(S.front_stairs); (void)hipFree(S.front_counts);
     if (S.front.host) (void)hipHostFree(S.front.host);
     (void)hipFree(S.desc_dev); (void)hipFree(S.block_records); (void)hipFree(S.pruned_hints);
     for (hipEvent_t e : S.events) (void)hipEventDestroy(e);
