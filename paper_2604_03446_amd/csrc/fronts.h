@@ -395,19 +395,11 @@ __global__ __launch_bounds__(PRUNED_THREADS, BS_DA ? 2 : 4) void k_front_points(
             }
         }
     } else {
+        __syncthreads();
         {
             const double cap[1] = {mc.cap_words};
             double l[1];
-            switch (wave) {
-            case 0: least_traffic<0, 0, 3>(v, a.size, cap, l); break;
-            case 1: least_traffic<0, 1, 3>(v, a.size, cap, l); break;
-            case 2: least_traffic<0, 2, 3>(v, a.size, cap, l); break;
-            case 3: least_traffic<1, 0, 2>(v, a.size, cap, l); break;
-            case 4: least_traffic<1, 1, 2>(v, a.size, cap, l); break;
-            case 5: least_traffic<2, 0, 3>(v, a.size, cap, l); break;
-            case 6: least_traffic<2, 1, 3>(v, a.size, cap, l); break;
-            default: least_traffic<2, 2, 3>(v, a.size, cap, l); break;
-            }
+            least_traffic<1>(tab, wave, cap, l);
             least[wave][lane] = l[0];
         }
         __syncthreads();

@@ -1186,6 +1186,13 @@ void pruned_layout(const std::vector<PrunedEntry> &entries, const std::vector<ui
             PrunedMember &m = members[member++];
             m.mc = e.plan->mc;
             m.slot = e.slot; m.cap = cap; m.mask = (uint32_t)e.mask; m.group = (uint32_t)g;
+            const DivTable &dv = e.plan->dv;
+            const double X[4] = {(double)dv.X[0], (double)dv.X[1], (double)dv.X[2], (double)dv.X[3]};
+            const double m1 = X[DI] * X[DK] * X[DL], m2 = X[DI] * X[DL] * X[DJ], sm = (double)m.mc.c_softmax * (X[DI] * X[DL]);
+            m.rf_words[0] = m.mc.BH * 3.0 * m1; m.rf_words[1] = m.mc.BH * 3.0 * m2;      // (whole numbers: exact)
+            m.mac_ops[0] = m.mc.BH * (m1 + sm); m.mac_ops[1] = m.mc.BH * m2;
+            m.e_rf0 = m.mc.e_rf * (m.rf_words[0] + m.rf_words[1]); m.e_mac0 = m.mc.e_mac * (m.mac_ops[0] + m.mac_ops[1]);
+            m.exact_k = e.plan->exact_k; m.pad_ = 0;
         }
         uint32_t *list = reinterpret_cast<uint32_t *>(base + list_off);
         for (int q = 0; q < 4; ++q) {

@@ -11,21 +11,20 @@
 //   2. the nine combinations on top of it, per accelerator.
 //
 // k_search_batch (batch.h) does both per problem and is bound by step 1: eight table values per row and tiling
-// from LDS, 270 rows, 32 LDS cycles each.  Here step 1 is done once per shape and distinct capacity, and without a
-// table: the rows are known at compile time (rows.h: 181 suffice), so they are straight-line code on one tiling per
-// lane, the operands' footprints and traffic options are registers, shared sums are formed once, and a row is
-// about four vector operations and three per capacity.
+// from LDS, 270 rows, 32 LDS cycles each.  Here step 1 is done once per shape and distinct capacity, over the rows that
+// the least traffic needs (rows.h: 181 suffice), each of them under all of a round's capacities: three operations per capacity.
 //
 // A work item is (shape, chunk of 64 tilings), lane = tiling, one block.  The block decodes the chunk, its waves take
-// the classes under four capacities each (step 1), then the accelerators one wave each (step 2).  Positions: each
+// an eighth of the rows each (step 1), then the accelerators one wave each (step 2).  Positions: each
 // wave publishes its values, takes the launch-wide lowest ones back, and only a value that nothing published beats is
-// followed up: the lowest class (f, combination, r), then the first row, then the first tiling that reach it.  Each
-// item leaves one record per problem and key for k_pruned_finish.
+// followed up, by the block's waves in turn: the lowest class (f, combination, r), then the first row, then the first tiling that
+// reach it.  Each item leaves one record per problem and key for k_pruned_finish.
 //
-// 64 accelerators x 8 attention shapes x 2 keys: 1.63 ms in k_search_batch, 0.29 ms here.  Bound by step 2's vector
-// issue (900 wave instructions per problem and chunk, step 1's share included) at 46 % of the issue rate: two blocks
-// per CU, reductions across lanes between short stretches of arithmetic.  128 registers do not hold it: 101 are
-// spilled (368 bytes of scratch per lane), 178 MB written and 110 MB read per such call where the records are 6.7 MB.
+// 64 accelerators x 8 attention shapes x 2 keys: 1.63 ms in k_search_batch, 0.20 ms here.  Of a block's 125 000 cycles (1088
+// blocks, two per CU) step 1 takes 24 000, step 2 49 000 (6000 per problem and wave, four waves on a SIMD), the
+// positions 23 000 (some 29 a block: ties with the optimum, not late news), the meetings of the waves the rest.  Before, 0.29 ms:
+// 38 000 cycles more for the capacities of 64 problems read one after the other, rows as straight-line code on six of the
+// eight waves, tile costs mode by mode and once per key, positions left to the wave whose problem it was.
 // What k_search_batch keeps (keep_shared): calls whose problems share little, where this kernel's step 1 would be
 // done for one accelerator at a time, and small ones, where a block's chain of problems is long against the
 // chip's other blocks, and two launches of more code count (a single 1764-tiling problem: 17 us against 11).
@@ -39,7 +38,6 @@ namespace mmee {
 constexpr int PRUNED_THREADS = 512;          // two blocks per CU, four waves per SIMD
 constexpr int PRUNED_WAVES = PRUNED_THREADS / 64;
 constexpr int PRUNED_MEMBERS = 64;           // problems of one group at most
-constexpr int PRUNED_CAPS = 4;               // capacities one wave carries through a class's rows
 constexpr int PRUNED_ROUND = 16;             // capacities per round of a shared chunk
 constexpr int PRUNED_INLINE = 3000;          // bytes of problem descriptions that ride in the kernel arguments
 
@@ -60,6 +58,11 @@ struct PrunedGroup {
 
 struct PrunedMember {
     ModelConst mc;
+    // MACs (times three: RF accesses) and MACs with their softmax elements, both times B*H, of the producer (repeated per j
+    // tile by recomputation) and the consumer; their energies without recomputation, which no tiling changes
+    double rf_words[2], mac_ops[2], e_rf0, e_mac0;
+    uint32_t exact_k;                        // the DRAM time is one exact product (ModelConst::dram_k)
+    uint32_t pad_;
     uint32_t slot;                           // where its N_OBJ final records and hints are
     uint32_t cap;                            // number of its capacity in the group's list
     uint32_t mask;                           // keys asked for
@@ -100,158 +103,97 @@ __device__ __forceinline__ T read_const(ConstBytes p)        // wave-uniform: sc
 __device__ __forceinline__ double nothing_fits() { return __hiloint2double(0x7fe00000, 0); }
 constexpr double FITS_BELOW = 1e300;
 
-// every option of every term, for one tiling (the unused ones cost nothing once inlined)
-struct TermOptions {
-    double bs[4][4], c[4];                   // buffer sizes of A, B, D, E; of C
-    double da[4][4], dac[4];                 // DRAM words of A, B, D, E; of an unfused C
-};
+__device__ const LeastOffsets least_dev = LEAST_OFF;
 
-__device__ __forceinline__ TermOptions term_options(const TilingF &v, const double (&size)[5])
+// The least traffic of a wave's piece of the rows, for this lane's tiling, under K capacities: Eq. (1), (2), (4), the mask,
+// Eq. (7), the running minima.  tab: the staged compact table; all its words are whole numbers (unscaled), so the
+// association is free.  As straight-line code on registers (options formed once, sums shared between rows: 4 + 3 K operations a row where
+// this has 14 + 3 K) the same took a block three times as long, 60 000 cycles for nine capacities: 24 KiB of
+// instructions that eight waves run once each are bound by their fetch, also where they hit the instruction cache.
+template <int K>
+__device__ __forceinline__ void least_traffic(const double *tab, uint32_t wave, const double (&cap)[K], double (&least)[K])
 {
-    TermOptions o;
-    const int own[4][2] = {{DI, DK}, {DK, DL}, {DL, DJ}, {DI, DJ}}, other[4][2] = {{DL, DJ}, {DI, DJ}, {DI, DK}, {DK, DL}};
-    auto fill = [](double (&out)[4], double base, double f0, double f1) {
-        out[0] = base; out[1] = base * f0; out[2] = base * f1; out[3] = out[1] * f1;
-    };
-#pragma unroll
-    for (int y = 0; y < 4; ++y) {
-        fill(o.bs[y], v.G[own[y][0]] * v.G[own[y][1]], v.D[own[y][0]], v.D[own[y][1]]);
-        fill(o.da[y], size[y], v.D[other[y][0]], v.D[other[y][1]]);
-    }
-    fill(o.c, v.G[DI] * v.G[DL], v.D[DI], v.D[DL]);
-#pragma unroll
-    for (int y = 0; y < 4; ++y) o.bs[y][3] = size[y];       // the whole matrix: uniform
-    o.c[3] = size[4];
-    const double whole = size[4];            // spilled by Op1, fetched by Op2, one softmax pass over S and P
-    o.dac[0] = whole * 4.0;
-    o.dac[1] = whole * (v.D[DK] + 3.0);
-    o.dac[2] = whole * (v.D[DJ] + 3.0);
-    o.dac[3] = whole * (v.D[DK] + v.D[DJ] + 2.0);
-    return o;
-}
-
-// Row I of class CLS under K capacities: Eq. (1), (2), (4), the mask, Eq. (7), the running minima.  All of it is
-// exact integers, so the association is free: sums that rows share are written alike and formed once.
-template <int CLS, int I, int K>
-__device__ __forceinline__ void least_row(const TermOptions &o, const double (&cap)[K], double (&least)[K])
-{
-    constexpr RowTerms R = LEAST[CLS].row[I];
-    double bs1 = (o.bs[0][R.bs[0]] + o.bs[1][R.bs[1]]) + o.c[R.c];
-    double bs2 = (o.bs[2][R.bs[2]] + o.bs[3][R.bs[3]]);
-    constexpr uint32_t DE = R.tau >> 2, AB = R.tau & 3;
-    if constexpr (DE == 3) bs1 = bs1 + (o.bs[2][R.bs[2]] + o.bs[3][R.bs[3]]);
-    else if constexpr (DE) bs1 = bs1 + o.bs[DE == 1 ? 2 : 3][R.bs[DE == 1 ? 2 : 3]];
-    if constexpr (AB == 0) bs2 = bs2 + o.c[R.c];
-    else if constexpr (AB == 3) bs2 = bs2 + ((o.bs[0][R.bs[0]] + o.bs[1][R.bs[1]]) + o.c[R.c]);
-    else bs2 = bs2 + (o.bs[AB - 1][R.bs[AB - 1]] + o.c[R.c]);
-    double da = o.da[0][R.da[0]] + o.da[1][R.da[1]];
-    if constexpr (R.dac != 4) da = da + o.dac[R.dac & 3];
-    da = da + (o.da[2][R.da[2]] + o.da[3][R.da[3]]);
-    const double bs = fmax(bs1, bs2);
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-        const bool fits = bs <= cap[k];
-        least[k] = fmin(least[k], __hiloint2double(fits ? __double2hiint(da) : 0x7fe00000, __double2loint(da)));
-    }
-}
-
-// rows [LO, LO + N) of a class
-template <int CLS, int LO, int K, int... I>
-__device__ __forceinline__ void least_rows_of(const TermOptions &o, const double (&cap)[K], double (&least)[K],
-                                              std::integer_sequence<int, I...>)
-{
-    (least_row<CLS, LO + I, K>(o, cap, least), ...);
-}
-
-constexpr int LEAST_RUN = 14;                // rows between two marks
-
-// Rows [LO, HI) of a class, a run at a time.  Options and sums are shared within a run only: without the mark
-// between runs (nothing but an opaque copy of the tiling) the compiler keeps every option and sum of a class for
-// its last use and spills hundreds of registers.
-template <int CLS, int LO, int HI, int K>
-__device__ __forceinline__ void least_runs(TilingF v, const double (&size)[5], const double (&cap)[K], double (&least)[K])
-{
-    constexpr int RUNS = (HI - LO + LEAST_RUN - 1) / LEAST_RUN, N = (HI - LO + RUNS - 1) / RUNS;
-    {
-        const TermOptions o = term_options(v, size);
-        least_rows_of<CLS, LO, K>(o, cap, least, std::make_integer_sequence<int, N>{});
-    }
-    if constexpr (RUNS > 1) {
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) { asm("" : "+v"(v.G[q])); asm("" : "+v"(v.D[q])); }
-        least_runs<CLS, LO + N, HI, K>(v, size, cap, least);
-    }
-}
-
-// piece PART of PARTS of a class's rows
-template <int CLS, int PART, int PARTS, int K>
-__device__ __forceinline__ void least_traffic(const TilingF &v, const double (&size)[5], const double (&cap)[K], double (&least)[K])
-{
-    constexpr int LO = LEAST[CLS].n * PART / PARTS, HI = LEAST[CLS].n * (PART + 1) / PARTS;
+    typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
+    ConstPtr<u32x8> offs = (ConstPtr<u32x8>)&least_dev.off[0][0];
+    const uint32_t lo = as_constant(least_dev.lo)[wave], hi = as_constant(least_dev.hi)[wave];
+    const char *col = reinterpret_cast<const char *>(tab) + (threadIdx.x & 63) * 8;
 #pragma unroll
     for (int k = 0; k < K; ++k) least[k] = nothing_fits();
-    least_runs<CLS, LO, HI, K>(v, size, cap, least);
+    u32x8 next = offs[lo];
+#pragma unroll 4
+    for (uint32_t i = lo; i < hi; ++i) {
+        const u32x8 off = next;
+        next = offs[min(i + 1, hi - 1)];
+        double w[NSEL];
+#pragma unroll
+        for (int q = 0; q < NSEL; ++q) w[q] = *reinterpret_cast<const double *>(col + off[q]);
+        const double bs = fmax(w[0] + w[2] + w[1], w[3] + w[2] + w[4]), da = w[5] + w[6] + w[7];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const bool fits = bs <= cap[k];
+            least[k] = fmin(least[k], __hiloint2double(fits ? __double2hiint(da) : 0x7fe00000, __double2loint(da)));
+        }
+    }
 }
 
 // ---- step 2: an accelerator's costs on top of it -----------------------------------------------
 
-// What the two operators contribute per (r, stationary mode): words and cycles over all their tile stages.
-struct StageTerms {
-    double br1[2][3], cy1[2][3], br2[3], cy2[3];
-    double e_rf[2], e_mac[2];
-};
+// What the two operators contribute per stationary mode, words and cycles over all their tile stages, without
+// recomputation (which multiplies the first operator's by D_J): tile_cost_f64 times the number of tiles, with the
+// products taken apart.  A tile's extent times its count is the matrix's, so what is left of a mode is the operands' sizes
+// times one factor per dimension -- D * ceil(G / width), nine in all instead of eighteen quotients -- and sums of two
+// or three such terms, some of them common to modes.  All of them are whole numbers below 2^53: the values are the same whatever
+// the association, and fused operations are exact.  58 operations instead of about 130.
+struct StageTerms { double br1[3], cy1[3], br2[3], cy2[3]; };
 
-__device__ __forceinline__ StageTerms stage_terms(const TilingF &v, const double (&X)[4], const ModelConst &mc)
+__device__ __forceinline__ StageTerms stage_terms(const TilingF &v, const double (&X)[4], const double (&size)[5], const ModelConst &mc)
 {
+    // D * ceil(G / b); the rounded quotient of G - 1/2 is never a whole number (cdiv_f64)
+    auto folds = [&](int q, double rcp_b) { return v.D[q] * __builtin_ceil((v.G[q] - 0.5) * rcp_b); };
+    const double row_i = folds(DI, mc.rcp_rows), row_k = folds(DK, mc.rcp_rows), row_l = folds(DL, mc.rcp_rows);
+    const double col_k = folds(DK, mc.rcp_cols), col_l = folds(DL, mc.rcp_cols), col_j = folds(DJ, mc.rcp_cols);
+    const double wide_k = folds(DK, mc.rcp_cols_g), wide_l = folds(DL, mc.rcp_cols_g), wide_j = folds(DJ, mc.rcp_cols_g);
+    const double A = size[0], B = size[1], D = size[2], E = size[3], C = size[4];
+    const double a_wide = A * wide_l, b_row = B * row_i, c_wide = C * wide_j, d_row = D * row_i, row_col = row_i * col_l;
     StageTerms t;
-    const double st1 = v.D[DI] * v.D[DK] * v.D[DL], st2 = v.D[DI] * v.D[DL] * v.D[DJ];
-#pragma unroll
-    for (uint32_t s = 0; s < 3; ++s) {
-        double words, cycles;
-        tile_cost_f64(v.G[DI], v.G[DK], v.G[DL], s, mc, words, cycles);
-        t.br1[0][s] = st1 * words; t.cy1[0][s] = st1 * cycles;
-        t.br1[1][s] = v.D[DJ] * t.br1[0][s]; t.cy1[1][s] = v.D[DJ] * t.cy1[0][s];
-        tile_cost_f64(v.G[DI], v.G[DL], v.G[DJ], s, mc, words, cycles);
-        t.br2[s] = st2 * words; t.cy2[s] = st2 * cycles;
-    }
-    const double m1 = X[DI] * X[DK] * X[DL], m2 = X[DI] * X[DL] * X[DJ], s1 = X[DI] * X[DL];
-#pragma unroll
-    for (int r = 0; r < 2; ++r) {
-        const double rho = r ? v.D[DJ] : 1.0;                // producer repeated per j tile (Sec. V-D)
-        const double mac = rho * m1 + m2;
-        t.e_rf[r] = mc.e_rf * (mc.BH * 3.0 * mac);
-        t.e_mac[r] = mc.e_mac * (mc.BH * (mac + (double)mc.c_softmax * (rho * s1)));
-    }
+    // m x r x n = I x K x L: weight, input, output stationary
+    t.br1[0] = __builtin_fma(B, v.D[DI], __builtin_fma(C, row_k, a_wide));  t.cy1[0] = X[DI] * (row_k * col_l);
+    t.br1[1] = __builtin_fma(A, v.D[DL], __builtin_fma(C, wide_k, b_row));  t.cy1[1] = X[DL] * (row_i * col_k);
+    t.br1[2] = __builtin_fma(C, v.D[DK], a_wide + b_row);                   t.cy1[2] = X[DK] * row_col;
+    // I x L x J
+    t.br2[0] = __builtin_fma(D, v.D[DI], __builtin_fma(E, row_l, c_wide));  t.cy2[0] = X[DI] * (row_l * col_j);
+    t.br2[1] = __builtin_fma(C, v.D[DJ], __builtin_fma(E, wide_l, d_row));  t.cy2[1] = X[DJ] * row_col;
+    t.br2[2] = __builtin_fma(E, v.D[DL], c_wide + d_row);                   t.cy2[2] = X[DL] * (row_i * col_j);
     return t;
 }
 
 // max(compute cycles, buffer<->RF time) of combination s1 + 3 s2, without the factor c_lat: a minimum of such times times
 // c_lat is the minimum of the products, bit for bit.  POW2: the buffer bandwidth is a power of two, gb1 and gb2 are the
-// two operators' shares of the time (br1, br2 times one exact constant).
+// two operators' shares of the time (br1, br2 times one exact constant).  r: the first operator's share once per j tile.
 template <bool POW2>
-__device__ __forceinline__ double combo_time(const StageTerms &t, const double (&gb1)[2][3], const double (&gb2)[3], const ModelConst &mc, int r, int c)
+__device__ __forceinline__ double combo_time(const StageTerms &t, const double (&gb1)[3], const double (&gb2)[3], const ModelConst &mc, double dj, int r, int c)
 {
-    const double cyc = t.cy1[r][c % 3] + t.cy2[c / 3];
-    if constexpr (POW2) return fmax(cyc, gb1[r][c % 3] + gb2[c / 3]);
-    else return fmax(cyc, buffer_time_general(mc, t.br1[r][c % 3] + t.br2[c / 3]));
+    auto both = [&](double one, double two) { return r ? __builtin_fma(dj, one, two) : one + two; };
+    const double cyc = both(t.cy1[c % 3], t.cy2[c / 3]);
+    if constexpr (POW2) return fmax(cyc, both(gb1[c % 3], gb2[c / 3]));
+    else return fmax(cyc, buffer_time_general(mc, both(t.br1[c % 3], t.br2[c / 3])));
 }
 
 // the row side of a candidate's costs, from its traffic; +inf both when no row fits
 struct RowSide { double words, e_part, time; };
-__device__ __forceinline__ RowSide row_side(const ModelConst &mc, double least)
+__device__ __forceinline__ RowSide row_side(const ModelConst &mc, double least, bool exact_k = false)
 {
     RowSide rs;
     const bool fits = least < FITS_BELOW;
     const double d = fits ? least : 0.0, over = fits ? 0.0 : pos_inf();
     rs.words = mc.BH * d;
     rs.e_part = fmax(mc.e_dram * rs.words, over);
-    rs.time = fmax(dram_time_general(mc, d), over);
+    rs.time = fmax(exact_k ? rs.words * mc.dram_k : dram_time_general(mc, d), over);
     return rs;
 }
 __device__ __forceinline__ double energy_of(const ModelConst &mc, const RowSide &rs, double br, double e_rf, double e_mac)
 {
-    double en = rs.e_part + mc.e_gb * (rs.words + mc.BH * br);
+    double en = rs.e_part + mc.e_gb * __builtin_fma(mc.BH, br, rs.words);     // (whole numbers: exact)
     en = en + e_rf;
     return en + e_mac;
 }
@@ -374,10 +316,12 @@ __global__ __launch_bounds__(PRUNED_THREADS, 4) void k_search_pruned(PrunedArgs 
     __shared__ double gd[8 * PRUNED_TC];                     // the chunk's boundary vectors: G[0..3], D[0..3] per tiling
     __shared__ double least[PRUNED_ROUND * LEAST_CLASSES][PRUNED_TC];
     __shared__ uint32_t div_lds[4 * MAXDIV];                 // the group's divisor lists
-    // per problem of the group and key, only touched by wave (member mod 8): the value, its class and tilings
+    // per problem of the group and key: the value, its class and tilings
     __shared__ Key best[PRUNED_MEMBERS][N_OBJ];
     __shared__ unsigned long long lanes_of[PRUNED_MEMBERS][N_OBJ];
     __shared__ uint32_t code_of[PRUNED_MEMBERS][N_OBJ];
+    __shared__ unsigned char follow_list[PRUNED_MEMBERS * N_OBJ];     // problems and keys whose position is wanted
+    __shared__ uint32_t n_follow;
 
     const double inf = pos_inf();
     const uint32_t lane = threadIdx.x & 63;
@@ -436,36 +380,37 @@ __global__ __launch_bounds__(PRUNED_THREADS, 4) void k_search_pruned(PrunedArgs 
 
     // members are sorted by capacity: a round's members follow those of the round before
     uint32_t m_lo = 0;
+    // lane m: the capacity of problem m (read one after the other, 64 of them took a quarter of the kernel)
+    static_assert(PRUNED_MEMBERS <= 64, "a lane per problem");
+    const uint32_t cap_of_member =
+        *reinterpret_cast<const uint32_t *>((const char *)(members + min(lane, G.n_members - 1) * sizeof(PrunedMember) + offsetof(PrunedMember, cap)));
+    if (threadIdx.x == 0) n_follow = 0;
 #pragma unroll 1
     for (uint32_t cap0 = 0; cap0 < G.n_caps; cap0 += PRUNED_ROUND) {
-        // ---- step 1.  Waves 0-3: class 2 (77 rows) under four capacities each; waves 4-7: classes 0 and 1 (65 + 39)
-        {
-            const uint32_t first = cap0 + (wave & 3) * PRUNED_CAPS;
-            if (first < G.n_caps) {
-                const TilingF v = this_tiling();
-                double cap[PRUNED_CAPS], l[PRUNED_CAPS];
+        // ---- step 1.  Every wave takes an eighth of the rows, all of one class, under all of the round's capacities; the waves
+        // of a class meet in the LDS minima (no row's traffic: nothing_fits, and bit patterns order like the values)
+        const uint32_t n_caps = min(G.n_caps - cap0, (uint32_t)PRUNED_ROUND);
+        for (uint32_t k = threadIdx.x; k < n_caps * LEAST_CLASSES * PRUNED_TC; k += PRUNED_THREADS) (&least[0][0])[k] = nothing_fits();
+        __syncthreads();                                     // (the staged table is there, too)
+        auto step1 = [&](auto most) {
+            constexpr int K = decltype(most)::value;
+            double cap[K], l[K];
 #pragma unroll
-                for (uint32_t k = 0; k < PRUNED_CAPS; ++k) cap[k] = caps[min(first + k, G.n_caps - 1)];
-                auto keep = [&](uint32_t cls) {
+            for (uint32_t k = 0; k < K; ++k) cap[k] = caps[cap0 + min(k, n_caps - 1)];
+            least_traffic<K>(tab, wave, cap, l);
+            const uint32_t cls = as_constant(least_dev.cls)[wave];
 #pragma unroll
-                    for (uint32_t k = 0; k < PRUNED_CAPS; ++k) least[((wave & 3) * PRUNED_CAPS + k) * LEAST_CLASSES + cls][lane] = l[k];
-                };
-                if (wave < 4) {
-                    least_traffic<2, 0, 1>(v, G.size, cap, l);
-                    keep(2);
-                } else {
-                    least_traffic<0, 0, 1>(v, G.size, cap, l);
-                    keep(0);
-                    least_traffic<1, 0, 1>(v, G.size, cap, l);
-                    keep(1);
-                }
-            }
-        }
+            for (uint32_t k = 0; k < K; ++k)
+                if (k < n_caps)
+                    (void)__hip_atomic_fetch_min(reinterpret_cast<unsigned long long *>(&least[k * LEAST_CLASSES + cls][lane]),
+                                                 (unsigned long long)__double_as_longlong(l[k]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        };
+        if (n_caps <= 2) step1(std::integral_constant<int, 2>{});
+        else if (n_caps <= 6) step1(std::integral_constant<int, 6>{});
+        else if (n_caps <= 10) step1(std::integral_constant<int, 10>{});
+        else step1(std::integral_constant<int, PRUNED_ROUND>{});
         __syncthreads();
-        uint32_t m_hi = m_lo;
-        while (m_hi < G.n_members &&
-               ((ConstPtr<uint32_t>)(members + m_hi * sizeof(PrunedMember) + offsetof(PrunedMember, cap)))[0] < cap0 + PRUNED_ROUND)
-            ++m_hi;
+        const uint32_t m_hi = (uint32_t)__popcll(__ballot(lane < G.n_members && cap_of_member < cap0 + PRUNED_ROUND));
 
         // ---- step 2.  This wave's problems: wave, wave + 8, ..., at most eight.  Lane 4 m + o looks after key o of the
         // m-th: it holds what has been published of it when the step begins; a value above that needs no class.
@@ -483,11 +428,15 @@ __global__ __launch_bounds__(PRUNED_THREADS, 4) void k_search_pruned(PrunedArgs 
             const PrunedMember mb = read_const<PrunedMember>(members + j * sizeof(PrunedMember));
             const ModelConst &mc = mb.mc;
             RowSide rs[LEAST_CLASSES];
+            auto row_sides = [&](bool exact_k) {
 #pragma unroll
-            for (uint32_t g = 0; g < LEAST_CLASSES; ++g) {
-                const double d = least[(mb.cap - cap0) * LEAST_CLASSES + g][lane];
-                rs[g] = row_side(mc, lane < nt ? d : nothing_fits());
-            }
+                for (uint32_t g = 0; g < LEAST_CLASSES; ++g) {
+                    const double d = least[(mb.cap - cap0) * LEAST_CLASSES + g][lane];
+                    rs[g] = row_side(mc, lane < nt ? d : nothing_fits(), exact_k);
+                }
+            };
+            if (mb.exact_k) row_sides(true);
+            else row_sides(false);
             auto keep = [&](uint32_t o, double p, double s, uint32_t code, bool reached) {
                 const uint32_t low = __builtin_amdgcn_readfirstlane(wave_min_u32(reached ? code : 0xFFFFFFFFu));
                 const unsigned long long who = __ballot(reached && code == low);
@@ -503,32 +452,31 @@ __global__ __launch_bounds__(PRUNED_THREADS, 4) void k_search_pruned(PrunedArgs 
                 if (lane == 0) { best[j][o].p = inf; best[j][o].s = 0.0; best[j][o].idx = ~0ull; }
                 return true;
             };
-            if (mb.mask & 1) {
-                const StageTerms t = stage_terms(this_tiling(), X, mc);
+            if (mb.mask & 3) {
+              const TilingF tiling = this_tiling();
+              const StageTerms t = stage_terms(tiling, X, G.size, mc);
+              const double dj = tiling.D[DJ];
+              if (mb.mask & 1) {
                 // the energy grows with the buffer<->RF words: the least of them decides
-                const double br2 = fmin(fmin(t.br2[0], t.br2[1]), t.br2[2]);
-                double val = inf;
-#pragma unroll
-                for (int g = 0; g < LEAST_CLASSES; ++g) {
-                    const int r = g == 2;
-                    const double br = fmin(fmin(t.br1[r][0], t.br1[r][1]), t.br1[r][2]) + br2;
-                    val = fmin(val, energy_of(mc, rs[g], br, t.e_rf[r], t.e_mac[r]));
-                }
+                const double br1 = fmin(fmin(t.br1[0], t.br1[1]), t.br1[2]), br2 = fmin(fmin(t.br2[0], t.br2[1]), t.br2[2]);
+                const double e_rf1 = mc.e_rf * __builtin_fma(dj, mb.rf_words[0], mb.rf_words[1]);
+                const double e_mac1 = mc.e_mac * __builtin_fma(dj, mb.mac_ops[0], mb.mac_ops[1]);
+                const double val = fmin(fmin(energy_of(mc, rs[0], br1 + br2, mb.e_rf0, mb.e_mac0), energy_of(mc, rs[1], br1 + br2, mb.e_rf0, mb.e_mac0)),
+                                        energy_of(mc, rs[2], __builtin_fma(dj, br1, br2), e_rf1, e_mac1));
                 const double p = uniform_f64(wave_min_f64(val));
                 // (its class is looked for below, where it matters: rarely)
                 if (!beaten(0, p) && lane == 0) { best[j][0].p = p; best[j][0].s = 0.0; best[j][0].idx = ~0ull; }
-            }
-            if (mb.mask & 2) {
-                const StageTerms t = stage_terms(this_tiling(), X, mc);   // (once more: kept across the energy it spills)
+              }
+              if (mb.mask & 2) {
                 auto latency = [&](auto pow2) {
                     constexpr bool POW2 = decltype(pow2)::value;
-                    double gb1[2][3], gb2[3], fastest[2] = {inf, inf};
+                    double gb1[3], gb2[3], fastest[2] = {inf, inf};
 #pragma unroll
-                    for (int s = 0; s < 3; ++s) { gb1[0][s] = t.br1[0][s] * mc.gb_k; gb1[1][s] = t.br1[1][s] * mc.gb_k; gb2[s] = t.br2[s] * mc.gb_k; }
+                    for (int s = 0; s < 3; ++s) { gb1[s] = t.br1[s] * mc.gb_k; gb2[s] = t.br2[s] * mc.gb_k; }
 #pragma unroll
                     for (int r = 0; r < 2; ++r) {
 #pragma unroll
-                        for (int c = 0; c < 9; ++c) fastest[r] = fmin(fastest[r], combo_time<POW2>(t, gb1, gb2, mc, r, c));
+                        for (int c = 0; c < 9; ++c) fastest[r] = fmin(fastest[r], combo_time<POW2>(t, gb1, gb2, mc, dj, r, c));
                         fastest[r] = mc.c_lat * fastest[r];
                     }
                     const double val = fmin(fmin(fmax(rs[0].time, fastest[0]), fmax(rs[1].time, fastest[0])), fmax(rs[2].time, fastest[1]));
@@ -541,7 +489,7 @@ __global__ __launch_bounds__(PRUNED_THREADS, 4) void k_search_pruned(PrunedArgs 
 #pragma unroll
                         for (int r = 0; r < 2; ++r)
 #pragma unroll
-                            for (int c = 8; c >= 0; --c) low[r] = mc.c_lat * combo_time<POW2>(t, gb1, gb2, mc, r, c) <= p ? (uint32_t)c : low[r];
+                            for (int c = 8; c >= 0; --c) low[r] = mc.c_lat * combo_time<POW2>(t, gb1, gb2, mc, dj, r, c) <= p ? (uint32_t)c : low[r];
                         uint32_t code = rs[2].time <= p && low[1] < 9 ? 10u + 2u * low[1] : 0xFFFFFFFFu;
                         code = rs[1].time <= p && low[0] < 9 ? min(code, 9u + 2u * low[0]) : code;
                         code = rs[0].time <= p && low[0] < 9 ? low[0] : code;
@@ -550,6 +498,7 @@ __global__ __launch_bounds__(PRUNED_THREADS, 4) void k_search_pruned(PrunedArgs 
                 };
                 if (mc.gb_pow2) latency(std::true_type{});
                 else latency(std::false_type{});
+              }
             }
             // the other two keys: candidate by candidate, one key at a time
 #pragma unroll 1
@@ -585,12 +534,20 @@ __global__ __launch_bounds__(PRUNED_THREADS, 4) void k_search_pruned(PrunedArgs 
             up = bits <= __hip_atomic_fetch_min(my_hint, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (!up) best[my_j][lane % N_OBJ].p = inf;
         }
-        unsigned long long follow = __ballot(up);
-        // ---- positions of the others
-        while (follow) {
-            const uint32_t which = __builtin_amdgcn_readfirstlane((uint32_t)__ffsll((long long)follow) - 1u);
-            follow &= follow - 1;
-            const uint32_t j = m_first + (which / N_OBJ) * PRUNED_WAVES, o = which % N_OBJ;
+        // ---- positions of the others, dealt out to the waves: those of a wave's own problems can be many
+        // (a wave then worked ten times as long as the rest)
+        {
+            const unsigned long long follow = __ballot(up);
+            uint32_t at = 0;
+            if (lane == 0 && follow) at = __hip_atomic_fetch_add(&n_follow, (uint32_t)__popcll(follow), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            at = __builtin_amdgcn_readfirstlane(at) + (uint32_t)__popcll(follow & ((1ull << lane) - 1));
+            if (up) follow_list[at] = (unsigned char)(my_j * N_OBJ + lane % N_OBJ);
+        }
+        __syncthreads();
+        const uint32_t follows = __builtin_amdgcn_readfirstlane(n_follow);
+        for (uint32_t at = wave; at < follows; at += PRUNED_WAVES) {
+            const uint32_t which = __builtin_amdgcn_readfirstlane((uint32_t)follow_list[at]);
+            const uint32_t j = which / N_OBJ, o = which % N_OBJ;
             const PrunedMember mb = read_const<PrunedMember>(members + j * sizeof(PrunedMember));
             ClassBest b;
             b.p = uniform_f64(best[j][o].p); b.s = uniform_f64(best[j][o].s);
@@ -606,10 +563,21 @@ __global__ __launch_bounds__(PRUNED_THREADS, 4) void k_search_pruned(PrunedArgs 
                     rs[g] = row_side(mb.mc, lane < nt ? d : nothing_fits());
                 }
                 const TilingF v = this_tiling();
-                uint32_t code = 0xFFFFFFFFu;
-#pragma unroll 1
-                for (uint32_t c = 0; c < 9; ++c)
-                    each_class(v, X, mb.mc, rs, c, [&](uint32_t cls_code, double en, double) { code = en == b.p ? min(code, cls_code) : code; });
+                const StageTerms t = stage_terms(v, X, G.size, mb.mc);
+                const double dj = v.D[DJ];
+                const double e_rf1 = mb.mc.e_rf * __builtin_fma(dj, mb.rf_words[0], mb.rf_words[1]);
+                const double e_mac1 = mb.mc.e_mac * __builtin_fma(dj, mb.mac_ops[0], mb.mac_ops[1]);
+                uint32_t low[LEAST_CLASSES] = {9, 9, 9};     // (descending combinations: the last one met is the lowest)
+#pragma unroll
+                for (int c = 8; c >= 0; --c) {
+                    const double br = t.br1[c % 3] + t.br2[c / 3];
+                    low[0] = energy_of(mb.mc, rs[0], br, mb.e_rf0, mb.e_mac0) == b.p ? (uint32_t)c : low[0];
+                    low[1] = energy_of(mb.mc, rs[1], br, mb.e_rf0, mb.e_mac0) == b.p ? (uint32_t)c : low[1];
+                    low[2] = energy_of(mb.mc, rs[2], __builtin_fma(dj, t.br1[c % 3], t.br2[c / 3]), e_rf1, e_mac1) == b.p ? (uint32_t)c : low[2];
+                }
+                uint32_t code = low[2] < 9 ? 10u + 2u * low[2] : 0xFFFFFFFFu;
+                code = low[1] < 9 ? min(code, 9u + 2u * low[1]) : code;
+                code = low[0] < 9 ? low[0] : code;
                 b.code = __builtin_amdgcn_readfirstlane(wave_min_u32(code));
                 b.lanes = __ballot(code == b.code);
             }
@@ -627,7 +595,8 @@ __global__ __launch_bounds__(PRUNED_THREADS, 4) void k_search_pruned(PrunedArgs 
             }
         }
         m_lo = m_hi;
-        __syncthreads();                                      // the round's minima are free again
+        __syncthreads();                                      // the round's minima and its list are free again
+        if (threadIdx.x == 0) n_follow = 0;
     }
     // ---- the item's records
     for (uint32_t k = threadIdx.x; k < G.n_members * N_OBJ; k += PRUNED_THREADS)

@@ -267,4 +267,40 @@ static_assert(KEPT.n == KEPT_ALL, "the arrays are sized for the kept rows");
 
 constexpr LeastRows LEAST[LEAST_CLASSES] = {least_rows(0, 0), least_rows(0, 1), least_rows(1, 1)};
 
+// The same rows as places in the compact table (every one of them is among the kept rows, up to equal terms), class after
+// class, and how eight waves share them, each a piece of one class.
+constexpr int LEAST_ALL = LEAST[0].n + LEAST[1].n + LEAST[2].n, LEAST_WAVES = 8;
+struct alignas(32) LeastOffsets {
+    uint32_t off[LEAST_ALL][NSEL];           // byte offsets of the entries' lines
+    uint32_t lo[LEAST_WAVES], hi[LEAST_WAVES], cls[LEAST_WAVES];
+};
+constexpr LeastOffsets least_offsets()
+{
+    LeastOffsets o{};
+    const int pieces[LEAST_CLASSES] = {3, 2, 3};
+    uint32_t first = 0;
+    int wave = 0;
+    for (int c = 0; c < LEAST_CLASSES; ++c) {
+        const uint32_t n = (uint32_t)LEAST[c].n;
+        for (uint32_t i = 0; i < n; ++i)
+            for (int q = 0; q < NSEL; ++q) o.off[first + i][q] = KEPT.place[row_entry(LEAST[c].row[i], q)] * KEPT_LINE;
+        for (int k = 0; k < pieces[c]; ++k, ++wave) {
+            o.lo[wave] = first + n * k / pieces[c];
+            o.hi[wave] = first + n * (k + 1) / pieces[c];
+            o.cls[wave] = (uint32_t)c;
+        }
+        first += n;
+    }
+    return o;
+}
+constexpr LeastOffsets LEAST_OFF = least_offsets();
+constexpr bool least_is_staged()
+{
+    for (int i = 0; i < LEAST_ALL; ++i)
+        for (int q = 0; q < NSEL; ++q)
+            if (LEAST_OFF.off[i][q] >= KEPT.used * KEPT_LINE) return false;
+    return true;
+}
+static_assert(least_is_staged(), "the compact table has all their entries");
+
 }  // namespace mmee
