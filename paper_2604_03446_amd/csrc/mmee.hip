@@ -1006,7 +1006,8 @@ void shape_constants(const DivTable &dv, double (&extent)[4], double (&size)[5])
 
 // Groups of problems with one shape, laid out as the kernel reads them.
 struct PrunedLayout {
-    std::vector<unsigned char> desc;
+    unsigned char *desc = nullptr;          // room for `bytes`
+    size_t bytes = 0;
     uint32_t n_groups = 0, n_members = 0, members_off = 0, n_items = 0;
     uint64_t n_keys = 0;    // records of all its items
 };
@@ -1141,24 +1142,35 @@ void keep_shared(const std::vector<PrunedEntry> &entries, const std::vector<uint
     else if (mixed_us < every_us) slices.erase(std::remove_if(slices.begin(), slices.end(), [&](const PrunedSlice &sl) { return !is_large(sl); }), slices.end());
 }
 
+size_t up16(size_t x) { return (x + 15) & ~(size_t)15; }
+
+// bytes of the descriptions, and where their parts begin
+size_t pruned_bytes(const std::vector<PrunedEntry> &entries, const std::vector<uint32_t> &order, const std::vector<PrunedSlice> &slices,
+                    size_t &members_off, size_t &caps_off, size_t &list_off)
+{
+    size_t n_members = 0, n_caps = 0, n_list = 0;
+    for (const PrunedSlice &sl : slices) {
+        n_members += sl.hi - sl.lo;
+        n_caps += sl.n_caps;
+        n_list += list_length(entries[order[sl.lo]].plan->dv);
+    }
+    members_off = up16(sizeof(PrunedGroup) * slices.size());
+    caps_off = up16(members_off + sizeof(PrunedMember) * n_members);
+    list_off = up16(caps_off + sizeof(double) * n_caps);
+    return up16(list_off + sizeof(uint32_t) * n_list);
+}
+
+// ... written to out.desc
 void pruned_layout(const std::vector<PrunedEntry> &entries, const std::vector<uint32_t> &order, const std::vector<PrunedSlice> &slices,
                    PrunedLayout &out)
 {
-    auto up16 = [](size_t x) { return (x + 15) & ~(size_t)15; };
-    size_t n_members = 0, n_caps = 0, n_list = 0;
-    for (const PrunedSlice &sl : slices) {
-        const DivTable &dv = entries[order[sl.lo]].plan->dv;
-        n_members += sl.hi - sl.lo;
-        n_caps += sl.n_caps;
-        n_list += list_length(dv);
-    }
-    const size_t members_off = up16(sizeof(PrunedGroup) * slices.size());
-    size_t caps_off = up16(members_off + sizeof(PrunedMember) * n_members), list_off = up16(caps_off + sizeof(double) * n_caps);
-    out.desc.resize(up16(list_off + sizeof(uint32_t) * n_list));
+    size_t members_off, caps_off, list_off, n_members = 0;
+    (void)pruned_bytes(entries, order, slices, members_off, caps_off, list_off);
+    for (const PrunedSlice &sl : slices) n_members += sl.hi - sl.lo;
     out.n_groups = (uint32_t)slices.size();
     out.n_members = (uint32_t)n_members;
     out.members_off = (uint32_t)members_off;
-    unsigned char *base = out.desc.data();
+    unsigned char *base = out.desc;
     PrunedGroup *groups = reinterpret_cast<PrunedGroup *>(base);
     PrunedMember *members = reinterpret_cast<PrunedMember *>(base + members_off);
     uint32_t item = 0, member = 0;
@@ -1219,8 +1231,8 @@ int launch_pruned(const PrunedLayout &l, const unsigned char *desc_dev, Key *key
     std::memset(&a, 0, offsetof(PrunedArgs, inl));
     a.desc = desc_dev;
     if (!desc_dev) {
-        if (l.desc.size() > sizeof(a.inl)) return MMEE_EINVAL;
-        std::memcpy(a.inl, l.desc.data(), l.desc.size());
+        if (l.bytes > sizeof(a.inl)) return MMEE_EINVAL;
+        std::memcpy(a.inl, l.desc, l.bytes);
     }
     a.n_groups = l.n_groups; a.n_items = l.n_items;
     a.members_off = l.members_off;
@@ -1262,16 +1274,18 @@ int enqueue_pruned(const std::vector<PrunedEntry> &entries, const std::vector<ui
     for (const PrunedSlice &sl : slices) items += (entries[order[sl.lo]].plan->T + PRUNED_TC - 1) / PRUNED_TC;
     if (items > 0x7fffffffull) return MMEE_EINVAL;
     PrunedLayout l;
+    size_t members_off, caps_off, list_off;
+    l.bytes = pruned_bytes(entries, order, slices, members_off, caps_off, list_off);
+    const bool inside = l.bytes <= (size_t)PRUNED_INLINE;
+    alignas(16) unsigned char small[PRUNED_INLINE];
+    int rc = inside ? MMEE_OK : ensure_desc(l.bytes);
+    if (rc) return rc;
+    l.desc = inside ? small : S.desc_host;
     pruned_layout(entries, order, slices, l);
-    const bool inside = l.desc.size() <= (size_t)PRUNED_INLINE;
-    int rc = inside ? MMEE_OK : ensure_desc(l.desc.size());
-    if (!rc) rc = ensure_block_records((size_t)l.n_keys * sizeof(Key));
+    rc = ensure_block_records((size_t)l.n_keys * sizeof(Key));
     if (rc) return rc;
     HIP_TRY(hipEventRecord(S.events[2 * ev_slot], S.stream));
-    if (!inside) {
-        std::memcpy(S.desc_host, l.desc.data(), l.desc.size());
-        HIP_TRY(hipMemcpyAsync(S.desc_dev, S.desc_host, l.desc.size(), hipMemcpyHostToDevice, S.stream));
-    }
+    if (!inside) HIP_TRY(hipMemcpyAsync(S.desc_dev, S.desc_host, l.bytes, hipMemcpyHostToDevice, S.stream));
     rc = launch_pruned(l, inside ? nullptr : S.desc_dev, static_cast<Key *>(S.block_records));
     if (rc) return rc;
     HIP_TRY(hipEventRecord(S.events[2 * ev_slot + 1], S.stream));
@@ -1602,28 +1616,36 @@ int mmee_chain_search_many(const mmee_chain *w, const mmee_hw *hw, const int *ob
     if (rc) return rc;
 
     // group neighbouring entries that describe the same problem into one pass
+    struct Stretch { uint32_t first, n; int mask; };
     struct Pass {
         uint32_t first, n; int mask; Plan plan; int rc; uint64_t evaluated; bool unproven;
-        size_t ev_slot = 0;
+        size_t ev_slot;
+        Pass(const Stretch &st) : first(st.first), n(st.n), mask(st.mask), evaluated(0), unproven(false), ev_slot(0) {}
     };
-    std::vector<Pass> passes;
+    std::vector<Stretch> stretches;
     std::vector<int> codes(count, MMEE_OK);
     for (uint32_t a = 0; a < count;) {
-        Pass ps;
-        ps.first = a; ps.n = 0; ps.mask = 0; ps.evaluated = 0; ps.unproven = false;
-        ps.rc = make_plan(w + a, hw + a, ps.plan);
+        Stretch st{a, 0, 0};
         uint32_t b = a;
         while (b < count && same_problem(w[a], hw[a], w[b], hw[b])) {
             int o = objectives[b];
             if (o < 0 || o >= N_OBJ) codes[b] = MMEE_EINVAL;     // this entry only; its neighbours still run
-            else if (ps.mask & (1 << o)) break;      // same objective twice: start a new pass
-            else ps.mask |= 1 << o;
-            ++b; ++ps.n;
+            else if (st.mask & (1 << o)) break;      // same objective twice: start a new pass
+            else st.mask |= 1 << o;
+            ++b; ++st.n;
         }
-        if (ps.n == 0) { ps.n = 1; b = a + 1; }
-        if (ps.mask == 0 && !ps.rc) ps.rc = MMEE_EINVAL;         // no valid objective in the group
-        passes.push_back(ps);
+        if (st.n == 0) { st.n = 1; b = a + 1; }
+        stretches.push_back(st);
         a = b;
+    }
+    // (a plan holds its divisor lists, 4 KiB: made in place, once their number is known)
+    std::vector<Pass> passes;
+    passes.reserve(stretches.size());
+    for (const Stretch &st : stretches) {
+        passes.emplace_back(st);
+        Pass &ps = passes.back();
+        ps.rc = make_plan(w + st.first, hw + st.first, ps.plan);
+        if (ps.mask == 0 && !ps.rc) ps.rc = MMEE_EINVAL;         // no valid objective in the group
     }
     rc = ensure_slots(passes.size());
     if (rc) return rc;
@@ -1713,11 +1735,20 @@ int mmee_chain_search_many(const mmee_chain *w, const mmee_hw *hw, const int *ob
     }
     const double seconds = now_seconds() - t_start;
     int first_bad = MMEE_OK;
+    size_t timed = (size_t)-1;
+    float timed_ms = 0.f;
     for (size_t s = 0; s < passes.size(); ++s) {
         Pass &ps = passes[s];
         float ms = 0.f;
         const size_t ev = ps.ev_slot;                        // a pass reports the device time of the launches it shared
-        if (ps.rc == MMEE_OK) (void)hipEventElapsedTime(&ms, S.events[2 * ev], S.events[2 * ev + 1]);
+        if (ps.rc == MMEE_OK) {
+            if (ev != timed) {                               // (asked for once, not for each of hundreds that shared them)
+                timed_ms = 0.f;
+                (void)hipEventElapsedTime(&timed_ms, S.events[2 * ev], S.events[2 * ev + 1]);
+                timed = ev;
+            }
+            ms = timed_ms;
+        }
         for (uint32_t a = ps.first; a < ps.first + ps.n; ++a) {
             int code = codes[a] ? codes[a] : ps.rc;
             if (code == MMEE_OK)
