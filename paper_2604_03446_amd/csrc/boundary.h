@@ -17,65 +17,11 @@ struct TilingF {                             // boundary vector of one tiling (E
     double G[4], D[4];
 };
 
-// digit q of tiling t: the intra-tile size x_G and the inter-tile count x_D of dimension q
-__device__ __forceinline__ void tiling_dim(const DivTable &dv, uint32_t t, int q, double &G, double &D)
-{
-    uint32_t radix = 1;
-    for (int k = 0; k < q; ++k) radix *= dv.ndiv[k];
-    const uint32_t g = dv.div[q][(t / radix) % dv.ndiv[q]];
-    G = (double)g;
-    D = (double)(dv.X[q] / g);
-}
-
-__device__ __forceinline__ TilingF tiling_of(const DivTable &dv, uint32_t t)
-{
-    TilingF v;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) tiling_dim(dv, t, q, v.G[q], v.D[q]);
-    return v;
-}
-
 // tile_X * {1, d0, d1, d0 d1}; option 4 = the operand takes no space
 __device__ __forceinline__ double footprint(double tile, double d0, double d1, uint32_t opt)
 {
     const double v = tile * ((opt & 1) ? d0 : 1.0) * ((opt & 2) ? d1 : 1.0);
     return opt >= 4 ? 0.0 : v;
-}
-
-// entry `ent` of the per-tiling table (layout.h), bh = B*H for the scaled DRAM terms, 1 for the raw ones
-__device__ __forceinline__ double table_entry(uint32_t ent, const TilingF &v, const double X[4], double bh)
-{
-    const double tA = v.G[DI] * v.G[DK], tB = v.G[DK] * v.G[DL], tC = v.G[DI] * v.G[DL], tD = v.G[DL] * v.G[DJ],
-                 tE = v.G[DI] * v.G[DJ];
-    if (ent < ENT_BS_DE) {                                   // BS_A[a] + BS_B[b]
-        const uint32_t k = ent - ENT_BS_AB;
-        return footprint(tA, v.D[DI], v.D[DK], k & 3) + footprint(tB, v.D[DK], v.D[DL], k >> 2);
-    }
-    if (ent < ENT_RET_DE) {                                  // BS_D[a] + BS_E[b]
-        const uint32_t k = ent - ENT_BS_DE;
-        return footprint(tD, v.D[DL], v.D[DJ], k & 3) + footprint(tE, v.D[DI], v.D[DJ], k >> 2);
-    }
-    if (ent < ENT_RET_AB) {                                  // tau_D BS_D[a] + tau_E BS_E[b]
-        const uint32_t k = ent - ENT_RET_DE;
-        return footprint(tD, v.D[DL], v.D[DJ], k % 5) + footprint(tE, v.D[DI], v.D[DJ], k / 5);
-    }
-    if (ent < ENT_BS_C) {                                    // tau_A BS_A[a] + tau_B BS_B[b]
-        const uint32_t k = ent - ENT_RET_AB;
-        return footprint(tA, v.D[DI], v.D[DK], k % 5) + footprint(tB, v.D[DK], v.D[DL], k / 5);
-    }
-    if (ent < ENT_DA_AB) return footprint(tC, v.D[DI], v.D[DL], ent - ENT_BS_C);
-    if (ent < ENT_DA_DE) {                                   // |A| {1, l_D, j_D, l_D j_D} + |B| {1, i_D, j_D, i_D j_D}
-        const uint32_t k = ent - ENT_DA_AB;
-        return bh * (footprint(X[DI] * X[DK], v.D[DL], v.D[DJ], k & 3) + footprint(X[DK] * X[DL], v.D[DI], v.D[DJ], k >> 2));
-    }
-    if (ent < ENT_DA_C) {                                    // |D| {1, i_D, k_D, i_D k_D} + |E| {1, k_D, l_D, k_D l_D}
-        const uint32_t k = ent - ENT_DA_DE;
-        return bh * (footprint(X[DL] * X[DJ], v.D[DI], v.D[DK], k & 3) + footprint(X[DI] * X[DJ], v.D[DK], v.D[DL], k >> 2));
-    }
-    // unfused C: spilled by Op1, fetched by Op2, plus one softmax pass over S and P; option 4: fused, no traffic
-    const uint32_t c = ent - ENT_DA_C;
-    const double spill = (c & 1) ? v.D[DK] : 1.0, fetch = (c & 2) ? v.D[DJ] : 1.0;
-    return c >= 4 ? 0.0 : bh * (X[DI] * X[DL]) * (spill + fetch + 2.0);
 }
 
 // ceil(a / b) for a whole number 1 <= a < 2^32 held in fp64, given 1 / b rounded once (ModelConst)
@@ -137,32 +83,40 @@ __device__ __forceinline__ ComboTerms combo_terms(const TilingF &v, const double
     return combo_terms_from(v, X, mc, r, br1, cy1, br2, cy2);
 }
 
-// One candidate, complete, from the problem description alone: the winner's cost record (Sec. V-D's
-// order of the energy terms, as eval_candidate).
-__device__ __forceinline__ void eval_candidate_direct(const uint4 *enc, const DivTable &dv, const ModelConst &mc, uint64_t idx,
+// The cost record of one decoded candidate (Sec. V-D's order of the energy terms, as eval_candidate).  Each selector names an
+// entry of a known kind, so an entry is two footprints and a sum: a switch over all kinds per selector, and the
+// tiling's digits once for the cost and once for the mapping, were three times the instructions, which a winner's lone thread
+// waits for one cache line after the other.
+__device__ __forceinline__ void eval_candidate_direct(const uint4 *enc, const DivTable &dv, const ModelConst &mc, const mmee_mapping &m,
                                                       mmee_cost &c)
 {
-    const uint32_t t = (uint32_t)(idx % mc.T), row = (uint32_t)(idx / mc.T);
-    const uint32_t lo = row % 15000;
-    uint32_t hi = row / 15000;
-    const uint32_t r = hi & 1; hi >>= 1;
-    const uint32_t s1 = hi % 3; hi /= 3;
-    const uint32_t s2 = hi % 3, f = hi / 3;
-    const uint4 e = enc[lo + ROWS_PER_GROUP * (r + 2 * f)];
+    uint32_t row, t;
+    split_index(m.idx, mc.T, row, t);
+    const uint32_t r = m.recompute, s1 = m.stat1, s2 = m.stat2, f = m.fused;
+    const uint4 e = enc[row % ROWS_PER_GROUP + ROWS_PER_GROUP * (r + 2 * f)];
     if (!(sel_of(e, ROW_FLAGS) & 1)) {
         c.bs_words = c.da_words = c.br_words = c.mac_total = c.comp_cycles = 0;
         c.energy_pj = pos_inf(); c.latency_cycles = pos_inf();
         c.valid = 0; c.reason = 1;
         return;
     }
-    const TilingF v = tiling_of(dv, t);
-    const double X[4] = {(double)dv.X[0], (double)dv.X[1], (double)dv.X[2], (double)dv.X[3]};
-    double w[NSEL];
+    TilingF v;
 #pragma unroll
-    for (int k = 0; k < NSEL; ++k) w[k] = table_entry(sel_of(e, k), v, X, 1.0);
+    for (int q = 0; q < 4; ++q) { v.G[q] = (double)m.xG[q]; v.D[q] = (double)m.xD[q]; }
+    const double X[4] = {(double)dv.X[0], (double)dv.X[1], (double)dv.X[2], (double)dv.X[3]};
+    // layout.h: the pairs' options are packed by fours, those of the retained ones by fives (4: not retained)
+    auto bs_of = [&](int one, int two, uint32_t opt) { return footprint(v.G[one] * v.G[two], v.D[one], v.D[two], opt); };
+    auto da_of = [&](int own0, int own1, int n0, int n1, uint32_t opt) { return footprint(X[own0] * X[own1], v.D[n0], v.D[n1], opt); };
+    const uint32_t ab = sel_of(e, 0) - ENT_BS_AB, ret_de = sel_of(e, 1) - ENT_RET_DE, bs_c = sel_of(e, 2) - ENT_BS_C, de = sel_of(e, 3) - ENT_BS_DE,
+                   ret_ab = sel_of(e, 4) - ENT_RET_AB, da_ab = sel_of(e, 5) - ENT_DA_AB, da_de = sel_of(e, 6) - ENT_DA_DE, da_c = sel_of(e, 7) - ENT_DA_C;
+    const double w_c = bs_of(DI, DL, bs_c);
+    const double bs1 = bs_of(DI, DK, ab & 3) + bs_of(DK, DL, ab >> 2) + w_c + (bs_of(DL, DJ, ret_de % 5) + bs_of(DI, DJ, ret_de / 5));
+    const double bs2 = bs_of(DL, DJ, de & 3) + bs_of(DI, DJ, de >> 2) + w_c + (bs_of(DI, DK, ret_ab % 5) + bs_of(DK, DL, ret_ab / 5));
+    const double through = da_c >= 4 ? 0.0 : X[DI] * X[DL] * (((da_c & 1) ? v.D[DK] : 1.0) + ((da_c & 2) ? v.D[DJ] : 1.0) + 2.0);
+    const double bs = fmax(bs1, bs2);                                    // Eq. (1), (2), (4)
+    const double da = da_of(DI, DK, DL, DJ, da_ab & 3) + da_of(DK, DL, DI, DJ, da_ab >> 2) +
+                      (da_of(DL, DJ, DI, DK, da_de & 3) + da_of(DI, DJ, DK, DL, da_de >> 2)) + through;      // Eq. (7)
     const ComboTerms ct = combo_terms(v, X, mc, r, s1, s2);
-    const double bs = fmax(w[0] + w[2] + w[1], w[3] + w[2] + w[4]);     // Eq. (1), (2), (4)
-    const double da = w[5] + w[6] + w[7];                                // Eq. (7)
     c.bs_words = (uint64_t)bs; c.da_words = (uint64_t)da; c.br_words = (uint64_t)ct.br;
     c.mac_total = (uint64_t)ct.mac; c.comp_cycles = (uint64_t)ct.cyc;
     if (bs > mc.cap_words) {
@@ -288,8 +242,8 @@ __device__ __forceinline__ void winner_record(const uint4 *enc, const DivTable &
 {
     __builtin_memset(&res, 0, sizeof(res));
     if (k.p < pos_inf()) {
-        eval_candidate_direct(enc, dv, mc, k.idx, res.cost);
         decode_candidate(dv, mc.T, k.idx, res.best);
+        eval_candidate_direct(enc, dv, mc, res.best, res.cost);
     } else {
         res.cost.energy_pj = pos_inf(); res.cost.latency_cycles = pos_inf();
         res.best.idx = ~0ull;
