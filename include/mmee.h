@@ -102,7 +102,8 @@ typedef struct mmee_result {
     uint64_t space;             /* size of the index space                                 */
     uint64_t evaluated;         /* candidates whose cost the search actually formed        */
     double seconds;             /* host wall time of the call (upload, kernels, readback)  */
-    double kernel_seconds;      /* device time of the search kernel alone (HIP events)     */
+    double kernel_seconds;      /* device time of the search's kernels (HIP events; one pruned
+                                   search or front by itself: the device's clock)          */
 } mmee_result;
 
 /* Counts of the offline stage (Sec. VI-B): loop-order x buffering-level rows per

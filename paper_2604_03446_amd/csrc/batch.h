@@ -67,6 +67,8 @@ struct BatchArgs {
     FinalRecord *final_out;                  // [result slot][N_OBJ]
     mmee_result *packed;                     // not null: the launch's one key of its one problem goes here, as a result record
     uint64_t space, evaluated;               // ... with these
+    Done *done;                              // [N_OBJ] not null: the host looks here for the launch's one problem
+    uint64_t number, *begin;                 // the call's number; when the search began (device memory)
     BatchInline inl;                         // inl.on: the launch's only problem is here, prob and first_items are unused
 };
 
@@ -106,6 +108,7 @@ __global__ __launch_bounds__(BATCH_THREADS, 4) void k_search_batch(BatchArgs a)
     ConstPtr<u32x8> row_offs = (ConstPtr<u32x8>)&kept_dev.off[0][0];
 
     const uint32_t item_lo = blockIdx.x * a.per_block, item_hi = min(item_lo + a.per_block, a.n_items);
+    if (a.done && blockIdx.x == 0 && threadIdx.x == 0) *a.begin = wall_clock64();
     if (item_lo >= item_hi) return;
     // the first item's problem: the last p with first_items[p] <= item; later items move p on
     const BatchProblem *probs;
@@ -490,6 +493,7 @@ __global__ __launch_bounds__(256) void k_batch_finish(BatchArgs a)
             *a.packed = res;
         } else
             write_record(a.final_out + (uint64_t)head_s.slot * N_OBJ + o, k, res);
+        if (a.done) say_done(a.done + o, a.number, a.begin);
     }
 }
 

@@ -249,6 +249,12 @@ __device__ __forceinline__ void winner_record(const uint4 *enc, const DivTable &
         res.best.idx = ~0ull;
     }
 }
+// Behind a record's last store, by the thread that made it (or one that has met all that did, each past a system-wide fence).
+__device__ __forceinline__ void say_done(Done *done, uint64_t number, const uint64_t *begin)
+{
+    done->ticks = wall_clock64() - *begin;
+    __hip_atomic_store(&done->number, number, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 __device__ __forceinline__ void write_record(FinalRecord *fr, const Key &k, const mmee_result &res)
 {
     fr->key = k;

@@ -59,6 +59,8 @@ struct FrontArgs {
     const uint4 *enc;
     FinalRecord *out;                        // [capacity], ascending
     uint32_t *n_out;                         // points of the front; TOO_MANY: walk it
+    Done *done;                              // where the host looks for the call's end
+    uint64_t number, *begin;                 // the call's number; when it began (device memory)
     uint32_t list[FRONT_DIVS];
 };
 
@@ -319,6 +321,7 @@ __global__ __launch_bounds__(PRUNED_THREADS, BS_DA ? 2 : 4) void k_front_points(
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const ModelConst &mc = a.mc;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *a.begin = wall_clock64();
     ConstBytes args = (ConstBytes)__builtin_amdgcn_kernarg_segment_ptr();
     div_lds[threadIdx.x] = ((ConstPtr<uint32_t>)(args + offsetof(FrontArgs, list)))[threadIdx.x];
     if (threadIdx.x == 0) filled = 0;
@@ -602,7 +605,10 @@ __global__ __launch_bounds__(MERGE_THREADS) void k_front_merge(FrontArgs a)
         fits = at == n_list || n < FRONT_POINTS;
     }
     if (!fits) {
-        if (threadIdx.x == 0) *a.n_out = TOO_MANY;
+        if (threadIdx.x == 0) {
+            *a.n_out = TOO_MANY;
+            say_done(a.done, a.number, a.begin);
+        }
         return;
     }
     if (n <= MERGE_THREADS) n = front_by_pairs<MERGE_THREADS>(points, keep, &n_left, n);
@@ -617,7 +623,12 @@ __global__ __launch_bounds__(MERGE_THREADS) void k_front_merge(FrontArgs a)
         winner_record(a.enc, dv_s, a.mc, me, res);
         write_record(a.out + place, me, res);
     }
-    if (threadIdx.x == 0) *a.n_out = n;
+    __threadfence_system();
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        *a.n_out = n;
+        say_done(a.done, a.number, a.begin);
+    }
 }
 
 }  // namespace mmee

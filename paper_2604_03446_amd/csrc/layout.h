@@ -110,6 +110,11 @@ struct Key {            // lexicographic objective key, lowest index wins ties
     uint64_t idx;
 };
 
+// How a call's last kernel says that its records are complete, in pinned host memory: the call's number, and how long its
+// kernels ran.  A host that looks for the number sees the records as soon as they are there; an end event, a synchronisation and
+// the start event are three more commands on the stream and an interrupt.
+struct Done { uint64_t number, ticks; };
+
 struct FinalRecord {    // what a search leaves on the device for the host to read
     Key key;
     uint64_t cost[8];   // mmee_cost image

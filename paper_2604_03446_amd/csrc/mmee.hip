@@ -120,6 +120,11 @@ struct State {
     void *block_records = nullptr;              // what the blocks of a pruned search leave for the reduction
     size_t block_records_cap = 0;
     unsigned long long *pruned_hints = nullptr;
+    // what a short call waits for instead of the stream (Done): one per key in pinned memory, the number of the last such call,
+    // the device's clock when its kernels began, and that clock's rate
+    Pinned done;
+    uint64_t call_number = 0, *call_begin = nullptr;
+    double clock_hz = 1e8;
 } S;
 
 // The device buffers one search pass works in.  The allocating entry points fill this from the
@@ -326,6 +331,9 @@ int ensure_ready()
         HIP_TRY(hipGetDevice(&dev));
         HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
         S.resident_blocks = (uint32_t)std::max(cus, 1) * BLOCKS_PER_CU;
+        int khz = 0;
+        HIP_TRY(hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev));
+        if (khz > 0) S.clock_hz = 1e3 * khz;
         // MMEE_RESIDENT_BLOCKS (read once, an even number from 2 up to what the chip holds): fewer persistent
         // blocks, i.e. another split of the work over blocks and another order of the reduction.  Results do
         // not depend on it; it exists so that a test can show that.
@@ -759,6 +767,45 @@ static_assert(sizeof(BatchArgs) <= 4096, "kernel arguments are limited to 4 KiB"
 
 // ---- batched search over the pruned rows -----------------------------------------------------
 
+// The next call that ends by saying so: its place, its number.
+int begin_signalled(Done *&done, uint64_t &number, uint64_t *&begin)
+{
+    const bool first = !S.done.host;
+    HIP_TRY(ensure_pinned(HipPinned{}, S.done, sizeof(Done) * N_OBJ));
+    if (first) std::memset(S.done.host, 0, sizeof(Done) * N_OBJ);
+    if (!S.call_begin) HIP_TRY(hipMalloc(&S.call_begin, sizeof(uint64_t)));
+    done = reinterpret_cast<Done *>(S.done.map);
+    number = ++S.call_number;
+    begin = S.call_begin;
+    return MMEE_OK;
+}
+
+// Until the records of the last signalled call are there (its keys: mask), and how long its kernels ran.  What does not come
+// within 20 ms (a long search, work ahead of it on the caller's stream, an error) is waited for as any other command is.
+int wait_signalled(int mask, double &seconds)
+{
+    const Done *done = reinterpret_cast<const Done *>(S.done.host);
+    const auto give_up = std::chrono::steady_clock::now() + std::chrono::milliseconds(20);
+    seconds = 0.0;
+    bool synchronised = false;
+    for (int o = 0; o < N_OBJ; ++o) {
+        if (!((mask >> o) & 1)) continue;
+        for (uint32_t look = 0; __atomic_load_n(&done[o].number, __ATOMIC_ACQUIRE) != S.call_number; ++look) {
+            if (synchronised) {
+                std::snprintf(g_last_error, sizeof(g_last_error), "a search ended without its records");
+                return MMEE_EDEVICE;
+            }
+            if (look % 256 == 255 && std::chrono::steady_clock::now() > give_up) {
+                HIP_TRY(hipStreamSynchronize(S.stream));
+                synchronised = true;
+            }
+            __builtin_ia32_pause();
+        }
+        seconds = std::max(seconds, (double)done[o].ticks / S.clock_hz);
+    }
+    return MMEE_OK;
+}
+
 // masks the batched kernel is built for; other key sets take the per-problem kernels
 bool batch_mask(int mask) { return mask == 1 || mask == 2 || mask == 3 || mask == 4 || mask == 8; }
 
@@ -876,9 +923,11 @@ struct BatchEntry {
 };
 
 // Enqueue the entries (all pruned searches) as few launches as their kernel variants allow: one per
-// (key set, exact DRAM constant, regrouped) combination present.  Events of slot `ev_slot` bracket it all.
-int enqueue_batches(std::vector<BatchEntry> &entries, uint32_t flags, size_t ev_slot)
+// (key set, exact DRAM constant, regrouped) combination present.  Events of slot `ev_slot` bracket it all, but for a lone
+// problem that rides in the arguments: `signalled`, it is waited for with wait_signalled.
+int enqueue_batches(std::vector<BatchEntry> &entries, uint32_t flags, size_t ev_slot, bool &signalled)
 {
+    signalled = false;
     if (entries.empty()) return MMEE_OK;
     struct Variant { int mask; bool fast, regroup; std::vector<size_t> members; uint64_t items = 0; uint32_t split = 1; };
     std::vector<Variant> variants;
@@ -943,7 +992,14 @@ int enqueue_batches(std::vector<BatchEntry> &entries, uint32_t flags, size_t ev_
         }
         launches.push_back(L);
     }
-    HIP_TRY(hipEventRecord(S.events[2 * ev_slot], S.stream));
+    Done *done = nullptr;
+    uint64_t number = 0, *begin = nullptr;
+    signalled = entries.size() == 1 && launches[0].in_args;
+    if (signalled) {
+        rc = begin_signalled(done, number, begin);
+        if (rc) return rc;
+    } else
+        HIP_TRY(hipEventRecord(S.events[2 * ev_slot], S.stream));
     if (off) HIP_TRY(hipMemcpyAsync(S.batch_dev, S.batch_host, off, hipMemcpyHostToDevice, S.stream));
     for (size_t k = 0; k < variants.size(); ++k) {
         const Variant &v = variants[k];
@@ -963,13 +1019,14 @@ int enqueue_batches(std::vector<BatchEntry> &entries, uint32_t flags, size_t ev_
         set_batch_tasks(a, v.split);
         a.item_keys = S.item_keys + N_OBJ * L.item0;
         a.final_out = S.final_map;
+        a.done = done; a.number = number; a.begin = begin;
         // persistent blocks, two per CU, each with a contiguous range of the items
         dim3 grid((uint32_t)std::min<uint64_t>(L.n_items, (uint64_t)S.resident_blocks));
         a.per_block = (uint32_t)((L.n_items + grid.x - 1) / grid.x);
         rc = launch_batch(v.mask, v.fast, v.regroup, grid, a);
         if (rc) return rc;
     }
-    HIP_TRY(hipEventRecord(S.events[2 * ev_slot + 1], S.stream));
+    if (!signalled) HIP_TRY(hipEventRecord(S.events[2 * ev_slot + 1], S.stream));
     return MMEE_OK;
 }
 
@@ -1320,7 +1377,7 @@ static_assert(sizeof(FrontArgs) <= 4096, "kernel arguments are limited to 4 KiB"
 constexpr size_t FRONT_N_AT = sizeof(FinalRecord) * FRONT_POINTS;     // where S.front has the number of its records
 
 // The front in two launches; its records and their number land in S.front (TOO_MANY: something outgrew its room,
-// walk the front).  Events of slot 0 bracket it.
+// walk the front).  Waited for with wait_signalled, as key 0.
 int enqueue_front(const Plan &p, bool bs_da, uint32_t capacity)
 {
     if (!S.front_points) HIP_TRY(hipMalloc(&S.front_points, sizeof(Key) * FRONT_BLOCKS * FRONT_BLOCK));
@@ -1361,7 +1418,10 @@ int enqueue_front(const Plan &p, bool bs_da, uint32_t capacity)
         a.step0 = (int32_t)((uint32_t)(bits >> 32) >> a.step_shift);
     }
     const uint32_t n_blocks = (uint32_t)((p.T + PRUNED_TC - 1) / PRUNED_TC) * (bs_da ? FRONT_SPLIT : 1);
-    HIP_TRY(hipEventRecord(S.events[0], S.stream));
+    {
+        const int rc = begin_signalled(a.done, a.number, a.begin);
+        if (rc) return rc;
+    }
     if (!S.front_clean) {
         hipLaunchKernelGGL(k_fill_words64, dim3((FRONT_STEPS + 255) / 256), dim3(256), 0, S.stream, S.front_stairs, (uint64_t)FRONT_STEPS, INF_BITS);
         hipLaunchKernelGGL(k_clear_words, dim3(1), dim3(64), 0, S.stream, S.front_counts, 2u);
@@ -1373,7 +1433,6 @@ int enqueue_front(const Plan &p, bool bs_da, uint32_t capacity)
     hipLaunchKernelGGL(k_front_merge, dim3(1), dim3(MERGE_THREADS), 0, S.stream, a);
     HIP_TRY(hipGetLastError());
     S.front_clean = true;
-    HIP_TRY(hipEventRecord(S.events[1], S.stream));
     return MMEE_OK;
 }
 
@@ -1653,7 +1712,11 @@ int mmee_chain_search_many(const mmee_chain *w, const mmee_hw *hw, const int *ob
     // the launch only (enqueue_batches), where the kernel is built for their key set.  Everything else goes
     // problem by problem.  `round_flags` adds MMEE_SEARCH_ORDERED_SUM on the second round, which repeats what the
     // first could not prove.
+    double signalled_seconds = -1.0;                         // device time of a search that said when it was done, and whose
+    size_t signalled_ev = 0;
     auto run_round = [&](uint32_t round_flags, bool only_unproven) -> int {
+        bool signalled = false;
+        bool others = false;                                 // anything beside the batched searches in the stream
         std::vector<PrunedEntry> pruned;
         std::vector<uint32_t> order;
         std::vector<PrunedSlice> slices;                     // the groups that share more than launches
@@ -1686,18 +1749,21 @@ int mmee_chain_search_many(const mmee_chain *w, const mmee_hw *hw, const int *ob
                 batch_pass.push_back(s);
             } else {
                 bool unproven = false;
+                others = true;
                 ps.rc = enqueue_search(ps.plan, ps.mask, round_flags, s, &ps.evaluated, nullptr, true, false,
                                        only_unproven ? nullptr : &unproven);
                 ps.unproven = unproven;
             }
         }
         if (!slices.empty()) {
+            others = true;
             const int src = enqueue_pruned(pruned, order, slices, slice_ev);
             for (size_t s = 0; s < passes.size(); ++s)
                 if (in_slice[s]) passes[s].rc = src;
         }
         if (!batch.empty()) {
-            int brc = enqueue_batches(batch, round_flags, batch_pass[0]);
+            int brc = enqueue_batches(batch, round_flags, batch_pass[0], signalled);
+            if (brc) signalled = false;
             for (size_t k = 0; k < batch.size(); ++k) {
                 Pass &ps = passes[batch_pass[k]];
                 ps.rc = brc;
@@ -1706,7 +1772,11 @@ int mmee_chain_search_many(const mmee_chain *w, const mmee_hw *hw, const int *ob
                 ps.ev_slot = batch_pass[0];
             }
         }
+        signalled_seconds = -1.0;
+        if (signalled) signalled_ev = batch_pass[0];
+        if (signalled && !others) return wait_signalled(batch[0].mask, signalled_seconds);
         HIP_TRY(hipStreamSynchronize(S.stream));
+        if (signalled) return wait_signalled(batch[0].mask, signalled_seconds);
         return MMEE_OK;
     };
     rc = run_round(flags, false);
@@ -1741,7 +1811,9 @@ int mmee_chain_search_many(const mmee_chain *w, const mmee_hw *hw, const int *ob
         Pass &ps = passes[s];
         float ms = 0.f;
         const size_t ev = ps.ev_slot;                        // a pass reports the device time of the launches it shared
-        if (ps.rc == MMEE_OK) {
+        if (ps.rc == MMEE_OK && signalled_seconds >= 0.0 && ev == signalled_ev) {
+            ms = (float)(signalled_seconds * 1e3);
+        } else if (ps.rc == MMEE_OK) {
             if (ev != timed) {                               // (asked for once, not for each of hundreds that shared them)
                 timed_ms = 0.f;
                 (void)hipEventElapsedTime(&timed_ms, S.events[2 * ev], S.events[2 * ev + 1]);
@@ -1799,18 +1871,18 @@ static int walk_front(const mmee_chain *w, const mmee_hw *hw, bool bs_da, uint32
     if (!(flags & MMEE_SEARCH_EXHAUSTIVE) && (p.T + PRUNED_TC - 1) / PRUNED_TC <= FRONT_CHUNKS) {
         rc = enqueue_front(p, bs_da, capacity);
         if (rc) return rc;
-        HIP_TRY(hipStreamSynchronize(S.stream));
+        double ksec = 0.0;
+        rc = wait_signalled(1, ksec);
+        if (rc) return rc;
         const FinalRecord *records = reinterpret_cast<const FinalRecord *>(S.front.host);
         const uint32_t n = *reinterpret_cast<const uint32_t *>(S.front.host + FRONT_N_AT);
         if (n != TOO_MANY) {
-            float ms = 0.f;
-            (void)hipEventElapsedTime(&ms, S.events[0], S.events[1]);
             const bool fits = n <= capacity;
             // counted as the walk counts: one pass over the candidates per point, and the one that finds nothing more
             const uint64_t formed = fits ? kept_row_count() * p.T * (bs_da ? 1ull : 9ull) * ((uint64_t)n + 1) : 0;
             const double seconds = fits ? now_seconds() - t_start : 0.0;
             *n_points = std::min(n, capacity);
-            for (uint32_t k = 0; k < *n_points; ++k) (void)unpack_record(p, records[k], formed, seconds, fits ? ms * 1e-3 : 0.0, out + k);
+            for (uint32_t k = 0; k < *n_points; ++k) (void)unpack_record(p, records[k], formed, seconds, fits ? ksec : 0.0, out + k);
             return !fits ? MMEE_EOVERFLOW : (n ? MMEE_OK : MMEE_ENOFEASIBLE);
         }
     }
@@ -2054,6 +2126,8 @@ void mmee_shutdown(void)
     if (S.decode.host) (void)hipHostFree(S.decode.host);
     (void)hipFree(S.front_points); (void)hipFree(S.front_stairs); (void)hipFree(S.front_counts);
     if (S.front.host) (void)hipHostFree(S.front.host);
+    if (S.done.host) (void)hipHostFree(S.done.host);
+    (void)hipFree(S.call_begin);
     (void)hipFree(S.desc_dev); (void)hipFree(S.block_records); (void)hipFree(S.pruned_hints);
     for (hipEvent_t e : S.events) (void)hipEventDestroy(e);
     hipStream_t keep = S.stream;
