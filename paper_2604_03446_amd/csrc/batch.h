@@ -9,7 +9,7 @@
 // offsets are wave-uniform and the per-tiling constants of the nine stationary combinations sit in
 // registers for the whole item.  Only the table entries that the rows refer to are staged (77 of 123
 // for the pruned rows), which lets two 512-thread blocks share a CU; the entries' places in the staged
-// table are known at compile time (rows.h), a row's offsets reach the waves as scalar loads.  A block takes a contiguous range
+// table are known at compile time (rows.h): immediate offsets of straight-line rows, or scalar loads.  A block takes a contiguous range
 // of items, waves carry their best (value, index) across the items of a problem, and each (block,
 // problem) stretch leaves one record per key; k_batch_finish, launched behind the search, reduces a
 // problem's records and writes the winner's full cost record and mapping.
@@ -83,6 +83,43 @@ __device__ __forceinline__ void batch_tables(const BatchArgs &a, const BatchProb
         probs = (const BatchProblem *)(args + offsetof(BatchArgs, inl));
         firsts = (ConstPtr<uint32_t>)(args + offsetof(BatchArgs, inl) + offsetof(BatchInline, firsts));
     }
+}
+
+// The least traffic (B*H * Eq. (7)) of wave PIECE's rows that fit, for the tiling whose table column is `col`; +inf: none does.
+// Straight-line code: the entries' places are immediate offsets of the LDS reads.  In a loop every row waited for its
+// offsets (a scalar load) and then for its entries, 330 cycles a row, more than half of a chunk's time, whatever the
+// number of reads (1050 instead of 2160 per tiling in a loop gained 2 %).  Kernels, us, loop -> here: 1600 chunks, energy
+// 48 -> 35, energy and latency 71 -> 59; 20736 chunks 356 -> 239 and 452 -> 331.  Rows come in runs with common entries of D, E and C (rows.h); a row compares its entries of A and B with what
+// the run leaves of the capacity: Eq. (1), (2), (4), whole numbers, so exact in any order.
+template <int RUN, int ROW, int... I>
+__device__ __forceinline__ void run_least(const char *col, double cap, double &least, std::integer_sequence<int, I...>)
+{
+    auto at = [&](uint32_t off) { return *reinterpret_cast<const double *>(col + off); };
+    constexpr const uint32_t (&run)[8] = PIECE_RUNS.run[RUN];
+    const double c = at(run[1]), room_bs = cap - (c + at(run[0])), room_ret = cap - (at(run[2]) + c), da = at(run[3]) + at(run[4]);
+    auto row = [&](auto n) {
+        constexpr const uint32_t (&off)[4] = PIECE_RUNS.row[ROW + decltype(n)::value];
+        const bool bs_fits = at(off[0]) <= room_bs, ret_fits = at(off[1]) <= room_ret;
+        least = fmin(least, (bs_fits & ret_fits) ? at(off[2]) + da : pos_inf());
+    };
+    (row(std::integral_constant<int, I>{}), ...);
+}
+template <int RUN, int ROW, int END>
+__device__ __forceinline__ void runs_least(const char *col, double cap, double &least)
+{
+    if constexpr (RUN < END) {
+        constexpr int N = (int)PIECE_RUNS.run[RUN][5];
+        run_least<RUN, ROW>(col, cap, least, std::make_integer_sequence<int, N>{});
+        if constexpr (RUN % 3 == 2) __builtin_amdgcn_sched_barrier(0);       // (all reads at once would not fit the registers)
+        runs_least<RUN + 1, ROW + N, END>(col, cap, least);
+    }
+}
+template <int PIECE>
+__device__ __forceinline__ double piece_least(const char *col, double cap)
+{
+    double least = pos_inf();
+    runs_least<(int)PIECE_RUNS.first_run[PIECE], (int)PIECE_RUNS.first_row[PIECE], (int)PIECE_RUNS.first_run[PIECE + 1]>(col, cap, least);
+    return least;
 }
 
 // MASK, FAST, REGROUP as in k_search.  Every block takes a contiguous range of the work items, so
@@ -285,8 +322,21 @@ __global__ __launch_bounds__(BATCH_THREADS, 4) void k_search_batch(BatchArgs a)
             ks = o == 2 ? en : 0.0;
         };
 
+        // One block to a chunk: the wave's piece as straight-line code.  Shared chunks (at most 256 of them, one to a block) take
+        // their rows in a loop: nothing repeats that would make up for fetching the code.
         double min_d = inf;
-        {
+        if (a.split == 1) {
+            switch (wave) {
+            case 0: min_d = piece_least<0>(tab_bytes, cap); break;
+            case 1: min_d = piece_least<1>(tab_bytes, cap); break;
+            case 2: min_d = piece_least<2>(tab_bytes, cap); break;
+            case 3: min_d = piece_least<3>(tab_bytes, cap); break;
+            case 4: min_d = piece_least<4>(tab_bytes, cap); break;
+            case 5: min_d = piece_least<5>(tab_bytes, cap); break;
+            case 6: min_d = piece_least<6>(tab_bytes, cap); break;
+            default: min_d = piece_least<7>(tab_bytes, cap); break;
+            }
+        } else {
             u32x8 off_next = row_offs[min(row_lo, KEPT.n - 1)];
 #pragma unroll 4
             for (uint32_t i = 0; i < n_rows; ++i) {

@@ -18,7 +18,7 @@
 // each), a bitonic sort per block and two levels of merges that sorted thousands of points, the 22 points of a
 // 4900-tiling problem took 65 + 27 + 26 us in three launches (a call of 134 us; walked 890), energy and latency of 17424 tilings
 // 34 + 16 + 22 (87 us; walked 380).  Now 30 + 12 us
-// (call 64) and 28 + 10 (54).
+// (call 58) and 31 + 10 (50).
 //
 // Room.  How many points a wave or a block has is a matter of the extents' divisors: without the staircase, over 600 shapes of
 // attention layers and GEMM chains at most 91 in a wave, 431 in the waves of a block, 118 in its front, 2917 in all blocks' (counted

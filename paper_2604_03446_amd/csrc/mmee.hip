@@ -819,43 +819,19 @@ void launch_batch_mask(bool fast, bool regroup, dim3 grid, const BatchArgs &a)
     hipLaunchKernelGGL((k_batch_finish<MASK>), dim3(a.n_prob), dim3(256), 0, S.stream, a);
 }
 
-// The kept rows shared out over the waves of a block, every wave a contiguous piece of one class's list (rows of a
-// class share r and f).
-struct BatchTasks { uint32_t lo[BATCH_WAVES], cnt[BATCH_WAVES], g[BATCH_WAVES]; };
-const BatchTasks &batch_tasks()
-{
-    static const BatchTasks tasks = [] {
-        BatchTasks t;
-        uint32_t waves[LEAST_CLASSES] = {1, 1, 1}, wv = 0;
-        const uint32_t group_of[LEAST_CLASSES] = {0, 2, 3};  // class (r, f) -> g = r + 2 f
-        for (int taken = LEAST_CLASSES; taken < BATCH_WAVES; ++taken) {
-            int most = 0;
-            for (int c = 1; c < LEAST_CLASSES; ++c)
-                if ((KEPT.rows[c] + waves[c] - 1) / waves[c] > (KEPT.rows[most] + waves[most] - 1) / waves[most]) most = c;
-            ++waves[most];
-        }
-        for (int c = 0; c < LEAST_CLASSES; ++c)
-            for (uint32_t k = 0; k < waves[c]; ++k, ++wv) {
-                const uint32_t n = KEPT.rows[c], lo = n * k / waves[c], hi = n * (k + 1) / waves[c];
-                t.lo[wv] = KEPT.first[c] + lo; t.cnt[wv] = hi - lo; t.g[wv] = group_of[c];
-            }
-        return t;
-    }();
-    return tasks;
-}
-
-// every wave's piece of its class's list, cut once more into one sub-piece per row share
+// The kept rows shared out over the waves of a block and the row shares (rows.h: the kernel has the pieces' runs compiled in).
 void set_batch_tasks(BatchArgs &a, uint32_t split)
 {
-    const BatchTasks &t = batch_tasks();
+    static_assert(PIECE_WAVES == BATCH_WAVES && BATCH_MAX_SPLIT == 4, "the pieces are those of the blocks");
+    const uint32_t group_of[LEAST_CLASSES] = {0, 2, 3};      // class (r, f) -> g = r + 2 f
     a.split = split;
     for (a.split_log2 = 0; (1u << a.split_log2) < split; ++a.split_log2) {}
     for (uint32_t sh = 0; sh < split; ++sh)
-        for (int wv = 0; wv < BATCH_WAVES; ++wv) {
-            const uint32_t n = t.cnt[wv], lo = n * sh / split, hi = n * (sh + 1) / split;
-            a.task_lo[sh * BATCH_WAVES + wv] = t.lo[wv] + lo;
-            a.task_cnt[sh * BATCH_WAVES + wv] = hi - lo;
-            a.task_g[sh * BATCH_WAVES + wv] = t.g[wv];
+        for (uint32_t wv = 0; wv < BATCH_WAVES; ++wv) {
+            const PieceRange p = piece_range(split, sh, wv);
+            a.task_lo[sh * BATCH_WAVES + wv] = KEPT.first[p.cls] + p.lo;
+            a.task_cnt[sh * BATCH_WAVES + wv] = p.n;
+            a.task_g[sh * BATCH_WAVES + wv] = group_of[p.cls];
         }
 }
 
@@ -1131,6 +1107,8 @@ void pruned_slices(const std::vector<PrunedEntry> &entries, std::vector<uint32_t
 // Sharing from four problems a group on whatever their size cost up to 208 % (64 problems of one chunk, energy: 118
 // us, 68 in batches), never sharing up to 270 % (64 problems of 324 chunks, energy: 475 us, 126 shared).  A pass of its
 // own costs 33 us a problem of one chunk and 105 us at 324 chunks (energy, latency and energy-delay product).
+// (Both kernels take two thirds of the time since: a round of k_search_batch 6 to 8 us instead of 9 to 11, a block of
+// k_search_pruned 62 us instead of 88.  The figures above and the constants are those of the fit; their ratio stands.)
 void keep_shared(const std::vector<PrunedEntry> &entries, const std::vector<uint32_t> &order, std::vector<PrunedSlice> &slices)
 {
     struct Batches {                         // chunks, and kinds of kernel: each is a launch of its own

@@ -240,12 +240,13 @@ struct alignas(32) KeptRows {
     uint32_t number[KEPT_ALL];               // levels/order + 15000 * (r + 2 f)
     uint32_t place[NENT];                    // table entry -> its line in the compact table, NENT: no row refers to it
 };
+constexpr KeptClass KEPT_CLASS[LEAST_CLASSES] = {kept_class(0, 0), kept_class(0, 1), kept_class(1, 1)};
 constexpr KeptRows kept_rows()
 {
     KeptRows k{};
     for (int e = 0; e < NENT; ++e) k.place[e] = NENT;
     for (int c = 0; c < LEAST_CLASSES; ++c) {
-        const KeptClass cls = kept_class(c == 2 ? 1u : 0u, c == 0 ? 0u : 1u);
+        const KeptClass &cls = KEPT_CLASS[c];
         k.first[c] = k.n;
         k.rows[c] = (uint32_t)cls.n;
         for (int i = 0; i < cls.n; ++i, ++k.n) {
@@ -264,6 +265,67 @@ constexpr KeptRows kept_rows()
 }
 constexpr KeptRows KEPT = kept_rows();
 static_assert(KEPT.n == KEPT_ALL, "the arrays are sized for the kept rows");
+
+// ---- the kept rows of k_search_batch's waves, in runs --------------------------------------------
+// A block's eight waves take a contiguous piece of one class's kept rows each; with `split` blocks to a chunk each of these
+// is cut once more.
+constexpr int PIECE_WAVES = 8;
+constexpr uint32_t WAVES_OF_CLASS[LEAST_CLASSES] = {3, 2, 3};
+struct PieceRange { uint32_t cls, lo, n; };                   // within the class's list
+constexpr PieceRange piece_range(uint32_t split, uint32_t share, uint32_t wave)
+{
+    uint32_t c = 0, k = wave;
+    while (k >= WAVES_OF_CLASS[c]) k -= WAVES_OF_CLASS[c++];
+    const uint32_t n = (uint32_t)KEPT_CLASS[c].n, lo = n * k / WAVES_OF_CLASS[c], cnt = n * (k + 1) / WAVES_OF_CLASS[c] - lo;
+    return {c, lo + cnt * share / split, cnt * (share + 1) / split - cnt * share / split};
+}
+
+// What the least traffic of a piece (split 1) needs: the rows that no other row of the piece covers, those with equal (D, E) and
+// C entries side by side: a run reads these five entries once, a row its three of A and B.  220 rows in 78 runs, 1050 reads per
+// tiling instead of 2160.
+constexpr int RUNS_MAX = 96;
+struct PieceRuns {
+    uint32_t run[RUNS_MAX][8];               // byte offsets: ret D E, bs C, bs D E, da D E, da C; number of rows
+    uint32_t row[KEPT_ALL][4];               // byte offsets: bs A B, ret A B, da A B
+    uint32_t first_run[PIECE_WAVES + 1], first_row[PIECE_WAVES];
+};
+constexpr PieceRuns piece_runs()
+{
+    PieceRuns out{};
+    uint32_t runs = 0, rows = 0;
+    for (uint32_t wave = 0; wave < PIECE_WAVES; ++wave) {
+        const PieceRange p = piece_range(1, 0, wave);
+        const KeptClass &cls = KEPT_CLASS[p.cls];
+        out.first_run[wave] = runs;
+        out.first_row[wave] = rows;
+        bool gone[KEPT_MAX] = {};
+        uint32_t sig[KEPT_MAX] = {};
+        for (uint32_t i = 0; i < p.n; ++i) sig[i] = row_signature(cls.row[p.lo + i]);
+        for (uint32_t i = 0; i < p.n; ++i)
+            for (uint32_t j = 0; j < p.n && !gone[i]; ++j)
+                gone[i] = j != i && (sig[j] & ~sig[i]) == 0 && (sig[j] != sig[i] || j < i);
+        for (uint32_t i = 0; i < p.n; ++i) {
+            if (gone[i]) continue;
+            const int of_run[5] = {1, 2, 3, 6, 7}, of_row[3] = {0, 4, 5};
+            uint32_t (&run)[8] = out.run[runs++];
+            for (int q = 0; q < 5; ++q) run[q] = row_entry(cls.row[p.lo + i], of_run[q]);
+            for (uint32_t j = i; j < p.n; ++j) {
+                bool same = !gone[j];
+                for (int q = 0; q < 5; ++q) same = same && row_entry(cls.row[p.lo + j], of_run[q]) == run[q];
+                if (!same) continue;
+                gone[j] = true;
+                ++run[5];
+                for (int q = 0; q < 3; ++q) out.row[rows][q] = KEPT.place[row_entry(cls.row[p.lo + j], of_row[q])] * KEPT_LINE;
+                ++rows;
+            }
+            for (int q = 0; q < 5; ++q) run[q] = KEPT.place[run[q]] * KEPT_LINE;
+        }
+    }
+    out.first_run[PIECE_WAVES] = runs;
+    return out;
+}
+constexpr PieceRuns PIECE_RUNS = piece_runs();
+static_assert(PIECE_RUNS.first_run[PIECE_WAVES] <= RUNS_MAX, "the array holds them");
 
 constexpr LeastRows LEAST[LEAST_CLASSES] = {least_rows(0, 0), least_rows(0, 1), least_rows(1, 1)};
 
