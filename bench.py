@@ -41,10 +41,10 @@ HBM_PEAK_GBS = 8000.0
 # HBM bytes per launch from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (summaries under profiles/), scaled by
 # what the same counters read for a 1 GiB device-to-device copy (x2.0 and x1.0).  Valid only for the kernel
 # sources they were taken with: any change to the sources turns "traffic" into null.
-COUNTERS_TAKEN_WITH = "04e073474efa1eae0cbbc0837479d41f7f4e113c42feb74cffd883d5563139f9"
-TRAFFIC = {"k_search_dense_long": (2 * 59047.0 + 384.0) * 1024.0,      # FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0, KiB per dispatch
-           "k_search_dense_bert": (2 * 24003.0 + 2352.0) * 1024.0,
-           "k_eval_batch": (2 * 20242.0 + 4195008.0) * 1024.0}
+COUNTERS_TAKEN_WITH = "a55baa54e241b86bc2fe437a3c9eca99632b9632366a072aa60f0251bce74b05"
+TRAFFIC = {"k_search_dense_long": (2 * 61073.0 + 385.0) * 1024.0,      # FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0, KiB per dispatch
+           "k_search_dense_bert": (2 * 24534.0 + 305.0) * 1024.0,
+           "k_eval_batch": (2 * 19965.0 + 4195187.0) * 1024.0}
 TRAFFIC_SOURCE = {"k_search_dense_long": "profiles/k_search_dense_long.md", "k_search_dense_bert": "profiles/k_search_dense_bert.md",
                   "k_eval_batch": "profiles/k_eval_batch_bert.md"}
 
