@@ -115,7 +115,7 @@ struct State {
     Key *front_points = nullptr;
     unsigned long long *front_stairs = nullptr;
     uint32_t *front_counts = nullptr;
-    bool front_clean = false;                   // staircase and counters are as a call must find them
+    bool front_clean = false;                   // staircase and counters are as a call must find them: a merge that was seen to end left them
     Pinned front;
     void *block_records = nullptr;              // what the blocks of a pruned search leave for the reduction
     size_t block_records_cap = 0;
@@ -1404,13 +1404,14 @@ int enqueue_front(const Plan &p, bool bs_da, uint32_t capacity)
         hipLaunchKernelGGL(k_fill_words64, dim3((FRONT_STEPS + 255) / 256), dim3(256), 0, S.stream, S.front_stairs, (uint64_t)FRONT_STEPS, INF_BITS);
         hipLaunchKernelGGL(k_clear_words, dim3(1), dim3(64), 0, S.stream, S.front_counts, 2u);
     }
-    S.front_clean = false;                     // (until both launches are in the stream: the merge cleans up)
+    // Until the merge, which cleans up, has been seen to end: launches into a stream under capture are in the stream and
+    // never run, nor do the two fills then, and a list that begins at whatever the counters hold lies outside its array.
+    S.front_clean = false;
     if (bs_da) hipLaunchKernelGGL(k_front_points<true>, dim3(n_blocks), dim3(PRUNED_THREADS), 0, S.stream, a);
     else hipLaunchKernelGGL(k_front_points<false>, dim3(n_blocks), dim3(PRUNED_THREADS), 0, S.stream, a);
     HIP_TRY(hipGetLastError());
     hipLaunchKernelGGL(k_front_merge, dim3(1), dim3(MERGE_THREADS), 0, S.stream, a);
     HIP_TRY(hipGetLastError());
-    S.front_clean = true;
     return MMEE_OK;
 }
 
@@ -1852,6 +1853,7 @@ static int walk_front(const mmee_chain *w, const mmee_hw *hw, bool bs_da, uint32
         double ksec = 0.0;
         rc = wait_signalled(1, ksec);
         if (rc) return rc;
+        S.front_clean = true;
         const FinalRecord *records = reinterpret_cast<const FinalRecord *>(S.front.host);
         const uint32_t n = *reinterpret_cast<const uint32_t *>(S.front.host + FRONT_N_AT);
         if (n != TOO_MANY) {
