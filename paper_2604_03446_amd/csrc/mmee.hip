@@ -1657,8 +1657,7 @@ int mmee_chain_search_many(const mmee_chain *w, const mmee_hw *hw, const int *ob
     struct Stretch { uint32_t first, n; int mask; };
     struct Pass {
         uint32_t first, n; int mask; Plan plan; int rc; uint64_t evaluated; bool unproven;
-        size_t ev_slot;
-        Pass(const Stretch &st) : first(st.first), n(st.n), mask(st.mask), evaluated(0), unproven(false), ev_slot(0) {}
+        Pass(const Stretch &st) : first(st.first), n(st.n), mask(st.mask), evaluated(0), unproven(false) {}
     };
     std::vector<Stretch> stretches;
     std::vector<int> codes(count, MMEE_OK);
@@ -1687,12 +1686,14 @@ int mmee_chain_search_many(const mmee_chain *w, const mmee_hw *hw, const int *ob
     }
     rc = ensure_slots(passes.size());
     if (rc) return rc;
+    // per pass: whether it ran in the round under way, whose events bracket its launches, what they took (apart from the passes,
+    // which lie 4 KiB from one another)
+    struct PassTime { size_t ev_slot = 0; double device_seconds = 0.0; bool ran = false; };
+    std::vector<PassTime> times(passes.size());
     // Pruned searches share launches: problems on few shapes the tables and the row side too (enqueue_pruned), others
     // the launch only (enqueue_batches), where the kernel is built for their key set.  Everything else goes
     // problem by problem.  `round_flags` adds MMEE_SEARCH_ORDERED_SUM on the second round, which repeats what the
-    // first could not prove.
-    double signalled_seconds = -1.0;                         // device time of a search that said when it was done, and whose
-    size_t signalled_ev = 0;
+    // first could not prove and leaves the other problems' device times alone: a round's times are taken at its end.
     auto run_round = [&](uint32_t round_flags, bool only_unproven) -> int {
         bool signalled = false;
         bool others = false;                                 // anything beside the batched searches in the stream
@@ -1715,10 +1716,11 @@ int mmee_chain_search_many(const mmee_chain *w, const mmee_hw *hw, const int *ob
         }
         for (size_t s = 0; s < passes.size(); ++s) {
             Pass &ps = passes[s];
-            if (!takes_part(ps)) continue;
-            ps.ev_slot = s;
+            times[s].ran = takes_part(ps);
+            if (!times[s].ran) continue;
+            times[s].ev_slot = s;
             if (in_slice[s]) {
-                ps.ev_slot = slice_ev;
+                times[s].ev_slot = slice_ev;
                 ps.evaluated = kept_row_count() * ps.plan.T * 9ull;
                 ps.unproven = false;
             } else if (!(round_flags & MMEE_SEARCH_EXHAUSTIVE) && batch_mask(ps.mask)) {
@@ -1748,14 +1750,33 @@ int mmee_chain_search_many(const mmee_chain *w, const mmee_hw *hw, const int *ob
                 ps.rc = brc;
                 ps.evaluated = batch[k].evaluated;
                 ps.unproven = !only_unproven && batch[k].unproven;
-                ps.ev_slot = batch_pass[0];
+                times[batch_pass[k]].ev_slot = batch_pass[0];
             }
         }
-        signalled_seconds = -1.0;
-        if (signalled) signalled_ev = batch_pass[0];
-        if (signalled && !others) return wait_signalled(batch[0].mask, signalled_seconds);
-        HIP_TRY(hipStreamSynchronize(S.stream));
-        if (signalled) return wait_signalled(batch[0].mask, signalled_seconds);
+        double signalled_seconds = 0.0;
+        if (!signalled || others) HIP_TRY(hipStreamSynchronize(S.stream));
+        if (signalled) {
+            const int wrc = wait_signalled(batch[0].mask, signalled_seconds);
+            if (wrc) return wrc;
+        }
+        size_t timed = (size_t)-1;
+        double timed_seconds = 0.0;
+        for (size_t s = 0; s < passes.size(); ++s) {
+            PassTime &t = times[s];
+            if (!t.ran) continue;
+            if (signalled && s == batch_pass[0]) {           // (the only one of its launch: no events were recorded)
+                t.device_seconds = signalled_seconds;
+                continue;
+            }
+            if (t.ev_slot != timed) {                        // (asked for once, not for each of hundreds that shared them)
+                if (passes[s].rc != MMEE_OK) continue;
+                float ms = 0.f;
+                (void)hipEventElapsedTime(&ms, S.events[2 * t.ev_slot], S.events[2 * t.ev_slot + 1]);
+                timed = t.ev_slot;
+                timed_seconds = ms * 1e-3;
+            }
+            t.device_seconds = timed_seconds;
+        }
         return MMEE_OK;
     };
     rc = run_round(flags, false);
@@ -1784,26 +1805,12 @@ int mmee_chain_search_many(const mmee_chain *w, const mmee_hw *hw, const int *ob
     }
     const double seconds = now_seconds() - t_start;
     int first_bad = MMEE_OK;
-    size_t timed = (size_t)-1;
-    float timed_ms = 0.f;
     for (size_t s = 0; s < passes.size(); ++s) {
         Pass &ps = passes[s];
-        float ms = 0.f;
-        const size_t ev = ps.ev_slot;                        // a pass reports the device time of the launches it shared
-        if (ps.rc == MMEE_OK && signalled_seconds >= 0.0 && ev == signalled_ev) {
-            ms = (float)(signalled_seconds * 1e3);
-        } else if (ps.rc == MMEE_OK) {
-            if (ev != timed) {                               // (asked for once, not for each of hundreds that shared them)
-                timed_ms = 0.f;
-                (void)hipEventElapsedTime(&timed_ms, S.events[2 * ev], S.events[2 * ev + 1]);
-                timed = ev;
-            }
-            ms = timed_ms;
-        }
         for (uint32_t a = ps.first; a < ps.first + ps.n; ++a) {
             int code = codes[a] ? codes[a] : ps.rc;
             if (code == MMEE_OK)
-                code = unpack_result(ps.plan, s, objectives[a], ps.evaluated, seconds, ms * 1e-3, out + a);
+                code = unpack_result(ps.plan, s, objectives[a], ps.evaluated, seconds, times[s].device_seconds, out + a);
             else
                 std::memset(out + a, 0, sizeof(mmee_result));
             if (rc_out) rc_out[a] = code;
