@@ -1123,7 +1123,7 @@ __global__ __launch_bounds__(SEARCH_THREADS, (popcount4(MASK) >= 3 || (MASK & 4 
 // (D, E) part held in registers.  All of these sums are exact integers below 2^53 (the host refuses workloads where
 // they are not), so their association is free, and a row needs no footprint of its own: it fits if the (A, B)
 // part does not exceed what the (D, E) part and C leave of the capacity, two comparisons.  Its energy (regrouped) or its
-// DRAM time is one addition of the two parts' shares.  A row over capacity costs +inf, whatever the combination: its
+// DRAM time, where a key needs only one of them, is one addition of the two parts' shares.  A row over capacity costs +inf, whatever the combination: its
 // lanes are masked out of the nine combinations, and a wave none of whose tilings the row fits passes over them.
 // Per (row, tiling) 3 operations before the nine combinations, whose per-tiling constants are lane registers for
 // the whole task, and 3/5 LDS reads.  With both footprints summed, their maximum, and the mask as selects it was 8
@@ -1192,10 +1192,11 @@ __global__ __launch_bounds__(DENSE_THREADS, 4) void k_search_dense(SearchArgs a)
     static_assert(!(MASK & 4) && popcount4(MASK) <= 2, "one or two of the scalar keys");
     constexpr bool OUTSIDE = !REGROUP && (MASK & 1) && !(MASK & 8) && !LIMIT;
     constexpr bool ENERGY = MASK != (1 << MMEE_OBJ_LATENCY) || LIMIT, TIME = MASK != (1 << MMEE_OBJ_ENERGY) || LATCAP;
-    // what a row's costs need of its traffic: a sum of the two parts' energies, of their times, the traffic itself
-    constexpr bool TWO = popcount4(MASK) == 2;
-    constexpr bool E_SUMS = ENERGY && REGROUP && !TWO, L_SUMS = TIME && FAST && !TWO;
-    constexpr bool WORDS = (ENERGY && !E_SUMS) || (TIME && !L_SUMS);
+    // What a row's costs need of its traffic.  The energy alone, or the time alone: a sum of the two parts' shares.  Both: the
+    // traffic itself, weighed per row, one operation more than two shares; with these the (D, E) parts of five p_D values
+    // are 20 doubles instead of 15 and 8 to 15 registers spill, which a short launch feels most (us per call: energy-delay product of
+    // 144 tilings 58, with two shares 72; of 1600 tilings 146 and 160; (latency, energy) of 1600 tilings 3 % apart).
+    constexpr bool E_SUMS = ENERGY && !TIME && REGROUP, L_SUMS = TIME && !ENERGY && FAST, WORDS = !E_SUMS && !L_SUMS;
     constexpr uint32_t ROWS_PER_STEP = popcount4(MASK) == 2 ? 1u : 5u;       // p_D values held in registers
     __shared__ double tab[DENSE_PAIRS * DENSE_PAIR_F64];
     __shared__ Key wave_best[N_OBJ][DENSE_WAVES];
@@ -1231,7 +1232,7 @@ __global__ __launch_bounds__(DENSE_THREADS, 4) void k_search_dense(SearchArgs a)
     const EncTable enc = {(ConstPtr<u32x4>)a.enc};
     ConstPtr<uint32_t> cls_list = as_constant(a.cls);
     // Regrouped, the DRAM side of the energy is whole numbers throughout, and with FAST the DRAM time is a whole number
-    // times one power of two: both are sums of an (A, B) and a (D, E) part, formed once per part.
+    // times one exact constant: either is the sum of an (A, B) and a (D, E) share, formed once per part.
     auto words_energy = [&](double words) { return FAST ? a.mc.e_sum * words : a.mc.e_sum * (words * a.mc.BH); };
     // A row fits if neither operator's footprint exceeds the capacity: what the (D, E) part and C leave of it is formed
     // once per task, a row compares its (A, B) part with that.  (Whole numbers below 2^53 throughout: exact.)
