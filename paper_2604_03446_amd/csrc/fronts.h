@@ -43,6 +43,9 @@ constexpr uint32_t FRONT_POINTS = 4096;      // points the merge takes at a time
 constexpr uint32_t FRONT_STEPS = 512;        // steps of the staircase: one per thread of a block
 constexpr uint32_t FRONT_DIVS = 512;         // divisors of a problem of FRONT_CHUNKS chunks: 240 + 136 + 1 + 1 at most
 constexpr uint32_t TOO_MANY = 0xFFFFFFFFu;
+// Which way a front took (mmee_front_way): a block's front outgrew FRONT_BLOCK or its pool; a block's points were sorted, or
+// merged wave by wave; the merge took the list in several turns, sorted what was left at the end, or before.
+enum : uint32_t { WAY_OUTGROWN = 1, WAY_POOL_SORTED = 2, WAY_WAVE_BY_WAVE = 4, WAY_TURNS = 8, WAY_SORTED = 16, WAY_SORTED_EARLY = 32 };
 constexpr int FRONT_ROWS = (KEPT_ALL + FRONT_SPLIT * PRUNED_WAVES - 1) / (FRONT_SPLIT * PRUNED_WAVES);     // rows per wave
 
 struct FrontArgs {
@@ -51,14 +54,15 @@ struct FrontArgs {
     double extent[4], size[5];
     uint32_t X[4], ndiv[4];
     uint32_t capacity;                       // records the caller has room for
+    uint32_t pool;                           // points the waves of a block may have together, at most POOL
     uint32_t step_shift;                     // a value's step: the upper word of its fp64, shifted, less step0, held to
     int32_t step0;                           // 0 .. FRONT_STEPS - 1 (goes up with the value, whatever these two are)
     Key *points;                             // [FRONT_BLOCKS * FRONT_BLOCK] the blocks' fronts, block after block as they end
     unsigned long long *stairs;              // [FRONT_STEPS] least second metric per step (bit patterns), +inf between calls
-    uint32_t *counts;                        // [0] points in the list; [1] not 0: a block's front outgrew FRONT_BLOCK; 0 between calls
+    uint32_t *counts;                        // [0] points in the list; [1] which way the blocks took; 0 between calls
     const uint4 *enc;
     FinalRecord *out;                        // [capacity], ascending
-    uint32_t *n_out;                         // points of the front; TOO_MANY: walk it
+    uint32_t *n_out;                         // [0] points of the front; TOO_MANY: walk it.  [1] which way it took
     Done *done;                              // where the host looks for the call's end
     uint64_t number, *begin;                 // the call's number; when it began (device memory)
     uint32_t list[FRONT_DIVS];
@@ -321,6 +325,7 @@ __global__ __launch_bounds__(PRUNED_THREADS, BS_DA ? 2 : 4) void k_front_points(
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const ModelConst &mc = a.mc;
+    const uint32_t room = min(a.pool, POOL);
     if (blockIdx.x == 0 && threadIdx.x == 0) *a.begin = wall_clock64();
     ConstBytes args = (ConstBytes)__builtin_amdgcn_kernarg_segment_ptr();
     div_lds[threadIdx.x] = ((ConstPtr<uint32_t>)(args + offsetof(FrontArgs, list)))[threadIdx.x];
@@ -344,7 +349,7 @@ __global__ __launch_bounds__(PRUNED_THREADS, BS_DA ? 2 : 4) void k_front_points(
     for (int q = 0; q < 4; ++q) { v.G[q] = gd[q * PRUNED_TC + lane]; v.D[q] = gd[(4 + q) * PRUNED_TC + lane]; }
     stage_kept(tab + lane, wave, v, a.size, 1.0);
 
-    uint32_t m, N;                                           // points of the block's front, entries sorted
+    uint32_t m, N, way = 0;                                  // points of the block's front, entries sorted, which way
     if constexpr (BS_DA) {
         __syncthreads();
         // every dataflow, the capacity plays no part; neither metric depends on the stationary modes
@@ -368,21 +373,23 @@ __global__ __launch_bounds__(PRUNED_THREADS, BS_DA ? 2 : 4) void k_front_points(
         drop_covered(a, P, S, steps, wave_least);
         // index so far: the row's place, then its lowest tiling
         auto mine = [&]() {
-            wave_front(P, S, id, points, &filled, POOL, [&](uint32_t place, double p, double s, uint32_t row, unsigned long long who) {
+            wave_front(P, S, id, points, &filled, room, [&](uint32_t place, double p, double s, uint32_t row, unsigned long long who) {
                 points[place].p = p; points[place].s = s;
                 points[place].idx = ((uint64_t)row << 32) | ((uint32_t)__ffsll((long long)who) - 1u);
             });
         };
         mine();
         __syncthreads();
-        if (filled <= PRUNED_THREADS) {
+        if (filled <= min(room, (uint32_t)PRUNED_THREADS)) {
             m = front_by_pairs<PRUNED_THREADS>(points, keep, &n_left, filled);
-        } else if (filled <= POOL) {
+        } else if (filled <= room) {
+            way = WAY_POOL_SORTED;
             m = front_of<PRUNED_THREADS, POOL>(points, low, keep, filled, N);
             close_up<PRUNED_THREADS, POOL>(points, keep, N);
         } else {
             // more than the pool holds (two long extents with hundreds of divisors): one wave after the other, each
             // beside the front of those before it
+            way = WAY_WAVE_BY_WAVE;
             m = 0;
             for (uint32_t turn = 0;; ++turn) {
                 __syncthreads();
@@ -391,7 +398,7 @@ __global__ __launch_bounds__(PRUNED_THREADS, BS_DA ? 2 : 4) void k_front_points(
                 if (wave == turn) mine();
                 __syncthreads();
                 const uint32_t n = filled;
-                if (n > POOL) { m = TOO_MANY; break; }
+                if (n > room) { m = TOO_MANY; break; }
                 m = front_of<PRUNED_THREADS, POOL>(points, low, keep, n, N);
                 close_up<PRUNED_THREADS, POOL>(points, keep, N);
                 if (turn == PRUNED_WAVES - 1) break;
@@ -444,18 +451,19 @@ __global__ __launch_bounds__(PRUNED_THREADS, BS_DA ? 2 : 4) void k_front_points(
             }
         drop_covered(a, P, S, steps, wave_least);
         // index so far: the class, then where the lanes are
-        wave_front(P, S, id, points, &filled, POOL, [&](uint32_t place, double p, double s, uint32_t code, unsigned long long who) {
+        wave_front(P, S, id, points, &filled, room, [&](uint32_t place, double p, double s, uint32_t code, unsigned long long who) {
             points[place].p = p; points[place].s = s; points[place].idx = ((uint64_t)code << 32) | place;
             lanes[place] = who;
         });
         __syncthreads();
         static_assert(BS_DA || POOL <= (uint32_t)PRUNED_THREADS, "a point per thread");
-        m = filled <= POOL ? front_by_pairs<PRUNED_THREADS>(points, keep, &n_left, filled) : TOO_MANY;
+        m = filled <= room ? front_by_pairs<PRUNED_THREADS>(points, keep, &n_left, filled) : TOO_MANY;
     }
     // the block's front, in any order, behind those of the blocks that ended before
     if (threadIdx.x == 0) {
         if (m <= FRONT_BLOCK) list_at = __hip_atomic_fetch_add(a.counts, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        else __hip_atomic_store(a.counts + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        else way |= WAY_OUTGROWN;
+        if (way) (void)__hip_atomic_fetch_or(a.counts + 1, way, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     if (m > FRONT_BLOCK) return;
     __syncthreads();
@@ -545,7 +553,8 @@ __global__ __launch_bounds__(MERGE_THREADS) void k_front_merge(FrontArgs a)
     unsigned long long *corner_p = reinterpret_cast<unsigned long long *>(low + 2 * FRONT_STEPS), *corner_idx = corner_p + FRONT_STEPS;
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t n_list = a.counts[0];
-    bool fits = a.counts[1] == 0;
+    uint32_t way = a.counts[1];
+    bool fits = !(way & WAY_OUTGROWN);
     double own = pos_inf();
     if (threadIdx.x < FRONT_STEPS) own = __longlong_as_double((long long)a.stairs[threadIdx.x]);
     {
@@ -565,6 +574,7 @@ __global__ __launch_bounds__(MERGE_THREADS) void k_front_merge(FrontArgs a)
     uint32_t n = 0;                                          // points in LDS
     bool sorted = false;
     for (uint32_t at = 0; fits && at < n_list;) {
+        if (at) way |= WAY_TURNS;
         const uint32_t upto = min(n_list, at + (FRONT_POINTS - n));
         constexpr uint32_t AHEAD = 4;                        // points a thread has under way
         for (uint32_t i0 = at; i0 < upto; i0 += AHEAD * MERGE_THREADS) {
@@ -594,6 +604,7 @@ __global__ __launch_bounds__(MERGE_THREADS) void k_front_merge(FrontArgs a)
         if (at < n_list && n <= FRONT_POINTS / 2) continue;
         if (!sorted) n = drop_behind_corners(a, points, n, least, corner_p, corner_idx, &filled);
         if (n > (at < n_list ? FRONT_POINTS / 2 : (uint32_t)MERGE_THREADS)) {
+            way |= at < n_list ? WAY_SORTED_EARLY : WAY_SORTED;
             uint32_t N;
             const uint32_t m = front_of<MERGE_THREADS, FRONT_POINTS>(points, low, keep, n, N);
             close_up<MERGE_THREADS, FRONT_POINTS>(points, keep, N);
@@ -606,7 +617,8 @@ __global__ __launch_bounds__(MERGE_THREADS) void k_front_merge(FrontArgs a)
     }
     if (!fits) {
         if (threadIdx.x == 0) {
-            *a.n_out = TOO_MANY;
+            a.n_out[0] = TOO_MANY;
+            a.n_out[1] = way;
             say_done(a.done, a.number, a.begin);
         }
         return;
@@ -626,7 +638,8 @@ __global__ __launch_bounds__(MERGE_THREADS) void k_front_merge(FrontArgs a)
     __threadfence_system();
     __syncthreads();
     if (threadIdx.x == 0) {
-        *a.n_out = n;
+        a.n_out[0] = n;
+        a.n_out[1] = way;
         say_done(a.done, a.number, a.begin);
     }
 }

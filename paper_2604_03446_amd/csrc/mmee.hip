@@ -67,6 +67,7 @@ namespace {
 char g_last_error[512] = "";
 std::mutex g_lock;
 uint64_t g_front_walks = 0;         // fronts walked point by point so far
+uint32_t g_front_way = 0;           // which way the last front in two launches took (fronts.h)
 
 struct State {
     bool ready = false;
@@ -100,6 +101,7 @@ struct State {
     // short index lists of mmee_decode and their mappings: pinned host memory the kernel reads and writes directly
     Pinned decode;
     uint32_t resident_blocks = 512;
+    uint32_t front_pool = FRONT_POOL_BS_DA;
     // batched search over the pruned rows: problem descriptors (pinned staging + device copy), one record
     // per work item and objective
     unsigned char *batch_host = nullptr, *batch_dev = nullptr;
@@ -340,6 +342,12 @@ int ensure_ready()
         if (const char *env = std::getenv("MMEE_RESIDENT_BLOCKS")) {
             const long v = std::atol(env);
             if (v >= 2 && v % 2 == 0 && (uint64_t)v <= S.resident_blocks) S.resident_blocks = (uint32_t)v;
+        }
+        // MMEE_FRONT_POOL (read once, up to what the kernel holds): less room for the points of a front's blocks, i.e. other
+        // ways to the same front; for tests of the ways that hardly any problem takes.
+        if (const char *env = std::getenv("MMEE_FRONT_POOL")) {
+            const long v = std::atol(env);
+            if (v >= 1 && v <= (long)FRONT_POOL_BS_DA) S.front_pool = (uint32_t)v;
         }
     }
     HIP_TRY(hipMalloc(&S.enc, sizeof(uint4) * N_DFROWS));
@@ -1352,7 +1360,7 @@ int unpack_result(const Plan &p, size_t slot, int objective, uint64_t evaluated,
 
 static_assert(sizeof(FrontArgs) <= 4096, "kernel arguments are limited to 4 KiB");
 
-constexpr size_t FRONT_N_AT = sizeof(FinalRecord) * FRONT_POINTS;     // where S.front has the number of its records
+constexpr size_t FRONT_N_AT = sizeof(FinalRecord) * FRONT_POINTS;     // where S.front has the number of its records, and which way
 
 // The front in two launches; its records and their number land in S.front (TOO_MANY: something outgrew its room,
 // walk the front).  Waited for with wait_signalled, as key 0.
@@ -1361,7 +1369,7 @@ int enqueue_front(const Plan &p, bool bs_da, uint32_t capacity)
     if (!S.front_points) HIP_TRY(hipMalloc(&S.front_points, sizeof(Key) * FRONT_BLOCKS * FRONT_BLOCK));
     if (!S.front_stairs) HIP_TRY(hipMalloc(&S.front_stairs, sizeof(unsigned long long) * FRONT_STEPS));
     if (!S.front_counts) HIP_TRY(hipMalloc(&S.front_counts, sizeof(uint32_t) * 2));
-    HIP_TRY(ensure_pinned(HipPinned{}, S.front, FRONT_N_AT + sizeof(uint32_t)));
+    HIP_TRY(ensure_pinned(HipPinned{}, S.front, FRONT_N_AT + 2 * sizeof(uint32_t)));
     FrontArgs a;
     std::memset(&a, 0, sizeof(a));
     a.mc = p.mc;
@@ -1371,6 +1379,7 @@ int enqueue_front(const Plan &p, bool bs_da, uint32_t capacity)
     if (list_length(p.dv) > FRONT_DIVS) return MMEE_EINVAL;
     pack_lists(p.dv, a.list);
     a.capacity = std::min<uint32_t>(capacity, FRONT_POINTS);
+    a.pool = S.front_pool;
     a.points = S.front_points; a.stairs = S.front_stairs; a.counts = S.front_counts; a.enc = S.enc;
     a.out = reinterpret_cast<FinalRecord *>(S.front.map);
     a.n_out = reinterpret_cast<uint32_t *>(S.front.map + FRONT_N_AT);
@@ -1862,7 +1871,8 @@ static int walk_front(const mmee_chain *w, const mmee_hw *hw, bool bs_da, uint32
         if (rc) return rc;
         S.front_clean = true;
         const FinalRecord *records = reinterpret_cast<const FinalRecord *>(S.front.host);
-        const uint32_t n = *reinterpret_cast<const uint32_t *>(S.front.host + FRONT_N_AT);
+        const uint32_t *out_n = reinterpret_cast<const uint32_t *>(S.front.host + FRONT_N_AT), n = out_n[0];
+        g_front_way = out_n[1];
         if (n != TOO_MANY) {
             const bool fits = n <= capacity;
             // counted as the walk counts: one pass over the candidates per point, and the one that finds nothing more
@@ -1915,6 +1925,11 @@ uint64_t mmee_front_walks(void)
 {
     std::lock_guard<std::mutex> guard(g_lock);
     return g_front_walks;
+}
+uint32_t mmee_front_way(void)
+{
+    std::lock_guard<std::mutex> guard(g_lock);
+    return g_front_way;
 }
 
 int mmee_chain_pareto(const mmee_chain *w, const mmee_hw *hw, uint32_t flags, mmee_result *out, uint32_t capacity,

@@ -2,8 +2,8 @@
 other kernels and must find the same points: fewer tilings than a chunk, whole chunks and remainders, one merge list
 and several, problems beyond what the chunked path takes, capacities nothing fits, room for fewer points than there are.
 The library counts the fronts it walks: every problem of at most 512 chunks of 64 tilings is to take the chunked path,
-also where a wave's front has more points than a wave has lanes, a block's waves more than the block's pool holds (they
-are then merged one by one) or the blocks more than a merge sorts at a time."""
+also where there are many points.  The counts are of points that are on the front of their wave, block or list, before the launch's
+staircase drops what other blocks cover; which of the kernels' ways the largest take is test_gpu_front_ways's."""
 import ctypes
 
 import pytest
