@@ -308,8 +308,7 @@ __device__ __forceinline__ void rows_of_class(uint32_t cls, uint32_t &first, uin
 }
 
 // ---- many problems: chunks of a shape, shared by its accelerators -------------------------------
-// Capacities are taken PRUNED_CAPS at a time by a wave and PRUNED_ROUND at a time by a block: a row then costs four
-// operations plus three per capacity.
+// Capacities are taken PRUNED_ROUND at a time, all of a round by every wave on its eighth of the rows (least_traffic).
 __global__ __launch_bounds__(PRUNED_THREADS, 4) void k_search_pruned(PrunedArgs a)
 {
     __shared__ double tab[KEPT_LINES * PRUNED_TC];           // recovery: entry-major, lane = tiling: conflict-free as it is

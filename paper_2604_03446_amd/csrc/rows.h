@@ -119,11 +119,6 @@ struct LeastRows {
     RowTerms row[LEAST_MAX];
 };
 
-constexpr uint32_t least_sort_key(const RowTerms &t)          // rows that share C's and A, B's terms side by side
-{
-    return (t.c << 20) | (t.dac << 16) | (t.bs[0] << 14) | (t.bs[1] << 12) | ((t.tau & 3u) << 10) | (t.da[0] << 8) | (t.da[1] << 6);
-}
-
 constexpr LeastRows least_rows(uint32_t r, uint32_t f)
 {
     LeastRows out{};
@@ -161,12 +156,6 @@ constexpr LeastRows least_rows(uint32_t r, uint32_t f)
                         out.n = n + 1;
                     }
     }
-    for (int i = 1; i < out.n; ++i)                           // insertion sort
-        for (int k = i; k > 0 && least_sort_key(out.row[k]) < least_sort_key(out.row[k - 1]); --k) {
-            const RowTerms t = out.row[k];
-            out.row[k] = out.row[k - 1];
-            out.row[k - 1] = t;
-        }
     return out;
 }
 
