@@ -788,6 +788,16 @@ int begin_signalled(Done *&done, uint64_t &number, uint64_t *&begin)
     return MMEE_OK;
 }
 
+// what a core does between two looks at a word in memory
+inline void between_looks()
+{
+#if defined(__x86_64__)
+    __builtin_ia32_pause();
+#elif defined(__aarch64__)
+    asm volatile("yield");
+#endif
+}
+
 // Until the records of the last signalled call are there (its keys: mask), and how long its kernels ran.  What does not come
 // within 20 ms (a long search, work ahead of it on the caller's stream, an error) is waited for as any other command is.
 int wait_signalled(int mask, double &seconds)
@@ -807,7 +817,7 @@ int wait_signalled(int mask, double &seconds)
                 HIP_TRY(hipStreamSynchronize(S.stream));
                 synchronised = true;
             }
-            __builtin_ia32_pause();
+            between_looks();
         }
         seconds = std::max(seconds, (double)done[o].ticks / S.clock_hz);
     }
