@@ -100,7 +100,9 @@ typedef struct mmee_result {
     mmee_mapping best;
     mmee_cost cost;
     uint64_t space;             /* size of the index space                                 */
-    uint64_t evaluated;         /* candidates whose cost the search actually formed        */
+    uint64_t evaluated;         /* candidates the search decided over: costed, or settled without (over the
+                                   buffer capacity, which costs +inf; over the surviving rows also those
+                                   of a tiling that move more DRAM words than another one that fits) */
     double seconds;             /* host wall time of the call (upload, kernels, readback)  */
     double kernel_seconds;      /* device time of the search's kernels (HIP events; one pruned
                                    search or front by itself: the device's clock)          */
@@ -124,7 +126,8 @@ enum {
 enum {
     MMEE_SEARCH_PRUNED = 0,             /* offline symbolic pruning on (the paper's method) */
     MMEE_SEARCH_EXHAUSTIVE = 1,         /* cost every candidate that denotes a dataflow (one that
-                                           exceeds the buffer capacity costs +inf)          */
+                                           exceeds the buffer capacity costs +inf, whatever
+                                           else it costs)                                   */
     /* When the four energies per access are whole numbers and the largest possible total stays
      * below 2^53, every term of the energy is an exact integer and the search adds a (row, tiling)
      * part and a (tiling, stationary modes) part per candidate; the result has the same bits as
@@ -172,7 +175,10 @@ int mmee_eval_batch(const mmee_workload *w, const mmee_hw *hw, uint64_t first_id
                     mmee_cost *out_costs);
 
 /* Optimal mapping under one objective; ties go to the lowest index (Sec. VI).
- * mmee_search uses the pruned row set. */
+ * mmee_search uses the pruned row set.
+ * A call of one problem over the surviving rows, and a front over them, keep a core of the host busy until the result is
+ * there, for 20 ms at most; what takes longer (work of the caller's ahead of it on the stream) is then
+ * waited for on the stream, as in the other calls.  Calls take turns: another thread's begins when this one returns. */
 int mmee_search(const mmee_workload *w, const mmee_hw *hw, int objective, mmee_result *out);
 int mmee_search_ex(const mmee_workload *w, const mmee_hw *hw, int objective, uint32_t flags,
                    mmee_result *out);

@@ -491,7 +491,7 @@ ModelConst pass_constants(const Plan &p, uint32_t flags, int mask = 8, bool *unp
     ModelConst mc = p.mc;
     // (any_time: the kernel regroups whatever the DRAM time needs; the others take the DRAM time as one exact
     // product where they regroup, and only the energy alone has no DRAM time: 2048 x 768 x 3072 x 768 chain,
-    // 60 B/cycle, exhaustive: 0.706 ms summed in order, 0.335 ms regrouped)
+    // 60 B/cycle, exhaustive, a buffer that everything fits: 0.418 ms summed in order, 0.327 ms regrouped)
     const bool allowed = (p.exact_k || any_time || mask == MASK_ENERGY) && !(flags & MMEE_SEARCH_ORDERED_SUM);
     const bool on_trust = allowed && !p.can_regroup && p.whole_energies && !(mask & 8) && unproven;
     mc.regroup = ((allowed && p.can_regroup) || on_trust) ? 1u : 0u;
@@ -575,16 +575,21 @@ void launch_dense(bool exact_k, dim3 grid, const SearchArgs &a)
 // key, k_search one pass for all; but with the lanes on rows k_search divides once per candidate where the DRAM time
 // is not one exact product, and keeps a code beside every minimum.  A problem of few chunks leaves the dense kernel's
 // blocks without work (188 items a chunk, 512 blocks), and each of its passes costs some 20 us at least.
-// Measured on 30 shapes of 1 to 14400 tilings for every key set and both kinds of bandwidth, the energy
-// regrouped, with its first sum fused and in order; k_search / dense, us:
-//   energy and latency, regrouped      T = 16: 41 / 50    900: 112 / 142    2800: 176 / 190    4900: 347 / 330    14400: x 0.92
-//   energy and latency, fused          T = 16: 43 / 50    144: x 1.25       900: x 0.98        4900: x 0.73
-//   energy and product, in order       T = 16: 44 / 56    900: 154 / 189    4900: 544 / 551    14400: x 0.99
-//   all four, regrouped                T = 1: 51 / 97     400: 185 / 212    900: 342 / 319     4900: 1395 / 813
-//   all four, bandwidth 60             T = 1: 56 / 99     144: 154 / 176    400: 259 / 214     4900: 2224 / 933
-//   three scalar keys, bandwidth 60    T = 16: 56 / 76    400: 174 / 158    4900: 1301 / 701
-// Energy, latency and energy-delay product with an exact DRAM time: 1.01 ms in k_search, 1.14 dense for 10692 tilings.
-// Near a bound the two differ by a few per cent (three and four chunks, two rounds of blocks: up to 8).
+// The bounds were set on 30 shapes of 1 to 14400 tilings for every key set and both kinds of bandwidth, the energy
+// regrouped, with its first sum fused and in order, before rows over capacity were passed over in the dense kernel.  Measured with the
+// kernels as they are, 23 shapes of 1 to 12168 tilings, a buffer that everything fits; k_search / dense, us per call:
+//   energy and latency, regrouped      T = 16: 40 / 49    784: 105 / 128    2500: 209 / 209    4900: 351 / 329    12168: 781 / 698
+//   energy and latency, fused          T = 16: 42 / 51    144: 63 / 78      500: 109 / 105     4900: 507 / 376
+//   energy and product, in order       T = 16: 43 / 53    784: 139 / 165    4900: 547 / 534    12168: 1270 / 1228
+//   all four, regrouped                T = 1: 50 / 97     500: 216 / 237    784: 299 / 303     4900: 1394 / 798
+//   all four, bandwidth 60             T = 1: 55 / 100    144: 153 / 155    500: 309 / 253     4900: 2222 / 919
+//   three scalar keys, bandwidth 60    T = 16: 55 / 77    500: 203 / 181    4900: 1303 / 690
+//   three scalar keys, regrouped       T = 16: 44 / 74    784: 139 / 226    4900: 518 / 601    12168: 1177 / 1285
+// Over these shapes, every key set, kind of sum and bandwidth, and two buffers the choice costs 0.8 % over the better kernel on
+// average, more than 5 % in 63 of 2530 cases: nearly all of them a small buffer on many tilings, where the dense kernel passes over
+// most rows and the bounds do not know it (256 KiB, in order: energy and product of 7744 tilings 854 / 331; three
+// scalar keys of 12168 tilings 1627 / 724).  Near a bound the two differ by a few per cent (three and four chunks, two rounds of
+// blocks: up to 8).
 uint32_t dense_from(int mask, bool exact_k, const ModelConst &mc)
 {
     constexpr uint32_t NEVER = 0xFFFFFFFFu;
@@ -705,7 +710,8 @@ int enqueue_search_in(const Bufs &B, const Plan &p, int mask, uint32_t flags, ui
         // candidate's latency is a maximum of a row part and a combination part, so the cap applies to the
         // two separately).  The second pass's energy record lands in the slot of this key.  The first pass
         // serves the latency key as well.  Of the scalar keys two go together in one pass (energy and latency of
-        // the 2048 x 768 x 3072 x 768 chain: 0.602 ms, in two passes 0.732), a third takes a pass of its own.
+        // the 2048 x 768 x 3072 x 768 chain: 0.347 ms, in two passes 0.397; with a buffer that everything fits 0.595 and
+        // 0.649), a third takes a pass of its own.
         const bool lex = mask & 4;
         const int scalar = (mask & 11) | (lex ? 2 : 0);
         SearchArgs first = a;
@@ -1125,8 +1131,13 @@ void pruned_slices(const std::vector<PrunedEntry> &entries, std::vector<uint32_t
 // Sharing from four problems a group on whatever their size cost up to 208 % (64 problems of one chunk, energy: 118
 // us, 68 in batches), never sharing up to 270 % (64 problems of 324 chunks, energy: 475 us, 126 shared).  A pass of its
 // own costs 33 us a problem of one chunk and 105 us at 324 chunks (energy, latency and energy-delay product).
-// (Both kernels take two thirds of the time since: a round of k_search_batch 6 to 8 us instead of 9 to 11, a block of
-// k_search_pruned 62 us instead of 88.  The figures above and the constants are those of the fit; their ratio stands.)
+// These figures and the constants are of the kernels of the fit.  Since then a round of k_search_batch takes 6 to 8 us instead
+// of 9 to 11 where every chunk has a block to itself (at most 256 chunks in a launch run the same rows as then), a block of
+// k_search_pruned 62 us instead of 88.  Both ways of 815 calls with the kernels as they are (2 to 640 problems on 1 to 40 shapes of 1
+// to 324 chunks): with a group of four problems or more the choice costs 1.2 % over the better way on average and 10 % or more in
+// 22 of 549 calls (32 problems on each of two shapes of 3 and 7 chunks, energy-delay product: 86 us in batches, 163 shared).  Of
+// the 266 calls without such a group, which stay in batches whatever the estimates say (none_large), 108 would be 10 % or more
+// faster shared (three problems on each of four shapes of 25 to 31 chunks, energy: 101 us, 44 shared).
 void keep_shared(const std::vector<PrunedEntry> &entries, const std::vector<uint32_t> &order, std::vector<PrunedSlice> &slices)
 {
     struct Batches {                         // chunks, and kinds of kernel: each is a launch of its own
