@@ -4,10 +4,10 @@
 A step is one complete exhaustive search of the long-context configuration (B=1, H=32,
 N=8192, d=128, fp16; 128x128 PEs, 8 MiB buffer, 1 KiB register files; tilings over all
 divisors: 6.77e9 candidate indices) for its objective, the energy: tiling tables are built,
-every candidate that denotes a dataflow is decoded and costed (buffer size, DRAM access,
-buffer<->RF traffic, cycles, energy), masked by the capacity constraint, and reduced on the
-device to the optimal mapping.  Nothing is pruned in the timed steps, so candidates/s counts
-costs really formed; the pruned search (the paper's method) is timed next to it as
+every candidate that denotes a dataflow is decoded, tested against the capacity and, where it fits,
+costed (buffer size, DRAM access, buffer<->RF traffic, cycles, energy), and reduced on the
+device to the optimal mapping.  Nothing is pruned in the timed steps; a candidate over the
+capacity costs +inf and is settled by the test.  The pruned search (the paper's method) is timed next to it as
 time-to-optimum, and the 1024-search hardware sweep as its own leg.
 
 Prints ONE JSON line.
@@ -26,25 +26,33 @@ sys.path.insert(0, ROOT)
 # the model's additions, multiplications, maxima and comparisons round one by one, so each
 # lane-operation is one operation.)
 ALU_PEAK_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
-# fp64-width operations the model needs per candidate of k_search_dense over the full row set, by how the energy is
-# added up.  Shared by the nine candidates of a (row, tiling) pair: two comparisons for Eq. (1), (2), (4) and the
-# capacity (what the row's (D, E) part leaves of it is formed once per five and more rows), one addition for Eq. (7)
-# or its energy = 3; in order the product with the DRAM energy as well = 4; with the latency both products = 5.  (Rows that
-# no tiling of a wave fits are counted like the others.)
-# Per candidate, energy: regrouped (every term an exact integer) one addition and the running minimum = 2; in order,
-# with the first sum as one fused operation (its product is exact): buffer words, fused sum, minimum = 3 (the two
+# fp64-width operations that an exhaustive search needs in k_search_dense, by how the energy is added up: per (row, tiling) pair,
+# which nine candidates share, per pair that fits the capacity, and per candidate that fits.
+# Every pair: two comparisons for Eq. (1), (2), (4) and the capacity (what the row's (D, E) part leaves of it is formed once per
+# five and more rows).  A pair that fits: one addition for Eq. (7) or its energy; in order the product with the DRAM
+# energy as well; with the latency both products.
+# A candidate that fits, energy: regrouped (every term an exact integer) one addition and the running minimum; in order,
+# with the first sum as one fused operation (its product is exact): buffer words, fused sum, minimum (the two
 # addends that all candidates of a tiling share go to the minima).  The latency adds a max and its minimum.
-OPS_ENERGY = {"regrouped": 2 + 3 / 9, "fused": 3 + 4 / 9}
-OPS_ENERGY_LATENCY = {"regrouped": 4 + 5 / 9, "fused": 5 + 5 / 9}
+OPS_ENERGY = {"regrouped": (2, 1, 2), "fused": (2, 2, 3)}
+OPS_ENERGY_LATENCY = {"regrouped": (2, 3, 4), "fused": (2, 3, 5)}
+# of the candidates that denote a dataflow, those within the buffer capacity (the CPU oracle's count over the whole space)
+WITHIN_CAPACITY = {"long": 2635657470, "bert": 1110940974}
+
+
+def operations(ops, dataflows, fit):
+    return ops[0] * (dataflows // 9) + ops[1] * (fit // 9) + ops[2] * fit
+
+
 HBM_PEAK_GBS = 8000.0
 
 # HBM bytes per launch from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (summaries under profiles/), scaled by
 # what the same counters read for a 1 GiB device-to-device copy (x2.0 and x1.0).  Valid only for the kernel
 # sources they were taken with: any change to the sources turns "traffic" into null.
-COUNTERS_TAKEN_WITH = "a55baa54e241b86bc2fe437a3c9eca99632b9632366a072aa60f0251bce74b05"
-TRAFFIC = {"k_search_dense_long": (2 * 61073.0 + 385.0) * 1024.0,      # FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0, KiB per dispatch
-           "k_search_dense_bert": (2 * 24534.0 + 305.0) * 1024.0,
-           "k_eval_batch": (2 * 19965.0 + 4195187.0) * 1024.0}
+COUNTERS_TAKEN_WITH = "4d73960ad0178b82bb6716adf660016fe4dead36341864bd6b2d9bdcfaf67f84"
+TRAFFIC = {"k_search_dense_long": (2 * 61857.0 + 385.0) * 1024.0,      # FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0, KiB per dispatch
+           "k_search_dense_bert": (2 * 24326.0 + 305.0) * 1024.0,
+           "k_eval_batch": (2 * 20247.0 + 4195164.0) * 1024.0}
 TRAFFIC_SOURCE = {"k_search_dense_long": "profiles/k_search_dense_long.md", "k_search_dense_bert": "profiles/k_search_dense_bert.md",
                   "k_eval_batch": "profiles/k_eval_batch_bert.md"}
 
@@ -81,7 +89,7 @@ def main():
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--profile-only", action="store_true",
                     help="run the timed steps only (for rocprofv3): no oracle, no extra legs")
-    ap.add_argument("--profile-leg", choices=["long", "bert", "sweep", "fronts", "eval"], default="long",
+    ap.add_argument("--profile-leg", choices=["long", "bert", "sweep", "fronts", "eval", "pruned"], default="long",
                     help="with --profile-only: which leg the timed steps run")
     args = ap.parse_args()
     if args.gpus != 1:
@@ -147,6 +155,12 @@ def main():
             for _ in range(args.warmup + args.steps):
                 M.mmee_front_bs_da(CONFIGS["bert"]["workload"], CONFIGS["bert"]["hw"])
                 M.mmee_pareto(CONFIGS["bert"]["workload"], CONFIGS["bert"]["hw"])
+        elif args.profile_leg == "pruned":
+            # one problem of 102 400 tilings over the surviving rows, both keys
+            timed_search({"workload": dict(B=1, H=24, N=3000, d=80, word_bytes=2, tiling_mode=1, c_softmax=10),
+                          "hw": dict(pe_rows=24, pe_cols=9, n_arrays=3, rf_bytes=200, gb_bytes=300 << 10, e_dram=171.3, e_gb=6.0,
+                                     e_rf=1.0, e_mac=1.0, dram_bw=60.0, gb_bw=200.0)},
+                         [M.OBJ_ENERGY, M.OBJ_LATENCY], M.SEARCH_PRUNED, args.steps, args.warmup)
         else:
             cfg = CONFIGS["bert"]
             buf = torch.empty((1 << 26) * 8, dtype=torch.int64, device="cuda")
@@ -166,9 +180,9 @@ def main():
     # beyond the size bound of the a-priori proof the search still starts regrouped and checks the outcome
     whole = all(float(cfg["hw"][k]).is_integer() for k in ("e_dram", "e_gb", "e_rf", "e_mac"))
     regrouped = M.mmee_energy_regrouped(cfg["workload"], cfg["hw"], M.SEARCH_EXHAUSTIVE) or whole
-    ops = OPS_ENERGY["regrouped" if regrouped else "fused"]
     step_s, kernel_s, stream_s, res = timed_search(cfg, objectives, M.SEARCH_EXHAUSTIVE, args.steps, args.warmup)
     evaluated = res[0].evaluated
+    ops = operations(OPS_ENERGY["regrouped" if regrouped else "fused"], evaluated, WITHIN_CAPACITY["long"])
     traffic, traffic_src = traffic_of("k_search_dense_long")
     out = {
         "metric": "candidate mappings evaluated/sec (every dataflow costed, energy-driven optimum)",
@@ -176,14 +190,14 @@ def main():
         "ms_per_step": step_s * 1e3, "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
         "dtype": "f64", "data": "synthetic",
         "config": {"workload": "long: " + describe(cfg), "space": res[0].space, "candidates_costed_per_step": evaluated,
-                   "objectives": ["energy"], "search": "exhaustive"},
+                   "candidates_within_capacity": WITHIN_CAPACITY["long"], "objectives": ["energy"], "search": "exhaustive"},
         "best": {"energy": {"idx": res[0].best.idx, "energy_pj": res[0].cost.energy_pj,
                             "latency_cycles": res[0].cost.latency_cycles}},
         "search_kernel_ms": kernel_s * 1e3, "stream_ms_per_step": stream_s * 1e3,
-        "roofline": {"bound": "alu", "achieved": ops * evaluated / kernel_s / 1e12, "peak": ALU_PEAK_TOPS,
+        "roofline": {"bound": "alu", "achieved": ops / kernel_s / 1e12, "peak": ALU_PEAK_TOPS,
                      "unit": "Tlane-op/s", "traffic": traffic, "traffic_source": traffic_src,
                      "kernel": "k_search_dense<energy%s>" % (", regrouped energy sum" if regrouped else ""),
-                     "ops_per_candidate": ops, "kernel_candidates_per_s": evaluated / kernel_s},
+                     "ops_per_candidate": ops / evaluated, "kernel_candidates_per_s": evaluated / kernel_s},
     }
     out["roofline"]["frac"] = out["roofline"]["achieved"] / out["roofline"]["peak"]
 
@@ -195,12 +209,12 @@ def main():
         for name, flags in (("regrouped", M.SEARCH_EXHAUSTIVE), ("ordered_sum", M.SEARCH_EXHAUSTIVE | M.SEARCH_ORDERED_SUM)):
             s_, k_, _, r_ = timed_search(bert, two, flags, 50, 5)
             reg = name == "regrouped" and M.mmee_energy_regrouped(bert["workload"], bert["hw"], flags)
-            ops_two = OPS_ENERGY_LATENCY["regrouped" if reg else "fused"]
-            ach = ops_two * r_[0].evaluated / k_ / 1e12
+            ops_two = operations(OPS_ENERGY_LATENCY["regrouped" if reg else "fused"], r_[0].evaluated, WITHIN_CAPACITY["bert"])
+            ach = ops_two / k_ / 1e12
             legs[name] = {"value": r_[0].evaluated / s_, "unit": "candidates/s", "ms_per_step": s_ * 1e3,
                           "search_kernel_ms": k_ * 1e3, "candidates_costed_per_step": r_[0].evaluated,
                           "roofline": {"bound": "alu", "achieved": ach, "peak": ALU_PEAK_TOPS, "unit": "Tlane-op/s",
-                                       "frac": ach / ALU_PEAK_TOPS, "ops_per_candidate": ops_two,
+                                       "frac": ach / ALU_PEAK_TOPS, "ops_per_candidate": ops_two / r_[0].evaluated,
                                        "kernel": "k_search_dense<energy+latency%s>" % (", regrouped energy sum" if reg else "")}}
         t_, src_ = traffic_of("k_search_dense_bert")
         legs["regrouped"]["roofline"].update(traffic=t_, traffic_source=src_)
@@ -244,7 +258,7 @@ def main():
             chains[name] = {"pruned_ms": dt_p * 1e3, "exhaustive_ms": dt_x * 1e3, "exhaustive_candidates": rx[0].evaluated,
                             "exhaustive_candidates_per_s": rx[0].evaluated / dt_x}
         beyond["chains_energy"] = chains
-        # both fronts of bert (Sec. VII-E, VII-C): over the surviving rows in three launches, exhaustively one or two passes per point
+        # both fronts of bert (Sec. VII-E, VII-C): over the surviving rows in two launches, exhaustively one or two passes per point
         for key, fn in (("front_energy_latency", M.mmee_pareto), ("front_bs_da", M.mmee_front_bs_da)):
             dt_p, (code_p, pts_p) = wall(lambda: fn(bert["workload"], bert["hw"], M.SEARCH_PRUNED), 5)
             dt_x, (code_x, pts_x) = wall(lambda: fn(bert["workload"], bert["hw"], M.SEARCH_EXHAUSTIVE), 2, 1)
@@ -291,10 +305,12 @@ def main():
         dt = time.perf_counter() - t1
         assert rc == 0 and idx[0] == res[0].best.idx, "GPU and oracle disagree"
         assert cost[0].energy_pj == res[0].cost.energy_pj and cost[0].latency_cycles == res[0].cost.latency_cycles
+        assert n_valid == WITHIN_CAPACITY["long"]
         out["cpu_baseline"] = {"value": evaluated / dt, "unit": "candidates/s", "cores": threads,
                                "host_cpus": os.cpu_count(), "kind": "oracle",
                                "sample": "the whole long space: all %d indices enumerated once, four objectives "
-                                         "kept, %d of them denote a dataflow and are costed" % (res[0].space, evaluated),
+                                         "kept, %d of them denote a dataflow, %d of these fit the buffer"
+                                         % (res[0].space, evaluated, n_valid),
                                "seconds": dt, "optimum_matches_gpu": True}
     print(json.dumps(out))
 
