@@ -1,5 +1,5 @@
 """Calls in which one problem's energies, regrouped on trust, have to be summed once more in order: the device times of the
-problems that the second round leaves alone are those of the first, and nothing is left for the next call."""
+problems that the repetition leaves alone are those of their own launches, and nothing is left for the next call."""
 import pytest
 
 pytestmark = pytest.mark.gpu
