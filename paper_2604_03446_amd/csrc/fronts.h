@@ -478,11 +478,10 @@ __global__ __launch_bounds__(PRUNED_THREADS, BS_DA ? 2 : 4) void k_front_points(
         for (uint32_t i = wave; i < m; i += PRUNED_WAVES) {
             Key k = points[i];
             const uint32_t slot = __builtin_amdgcn_readfirstlane((uint32_t)k.idx);
-            const unsigned long long who = lanes[slot];
             ClassBest b;
             b.p = uniform_f64(k.p); b.s = uniform_f64(k.s);
             b.code = __builtin_amdgcn_readfirstlane((uint32_t)(k.idx >> 32));
-            b.lanes = ((unsigned long long)__builtin_amdgcn_readfirstlane((uint32_t)(who >> 32)) << 32) | __builtin_amdgcn_readfirstlane((uint32_t)who);
+            b.lanes = uniform_u64(lanes[slot]);
             uint32_t cls, combo, row_lo, n_rows;
             class_of_code(b.code, cls, combo);
             rows_of_class(cls, row_lo, n_rows);

@@ -5,11 +5,10 @@
 //   k_compact_rows   offline:  ballot + prefix compaction of surviving rows
 //   k_build_tilings  online:   tiling id -> boundaries -> per-tiling tables (the boundary-matrix side)
 //   k_search         online:   contraction, capacity mask, energy/latency, hierarchical argmin (lane = row)
-//   k_search_dense   online:   the same for one or two keys over the full row set (lane = tiling)
 //   k_front_step     online:   one point of the buffer-size / DRAM-access front
 //   k_eval_batch     online:   the same model, one 64-byte record per candidate
 //   k_decode         online:   index -> mapping
-// The searches over the surviving rows: k_search_batch, k_batch_finish (batch.h), and for many problems of one shape
+// One or two keys over the full row set: k_search_dense (dense.h).  The searches over the surviving rows: k_search_batch, k_batch_finish (batch.h), and for many problems of one shape
 // k_search_pruned, k_pruned_finish (pruned.h).  Both fronts over them: k_front_points, k_front_merge (fronts.h).
 #pragma once
 #include <hip/hip_runtime.h>
@@ -94,7 +93,20 @@ __device__ __forceinline__ Key wave_min(Key k)
 // that wave-uniform reads become scalar loads even next to atomics and inline assembly.
 template <class T> using ConstPtr = const T __attribute__((address_space(4))) *;
 typedef ConstPtr<double> ConstF64;
+typedef ConstPtr<unsigned char> ConstBytes;
 template <class T> __device__ __forceinline__ ConstPtr<T> as_constant(const T *p) { return (ConstPtr<T>)p; }
+
+template <class T>
+__device__ __forceinline__ T read_const(ConstBytes p)        // wave-uniform: scalar loads
+{
+    static_assert(sizeof(T) % 4 == 0, "whole words");
+    uint32_t buf[sizeof(T) / 4];
+#pragma unroll
+    for (uint32_t k = 0; k < sizeof(T) / 4; ++k) buf[k] = ((ConstPtr<uint32_t>)p)[k];
+    T out;
+    __builtin_memcpy(&out, buf, sizeof(T));
+    return out;
+}
 
 // value-only wave reductions and wave-uniform reads (used by the lazy argmin)
 __device__ __forceinline__ double wave_min_f64(double x)
@@ -129,6 +141,13 @@ __device__ __forceinline__ double uniform_f64(double x)
     unsigned long long b = (unsigned long long)__double_as_longlong(x);
     uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b), hi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
     return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+// (the builtin returns an int: its low word must not be widened with its sign)
+__device__ __forceinline__ uint64_t uniform_u64(uint64_t x)
+{
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)x), hi = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(x >> 32));
+    return ((uint64_t)hi << 32) | lo;
 }
 
 // ---------------------------------------------------------------------------
@@ -553,12 +572,6 @@ struct SearchArgs {
     uint32_t n_cc, n_fc;
     uint32_t n_coarse_items;
     uint32_t n_items;
-    // k_search_dense: the (order, r, f) classes that denote dataflows (order + 24 * (r + 2 f)),
-    // and the split of its items: chunks [0, d_ncc) are handed out as groups of whole tasks
-    // (d_gc groups per chunk), the chunks after them as groups of fifths of tasks (d_gf per chunk)
-    const uint32_t *cls;
-    uint32_t n_cls;
-    uint32_t d_ncc, d_gc, d_gf;
     const double *btab;
     const double *ctab_s;
     ModelConst mc;
@@ -567,13 +580,8 @@ struct SearchArgs {
     uint32_t *work_counter;
     FinalRecord *final_out;      // [N_OBJ]
     double e_limit;              // LIMIT kernels only: candidates with energy >= e_limit are left out
-    Key *final_key_dev;          // [N_OBJ] the winning keys once more, in device memory, for a pass that follows
-    const Key *lat_cap;          // LATCAP kernels only: candidates with a latency above lat_cap->p are left out
     const uint64_t *ctab_e;
     DivTable const *dv;          // device copy, for the final record's mapping
-    // k_search_dense, scalar keys: per key the lowest value any wave of the launch has recorded so far, as
-    // the bit pattern of the (non-negative) double; +inf between launches.  Null: no sharing between blocks.
-    unsigned long long *hints;
 };
 
 constexpr unsigned long long INF_BITS = 0x7ff0000000000000ull;
@@ -708,10 +716,11 @@ __device__ __forceinline__ void pin(double &x) { asm("" : "+v"(x)); }
 
 // Block and grid stages of the argmin: the waves' LDS slots -> one record per block -> ticket;
 // the last block to arrive reduces all records and writes the winner's cost and mapping.
-template <int MASK, int THREADS = SEARCH_THREADS>
-__device__ __forceinline__ void finish_grid(const SearchArgs &a, Key (*wave_best)[THREADS / 64],
+template <int MASK>
+__device__ __forceinline__ void finish_grid(const SearchArgs &a, Key (*wave_best)[SEARCH_THREADS / 64],
                                             uint32_t *is_last_flag)
 {
+    constexpr int THREADS = SEARCH_THREADS;
     const double inf = pos_inf();
     const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     __syncthreads();
@@ -763,7 +772,6 @@ __device__ __forceinline__ void finish_grid(const SearchArgs &a, Key (*wave_best
             if (key_less(wave_best[o][wv], k)) k = wave_best[o][wv];
         FinalRecord *fr = a.final_out + o;
         fr->key = k;
-        if (a.final_key_dev) a.final_key_dev[o] = k;
         mmee_cost c;
         mmee_mapping m;
         if (k.p < inf) {
@@ -784,7 +792,6 @@ __device__ __forceinline__ void finish_grid(const SearchArgs &a, Key (*wave_best
         for (int q = 0; q < 7; ++q) fr->map[q] = mbuf[q];
     }
     if (threadIdx.x == 0) { *a.ticket = 0; *a.work_counter = 0; }   // ready for the next launch on this stream
-    if (threadIdx.x < N_OBJ && a.hints) a.hints[threadIdx.x] = INF_BITS;
 }
 
 // MASK: bit0 energy, bit1 latency, bit2 latency-then-energy, bit3 energy-delay product (Sec. VII-K).
@@ -1111,445 +1118,6 @@ __global__ __launch_bounds__(SEARCH_THREADS, (popcount4(MASK) >= 3 || (MASK & 4 
         }
     }
     finish_grid<MASK>(a, wave_best, &is_last);
-}
-
-// ---------------------------------------------------------------------------
-// Exhaustive search over the full row set.
-//
-// The rows of one (order, r, f) class are the 5^4 buffering levels, and the selectors split: those of
-// A and B (buffer, retained, DRAM) depend on (p_A, p_B) only, those of D and E on (p_D, p_E) only,
-// those of C on the class (k_build_rows).  So here a lane is a tiling, a wave takes the 125 rows of a
-// (class, p_E) task, all selectors are wave-uniform, and a row is an (A, B) part shared by five rows next to a
-// (D, E) part held in registers.  All of these sums are exact integers below 2^53 (the host refuses workloads where
-// they are not), so their association is free, and a row needs no footprint of its own: it fits if the (A, B)
-// part does not exceed what the (D, E) part and C leave of the capacity, two comparisons.  Its energy (regrouped) or its
-// DRAM time, where a key needs only one of them, is one addition of the two parts' shares.  A row over capacity costs +inf, whatever the combination: its
-// lanes are masked out of the nine combinations, and a wave none of whose tilings the row fits passes over them.
-// Per (row, tiling) 3 operations before the nine combinations, whose per-tiling constants are lane registers for
-// the whole task, and 3/5 LDS reads.  With both footprints summed, their maximum, and the mask as selects it was 8
-// operations: 12544-tiling attention layer (8192 x 128, buffer 8 MiB), energy, 0.393 ms in the kernel, now 0.317; 10692-tiling
-// chain (2048 x 768 x 3072 x 768) with a buffer that everything fits 0.351 and 0.328, with one of 1 MiB 0.373 and 0.201.
-//
-// A block stages one chunk of TC tilings (stage_tables_direct below) and its waves take neighbouring tasks.
-// Persistent blocks, global work counter and grid finish as in k_search; the last chunks are handed
-// out in fifths of tasks (one p_D each) to even out the end.
-//
-// Registers decide the shape of the row loop.  One key: the 18 per-tiling constants, the (D, E) parts of all
-// five p_D values and nine minima fit 128 registers (four waves per SIMD).  Two keys together hold
-// 18 minima: there one p_D value at a time is kept, the (A, B) parts are read once per row instead of
-// once per five rows -- three LDS reads (12 cycles of the CU's LDS pipe) against the row's 41 operations
-// (164 cycles of each SIMD) -- and the parts' traffic is added before it is weighed, one operation less than two shares
-// per row.  Two p_D values at a time spill: energy and latency of a 4900-tiling layer 0.355 ms, 0.264 with one (0.307
-// with footprints and selects).
-constexpr int DENSE_THREADS = 512;           // eight waves, two blocks per CU
-constexpr int DENSE_BLOCKS_PER_CU = 2;
-constexpr int DENSE_WAVES = DENSE_THREADS / 64;
-
-// k_search_dense keeps its table slice as pairs of entries: the direct global-to-LDS load writes one
-// contiguous KiB per wave instruction (lane l's 16 bytes at base + 16 l), i.e. the 64 tilings of two
-// entries; 16 bytes of padding per pair spread the pairs over the banks for the reads that go across
-// entries.  Entry e of tiling t: tab[dense_at(e) + t].
-constexpr int DENSE_PAIRS = (NENT + 1) / 2;
-constexpr int DENSE_PAIR_F64 = 2 * TC + 2;
-__device__ __forceinline__ uint32_t dense_at(uint32_t e) { return e * (DENSE_PAIR_F64 / 2) - (e & 1u); }
-
-// The chunk's 64 tilings of every entry, straight from the global table into LDS: no registers, no
-// LDS write instructions, all of a wave's loads in flight at once.  Columns beyond the last tiling exist
-// in the global table (it is padded to whole chunks and repeats its last tiling there); so does the
-// entry after the last one of an odd count.
-// RAW: the DRAM terms without the B*H factor in the place of the scaled ones.
-template <int WAVES, bool RAW>
-__device__ __forceinline__ void stage_tables_direct(const SearchArgs &a, double *tab, uint32_t t0, uint32_t wave, uint32_t lane)
-{
-    static_assert(NENT + 1 <= NENT_ALL, "the pair of the last entry reads one entry beyond it");
-    for (uint32_t pair = wave; pair < (uint32_t)DENSE_PAIRS; pair += WAVES) {
-        const uint32_t place = 2 * pair + (lane >> 5);
-        const uint32_t e = RAW && place >= (uint32_t)ENT_DA_AB && place < (uint32_t)NENT ? place + ENT_RAW_DA : place;
-        const double *src = a.btab + (uint64_t)e * a.mc.tpad + t0 + 2 * (lane & 31);
-        __builtin_amdgcn_global_load_lds(src, tab + pair * DENSE_PAIR_F64, 16, 0, 0);
-    }
-    __builtin_amdgcn_s_waitcnt(0);               // the loads count as vector memory operations: all of them have landed
-}
-
-// SUM: how a candidate's energy is added up (ModelConst::regroup and gb_product_exact decide).  SUM_ORDERED forms it term by term,
-// 6 operations per candidate with the minimum; SUM_FUSED forms the first sum with one fused multiply-add whose
-// product is exact, i.e. with the bits of the two separate roundings; SUM_REGROUPED adds a row and a tiling part.
-// The energy key alone leaves the two addends that all candidates of a (tiling, r) share, the register-file
-// and MAC parts, to the nine minima: adding a constant and rounding keeps the order, so the minimum of the
-// finished sums is the finished sum of the minimum, bit for bit (OUTSIDE).  Per candidate that is addition,
-// multiplication, addition, minimum (4), with SUM_FUSED 3, with SUM_REGROUPED 2.  The kernel is bound by
-// VALU issue, so its time follows these counts: energy key of a 2048 x 768 x 3072 x 768 chain (3.6e9
-// candidates, a buffer that everything fits) 0.503 ms with four operations, 0.417 with three, 0.328 with two.
-//
-// FAST: the DRAM time is one exact multiply of the B*H-scaled traffic (ModelConst::dram_k).  Otherwise the table
-// slice holds the traffic per instance and the time is dram_time_general; a true division here cost
-// 1.2 to 5 times the whole rest of the loop (energy and latency of the chain above at 60 B/cycle: 2.05 ms, now 0.67).
-template <int MASK, bool FAST, bool LIMIT = false, int SUM = SUM_ORDERED, bool LATCAP = false>
-__global__ __launch_bounds__(DENSE_THREADS, 4) void k_search_dense(SearchArgs a)
-{
-    static_assert(!LATCAP || (MASK == 1 && !LIMIT), "the latency cap goes with the energy key alone");
-    constexpr bool REGROUP = SUM == SUM_REGROUPED;
-    static_assert(!(MASK & 4) && popcount4(MASK) <= 2, "one or two of the scalar keys");
-    constexpr bool OUTSIDE = !REGROUP && (MASK & 1) && !(MASK & 8) && !LIMIT;
-    constexpr bool ENERGY = MASK != (1 << MMEE_OBJ_LATENCY) || LIMIT, TIME = MASK != (1 << MMEE_OBJ_ENERGY) || LATCAP;
-    // What a row's costs need of its traffic.  The energy alone, or the time alone: a sum of the two parts' shares.  Both: the
-    // traffic itself, weighed per row, one operation more than two shares; with these the (D, E) parts of five p_D values
-    // are 20 doubles instead of 15 and 8 to 15 registers spill, which a short launch feels most (us per call: energy-delay product of
-    // 144 tilings 58, with two shares 72; of 1600 tilings 146 and 160; (latency, energy) of 1600 tilings 3 % apart).
-    constexpr bool E_SUMS = ENERGY && !TIME && REGROUP, L_SUMS = TIME && !ENERGY && FAST, WORDS = !E_SUMS && !L_SUMS;
-    constexpr uint32_t ROWS_PER_STEP = popcount4(MASK) == 2 ? 1u : 5u;       // p_D values held in registers
-    __shared__ double tab[DENSE_PAIRS * DENSE_PAIR_F64];
-    __shared__ Key wave_best[N_OBJ][DENSE_WAVES];
-    __shared__ uint32_t is_last;
-    __shared__ uint32_t s_item;
-    // Scalar keys: the lowest value any wave of this block has recorded (bit pattern; the keys are
-    // non-negative, so the patterns order like the values), refreshed once per item from the launch-wide
-    // one.  A wave whose values all lie strictly above it cannot hold the optimum and recovers no position.
-    __shared__ unsigned long long hint_bits[N_OBJ];
-
-    const double inf = pos_inf();
-    const uint32_t lane = threadIdx.x & 63;
-    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (lane < N_OBJ) { wave_best[lane][wave].p = inf; wave_best[lane][wave].s = 0.0; wave_best[lane][wave].idx = ~0ull; }
-    if (threadIdx.x < N_OBJ) hint_bits[threadIdx.x] = INF_BITS;
-    unsigned long long hint_seen[N_OBJ];          // thread 0: the launch-wide values as last read
-#pragma unroll
-    for (int o = 0; o < N_OBJ; ++o) hint_seen[o] = INF_BITS;
-    double run_p[N_OBJ];
-    uint64_t run_idx[N_OBJ];
-#pragma unroll
-    for (int o = 0; o < N_OBJ; ++o) { run_p[o] = inf; run_idx[o] = ~0ull; }
-    // encoded rows through the constant address space: wave-uniform row numbers, scalar loads
-    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    struct EncTable {
-        ConstPtr<u32x4> p;
-        __device__ __forceinline__ uint4 operator[](uint32_t row) const
-        {
-            const u32x4 v = p[row];
-            return make_uint4(v.x, v.y, v.z, v.w);
-        }
-    };
-    const EncTable enc = {(ConstPtr<u32x4>)a.enc};
-    ConstPtr<uint32_t> cls_list = as_constant(a.cls);
-    // Regrouped, the DRAM side of the energy is whole numbers throughout, and with FAST the DRAM time is a whole number
-    // times one exact constant: either is the sum of an (A, B) and a (D, E) share, formed once per part.
-    auto words_energy = [&](double words) { return FAST ? a.mc.e_sum * words : a.mc.e_sum * (words * a.mc.BH); };
-    // A row fits if neither operator's footprint exceeds the capacity: what the (D, E) part and C leave of it is formed
-    // once per task, a row compares its (A, B) part with that.  (Whole numbers below 2^53 throughout: exact.)
-    struct AbPart { double bs, ret, da, e, l; };
-    struct DePart { double room_bs, room_ret, da, e, l; };
-    // LATCAP: the second pass of the (latency, energy) key over the full row set.  The first pass found
-    // the lowest latency; a candidate's latency max(l_dram, constant) stays within it exactly when both
-    // parts do, so the cap masks rows and combinations separately and the pass costs what an
-    // energy-only pass costs.
-    const double lat_cap = LATCAP ? uniform_f64(a.lat_cap->p) : inf;
-
-    uint32_t upcoming = blockIdx.x;
-    while (true) {
-        if (threadIdx.x == 0) {
-            s_item = upcoming;
-            {
-                // exchange with the launch-wide values read during the previous item: take what is lower there,
-                // hand over what is lower here (no reply awaited)
-                if (a.hints) {
-#pragma unroll
-                    for (int o = 0; o < N_OBJ; ++o) {
-                        if (!((MASK >> o) & 1)) continue;
-                        const unsigned long long here = hint_bits[o];
-                        if (hint_seen[o] < here) atomicMin(&hint_bits[o], hint_seen[o]);
-                        else if (here < hint_seen[o])
-                            (void)__hip_atomic_fetch_min(a.hints + o, here, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    }
-                }
-            }
-        }
-        __syncthreads();                          // also: the previous item's LDS readers are done
-        const uint32_t item = s_item;
-        if (item >= a.n_items) break;
-        if (threadIdx.x == 0) {
-            upcoming = gridDim.x + __hip_atomic_fetch_add(a.work_counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            {
-                if (a.hints) {
-#pragma unroll
-                    for (int o = 0; o < N_OBJ; ++o)
-                        if ((MASK >> o) & 1) hint_seen[o] = __hip_atomic_load(a.hints + o, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                }
-            }
-        }
-        const bool fine = item >= a.n_coarse_items;
-        uint32_t chunk, group;
-        if (!fine) { chunk = item / a.d_gc; group = item % a.d_gc; }
-        else { const uint32_t j = item - a.n_coarse_items; chunk = a.d_ncc + j / a.d_gf; group = j % a.d_gf; }
-        const uint32_t t0 = chunk * TC;
-        const uint32_t nt = min((uint32_t)TC, a.mc.T - t0);
-        stage_tables_direct<DENSE_WAVES, !FAST>(a, tab, t0, wave, lane);
-        __syncthreads();
-
-        const uint32_t per_class = fine ? 25u : 5u;
-        const uint32_t task = group * DENSE_WAVES + wave;
-        if (task >= a.n_cls * per_class) continue;            // no barrier below: safe to leave early
-        const uint32_t cls = cls_list[task / per_class], part = task % per_class;
-        const uint32_t rank = cls % 24, g = cls / 24, r = g & 1;
-        const uint32_t pE = fine ? part / 5 : part, pd0 = fine ? part % 5 : 0u, npd = fine ? 1u : 5u;
-        const uint32_t row0 = 625u * rank + ROWS_PER_GROUP * g;         // (p_A, p_B, p_D, p_E) = 0
-        const uint32_t row_de0 = row0 + 25u * (pd0 + 5u * pE);          // first row of the task
-
-        // this lane's tiling: beyond the chunk, its last tiling once more, masked out by the capacity
-        const uint32_t tl = min(lane, nt - 1);
-        const double cap = lane < nt ? a.mc.cap_words : -1.0;
-        const double *cs = a.ctab_s + ((uint64_t)(t0 + tl) * 2 + r) * NCS;
-        double gb[9], latc[9];
-#pragma unroll
-        for (int c = 0; c < 9; ++c) { gb[c] = cs[c]; latc[c] = cs[9 + c]; }
-        const double e_rf_part = REGROUP ? 0.0 : cs[18], e_mac_part = REGROUP ? 0.0 : cs[19];
-        double too_slow[9];                                   // 0, or +inf for a combination beyond the cap
-#pragma unroll
-        for (int c = 0; c < 9; ++c) {
-            too_slow[c] = LATCAP && !(latc[c] <= lat_cap && lat_cap < inf) ? inf : 0.0;   // no cap found: nothing qualifies
-            if constexpr (LATCAP && REGROUP) gb[c] = fmax(gb[c], too_slow[c]);
-        }
-        const double *col = tab + tl;                         // entry e of this tiling: col[dense_at(e)]
-
-        // the class row and the task's (D, E) rows: all requested before the first is used
-        const uint4 e_c = enc[row0];
-        uint4 e_de[ROWS_PER_STEP];
-#pragma unroll
-        for (uint32_t q = 0; q < ROWS_PER_STEP; ++q) e_de[q] = enc[row_de0 + 25u * min(q, npd - 1)];
-        const double c_bs = col[dense_at(sel_of(e_c, 2))], c_da = col[dense_at(sel_of(e_c, 7))];
-
-        double bestE[9], bestL[9], bestP[9];
-#pragma unroll
-        for (int c9 = 0; c9 < 9; ++c9) bestE[c9] = bestL[c9] = bestP[c9] = inf;
-
-        // one row of this lane's tiling that fits: B*H * Eq. (7), then the nine combinations
-        auto cost_row = [&](const AbPart &x, const DePart &y) {
-            double e_part = 0.0, l_dram = 0.0, dram_words = 0.0;
-            if constexpr (E_SUMS) e_part = x.e + y.e;
-            if constexpr (L_SUMS) l_dram = x.l + y.l;
-            if constexpr (WORDS) {
-                const double traffic = x.da + y.da;
-                if constexpr (ENERGY && REGROUP) {
-                    if constexpr (!E_SUMS) e_part = words_energy(traffic);
-                } else if constexpr (ENERGY) {
-                    dram_words = FAST ? traffic : traffic * a.mc.BH;
-                    e_part = a.mc.e_dram * dram_words;
-                }
-                if constexpr (TIME && !L_SUMS) l_dram = FAST ? traffic * a.mc.dram_k : dram_time_general(a.mc, traffic);
-            }
-            if constexpr (LATCAP) {
-                if (!(l_dram <= lat_cap)) return;
-            }
-#pragma unroll
-            for (int c9 = 0; c9 < 9; ++c9) {
-                double en = 0.0;
-                if constexpr (ENERGY && REGROUP) {
-                    en = e_part + gb[c9];
-                } else if constexpr (ENERGY) {
-                    double gb_words = dram_words + gb[c9];
-                    if constexpr (SUM == SUM_FUSED) en = __builtin_fma(a.mc.e_gb, gb_words, e_part);
-                    else en = e_part + a.mc.e_gb * gb_words;
-                    if constexpr (!OUTSIDE) {
-                        en = en + e_rf_part;
-                        en = en + e_mac_part;
-                    }
-                    if constexpr (LATCAP) en = fmax(en, too_slow[c9]);
-                }
-                double lat = fmax(l_dram, latc[c9]);
-                if constexpr (LIMIT) {
-                    bool out_of_range = !(en < a.e_limit);
-                    en = out_of_range ? inf : en;
-                    lat = out_of_range ? inf : lat;
-                }
-                if constexpr (MASK & 8) bestP[c9] = fmin(bestP[c9], en * lat);
-                if constexpr (MASK & 1) bestE[c9] = fmin(bestE[c9], en);
-                if constexpr (MASK & 2) bestL[c9] = fmin(bestL[c9], lat);
-            }
-        };
-
-        // (D, E) parts of up to ROWS_PER_STEP p_D values in registers, the class's C terms riding on them; the
-        // (A, B) parts are read one step ahead of their use and their selectors one step ahead of that
-        for (uint32_t q0 = 0;;) {
-            DePart y[ROWS_PER_STEP];
-#pragma unroll
-            for (uint32_t q = 0; q < ROWS_PER_STEP; ++q) {
-                y[q].room_bs = cap - (c_bs + col[dense_at(sel_of(e_de[q], 1))]);
-                y[q].room_ret = cap - (col[dense_at(sel_of(e_de[q], 3))] + c_bs);
-                y[q].da = c_da + col[dense_at(sel_of(e_de[q], 6))];
-                if constexpr (E_SUMS) y[q].e = words_energy(y[q].da);
-                if constexpr (L_SUMS) y[q].l = y[q].da * a.mc.dram_k;
-            }
-            double x_bs = col[dense_at(sel_of(e_c, 0))], x_ret = col[dense_at(sel_of(e_c, 4))],
-                   x_da = col[dense_at(sel_of(e_c, 5))];                  // row0 is (p_A, p_B) = 0
-            uint4 e_ab = enc[row0 + 1];
-            // the loop over (p_A, p_B), for a whole step of p_D values or for one
-            auto ab_loop = [&](auto count) {
-                constexpr int N = decltype(count)::value;
-#pragma unroll 5
-                for (uint32_t ab = 0; ab < 25; ++ab) {
-                    AbPart x;
-                    x.bs = x_bs; x.ret = x_ret; x.da = x_da;
-                    if constexpr (E_SUMS) { x.e = words_energy(x_da); pin(x.e); }
-                    if constexpr (L_SUMS) { x.l = x_da * a.mc.dram_k; pin(x.l); }
-                    x_bs = col[dense_at(sel_of(e_ab, 0))];
-                    x_ret = col[dense_at(sel_of(e_ab, 4))];
-                    x_da = col[dense_at(sel_of(e_ab, 5))];
-                    e_ab = enc[row0 + min(ab + 2, 24u)];
-#pragma unroll
-                    for (int q = 0; q < N; ++q)
-                        if ((x.bs <= y[q].room_bs) & (x.ret <= y[q].room_ret)) cost_row(x, y[q]);
-                }
-            };
-            if (q0 + ROWS_PER_STEP <= npd) ab_loop(std::integral_constant<int, ROWS_PER_STEP>{});
-            else ab_loop(std::integral_constant<int, 1>{});
-            q0 += ROWS_PER_STEP;
-            if (ROWS_PER_STEP == 5 || q0 >= npd) break;
-#pragma unroll
-            for (uint32_t q = 0; q < ROWS_PER_STEP; ++q) e_de[q] = enc[row_de0 + 25u * min(q0 + q, npd - 1)];
-        }
-
-        if constexpr (OUTSIDE) {
-#pragma unroll
-            for (int c9 = 0; c9 < 9; ++c9) bestE[c9] = (bestE[c9] + e_rf_part) + e_mac_part;
-        }
-
-        // index row (Sec. VI-A numbering) of the task's row number `code`, combination 0
-        auto index_row_of = [&](uint32_t code) { return index_row_base(row_de0 + 25u * (code / 25u) + code % 25u); };
-
-        {
-#pragma unroll
-            for (int o = 0; o < N_OBJ; ++o) {
-                if (!((MASK >> o) & 1)) continue;
-                const double *best = o == 0 ? bestE : (o == 1 ? bestL : bestP);
-                double mine_v = best[0];
-#pragma unroll
-                for (int c9 = 1; c9 < 9; ++c9) mine_v = fmin(mine_v, best[c9]);
-                const double hint = __longlong_as_double((long long)hint_bits[o]);
-                if (!__ballot(mine_v <= run_p[o] && mine_v < inf && mine_v <= hint)) continue;   // the usual case: nothing new here
-                const double wave_v = uniform_f64(wave_min_f64(mine_v));
-                // the lowest combination in which some tiling reaches the minimum: its candidates
-                // precede those of every higher combination
-                uint32_t cstar = 9;
-#pragma unroll
-                for (int c9 = 8; c9 >= 0; --c9) cstar = best[c9] == wave_v ? (uint32_t)c9 : cstar;
-                const uint32_t c_u = __builtin_amdgcn_readfirstlane(wave_min_u32(cstar));
-                const uint32_t combo_rows = 30000u * (c_u % 3) + 90000u * (c_u / 3);
-                const uint64_t lowest_possible = (uint64_t)t0 + (uint64_t)a.mc.T * (index_row_of(0) + combo_rows);
-                if (!(wave_v < run_p[o] || lowest_possible < run_idx[o])) continue;
-                // Make the value known before its position is: of the waves of a block that reach this point
-                // together, only those holding the lowest value go on (the holder of the lowest value always
-                // passes its own mark, so what the others leave out is recorded by it).
-                if (lane == 0) atomicMin(&hint_bits[o], (unsigned long long)__double_as_longlong(wave_v));
-                if (wave_v > __longlong_as_double((long long)hint_bits[o])) continue;
-                // Recover the row: the first row of the task (index order) in which a tiling reaches the
-                // minimum under combination c_u holds the lowest index, at its lowest such tiling.  Rows are
-                // costed again with the very operations of the loop above.
-                double gb_u = gb[0], latc_u = latc[0], slow_u = too_slow[0], best_u = best[0];
-#pragma unroll
-                for (int c9 = 1; c9 < 9; ++c9) {
-                    gb_u = c_u == (uint32_t)c9 ? gb[c9] : gb_u;
-                    latc_u = c_u == (uint32_t)c9 ? latc[c9] : latc_u;
-                    slow_u = c_u == (uint32_t)c9 ? too_slow[c9] : slow_u;
-                    best_u = c_u == (uint32_t)c9 ? best[c9] : best_u;
-                }
-                // one row of one tiling: table values x (A, B), y (D, E), the class's C terms, the tiling's constants
-                auto recost = [&](double x_bs, double x_ret, double x_da, double y_ret, double y_bs, double y_da, double cbs,
-                                  double cda, double cap_t, double gb_t, double latc_t, double slow_t, double rf_t, double mac_t) {
-                    const double bs1 = (x_bs + cbs) + y_ret;
-                    const double bs2 = y_bs + (cbs + x_ret);
-                    const double traffic2 = x_da + (cda + y_da);
-                    const double dram2 = FAST ? traffic2 : traffic2 * a.mc.BH;
-                    bool ok2 = fmax(bs1, bs2) <= cap_t;
-                    // (regrouped: the very sum of the loop, also where a total taken on trust is not exact)
-                    double e2 = !REGROUP ? a.mc.e_dram * dram2 : (E_SUMS ? words_energy(x_da) + words_energy(cda + y_da) : words_energy(traffic2));
-                    double l2;
-                    if constexpr (FAST) l2 = traffic2 * a.mc.dram_k;
-                    else l2 = dram_time_general(a.mc, traffic2);
-                    if constexpr (LATCAP) ok2 = ok2 & (l2 <= lat_cap);
-                    const double over2 = __hiloint2double(ok2 ? 0 : 0x7ff00000, 0);
-                    e2 = fmax(e2, over2);
-                    l2 = fmax(l2, over2);
-                    pin(e2);
-                    pin(l2);
-                    double en2;
-                    if constexpr (REGROUP) {
-                        en2 = e2 + gb_t;
-                    } else {
-                        double gb2 = dram2 + gb_t;
-                        en2 = e2 + a.mc.e_gb * gb2;
-                        en2 = en2 + rf_t;
-                        en2 = en2 + mac_t;
-                        if constexpr (LATCAP) en2 = fmax(en2, slow_t);
-                    }
-                    double lat2 = fmax(l2, latc_t);
-                    if constexpr (LIMIT) {
-                        const bool out_of_range = !(en2 < a.e_limit);
-                        en2 = out_of_range ? inf : en2;
-                        lat2 = out_of_range ? inf : lat2;
-                    }
-                    return o == 0 ? en2 : (o == 1 ? lat2 : en2 * lat2);
-                };
-                const uint32_t n_codes = npd * 25u;
-                uint32_t found_code = 0xFFFFFFFFu, found_lane = 0;
-                // only a tiling whose own minimum under c_u is the wave's can hold it
-                unsigned long long cands = __ballot(best_u == wave_v);
-                if (__popcll(cands) <= 4) {
-                    // few such tilings: one at a time with lane = row (64 rows of the task per step)
-                    while (cands) {
-                        const uint32_t l = __builtin_amdgcn_readfirstlane((uint32_t)__ffsll((long long)cands) - 1u);
-                        cands &= cands - 1;
-                        const double *col_l = tab + l;                  // l < nt: a lane beyond the chunk holds +inf
-                        const double cbs_l = lane_value_f64(c_bs, l), cda_l = lane_value_f64(c_da, l);
-                        const double gb_l = lane_value_f64(gb_u, l), latc_l = lane_value_f64(latc_u, l), slow_l = lane_value_f64(slow_u, l);
-                        const double rf_l = lane_value_f64(e_rf_part, l), mac_l = lane_value_f64(e_mac_part, l);
-                        for (uint32_t code0 = 0; code0 < n_codes && code0 < found_code; code0 += 64) {
-                            const uint32_t code = min(code0 + lane, n_codes - 1);
-                            const uint4 e_de = a.enc[row_de0 + 25u * (code / 25u)];
-                            const uint4 e_ab = a.enc[row0 + code % 25u];
-                            const double val2 = recost(col_l[dense_at(sel_of(e_ab, 0))], col_l[dense_at(sel_of(e_ab, 4))],
-                                                       col_l[dense_at(sel_of(e_ab, 5))], col_l[dense_at(sel_of(e_de, 1))],
-                                                       col_l[dense_at(sel_of(e_de, 3))], col_l[dense_at(sel_of(e_de, 6))], cbs_l, cda_l,
-                                                       a.mc.cap_words, gb_l, latc_l, slow_l, rf_l, mac_l);
-                            const unsigned long long hits = __ballot(code0 + lane < n_codes && val2 == wave_v);
-                            if (!hits) continue;
-                            const uint32_t c_hit = code0 + (uint32_t)__ffsll((long long)hits) - 1u;
-                            if (c_hit < found_code) { found_code = c_hit; found_lane = l; }   // ascending tilings: the lower one stays
-                            break;
-                        }
-                        if (found_code == 0) break;
-                    }
-                } else {
-                    for (uint32_t code = 0; code < n_codes; ++code) {
-                        const uint4 e_de = enc[row_de0 + 25u * (code / 25u)];
-                        const uint4 e_ab = enc[row0 + code % 25u];
-                        const double val2 = recost(col[dense_at(sel_of(e_ab, 0))], col[dense_at(sel_of(e_ab, 4))],
-                                                   col[dense_at(sel_of(e_ab, 5))], col[dense_at(sel_of(e_de, 1))],
-                                                   col[dense_at(sel_of(e_de, 3))], col[dense_at(sel_of(e_de, 6))], c_bs, c_da, cap,
-                                                   gb_u, latc_u, slow_u, e_rf_part, e_mac_part);
-                        const unsigned long long hits = __ballot(val2 == wave_v);
-                        if (!hits) continue;
-                        found_code = code;
-                        found_lane = (uint32_t)__ffsll((long long)hits) - 1u;
-                        break;
-                    }
-                }
-                if (found_code != 0xFFFFFFFFu) {
-                    const uint64_t idx = (uint64_t)t0 + found_lane + (uint64_t)a.mc.T * (index_row_of(found_code) + combo_rows);
-                    if (wave_v < run_p[o] || idx < run_idx[o]) { run_p[o] = wave_v; run_idx[o] = idx; }
-                }
-            }
-        }
-    }
-
-    {
-        if (lane == 0) {
-#pragma unroll
-            for (int o = 0; o < N_OBJ; ++o) {
-                if (!((MASK >> o) & 1)) continue;
-                wave_best[o][wave].p = run_p[o]; wave_best[o][wave].s = 0.0; wave_best[o][wave].idx = run_idx[o];
-            }
-        }
-    }
-    finish_grid<MASK, DENSE_THREADS>(a, wave_best, &is_last);
 }
 
 // One step of the buffer-size / DRAM-access front (Sec. VII-C): the (buffer size, DRAM access,

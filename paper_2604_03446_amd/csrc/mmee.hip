@@ -17,6 +17,7 @@
 #include "batch.h"
 #include "pruned.h"
 #include "fronts.h"
+#include "dense.h"
 #include "pinned.h"
 
 // ---- fixed scratch of the entry point that allocates nothing (mmee_search_noalloc) ------------
@@ -553,7 +554,7 @@ void launch_search_limited(bool exact_k, dim3 grid, const SearchArgs &a)
 // candidates with energy below a.e_limit (first pass of a step of the Pareto walk).  LATCAP: only those with a
 // latency within a.lat_cap (second pass of the (latency, energy) key).
 template <int MASK, bool LIMIT = false, bool LATCAP = false>
-void launch_dense(bool exact_k, dim3 grid, const SearchArgs &a)
+void launch_dense(bool exact_k, dim3 grid, const DenseArgs &a)
 {
     // keys that do not look at the energy or at the DRAM time need one variant only
     constexpr bool ENERGY = MASK != (1 << MMEE_OBJ_LATENCY) || LIMIT, TIME = MASK != MASK_ENERGY || LATCAP;
@@ -605,6 +606,88 @@ uint32_t dense_from(int mask, bool exact_k, const ModelConst &mc)
     return 0;
 }
 
+uint32_t list_length(const DivTable &dv);
+void pack_lists(const DivTable &dv, uint32_t *list);
+void shape_constants(const DivTable &dv, double (&extent)[4], double (&size)[5]);
+
+// One pass of these keys over the full row set in k_search_dense, or two or three (the launches share the arguments).
+int enqueue_dense(const Bufs &B, const Plan &p, const ModelConst &mc, int mask, const double *e_limit)
+{
+    if (list_length(p.dv) > DENSE_DIVS) return MMEE_EINVAL;
+    DenseArgs a;
+    std::memset(&a, 0, sizeof(a));
+    a.mc = mc;
+    // a chunk's tilings: k's divisors fastest, then j's, l's, i's
+    const int radix_order[4] = {DK, DJ, DL, DI};
+    double radix = 1.0;
+    for (int q : radix_order) {
+        a.dg.rcp_radix[q] = 1.0 / radix;
+        a.dg.rcp_n[q] = 1.0 / (double)p.dv.ndiv[q];
+        radix *= (double)p.dv.ndiv[q];
+    }
+    shape_constants(p.dv, a.extent, a.size);
+    for (int q = 0; q < 4; ++q) { a.X[q] = p.dv.X[q]; a.ndiv[q] = p.dv.ndiv[q]; }
+    pack_lists(p.dv, a.list);
+    a.enc = B.enc; a.cls = B.cls_dev; a.n_cls = B.n_cls;
+    const uint32_t n_chunks = (uint32_t)((p.T + PRUNED_TC - 1) / PRUNED_TC), blocks = B.resident_blocks / BLOCKS_PER_CU * DENSE_BLOCKS_PER_CU;
+    // Items: three quarters of the chunks in items of a quarter of a block's share of the tasks, a fifth in items a third as large, the
+    // rest in the smallest.  Every item costs a block some 2 us (its tables, and waves that wait for its last task), every task
+    // too many at the end all blocks up to 19 us.  us a call, so / all items a quarter of a block's share / an eighth / a twentieth: 12544
+    // tilings (8192 x 128), energy 251 / 273 / 272 / 305; 4900 tilings (512 x 64), energy and latency 259 / 275 / 277 / 302.
+    const double per_block = (double)n_chunks * B.n_cls * 5.0 / blocks, share[3] = {0.75, 0.2, 1.0}, part[3] = {0.25, 0.08, 0.03};
+    uint64_t n_items = 0;
+    uint32_t chunk = 0;
+    for (int k = 0; k < 3; ++k) {
+        const double tasks = std::max(part[k] * per_block, 1.6);
+        DenseArgs::Phase &ph = a.phase[k];
+        ph.item = (uint32_t)n_items; ph.chunk = chunk;
+        ph.groups = std::max(1u, (uint32_t)(B.n_cls * 5.0 / tasks));
+        const uint32_t n = std::min(n_chunks - chunk, (uint32_t)(share[k] * n_chunks));
+        chunk += n;
+        n_items += (uint64_t)n * ph.groups;
+    }
+    if (n_items > 0x7fffffffull) return MMEE_EINVAL;
+    a.n_items = (uint32_t)n_items;
+    // persistent blocks: as many as the chip holds at once
+    const dim3 grid((uint32_t)std::min<uint64_t>(n_items, blocks));
+    if (grid.x > B.partials_cap) return MMEE_EINVAL;
+    a.partials = B.partials; a.ticket = B.ticket; a.work_counter = B.ticket + 1; a.hints = B.hints;
+    a.final_out = B.final_dev;
+    // The (latency, energy) key over the full row set is two passes that each cost what a single scalar
+    // key costs: the lowest latency first, then the lowest energy among the candidates that reach it (a
+    // candidate's latency is a maximum of a row part and a combination part, so the cap applies to the
+    // two separately).  The second pass's energy record lands in the slot of this key.  The first pass
+    // serves the latency key as well.  Of the scalar keys two go together in one pass (energy and latency of
+    // the 2048 x 768 x 3072 x 768 chain: 0.347 ms, in two passes 0.397; with a buffer that everything fits 0.595 and
+    // 0.649), a third takes a pass of its own.
+    const bool lex = mask & 4;
+    a.final_key_dev = B.key_dev;
+    if (e_limit) {
+        // two scalar passes, as for the unbounded key; the second needs no energy bound: the
+        // lowest energy among the candidates within the latency found is below it
+        if (mask != 4) return MMEE_EINVAL;
+        a.e_limit = *e_limit;
+        launch_dense<2, true>(p.exact_k, grid, a);
+    } else
+        switch ((mask & 11) | (lex ? 2 : 0)) {
+        case 1: launch_dense<1>(p.exact_k, grid, a); break;
+        case 2: launch_dense<2>(p.exact_k, grid, a); break;
+        case 8: launch_dense<8>(p.exact_k, grid, a); break;
+        case 9: launch_dense<9>(p.exact_k, grid, a); break;
+        case 10: launch_dense<10>(p.exact_k, grid, a); break;
+        default: launch_dense<3>(p.exact_k, grid, a); break;
+        }
+    a.final_key_dev = nullptr;
+    if (lex) {
+        DenseArgs second = a;
+        second.lat_cap = B.key_dev + 1;
+        second.final_out = a.final_out + 2;
+        launch_dense<1, false, true>(p.exact_k, grid, second);
+    }
+    if (!e_limit && ((mask & 11) | (lex ? 2 : 0)) == 11) launch_dense<8>(p.exact_k, grid, a);
+    return MMEE_OK;
+}
+
 // enqueue one pass (tables + search; the final records land in b.final_dev) in the buffers b
 int enqueue_search_in(const Bufs &B, const Plan &p, int mask, uint32_t flags, uint64_t *evaluated,
                       const double *e_limit = nullptr, bool build_tables = true, bool bs_da_step = false,
@@ -618,6 +701,17 @@ int enqueue_search_in(const Bufs &B, const Plan &p, int mask, uint32_t flags, ui
     if (dense && p.T < dense_from(mask, p.exact_k, mc)) {
         dense = false;
         mc = pass_constants(p, flags, mask, unproven);
+    }
+    if (dense) {
+        uint64_t nrows = 0;
+        for (int g = 0; g < 4; ++g) nrows += B.counts[0][g];
+        if (B.ev_begin) HIP_TRY(hipEventRecord(B.ev_begin, S.stream));
+        const int drc = enqueue_dense(B, p, mc, mask, e_limit);
+        if (drc) return drc;
+        HIP_TRY(hipGetLastError());
+        if (B.ev_end) HIP_TRY(hipEventRecord(B.ev_end, S.stream));
+        *evaluated = nrows * p.T * 9ull;
+        return MMEE_OK;
     }
     int rc = build_tables ? launch_tilings(p, mc, B, B.dv_dev) : MMEE_OK;
     if (rc) return rc;
@@ -659,29 +753,14 @@ int enqueue_search_in(const Bufs &B, const Plan &p, int mask, uint32_t flags, ui
     }
     a.btab = B.btab; a.ctab_s = B.ctab_s; a.ctab_e = B.ctab_e;
     a.mc = mc;
-    uint64_t n_items;
-    if (dense) {
-        a.cls = B.cls_dev; a.n_cls = B.n_cls;
-        const uint32_t n_chunks = (uint32_t)((p.T + TC - 1) / TC);
-        a.d_gc = (B.n_cls * 5 + DENSE_WAVES - 1) / DENSE_WAVES;
-        a.d_gf = (B.n_cls * 25 + DENSE_WAVES - 1) / DENSE_WAVES;
-        // fifths of tasks for the last chunks: about one whole-task item per resident block
-        const uint32_t dense_blocks = B.resident_blocks / BLOCKS_PER_CU * DENSE_BLOCKS_PER_CU;
-        const uint32_t fine_chunks = std::min<uint32_t>(n_chunks, (dense_blocks + a.d_gc - 1) / a.d_gc);
-        a.d_ncc = n_chunks - fine_chunks;
-        a.n_coarse_items = a.d_ncc * a.d_gc;
-        n_items = (uint64_t)a.n_coarse_items + (uint64_t)fine_chunks * a.d_gf;
-    } else {
-        n_items = (uint64_t)rb * ((uint64_t)a.n_cc + a.n_fc);
-        a.n_coarse_items = rb * a.n_cc;
-    }
+    const uint64_t n_items = (uint64_t)rb * ((uint64_t)a.n_cc + a.n_fc);
+    a.n_coarse_items = rb * a.n_cc;
     if (n_items == 0 || n_items > 0x7fffffffull) return MMEE_EINVAL;
     a.n_items = (uint32_t)n_items;
     // persistent blocks: as many as the chip holds at once (LDS allows two per CU)
-    const uint64_t nblocks = std::min<uint64_t>(
-        n_items, dense ? (uint64_t)B.resident_blocks / BLOCKS_PER_CU * DENSE_BLOCKS_PER_CU : (uint64_t)B.resident_blocks);
+    const uint64_t nblocks = std::min<uint64_t>(n_items, (uint64_t)B.resident_blocks);
     if (nblocks > B.partials_cap) return MMEE_EINVAL;
-    a.partials = B.partials; a.ticket = B.ticket; a.work_counter = B.ticket + 1; a.hints = B.hints;
+    a.partials = B.partials; a.ticket = B.ticket; a.work_counter = B.ticket + 1;
     a.final_out = B.final_dev;
     a.dv = B.dv_dev;
     if (B.ev_begin) HIP_TRY(hipEventRecord(B.ev_begin, S.stream));
@@ -693,46 +772,8 @@ int enqueue_search_in(const Bufs &B, const Plan &p, int mask, uint32_t flags, ui
     } else if (e_limit) {
         if (mask != 4) return MMEE_EINVAL;
         a.e_limit = *e_limit;
-        if (dense) {
-            // two scalar passes, as for the unbounded key below; the second needs no energy bound: the
-            // lowest energy among the candidates within the latency found is below it
-            SearchArgs first = a, second = a;
-            first.final_key_dev = B.key_dev;
-            launch_dense<2, true>(p.exact_k, grid, first);
-            second.lat_cap = B.key_dev + 1;
-            second.final_out = a.final_out + 2;
-            launch_dense<1, false, true>(p.exact_k, grid, second);
-        } else
-            launch_search_limited(p.exact_k, grid, a);
-    } else if (dense) {
-        // The (latency, energy) key over the full row set is two passes that each cost what a single scalar
-        // key costs: the lowest latency first, then the lowest energy among the candidates that reach it (a
-        // candidate's latency is a maximum of a row part and a combination part, so the cap applies to the
-        // two separately).  The second pass's energy record lands in the slot of this key.  The first pass
-        // serves the latency key as well.  Of the scalar keys two go together in one pass (energy and latency of
-        // the 2048 x 768 x 3072 x 768 chain: 0.347 ms, in two passes 0.397; with a buffer that everything fits 0.595 and
-        // 0.649), a third takes a pass of its own.
-        const bool lex = mask & 4;
-        const int scalar = (mask & 11) | (lex ? 2 : 0);
-        SearchArgs first = a;
-        first.final_key_dev = B.key_dev;
-        switch (scalar) {
-        case 1: launch_dense<1>(p.exact_k, grid, first); break;
-        case 2: launch_dense<2>(p.exact_k, grid, first); break;
-        case 8: launch_dense<8>(p.exact_k, grid, first); break;
-        case 9: launch_dense<9>(p.exact_k, grid, first); break;
-        case 10: launch_dense<10>(p.exact_k, grid, first); break;
-        default: launch_dense<3>(p.exact_k, grid, first); break;
-        }
-        if (lex) {
-            SearchArgs second = a;
-            second.lat_cap = B.key_dev + 1;
-            second.final_out = a.final_out + 2;
-            launch_dense<1, false, true>(p.exact_k, grid, second);
-        }
-        if (scalar == 11) launch_dense<8>(p.exact_k, grid, a);
-    }
-    else
+        launch_search_limited(p.exact_k, grid, a);
+    } else
     switch (mask) {
     case 1: launch_search_mask<1>(p.exact_k, grid, a); break;
     case 2: launch_search_mask<2>(p.exact_k, grid, a); break;

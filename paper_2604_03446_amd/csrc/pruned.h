@@ -41,8 +41,6 @@ constexpr int PRUNED_MEMBERS = 64;           // problems of one group at most
 constexpr int PRUNED_ROUND = 16;             // capacities per round of a shared chunk
 constexpr int PRUNED_INLINE = 3000;          // bytes of problem descriptions that ride in the kernel arguments
 
-typedef ConstPtr<unsigned char> ConstBytes;
-
 // A group: problems with one shape and tiling mode.  Offsets are bytes from the start of the descriptions.
 struct PrunedGroup {
     uint32_t first_item, n_items;            // its work items, one block each
@@ -84,17 +82,6 @@ __device__ __forceinline__ ConstBytes pruned_desc(const PrunedArgs &a)
 {
     if (a.desc) return as_constant(a.desc);
     return (ConstBytes)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(PrunedArgs, inl);
-}
-template <class T>
-__device__ __forceinline__ T read_const(ConstBytes p)        // wave-uniform: scalar loads
-{
-    static_assert(sizeof(T) % 4 == 0, "whole words");
-    uint32_t buf[sizeof(T) / 4];
-#pragma unroll
-    for (uint32_t k = 0; k < sizeof(T) / 4; ++k) buf[k] = ((ConstPtr<uint32_t>)p)[k];
-    T out;
-    __builtin_memcpy(&out, buf, sizeof(T));
-    return out;
 }
 
 // ---- step 1: the least traffic of a class ------------------------------------------------------
@@ -551,8 +538,7 @@ __global__ __launch_bounds__(PRUNED_THREADS, 4) void k_search_pruned(PrunedArgs 
             ClassBest b;
             b.p = uniform_f64(best[j][o].p); b.s = uniform_f64(best[j][o].s);
             b.code = __builtin_amdgcn_readfirstlane(code_of[j][o]);
-            const unsigned long long who = lanes_of[j][o];
-            b.lanes = ((unsigned long long)__builtin_amdgcn_readfirstlane((uint32_t)(who >> 32)) << 32) | __builtin_amdgcn_readfirstlane((uint32_t)who);
+            b.lanes = uniform_u64(lanes_of[j][o]);
             if (o == MMEE_OBJ_ENERGY) {
                 // the lowest class in which one of these tilings has it
                 RowSide rs[LEAST_CLASSES];
