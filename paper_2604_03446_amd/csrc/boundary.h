@@ -87,7 +87,7 @@ __device__ __forceinline__ ComboTerms combo_terms(const TilingF &v, const double
 // entry of a known kind, so an entry is two footprints and a sum: a switch over all kinds per selector, and the
 // tiling's digits once for the cost and once for the mapping, were three times the instructions, which a winner's lone thread
 // waits for one cache line after the other.
-__device__ __forceinline__ void eval_candidate_direct(const uint4 *enc, const DivTable &dv, const ModelConst &mc, const mmee_mapping &m,
+__device__ __forceinline__ void eval_candidate_direct(const uint4 *enc, const uint32_t (&extent)[4], const ModelConst &mc, const mmee_mapping &m,
                                                       mmee_cost &c)
 {
     uint32_t row, t;
@@ -103,7 +103,7 @@ __device__ __forceinline__ void eval_candidate_direct(const uint4 *enc, const Di
     TilingF v;
 #pragma unroll
     for (int q = 0; q < 4; ++q) { v.G[q] = (double)m.xG[q]; v.D[q] = (double)m.xD[q]; }
-    const double X[4] = {(double)dv.X[0], (double)dv.X[1], (double)dv.X[2], (double)dv.X[3]};
+    const double X[4] = {(double)extent[0], (double)extent[1], (double)extent[2], (double)extent[3]};
     // layout.h: the pairs' options are packed by fours, those of the retained ones by fives (4: not retained)
     auto bs_of = [&](int one, int two, uint32_t opt) { return footprint(v.G[one] * v.G[two], v.D[one], v.D[two], opt); };
     auto da_of = [&](int own0, int own1, int n0, int n1, uint32_t opt) { return footprint(X[own0] * X[own1], v.D[n0], v.D[n1], opt); };
@@ -219,13 +219,7 @@ __device__ __forceinline__ void stage_kept(double *tab_lane, uint32_t wave, cons
 }
 
 // X / g for a divisor g of X < 2^32: the reciprocal to about fifty bits, and rounding to the whole number there is
-__device__ __forceinline__ double whole_quotient(double X, double g)
-{
-    double y = __builtin_amdgcn_rcp(g);
-    y = __builtin_fma(__builtin_fma(-g, y, 1.0), y, y);
-    y = __builtin_fma(__builtin_fma(-g, y, 1.0), y, y);
-    return __builtin_rint(X * y);
-}
+__device__ __forceinline__ double whole_quotient(double X, double g) { return __builtin_rint(X * reciprocal(g)); }
 
 // Digit q of a tiling number.  Quotients by reciprocals (t < 2^22, radix <= 2^22: t + 0.5
 // over a whole number stays 2^-23 away from whole numbers, the rounding errors are far below that).
@@ -238,21 +232,27 @@ __device__ __forceinline__ uint32_t digit_of(uint32_t t, double rcp_radix, doubl
 }
 
 // a winner's record
-__device__ __forceinline__ void winner_record(const uint4 *enc, const DivTable &dv, const ModelConst &mc, const Key &k, mmee_result &res)
+template <class Div>
+__device__ __forceinline__ void winner_record_with(const uint4 *enc, const uint32_t (&X)[4], const uint32_t (&ndiv)[4], Div &&div, const ModelConst &mc,
+                                                   const Key &k, mmee_result &res)
 {
     __builtin_memset(&res, 0, sizeof(res));
     if (k.p < pos_inf()) {
-        decode_candidate(dv, mc.T, k.idx, res.best);
-        eval_candidate_direct(enc, dv, mc, res.best, res.cost);
+        decode_candidate_with(X, ndiv, div, mc.T, k.idx, res.best);
+        eval_candidate_direct(enc, X, mc, res.best, res.cost);
     } else {
         res.cost.energy_pj = pos_inf(); res.cost.latency_cycles = pos_inf();
         res.best.idx = ~0ull;
     }
 }
-// Behind a record's last store, by the thread that made it (or one that has met all that did, each past a system-wide fence).
-__device__ __forceinline__ void say_done(Done *done, uint64_t number, const uint64_t *begin)
+__device__ __forceinline__ void winner_record(const uint4 *enc, const DivTable &dv, const ModelConst &mc, const Key &k, mmee_result &res)
 {
-    done->ticks = wall_clock64() - *begin;
+    winner_record_with(enc, dv.X, dv.ndiv, [&](int q, uint32_t digit) { return dv.div[q][digit]; }, mc, k, res);
+}
+// Behind a record's last store, by the thread that made it (or one that has met all that did, each past a system-wide fence).
+__device__ __forceinline__ void say_done(Done *done, uint64_t number, uint64_t began)
+{
+    done->ticks = wall_clock64() - began;
     __hip_atomic_store(&done->number, number, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 __device__ __forceinline__ void write_record(FinalRecord *fr, const Key &k, const mmee_result &res)

@@ -618,7 +618,7 @@ __global__ __launch_bounds__(MERGE_THREADS) void k_front_merge(FrontArgs a)
         if (threadIdx.x == 0) {
             a.n_out[0] = TOO_MANY;
             a.n_out[1] = way;
-            say_done(a.done, a.number, a.begin);
+            say_done(a.done, a.number, *a.begin);
         }
         return;
     }
@@ -639,7 +639,7 @@ __global__ __launch_bounds__(MERGE_THREADS) void k_front_merge(FrontArgs a)
     if (threadIdx.x == 0) {
         a.n_out[0] = n;
         a.n_out[1] = way;
-        say_done(a.done, a.number, a.begin);
+        say_done(a.done, a.number, *a.begin);
     }
 }
 

@@ -468,16 +468,31 @@ __device__ __forceinline__ void split_index(uint64_t idx, uint32_t T, uint32_t &
     t = (uint32_t)rest;
 }
 
-__device__ __forceinline__ void decode_candidate(const DivTable &dv, uint32_t T, uint64_t idx, mmee_mapping &m)
+// 1 / g to about fifty bits, for a whole number 1 <= g < 2^32
+__device__ __forceinline__ double reciprocal(double g)
+{
+    double y = __builtin_amdgcn_rcp(g);
+    y = __builtin_fma(__builtin_fma(-g, y, 1.0), y, y);
+    return __builtin_fma(__builtin_fma(-g, y, 1.0), y, y);
+}
+
+// div(q, digit): the divisor lists, wherever they are
+template <class Div>
+__device__ __forceinline__ void decode_candidate_with(const uint32_t (&X)[4], const uint32_t (&ndiv)[4], Div &&div, uint32_t T, uint64_t idx, mmee_mapping &m)
 {
     uint32_t t, row;
     split_index(idx, T, row, t);
     m.idx = idx;
+    // Whole quotients by fp64 (t, ndiv and X < 2^32): half a step above a whole number is further from the next one than
+    // the rounding errors; a 32-bit division is some 35 instructions, and a lone thread waits for each.
+#pragma unroll
     for (int q = 0; q < 4; ++q) {
-        uint32_t digit = t % dv.ndiv[q];
-        t /= dv.ndiv[q];
-        m.xG[q] = dv.div[q][digit];
-        m.xD[q] = dv.X[q] / m.xG[q];
+        const double n = (double)ndiv[q], y = reciprocal(n);
+        const uint32_t above = (uint32_t)(((double)t + 0.5) * y);
+        m.xG[q] = div(q, t - above * ndiv[q]);
+        t = above;
+        const double g = (double)m.xG[q];
+        m.xD[q] = (uint32_t)__builtin_rint((double)X[q] * reciprocal(g));
     }
     for (int y = 0; y < 4; ++y) { m.level[y] = (uint8_t)(row % 5); row /= 5; }
     uint32_t ord = order_of_rank(row % 24); row /= 24;
@@ -486,6 +501,11 @@ __device__ __forceinline__ void decode_candidate(const DivTable &dv, uint32_t T,
     m.stat1 = (uint8_t)(row % 3); row /= 3;
     m.stat2 = (uint8_t)(row % 3); row /= 3;
     m.fused = (uint8_t)row;
+}
+
+__device__ __forceinline__ void decode_candidate(const DivTable &dv, uint32_t T, uint64_t idx, mmee_mapping &m)
+{
+    decode_candidate_with(dv.X, dv.ndiv, [&](int q, uint32_t digit) { return dv.div[q][digit]; }, T, idx, m);
 }
 
 __global__ void k_decode(DivTable dv, uint32_t T, const uint64_t *__restrict__ idx, uint64_t n, mmee_mapping *out)

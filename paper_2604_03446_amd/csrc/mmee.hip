@@ -38,7 +38,10 @@ constexpr size_t OFF_RENC0 = OFF_ROWS1 + up256(sizeof(uint32_t) * N_DFROWS);
 constexpr size_t OFF_RENC1 = OFF_RENC0 + up256(sizeof(uint4) * N_DFROWS);
 constexpr size_t OFF_COUNTS = OFF_RENC1 + up256(sizeof(uint4) * N_DFROWS);
 constexpr size_t OFF_TICKET = OFF_COUNTS + up256(sizeof(uint32_t) * 8);
-constexpr size_t OFF_KEYS = OFF_TICKET + up256(sizeof(uint32_t) * 2);
+// Behind the two words of the exhaustive search the tickets of k_search_batch, 0 from the load on but while a launch uses one.  A call
+// takes the next one: calls that overlap, though they may not, leave none of them with a count that a later call would go on from.
+constexpr uint32_t TICKETS = 1024;
+constexpr size_t OFF_KEYS = OFF_TICKET + up256(sizeof(uint32_t) * (2 + TICKETS));
 constexpr size_t OFF_PARTIALS = OFF_KEYS + up256(sizeof(Key) * N_OBJ);
 constexpr size_t OFF_FINAL = OFF_PARTIALS + up256(sizeof(Key) * N_OBJ * MAX_BLOCKS);
 constexpr size_t OFF_DV = OFF_FINAL + up256(sizeof(FinalRecord) * N_OBJ);
@@ -358,7 +361,7 @@ int ensure_ready()
     HIP_TRY(hipMalloc(&S.rows[1], sizeof(uint32_t) * N_DFROWS));
     HIP_TRY(hipMalloc(&S.counts_dev, sizeof(uint32_t) * 8));
     HIP_TRY(hipMalloc(&S.key_dev, sizeof(Key) * N_OBJ));
-    HIP_TRY(hipMalloc(&S.ticket, 2 * sizeof(uint32_t)));        // [0] finish ticket, [1] work counter
+    HIP_TRY(hipMalloc(&S.ticket, 3 * sizeof(uint32_t)));        // [0] finish ticket, [1] work counter, [2] k_search_batch's ticket
     HIP_TRY(hipMalloc(&S.hints, N_OBJ * sizeof(unsigned long long)));
     {
         // +inf until a launch lowers them; the last block of every launch puts +inf back
@@ -367,7 +370,7 @@ int ensure_ready()
     }
     // on the library's stream, like the kernels that follow: a caller's non-blocking stream is not
     // ordered against the null stream
-    HIP_TRY(hipMemsetAsync(S.ticket, 0, 2 * sizeof(uint32_t), S.stream));
+    HIP_TRY(hipMemsetAsync(S.ticket, 0, 3 * sizeof(uint32_t), S.stream));
     HIP_TRY(hipMemsetAsync(S.rows[0], 0, sizeof(uint32_t) * N_DFROWS, S.stream));
     HIP_TRY(hipMemsetAsync(S.rows[1], 0, sizeof(uint32_t) * N_DFROWS, S.stream));
     for (int w = 0; w < 2; ++w) {
@@ -880,17 +883,16 @@ void launch_batch_mask(bool fast, bool regroup, dim3 grid, const BatchArgs &a)
     if (regroup) hipLaunchKernelGGL((k_search_batch<MASK, true, true>), grid, dim3(BATCH_THREADS), 0, S.stream, a);
     else if (fast) hipLaunchKernelGGL((k_search_batch<MASK, true, false>), grid, dim3(BATCH_THREADS), 0, S.stream, a);
     else hipLaunchKernelGGL((k_search_batch<MASK, false, false>), grid, dim3(BATCH_THREADS), 0, S.stream, a);
-    // the problems' records are complete when the search kernel has ended: one block per problem finishes
-    hipLaunchKernelGGL((k_batch_finish<MASK>), dim3(a.n_prob), dim3(256), 0, S.stream, a);
+    // the problems' records are complete when the search kernel has ended: one block per problem finishes (a lone problem the search's own)
+    if (!a.inl.on) hipLaunchKernelGGL((k_batch_finish<MASK>), dim3(a.n_prob), dim3(256), 0, S.stream, a);
 }
 
 // The kept rows shared out over the waves of a block and the row shares (rows.h: the kernel has the pieces' runs compiled in).
 void set_batch_tasks(BatchArgs &a, uint32_t split)
 {
-    static_assert(PIECE_WAVES == BATCH_WAVES && BATCH_MAX_SPLIT == 4, "the pieces are those of the blocks");
+    static_assert(PIECE_WAVES == BATCH_WAVES, "the pieces are those of the blocks");
     const uint32_t group_of[LEAST_CLASSES] = {0, 2, 3};      // class (r, f) -> g = r + 2 f
     a.split = split;
-    for (a.split_log2 = 0; (1u << a.split_log2) < split; ++a.split_log2) {}
     for (uint32_t sh = 0; sh < split; ++sh)
         for (uint32_t wv = 0; wv < BATCH_WAVES; ++wv) {
             const PieceRange p = piece_range(split, sh, wv);
@@ -900,13 +902,10 @@ void set_batch_tasks(BatchArgs &a, uint32_t split)
         }
 }
 
-// a launch with few chunks leaves most of the chip idle: let several blocks share a chunk's rows
-uint32_t batch_split(uint64_t chunks, uint32_t resident_blocks)
-{
-    uint32_t split = 1;
-    while (split < BATCH_MAX_SPLIT && chunks * split * 2 <= resident_blocks) split *= 2;
-    return split;
-}
+// Blocks that share a chunk's rows: two while both have a CU to themselves, which is as long as no CU has to take a second block.
+// (Call, us, 1 block / 2: 1 chunk 20.6 / 19.4, 12 chunks 21.5 / 20.7, 46 chunks 21.7 / 21.0, 77 chunks 15.9 / 15.9 without the
+// host's wait, 144 chunks 26.1 / 29.1.)
+uint32_t batch_split(uint64_t chunks, uint32_t resident_blocks) { return chunks * 4 <= resident_blocks ? 2 : 1; }
 
 void fill_batch_head(BatchProblemHead &h, uint32_t *list, const Plan &p, const ModelConst &mc, uint32_t slot, uint32_t first_item, uint32_t split)
 {
@@ -1061,9 +1060,10 @@ int enqueue_batches(std::vector<BatchEntry> &entries, uint32_t flags, size_t ev_
         a.item_keys = S.item_keys + N_OBJ * L.item0;
         a.final_out = S.final_map;
         a.done = done; a.number = number; a.begin = begin;
+        a.ticket = S.ticket + 2;
         // persistent blocks, two per CU, each with a contiguous range of the items
         dim3 grid((uint32_t)std::min<uint64_t>(L.n_items, (uint64_t)S.resident_blocks));
-        a.per_block = (uint32_t)((L.n_items + grid.x - 1) / grid.x);
+        a.per_block = a.n_items / grid.x; a.extra = a.n_items % grid.x;
         rc = launch_batch(v.mask, v.fast, v.regroup, grid, a);
         if (rc) return rc;
     }
@@ -1507,6 +1507,7 @@ struct NoAllocDevice {
     bool built = false;                  // offline stage done in it
     uint32_t counts[2][4] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
     uint32_t resident_blocks = 0;
+    uint32_t tickets = 0;                // handed out
 } g_noalloc[NOALLOC_MAX_DEVICES];
 
 // First call on a device: the address of that device's array, then the offline stage (row encoding,
@@ -2155,10 +2156,11 @@ int mmee_search_noalloc(const mmee_workload *w, const mmee_hw *hw, int objective
         a.enc = b.enc;
         set_batch_tasks(a, split);
         a.item_keys = b.partials;
+        a.ticket = b.ticket + 2 + d->tickets++ % noalloc::TICKETS;
         a.packed = out_dev; a.space = p.space;
         a.evaluated = ((uint64_t)d->counts[1][0] + d->counts[1][1] + d->counts[1][2] + d->counts[1][3]) * p.T * 9ull;
         const dim3 grid(std::min(a.n_items, b.resident_blocks));
-        a.per_block = (a.n_items + grid.x - 1) / grid.x;
+        a.per_block = a.n_items / grid.x; a.extra = a.n_items % grid.x;
         return launch_batch(1 << objective, p.exact_k, mc.regroup != 0, grid, a);
     }
     // the finish ticket and the work counter must start at zero whatever the last call left

@@ -224,6 +224,7 @@ constexpr uint32_t row_entry(const RowTerms &t, int k)
 constexpr int KEPT_ALL = 270, KEPT_LINE = 64 * 8;
 struct alignas(32) KeptRows {
     uint32_t off[KEPT_ALL][NSEL];            // a row's entries, as byte offsets of their lines
+    uint32_t packed[KEPT_ALL][NSEL / 2];     // ... two to a word
     uint32_t first[LEAST_CLASSES], rows[LEAST_CLASSES];
     uint32_t n, used;
     uint32_t number[KEPT_ALL];               // levels/order + 15000 * (r + 2 f)
@@ -249,16 +250,20 @@ constexpr KeptRows kept_rows()
     for (int e = 0; e < NENT; ++e)
         if (k.place[e] == 0) k.place[e] = k.used++;
     for (uint32_t i = 0; i < k.n; ++i)
-        for (int q = 0; q < NSEL; ++q) k.off[i][q] = k.place[k.off[i][q]] * KEPT_LINE;
+        for (int q = 0; q < NSEL; ++q) {
+            k.off[i][q] = k.place[k.off[i][q]] * KEPT_LINE;
+            k.packed[i][q / 2] |= k.off[i][q] << (16 * (q & 1));
+        }
     return k;
 }
 constexpr KeptRows KEPT = kept_rows();
-static_assert(KEPT.n == KEPT_ALL, "the arrays are sized for the kept rows");
+static_assert(KEPT.n == KEPT_ALL && KEPT.used * KEPT_LINE <= 1 << 16, "the arrays are sized for the kept rows, 16 bits hold an offset");
 
 // ---- the kept rows of k_search_batch's waves, in runs --------------------------------------------
-// A block's eight waves take a contiguous piece of one class's kept rows each; with `split` blocks to a chunk each of these
+// A block's eight waves take a contiguous piece of one class's kept rows each; with two blocks to a chunk (`split`) each of these
 // is cut once more.
 constexpr int PIECE_WAVES = 8;
+constexpr uint32_t PIECE_SPLITS = 2;
 constexpr uint32_t WAVES_OF_CLASS[LEAST_CLASSES] = {3, 2, 3};
 struct PieceRange { uint32_t cls, lo, n; };                   // within the class's list
 constexpr PieceRange piece_range(uint32_t split, uint32_t share, uint32_t wave)
@@ -269,21 +274,23 @@ constexpr PieceRange piece_range(uint32_t split, uint32_t share, uint32_t wave)
     return {c, lo + cnt * share / split, cnt * (share + 1) / split - cnt * share / split};
 }
 
-// What the least traffic of a piece (split 1) needs: the rows that no other row of the piece covers, those with equal (D, E) and
-// C entries side by side: a run reads these five entries once, a row its three of A and B.  220 rows in 78 runs, 1050 reads per
-// tiling instead of 2160.
-constexpr int RUNS_MAX = 96;
+// What the least traffic of a piece needs: the rows that no other row of the piece covers, those with equal (D, E) and
+// C entries side by side: a run reads these five entries once, a row its three of A and B.  One block to a chunk: 220 rows in 78 runs,
+// 1050 reads per tiling instead of 2160.  Piece: share * 8 + wave.
+constexpr int RUNS_MAX = 144;
+template <uint32_t SPLIT>
 struct PieceRuns {
     uint32_t run[RUNS_MAX][8];               // byte offsets: ret D E, bs C, bs D E, da D E, da C; number of rows
     uint32_t row[KEPT_ALL][4];               // byte offsets: bs A B, ret A B, da A B
-    uint32_t first_run[PIECE_WAVES + 1], first_row[PIECE_WAVES];
+    uint32_t first_run[SPLIT * PIECE_WAVES + 1], first_row[SPLIT * PIECE_WAVES];
 };
-constexpr PieceRuns piece_runs()
+template <uint32_t SPLIT>
+constexpr PieceRuns<SPLIT> piece_runs()
 {
-    PieceRuns out{};
+    PieceRuns<SPLIT> out{};
     uint32_t runs = 0, rows = 0;
-    for (uint32_t wave = 0; wave < PIECE_WAVES; ++wave) {
-        const PieceRange p = piece_range(1, 0, wave);
+    for (uint32_t wave = 0; wave < SPLIT * PIECE_WAVES; ++wave) {
+        const PieceRange p = piece_range(SPLIT, wave / PIECE_WAVES, wave % PIECE_WAVES);
         const KeptClass &cls = KEPT_CLASS[p.cls];
         out.first_run[wave] = runs;
         out.first_row[wave] = rows;
@@ -310,11 +317,18 @@ constexpr PieceRuns piece_runs()
             for (int q = 0; q < 5; ++q) run[q] = KEPT.place[run[q]] * KEPT_LINE;
         }
     }
-    out.first_run[PIECE_WAVES] = runs;
+    out.first_run[SPLIT * PIECE_WAVES] = runs;
     return out;
 }
-constexpr PieceRuns PIECE_RUNS = piece_runs();
-static_assert(PIECE_RUNS.first_run[PIECE_WAVES] <= RUNS_MAX, "the array holds them");
+constexpr PieceRuns<1> PIECE_RUNS_1 = piece_runs<1>();        // (no variable template: the device compiler reads one from memory)
+constexpr PieceRuns<2> PIECE_RUNS_2 = piece_runs<2>();
+static_assert(PIECE_RUNS_1.first_run[PIECE_WAVES] <= RUNS_MAX && PIECE_RUNS_2.first_run[2 * PIECE_WAVES] <= RUNS_MAX, "the arrays hold them");
+template <uint32_t SPLIT>
+constexpr const PieceRuns<SPLIT> &pieces()
+{
+    if constexpr (SPLIT == 1) return PIECE_RUNS_1;
+    else return PIECE_RUNS_2;
+}
 
 constexpr LeastRows LEAST[LEAST_CLASSES] = {least_rows(0, 0), least_rows(0, 1), least_rows(1, 1)};
 
