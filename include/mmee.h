@@ -176,7 +176,7 @@ int mmee_eval_batch(const mmee_workload *w, const mmee_hw *hw, uint64_t first_id
 
 /* Optimal mapping under one objective; ties go to the lowest index (Sec. VI).
  * mmee_search uses the pruned row set.
- * A call of one problem over the surviving rows, and a front over them, keep a core of the host busy until the result is
+ * A call of one problem, and a front over the surviving rows, keep a core of the host busy until the result is
  * there, for 20 ms at most; what takes longer (work of the caller's ahead of it on the stream) is then
  * waited for on the stream, as in the other calls.  Calls take turns: another thread's begins when this one returns. */
 int mmee_search(const mmee_workload *w, const mmee_hw *hw, int objective, mmee_result *out);

@@ -166,10 +166,8 @@ __global__ __launch_bounds__(BATCH_THREADS, 4) void k_search_batch(BatchArgs a)
     const double inf = pos_inf();
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // The arguments lie in host memory, and each look at a line that no cache holds yet takes a microsecond: all of them are asked for at
-    // once (7 us of a block with one chunk, 0.8 less).  So are the rows that a position may be recovered from.
-    if (wave == BATCH_WAVES - 1 && lane < sizeof(BatchArgs) / 64)
-        (void)*(const volatile uint32_t __attribute__((address_space(1))) *)((const char __attribute__((address_space(1))) *)__builtin_amdgcn_kernarg_segment_ptr() + lane * 64);
+    // (0.8 us less of a block with one chunk, 7 us)  So are the rows that a position may be recovered from asked for.
+    if (wave == BATCH_WAVES - 1) ask_for_arguments<BatchArgs>(lane);
     static_assert(KEPT_ALL <= BATCH_THREADS, "a thread per row");
     if (threadIdx.x < KEPT_ALL) {
         rows_lds[threadIdx.x] = *reinterpret_cast<const uint4 *>(kept_dev.packed[threadIdx.x]);

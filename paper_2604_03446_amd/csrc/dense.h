@@ -129,6 +129,9 @@ struct DenseArgs {
     // per key the lowest value any wave of the launch has recorded so far, as the bit pattern of the (non-negative)
     // double; +inf between launches
     unsigned long long *hints;
+    Done *done;                              // [N_OBJ] not null: the host looks here for the launch's records
+    uint64_t number, *begin;                 // the call's number; when the search began (device memory)
+    uint32_t first_launch, pad_;             // of the call: it says when
     uint32_t list[DENSE_DIVS];               // the four divisor lists one after the other
 };
 
@@ -184,6 +187,9 @@ __global__ __launch_bounds__(DENSE_THREADS, 4) void k_search_dense(DenseArgs a)
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const ModelConst &mc = a.mc;
     ConstBytes args = (ConstBytes)__builtin_amdgcn_kernarg_segment_ptr();
+    if (wave == DENSE_WAVES - 1) ask_for_arguments<DenseArgs>(lane);
+    if (a.done && a.first_launch && blockIdx.x == 0 && threadIdx.x == 0)
+        __hip_atomic_store(a.begin, (uint64_t)wall_clock64(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (threadIdx.x < N_OBJ) hint_bits[threadIdx.x] = INF_BITS;
     if (threadIdx.x < PRUNED_TC) tab[DENSE_ZERO * PRUNED_TC + lane] = 0.0;
     {
@@ -709,12 +715,13 @@ __global__ __launch_bounds__(DENSE_THREADS, 4) void k_search_dense(DenseArgs a)
             __hip_atomic_store(&dst->idx, k.idx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __hip_atomic_store(reinterpret_cast<uint64_t *>(&dst->p), (uint64_t)__double_as_longlong(k.p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
-        const uint32_t ticket = __hip_atomic_fetch_add(a.ticket, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-        is_last = ticket == gridDim.x - 1;
+        // records and ticket meet where all XCDs see them; the wait keeps the ticket behind the records, and nothing else has to be
+        // written back
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        is_last = __hip_atomic_fetch_add(a.ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
     }
     __syncthreads();
     if (!is_last) return;
-    __threadfence();
 #pragma unroll
     for (int o = 0; o < N_OBJ; ++o) {
         if (!((MASK >> o) & 1)) continue;
@@ -742,6 +749,7 @@ __global__ __launch_bounds__(DENSE_THREADS, 4) void k_search_dense(DenseArgs a)
         mmee_result res;
         winner_record(a.enc, dv_s, mc, k, res);
         write_record(a.final_out + o, k, res);
+        if (a.done) say_done(a.done + o, a.number, __hip_atomic_load(a.begin, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
     }
 }
 

@@ -468,6 +468,15 @@ __device__ __forceinline__ void split_index(uint64_t idx, uint32_t T, uint32_t &
     t = (uint32_t)rest;
 }
 
+// The arguments of a launch lie in host memory, a microsecond for each line's first reader: a wave asks for all of their lines at once.
+template <class Args>
+__device__ __forceinline__ void ask_for_arguments(uint32_t lane)
+{
+    static_assert(sizeof(Args) <= 64 * 64, "a lane per line");
+    typedef const char __attribute__((address_space(1))) *Bytes;
+    if (lane < sizeof(Args) / 64) (void)*(const volatile uint32_t __attribute__((address_space(1))) *)((Bytes)__builtin_amdgcn_kernarg_segment_ptr() + lane * 64);
+}
+
 // 1 / g to about fifty bits, for a whole number 1 <= g < 2^32
 __device__ __forceinline__ double reciprocal(double g)
 {

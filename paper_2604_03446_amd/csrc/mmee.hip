@@ -152,6 +152,7 @@ struct Bufs {
     FinalRecord *final_dev = nullptr;           // device address of this pass's N_OBJ records
     DivTable *dv_dev = nullptr;                 // this pass's copy of the divisor lists
     hipEvent_t ev_begin = nullptr, ev_end = nullptr;   // null: the pass is not timed
+    bool *signalled = nullptr;                  // not null: the pass is the call's only one and may be waited for with wait_signalled; set if so
     uint32_t resident_blocks = 512;
 };
 
@@ -613,6 +614,8 @@ uint32_t list_length(const DivTable &dv);
 void pack_lists(const DivTable &dv, uint32_t *list);
 void shape_constants(const DivTable &dv, double (&extent)[4], double (&size)[5]);
 
+int begin_signalled(Done *&done, uint64_t &number, uint64_t *&begin);
+
 // One pass of these keys over the full row set in k_search_dense, or two or three (the launches share the arguments).
 int enqueue_dense(const Bufs &B, const Plan &p, const ModelConst &mc, int mask, const double *e_limit)
 {
@@ -656,6 +659,11 @@ int enqueue_dense(const Bufs &B, const Plan &p, const ModelConst &mc, int mask, 
     if (grid.x > B.partials_cap) return MMEE_EINVAL;
     a.partials = B.partials; a.ticket = B.ticket; a.work_counter = B.ticket + 1; a.hints = B.hints;
     a.final_out = B.final_dev;
+    if (B.signalled) {
+        const int rc = begin_signalled(a.done, a.number, a.begin);
+        if (rc) return rc;
+        a.first_launch = 1;
+    }
     // The (latency, energy) key over the full row set is two passes that each cost what a single scalar
     // key costs: the lowest latency first, then the lowest energy among the candidates that reach it (a
     // candidate's latency is a maximum of a row part and a combination part, so the cap applies to the
@@ -681,10 +689,12 @@ int enqueue_dense(const Bufs &B, const Plan &p, const ModelConst &mc, int mask, 
         default: launch_dense<3>(p.exact_k, grid, a); break;
         }
     a.final_key_dev = nullptr;
+    a.first_launch = 0;
     if (lex) {
         DenseArgs second = a;
         second.lat_cap = B.key_dev + 1;
         second.final_out = a.final_out + 2;
+        if (a.done) second.done = a.done + 2;
         launch_dense<1, false, true>(p.exact_k, grid, second);
     }
     if (!e_limit && ((mask & 11) | (lex ? 2 : 0)) == 11) launch_dense<8>(p.exact_k, grid, a);
@@ -708,11 +718,12 @@ int enqueue_search_in(const Bufs &B, const Plan &p, int mask, uint32_t flags, ui
     if (dense) {
         uint64_t nrows = 0;
         for (int g = 0; g < 4; ++g) nrows += B.counts[0][g];
-        if (B.ev_begin) HIP_TRY(hipEventRecord(B.ev_begin, S.stream));
+        if (B.ev_begin && !B.signalled) HIP_TRY(hipEventRecord(B.ev_begin, S.stream));
         const int drc = enqueue_dense(B, p, mc, mask, e_limit);
         if (drc) return drc;
         HIP_TRY(hipGetLastError());
-        if (B.ev_end) HIP_TRY(hipEventRecord(B.ev_end, S.stream));
+        if (B.signalled) *B.signalled = true;
+        else if (B.ev_end) HIP_TRY(hipEventRecord(B.ev_end, S.stream));
         *evaluated = nrows * p.T * 9ull;
         return MMEE_OK;
     }
@@ -804,11 +815,12 @@ int enqueue_search_in(const Bufs &B, const Plan &p, int mask, uint32_t flags, ui
 // the same in the cached buffers of the allocating entry points, result slot `slot`
 int enqueue_search(const Plan &p, int mask, uint32_t flags, size_t slot, uint64_t *evaluated,
                    const double *e_limit = nullptr, bool build_tables = true, bool bs_da_step = false,
-                   bool *unproven = nullptr)
+                   bool *unproven = nullptr, bool *signalled = nullptr)
 {
     Bufs b;
     int rc = state_bufs(p, slot, b);
     if (rc) return rc;
+    b.signalled = signalled;
     return enqueue_search_in(b, p, mask, flags, evaluated, e_limit, build_tables, bs_da_step, unproven);
 }
 
@@ -1767,8 +1779,9 @@ int mmee_chain_search_many(const mmee_chain *w, const mmee_hw *hw, const int *ob
     // problem by problem.  `round_flags` adds MMEE_SEARCH_ORDERED_SUM on the second round, which repeats what the
     // first could not prove and leaves the other problems' device times alone: a round's times are taken at its end.
     auto run_round = [&](uint32_t round_flags, bool only_unproven) -> int {
-        bool signalled = false;
-        bool others = false;                                 // anything beside the batched searches in the stream
+        bool signalled = false;                              // the stream holds one search, of the pass below, and it says when it is done
+        size_t signalled_pass = 0;
+        bool others = false;                                 // anything beside the batched searches and that one in the stream
         std::vector<PrunedEntry> pruned;
         std::vector<uint32_t> order;
         std::vector<PrunedSlice> slices;                     // the groups that share more than launches
@@ -1802,10 +1815,11 @@ int mmee_chain_search_many(const mmee_chain *w, const mmee_hw *hw, const int *ob
                 batch_pass.push_back(s);
             } else {
                 bool unproven = false;
-                others = true;
                 ps.rc = enqueue_search(ps.plan, ps.mask, round_flags, s, &ps.evaluated, nullptr, true, false,
-                                       only_unproven ? nullptr : &unproven);
+                                       only_unproven ? nullptr : &unproven, passes.size() == 1 ? &signalled : nullptr);
                 ps.unproven = unproven;
+                signalled_pass = s;
+                others = others || !signalled;
             }
         }
         if (!slices.empty()) {
@@ -1817,6 +1831,7 @@ int mmee_chain_search_many(const mmee_chain *w, const mmee_hw *hw, const int *ob
         if (!batch.empty()) {
             int brc = enqueue_batches(batch, round_flags, batch_pass[0], signalled);
             if (brc) signalled = false;
+            signalled_pass = batch_pass[0];
             for (size_t k = 0; k < batch.size(); ++k) {
                 Pass &ps = passes[batch_pass[k]];
                 ps.rc = brc;
@@ -1828,7 +1843,7 @@ int mmee_chain_search_many(const mmee_chain *w, const mmee_hw *hw, const int *ob
         double signalled_seconds = 0.0;
         if (!signalled || others) HIP_TRY(hipStreamSynchronize(S.stream));
         if (signalled) {
-            const int wrc = wait_signalled(batch[0].mask, signalled_seconds);
+            const int wrc = wait_signalled(passes[signalled_pass].mask, signalled_seconds);
             if (wrc) return wrc;
         }
         size_t timed = (size_t)-1;
@@ -1836,7 +1851,7 @@ int mmee_chain_search_many(const mmee_chain *w, const mmee_hw *hw, const int *ob
         for (size_t s = 0; s < passes.size(); ++s) {
             PassTime &t = times[s];
             if (!t.ran) continue;
-            if (signalled && s == batch_pass[0]) {           // (the only one of its launch: no events were recorded)
+            if (signalled && s == signalled_pass) {          // (no events were recorded)
                 t.device_seconds = signalled_seconds;
                 continue;
             }
