@@ -575,44 +575,35 @@ void launch_dense(bool exact_k, dim3 grid, const DenseArgs &a)
     else with_sum(std::integral_constant<int, ENERGY ? SUM_ORDERED : SUM_REGROUPED>{});
 }
 
-// The fewest tilings at which the dense kernel takes these keys over the full row set.  One key always went there.  For
-// several it needs one pass for two scalar keys and one more for the (latency, energy) key and for a third scalar
-// key, k_search one pass for all; but with the lanes on rows k_search divides once per candidate where the DRAM time
-// is not one exact product, and keeps a code beside every minimum.  A problem of few chunks leaves the dense kernel's
-// blocks without work (188 items a chunk, 512 blocks), and each of its passes costs some 20 us at least.
-// The bounds were set on 30 shapes of 1 to 14400 tilings for every key set and both kinds of bandwidth, the energy
-// regrouped, with its first sum fused and in order, before rows over capacity were passed over in the dense kernel.  Measured with the
-// kernels as they are, 23 shapes of 1 to 12168 tilings, a buffer that everything fits; k_search / dense, us per call:
-//   energy and latency, regrouped      T = 16: 40 / 49    784: 105 / 128    2500: 209 / 209    4900: 351 / 329    12168: 781 / 698
-//   energy and latency, fused          T = 16: 42 / 51    144: 63 / 78      500: 109 / 105     4900: 507 / 376
-//   energy and product, in order       T = 16: 43 / 53    784: 139 / 165    4900: 547 / 534    12168: 1270 / 1228
-//   all four, regrouped                T = 1: 50 / 97     500: 216 / 237    784: 299 / 303     4900: 1394 / 798
-//   all four, bandwidth 60             T = 1: 55 / 100    144: 153 / 155    500: 309 / 253     4900: 2222 / 919
-//   three scalar keys, bandwidth 60    T = 16: 55 / 77    500: 203 / 181    4900: 1303 / 690
-//   three scalar keys, regrouped       T = 16: 44 / 74    784: 139 / 226    4900: 518 / 601    12168: 1177 / 1285
-// Over these shapes, every key set, kind of sum and bandwidth, and two buffers the choice costs 0.8 % over the better kernel on
-// average, more than 5 % in 63 of 2530 cases: nearly all of them a small buffer on many tilings, where the dense kernel passes over
-// most rows and the bounds do not know it (256 KiB, in order: energy and product of 7744 tilings 854 / 331; three
-// scalar keys of 12168 tilings 1627 / 724).  Near a bound the two differ by a few per cent (three and four chunks, two rounds of
-// blocks: up to 8).
-uint32_t dense_from(int mask, bool exact_k, const ModelConst &mc)
+void shape_constants(const DivTable &dv, double (&extent)[4], double (&size)[5]);
+
+// The fewest tilings at which the dense kernel takes these keys over the full row set.  One or two scalar keys are one pass and always
+// go there; the (latency, energy) key is one more, and so is a third scalar key.  k_search takes all keys in one pass, with the
+// lanes on rows: it divides once per candidate where the DRAM time is not one exact product, keeps a code beside every
+// minimum, and tries the rows that do not fit as well, which the dense kernel passes over.  So k_search is left where a pass costs more
+// than that saves: few tilings, and three scalar keys or four keys with a buffer that holds most of what there is.  us per
+// call, k_search / dense, buffer for everything | for a sixteenth of it, 14 shapes of 1 to 11664 tilings:
+//   energy and latency      regrouped    T = 1: 38 / 34      500: 1.09 | 1.89 times     4900: 354 / 301 | 4.0 times
+//   product and latency     in order     T = 1: 1.02 times   500: 1.01 | 2.38           4900: 1.03 | 4.4
+//   two kinds of latency    regrouped    T = 1: 1.00 times   36: 1.27 | 1.61            4900: 2.67 | 7.2
+//   energy and both         in order     T = 1: 0.86 times   36: 1.18 | 1.64            4900: 2.07 | 7.8
+//   three scalar keys       regrouped    T = 36: 0.91 | 1.21   500: 0.84 | 1.46         4900: 519 / 547 | 3.2 times
+//                           bandwidth 60 T = 36: 1.26 | 1.70   500: 1.40 | 2.63         4900: 2.12 | 7.5
+//   all four                in order     T = 36: 0.89 | 1.25   225: 0.92 | 1.89         500: 0.98 | 2.18     4900: 1.44 | 5.6
+// Buffers of a half to a quarter of everything lie between; the line is drawn where no shape loses.
+uint32_t dense_from(const Plan &p, int mask)
 {
-    constexpr uint32_t NEVER = 0xFFFFFFFFu;
-    struct Row { int mask; uint32_t exact[3], division[2]; };        // exact: regrouped, fused, in order; division: regrouped, not
-    static const Row rows[] = {
-        {3, {3000, 224, 1100}, {8, 8}},        {9, {4500, 2500, 8000}, {16, 32}},     {10, {4500, 2500, 8000}, {16, 32}},
-        {11, {NEVER, NEVER, NEVER}, {224, 512}}, {5, {512, 400, 448}, {32, 32}},      {6, {352, 352, 352}, {32, 32}},
-        {7, {224, 224, 224}, {32, 32}},        {12, {512, 576, 1000}, {32, 224}},     {13, {1150, 1150, 1500}, {352, 448}},
-        {14, {352, 352, 352}, {32, 32}},       {15, {850, 850, 850}, {224, 352}},
-    };
-    for (const Row &r : rows)
-        if (r.mask == mask) return exact_k ? r.exact[mc.regroup ? 0 : (mc.gb_product_exact ? 1 : 2)] : r.division[mc.regroup ? 0 : 1];
-    return 0;
+    constexpr uint32_t NEVER = 0xFFFFFFFFu, HALF_A_CHUNK = PRUNED_TC / 2, FEW = 7 * PRUNED_TC;
+    if (popcount4(mask) == 1 || (!(mask & 4) && mask != 11)) return 0;
+    double extent[4], size[5];
+    shape_constants(p.dv, extent, size);
+    const bool roomy = 4.0 * p.mc.cap_words > size[0] + size[1] + size[2] + size[3] + size[4];
+    if (!roomy || !p.exact_k) return HALF_A_CHUNK;
+    return mask == 11 ? NEVER : (mask == 13 || mask == 15 ? FEW : HALF_A_CHUNK);
 }
 
 uint32_t list_length(const DivTable &dv);
 void pack_lists(const DivTable &dv, uint32_t *list);
-void shape_constants(const DivTable &dv, double (&extent)[4], double (&size)[5]);
 
 int begin_signalled(Done *&done, uint64_t &number, uint64_t *&begin);
 
@@ -668,9 +659,7 @@ int enqueue_dense(const Bufs &B, const Plan &p, const ModelConst &mc, int mask, 
     // key costs: the lowest latency first, then the lowest energy among the candidates that reach it (a
     // candidate's latency is a maximum of a row part and a combination part, so the cap applies to the
     // two separately).  The second pass's energy record lands in the slot of this key.  The first pass
-    // serves the latency key as well.  Of the scalar keys two go together in one pass (energy and latency of
-    // the 2048 x 768 x 3072 x 768 chain: 0.347 ms, in two passes 0.397; with a buffer that everything fits 0.595 and
-    // 0.649), a third takes a pass of its own.
+    // serves the latency key as well.  Of the scalar keys two go together in one pass, a third takes a pass of its own.
     const bool lex = mask & 4;
     a.final_key_dev = B.key_dev;
     if (e_limit) {
@@ -711,7 +700,7 @@ int enqueue_search_in(const Bufs &B, const Plan &p, int mask, uint32_t flags, ui
     // tilings excepted
     bool dense = which == 0 && !bs_da_step && B.cls_dev;
     ModelConst mc = pass_constants(p, flags, bs_da_step ? 8 : mask, unproven, dense);
-    if (dense && p.T < dense_from(mask, p.exact_k, mc)) {
+    if (dense && p.T < dense_from(p, mask)) {
         dense = false;
         mc = pass_constants(p, flags, mask, unproven);
     }

@@ -41,3 +41,30 @@ def test_long_searches_against_the_pruned_ones(I, K, L, J, mode):
         for o in range(4):
             a, b = (M.mmee_chain_search_multi(c, dict(H, gb_bytes=gb), [o], f)[0] for f in (M.SEARCH_EXHAUSTIVE, M.SEARCH_PRUNED))
             assert bytes(a.best) + bytes(a.cost) == bytes(b.best) + bytes(b.cost), (gb, o)
+
+
+# 30, 32, 36, 441, 448 and 450 tilings: both sides of the lines below which several keys are one pass of k_search
+@pytest.mark.parametrize("I, K, L, J", [(16, 4, 2, 1), (8, 2, 8, 1), (4, 8, 4, 1), (64, 64, 36, 1), (64, 24, 24, 1), (16, 16, 12, 4)])
+@pytest.mark.parametrize("hw", [dict(gb_bytes=1 << 40), dict(gb_bytes=200), dict(gb_bytes=1 << 40, dram_bw=60.0, gb_bw=100.0), dict(gb_bytes=1 << 40, e_dram=171.3, e_gb=5.7)])
+def test_several_keys_against_each_alone(I, K, L, J, hw):
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_2604_03446_amd as M
+    c, h = dict(batch=2, I=I, K=K, L=L, J=J, word_bytes=2, tiling_mode=1, c_softmax=10), dict(H, **hw)
+    alone = [M.mmee_chain_search_multi(c, h, [o], M.SEARCH_EXHAUSTIVE)[0] for o in range(4)]
+    for mask in range(1, 16):
+        keys = [o for o in range(4) if mask >> o & 1]
+        for o, got in zip(keys, M.mmee_chain_search_multi(c, h, keys, M.SEARCH_EXHAUSTIVE)):
+            assert bytes(got.best) + bytes(got.cost) == bytes(alone[o].best) + bytes(alone[o].cost), (keys, o)
+            assert 0 < got.kernel_seconds < got.seconds, (keys, o)
+
+
+def test_a_search_longer_than_the_host_looks_for():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_2604_03446_amd as M
+    c = dict(batch=1, I=360, K=360, L=360, J=360, word_bytes=2, tiling_mode=1, c_softmax=10)     # 331 776 tilings, 1.8e11 candidates
+    h = dict(H, gb_bytes=1 << 40, e_dram=171.3, e_gb=5.7)
+    for a, b in zip(*(M.mmee_chain_search_multi(c, h, [0, 1, 2, 3], f) for f in (M.SEARCH_EXHAUSTIVE, M.SEARCH_PRUNED))):
+        assert bytes(a.best) + bytes(a.cost) == bytes(b.best) + bytes(b.cost)
+        assert 0 < a.kernel_seconds < a.seconds
