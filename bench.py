@@ -28,14 +28,14 @@ sys.path.insert(0, ROOT)
 ALU_PEAK_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
 # fp64-width operations that an exhaustive search needs in k_search_dense, by how the energy is added up: per (row, tiling) pair,
 # which nine candidates share, per pair that fits the capacity, and per candidate that fits.
-# Every pair: two comparisons for Eq. (1), (2), (4) and the capacity (what the row's (D, E) part leaves of it is formed once per
-# five and more rows).  A pair that fits: one addition for Eq. (7) or its energy; in order the product with the DRAM
+# Every pair: nothing (which rows fit is a staircase: Eq. (1), (2), (4) and the capacity are compared at its edges, and once per
+# several rows elsewhere).  A pair that fits: one addition for Eq. (7) or its energy; in order the product with the DRAM
 # energy as well; with the latency both products.
 # A candidate that fits, energy: regrouped (every term an exact integer) one addition and the running minimum; in order,
 # with the first sum as one fused operation (its product is exact): buffer words, fused sum, minimum (the two
 # addends that all candidates of a tiling share go to the minima).  The latency adds a max and its minimum.
-OPS_ENERGY = {"regrouped": (2, 1, 2), "fused": (2, 2, 3)}
-OPS_ENERGY_LATENCY = {"regrouped": (2, 3, 4), "fused": (2, 3, 5)}
+OPS_ENERGY = {"regrouped": (0, 1, 2), "fused": (0, 2, 3)}
+OPS_ENERGY_LATENCY = {"regrouped": (0, 3, 4), "fused": (0, 3, 5)}
 # of the candidates that denote a dataflow, those within the buffer capacity (the CPU oracle's count over the whole space)
 WITHIN_CAPACITY = {"long": 2635657470, "bert": 1110940974}
 
@@ -49,10 +49,10 @@ HBM_PEAK_GBS = 8000.0
 # HBM bytes per launch from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (summaries under profiles/), scaled by
 # what the same counters read for a 1 GiB device-to-device copy (x2.0 and x1.0).  Valid only for the kernel
 # sources they were taken with: any change to the sources turns "traffic" into null.
-COUNTERS_TAKEN_WITH = "4d73960ad0178b82bb6716adf660016fe4dead36341864bd6b2d9bdcfaf67f84"
-TRAFFIC = {"k_search_dense_long": (2 * 61857.0 + 385.0) * 1024.0,      # FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0, KiB per dispatch
-           "k_search_dense_bert": (2 * 24326.0 + 305.0) * 1024.0,
-           "k_eval_batch": (2 * 20247.0 + 4195164.0) * 1024.0}
+COUNTERS_TAKEN_WITH = "62b4c2a21c8e8038271abb25dba0c916065628315d1264d5d1100765c2fd9c23"
+TRAFFIC = {"k_search_dense_long": (2 * 265.0 + 161.0) * 1024.0,      # FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0, KiB per dispatch
+           "k_search_dense_bert": (2 * 258.0 + 196.0) * 1024.0,
+           "k_eval_batch": (2 * 19957.0 + 4195190.0) * 1024.0}
 TRAFFIC_SOURCE = {"k_search_dense_long": "profiles/k_search_dense_long.md", "k_search_dense_bert": "profiles/k_search_dense_bert.md",
                   "k_eval_batch": "profiles/k_eval_batch_bert.md"}
 
@@ -60,7 +60,7 @@ TRAFFIC_SOURCE = {"k_search_dense_long": "profiles/k_search_dense_long.md", "k_s
 def kernel_sources_digest():
     import hashlib
     h = hashlib.sha256()
-    for f in ("layout.h", "rows.h", "kernels.h", "boundary.h", "batch.h", "pruned.h", "fronts.h", "pinned.h", "mmee.hip"):
+    for f in ("layout.h", "rows.h", "kernels.h", "boundary.h", "batch.h", "pruned.h", "fronts.h", "dense.h", "pinned.h", "mmee.hip"):
         with open(os.path.join(ROOT, "paper_2604_03446_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()
@@ -110,8 +110,8 @@ def main():
     offline_ms = (time.perf_counter() - t0) * 1e3
 
     def timed_search(cfg, objectives, flags, steps, warmup):
-        """`steps` searches back to back: wall time per step, kernel time per step (HIP events inside the
-        library, on the stream the kernels run on), stream time per step, last results."""
+        """`steps` searches back to back: wall time per step, kernel time per step (the library's own figure:
+        the device's clock from the first block to the last record), stream time per step, last results."""
         w, h = M.workload(cfg["workload"]), M.hw(cfg["hw"])      # C structs once, not per call
         for _ in range(warmup):
             M.mmee_search_multi(w, h, objectives, flags)

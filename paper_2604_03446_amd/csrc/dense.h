@@ -27,8 +27,8 @@
 // rounds of eight the waves wait for the slowest).  Persistent blocks, items from a global counter, the last ones small.
 //
 // What it measured, us a call, before (rows tested one by one, tables from memory, eight tasks an item) and now: 12544 tilings (8192 x
-// 128, all divisors, 8 MiB), energy 336 and 251; 4900 tilings (512 x 64, 256 KiB), energy and latency 295 and 259, energy alone 184 and 136;
-// 10692 tilings (2048 x 768 x 3072 x 768, 1 MiB), energy 217 and 95.  Vector issue bounds it where most rows fit (87 % of the
+// 128, all divisors, 8 MiB), energy 338 and 239; 4900 tilings (512 x 64, 256 KiB), energy and latency 295 and 246;
+// 10692 tilings (2048 x 768 x 3072 x 768, 1 MiB), energy 218 and 86.  Vector issue bounds it where most rows fit (84 % of the
 // first one's cycles); small buffers are bound by what a task costs before its first row.
 //
 // Argmin: lazy.  Only minima are kept; a position is recovered where the optimum can be, by costing the task's rows again.
