@@ -253,9 +253,9 @@ int mmee_chain_front_bs_da(const mmee_chain *c, const mmee_hw *hw, uint32_t flag
  * The first call on a device runs the offline stage into the array and reads its counts and row
  * numbers back (one synchronisation of that stream, still no allocation): make it outside any capture.  All calls on one GPU
  * share that GPU's array, which keeps the last call's contents; what must start at zero is cleared
- * by a kernel at the start of each call, or by the last block that used it.  Calls that overlap on one GPU (different streams, or
- * the same stream replayed while an earlier launch still runs) race; so does this call against
- * any other search in flight on a different stream. */
+ * by a kernel at the start of each call, or left at zero by the call before.  Calls that overlap on one GPU (different streams, or
+ * a captured call replayed while an earlier launch of it still runs) race; so does this call against
+ * any other search in flight on a different stream.  What a race spoils are the results of the calls in it, none after them. */
 int mmee_search_noalloc(const mmee_workload *w, const mmee_hw *hw, int objective, uint32_t flags,
                         mmee_result *out_dev);
 

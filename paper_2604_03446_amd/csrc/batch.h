@@ -65,7 +65,7 @@ struct BatchArgs {
     FinalRecord *final_out;                  // [result slot][N_OBJ]
     mmee_result *packed;                     // not null: the launch's one key of its one problem goes here, as a result record
     uint64_t space, evaluated;               // ... with these
-    uint32_t *ticket;                        // inl.on: blocks that have left their records; 0 between launches
+    uint32_t *ticket;                        // inl.on: blocks that have left their records, modulo the launch's blocks; 0 between launches
     Done *done;                              // [N_OBJ] not null: the host looks here for the launch's one problem
     uint64_t number, *begin;                 // the call's number; when the search began (device memory)
     BatchInline inl;                         // inl.on: the launch's only problem is here, prob and first_items are unused
@@ -535,15 +535,15 @@ __global__ __launch_bounds__(BATCH_THREADS, 4) void k_search_batch(BatchArgs a)
 
     // A launch of one problem: the last block to arrive reduces the blocks' records, its first wave alone.  Records and ticket are
     // agent-scope atomics, which meet where all XCDs see them; the wait keeps the ticket behind the records, so nothing else needs to
-    // be written back.  (A second launch for this took 6.5 us from the last record to the result, this 4.)
+    // be written back.  (A second launch for this took 6.5 us from the last record to the result, this 4.)  The last arrival turns the
+    // ticket to 0 in the same operation: launches that overlap lose no count, and whole launches leave it at 0.
     const uint32_t n_blocks = gridDim.x;
     uint32_t arrived = 0;
     if (lane == 0) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        arrived = __hip_atomic_fetch_add(a.ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        arrived = atomicInc(a.ticket, n_blocks - 1);
     }
     if ((uint32_t)__builtin_amdgcn_readfirstlane(arrived) != n_blocks - 1) return;
-    if (lane == 0) __hip_atomic_store(a.ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);    // for the next launch
     uint64_t began = 0;
     if (a.done) began = __hip_atomic_load(a.begin, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     Key best;

@@ -38,10 +38,12 @@ constexpr size_t OFF_RENC0 = OFF_ROWS1 + up256(sizeof(uint32_t) * N_DFROWS);
 constexpr size_t OFF_RENC1 = OFF_RENC0 + up256(sizeof(uint4) * N_DFROWS);
 constexpr size_t OFF_COUNTS = OFF_RENC1 + up256(sizeof(uint4) * N_DFROWS);
 constexpr size_t OFF_TICKET = OFF_COUNTS + up256(sizeof(uint32_t) * 8);
-// Behind the two words of the exhaustive search the tickets of k_search_batch, 0 from the load on but while a launch uses one.  A call
-// takes the next one: calls that overlap, though they may not, leave none of them with a count that a later call would go on from.
-constexpr uint32_t TICKETS = 1024;
-constexpr size_t OFF_KEYS = OFF_TICKET + up256(sizeof(uint32_t) * (2 + TICKETS));
+// Behind the two words of the exhaustive search the tickets of k_search_batch, 0 from the load on but while a launch uses one.  A ticket
+// serves launches of one number of blocks, which it counts modulo that number: calls that overlap, though they may not (two replays of a
+// captured one, say), spoil each other but leave it at 0 once all have ended, and no later call goes on from a count of theirs.  Of the
+// tickets for its number of blocks a call takes the next one.
+constexpr uint32_t TICKETS = 16;
+constexpr size_t OFF_KEYS = OFF_TICKET + up256(sizeof(uint32_t) * (2 + TICKETS * MAX_BLOCKS));
 constexpr size_t OFF_PARTIALS = OFF_KEYS + up256(sizeof(Key) * N_OBJ);
 constexpr size_t OFF_FINAL = OFF_PARTIALS + up256(sizeof(Key) * N_OBJ * MAX_BLOCKS);
 constexpr size_t OFF_DV = OFF_FINAL + up256(sizeof(FinalRecord) * N_OBJ);
@@ -2160,10 +2162,10 @@ int mmee_search_noalloc(const mmee_workload *w, const mmee_hw *hw, int objective
         a.enc = b.enc;
         set_batch_tasks(a, split);
         a.item_keys = b.partials;
-        a.ticket = b.ticket + 2 + d->tickets++ % noalloc::TICKETS;
         a.packed = out_dev; a.space = p.space;
         a.evaluated = ((uint64_t)d->counts[1][0] + d->counts[1][1] + d->counts[1][2] + d->counts[1][3]) * p.T * 9ull;
         const dim3 grid(std::min(a.n_items, b.resident_blocks));
+        a.ticket = b.ticket + 2 + noalloc::TICKETS * (grid.x - 1) + d->tickets++ % noalloc::TICKETS;
         a.per_block = a.n_items / grid.x; a.extra = a.n_items % grid.x;
         return launch_batch(1 << objective, p.exact_k, mc.regroup != 0, grid, a);
     }

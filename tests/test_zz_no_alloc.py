@@ -71,6 +71,68 @@ def test_noalloc_infeasible_and_too_big(M):
                 M.mmee_search_ex(cfg["workload"], cfg["hw"], M.OBJ_EDP, M.SEARCH_PRUNED), "after refusal")
 
 
+def captured(M, w, h, objective, buf, stream):
+    import torch
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        M.mmee_search_noalloc(w, h, objective, M.SEARCH_PRUNED, buf.data_ptr())
+    return graph
+
+
+def replayed(M, graph, buf):
+    import torch
+    buf.fill_(0xAB)
+    graph.replay()
+    torch.cuda.synchronize()
+    return M.Result.from_buffer_copy(buf.cpu().numpy().tobytes())
+
+
+def test_replays_of_a_captured_call(M):
+    """The blocks' count is part of the graph: every replay finds it at zero, whatever ran in between."""
+    import torch
+    stream, bufs = torch.cuda.Stream(), [torch.zeros(C.sizeof(M.Result), dtype=torch.uint8, device="cuda") for _ in range(8)]
+    problems = [(CONFIGS[name]["workload"], CONFIGS[name]["hw"], o) for name in ("tiny", "long") for o in range(4)]
+    wants = [M.mmee_search_ex(w, h, o, M.SEARCH_PRUNED) for w, h, o in problems]
+    run_noalloc(M, *problems[0], M.SEARCH_PRUNED)            # (the first call on a device is made outside any capture)
+    M.mmee_set_stream(stream.cuda_stream)
+    try:
+        graphs = [captured(M, w, h, o, buf, stream) for (w, h, o), buf in zip(problems, bufs)]
+        for turn in range(5):
+            for k, (graph, buf, want) in enumerate(zip(graphs, bufs, wants)):
+                assert_same(replayed(M, graph, buf), want, (turn, k))
+                w, h, o = problems[(k + turn) % 8]
+                assert_same(run_noalloc(M, w, h, o, M.SEARCH_PRUNED), wants[(k + turn) % 8], (turn, k))
+    finally:
+        M.mmee_set_stream(None)
+
+
+def test_calls_that_overlapped_leave_nothing_behind(M):
+    """Two graphs of one search, sixteen calls apart, count their blocks at one word.  Replayed side by side, which callers may not
+    do, they may spoil each other; each of them alone is right again afterwards."""
+    import torch
+    a, b = torch.cuda.Stream(), torch.cuda.Stream()
+    bufs = [torch.zeros(C.sizeof(M.Result), dtype=torch.uint8, device="cuda") for _ in range(2)]
+    w, h = CONFIGS["long"]["workload"], CONFIGS["long"]["hw"]
+    want = M.mmee_search_ex(w, h, M.OBJ_ENERGY, M.SEARCH_PRUNED)
+    run_noalloc(M, w, h, M.OBJ_ENERGY, M.SEARCH_PRUNED)
+    M.mmee_set_stream(a.cuda_stream)
+    try:
+        graphs = [captured(M, w, h, M.OBJ_ENERGY, bufs[0], a)]
+        for _ in range(15):
+            run_noalloc(M, w, h, M.OBJ_ENERGY, M.SEARCH_PRUNED)
+        graphs.append(captured(M, w, h, M.OBJ_ENERGY, bufs[1], a))
+        for turn in range(20):
+            for _ in range(10):
+                for stream, graph in zip((a, b), graphs):
+                    with torch.cuda.stream(stream):
+                        graph.replay()
+            torch.cuda.synchronize()
+            for graph, buf in zip(graphs, bufs):
+                assert_same(replayed(M, graph, buf), want, turn)
+    finally:
+        M.mmee_set_stream(None)
+
+
 SETUP = r"""
 import os, sys, time
 sys.path.insert(0, %r)
