@@ -515,11 +515,12 @@ int launch_tilings(const Plan &p, const ModelConst &mc, const Bufs &b, DivTable 
     return MMEE_OK;
 }
 
-// the cached, growing buffers of the allocating entry points, for the pass in result slot `slot`
-int state_bufs(const Plan &p, size_t slot, Bufs &b)
+// the cached, growing buffers of the allocating entry points, for the pass in result slot `slot`; `tables`: the per-tiling ones too (2
+// KiB a tiling, which the dense kernel has no use for)
+int state_bufs(const Plan &p, size_t slot, bool tables, Bufs &b)
 {
     if (slot >= S.slots) return MMEE_EINVAL;
-    int rc = ensure_tilings(p.mc.tpad);
+    int rc = tables ? ensure_tilings(p.mc.tpad) : MMEE_OK;
     if (rc) return rc;
     // persistent blocks: never more than the chip holds at once
     rc = ensure_partials(S.resident_blocks);
@@ -602,6 +603,12 @@ uint32_t dense_from(const Plan &p, int mask)
     const bool roomy = 4.0 * p.mc.cap_words > size[0] + size[1] + size[2] + size[3] + size[4];
     if (!roomy || !p.exact_k) return HALF_A_CHUNK;
     return mask == 11 ? NEVER : (mask == 13 || mask == 15 ? FEW : HALF_A_CHUNK);
+}
+
+// whether these keys' pass goes through the dense kernel
+bool goes_dense(const Plan &p, int mask, uint32_t flags, bool bs_da_step)
+{
+    return (flags & MMEE_SEARCH_EXHAUSTIVE) && !bs_da_step && p.T >= dense_from(p, mask);
 }
 
 uint32_t list_length(const DivTable &dv);
@@ -700,12 +707,8 @@ int enqueue_search_in(const Bufs &B, const Plan &p, int mask, uint32_t flags, ui
     const int which = (flags & MMEE_SEARCH_EXHAUSTIVE) ? 0 : 1;
     // the full row set goes through the dense kernel (lane = tiling, wave = 125 rows of a class), several keys on few
     // tilings excepted
-    bool dense = which == 0 && !bs_da_step && B.cls_dev;
-    ModelConst mc = pass_constants(p, flags, bs_da_step ? 8 : mask, unproven, dense);
-    if (dense && p.T < dense_from(p, mask)) {
-        dense = false;
-        mc = pass_constants(p, flags, mask, unproven);
-    }
+    const bool dense = B.cls_dev && goes_dense(p, mask, flags, bs_da_step);
+    const ModelConst mc = pass_constants(p, flags, bs_da_step ? 8 : mask, unproven, dense);
     if (dense) {
         uint64_t nrows = 0;
         for (int g = 0; g < 4; ++g) nrows += B.counts[0][g];
@@ -809,7 +812,7 @@ int enqueue_search(const Plan &p, int mask, uint32_t flags, size_t slot, uint64_
                    bool *unproven = nullptr, bool *signalled = nullptr)
 {
     Bufs b;
-    int rc = state_bufs(p, slot, b);
+    int rc = state_bufs(p, slot, !goes_dense(p, mask, flags, bs_da_step), b);
     if (rc) return rc;
     b.signalled = signalled;
     return enqueue_search_in(b, p, mask, flags, evaluated, e_limit, build_tables, bs_da_step, unproven);

@@ -68,3 +68,17 @@ def test_a_search_longer_than_the_host_looks_for():
     for a, b in zip(*(M.mmee_chain_search_multi(c, h, [0, 1, 2, 3], f) for f in (M.SEARCH_EXHAUSTIVE, M.SEARCH_PRUNED))):
         assert bytes(a.best) + bytes(a.cost) == bytes(b.best) + bytes(b.cost)
         assert 0 < a.kernel_seconds < a.seconds
+
+
+def test_a_large_search_takes_no_memory_per_tiling():
+    """102 400 tilings: the tables of the searches that keep them in memory are 2 KiB a tiling."""
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_2604_03446_amd as M
+    small, large = (dict(batch=1, I=n, K=80, L=n, J=80, word_bytes=2, tiling_mode=1, c_softmax=10) for n in (1, 3000))
+    M.mmee_shutdown()
+    M.mmee_chain_search_multi(small, H, [0], M.SEARCH_EXHAUSTIVE)
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    M.mmee_chain_search_multi(large, dict(H, gb_bytes=64 << 10), [0], M.SEARCH_EXHAUSTIVE)
+    assert free - torch.cuda.mem_get_info()[0] < 32 << 20
