@@ -616,7 +616,9 @@ __global__ __launch_bounds__(DENSE_THREADS, 4) void k_search_dense(DenseArgs a)
                     const double a2 = lo(wa), b2 = lo(wb), d2 = lo(wd), e2 = lo(w_e), c2 = lo(wc);
                     const double bs1 = (a2 + b2) + (c2 + ((code / 25u ? d2 : 0.0) + (pE ? e2 : 0.0)));
                     const double bs2 = (c2 + (d2 + e2)) + ((code % 5u ? a2 : 0.0) + (code / 5u % 5u ? b2 : 0.0));
-                    // (the very sum of the loop, also where a total taken on trust is not exact)
+                    // The very sum of the loop, also where a total taken on trust is not exact (E_SUMS).  With one p_D value a step the loop
+                    // adds the same words in another order, which is the same sum as long as they are whole.
+                    static_assert(WORDS || ROWS_PER_STEP == 5, "shares that are not exact are summed as in the loop");
                     const double ab = hi(wa) + hi(wb), de = hi(wc) + (hi(wd) + hi(w_e)), traffic2 = ab + de;
                     bool ok2 = fmax(bs1, bs2) <= cap;
                     double dram2 = 0.0, en2 = traffic2, l2 = traffic2;
