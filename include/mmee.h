@@ -104,8 +104,11 @@ typedef struct mmee_result {
                                    buffer capacity, which costs +inf; over the surviving rows also those
                                    of a tiling that move more DRAM words than another one that fits) */
     double seconds;             /* host wall time of the call (upload, kernels, readback)  */
-    double kernel_seconds;      /* device time of the search's kernels (HIP events; one pruned
-                                   search or front by itself: the device's clock)          */
+    double kernel_seconds;      /* device time of the search's kernels: by HIP events (start of the first
+                                   to end of the last launch), or, where a call of one problem ends
+                                   without events, by the device's clock from the first block to the last
+                                   record (most pruned and most exhaustive searches of one problem, fronts
+                                   over the surviving rows): some microseconds less          */
 } mmee_result;
 
 /* Counts of the offline stage (Sec. VI-B): loop-order x buffering-level rows per

@@ -149,7 +149,7 @@ struct Bufs {
     Key *partials = nullptr;
     size_t partials_cap = 0;                    // blocks the partial records have room for
     uint32_t *ticket = nullptr;                 // [0] finish ticket, [1] work counter
-    unsigned long long *hints = nullptr;        // [N_OBJ] launch-wide lowest values of the dense kernel; null: not shared
+    unsigned long long *hints = nullptr;        // [N_OBJ] launch-wide lowest values of the dense kernel, there where cls_dev is
     Key *key_dev = nullptr;
     FinalRecord *final_dev = nullptr;           // device address of this pass's N_OBJ records
     DivTable *dv_dev = nullptr;                 // this pass's copy of the divisor lists
