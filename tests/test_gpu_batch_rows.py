@@ -11,7 +11,7 @@ SHAPES = [dict(I=96, K=60, L=96, J=60),                      # 20736 tilings, 32
 
 
 @pytest.mark.parametrize("shape", SHAPES)
-@pytest.mark.parametrize("hw", [dict(), dict(gb_bytes=1 << 40, e_dram=171.3), dict(gb_bytes=24), dict(gb_bytes=8), dict(dram_bw=60.0, gb_bw=100.0, n_arrays=3, e_gb=5.7)])
+@pytest.mark.parametrize("hw", [dict(), dict(gb_bytes=1 << 40, e_dram=171.3), dict(gb_bytes=24), dict(gb_bytes=4), dict(dram_bw=60.0, gb_bw=100.0, n_arrays=3, e_gb=5.7)])
 def test_straight_line_rows(shape, hw):
     import torch
     assert torch.cuda.is_available(), "GPU tests need a GPU"
@@ -20,9 +20,9 @@ def test_straight_line_rows(shape, hw):
     for keys in ([0], [1], [2], [3], [0, 1]):
         got, codes = M.mmee_chain_search_many([(c, h, o) for o in keys], M.SEARCH_PRUNED)
         want, want_codes = M.mmee_chain_search_many([(c, h, o) for o in keys], M.SEARCH_EXHAUSTIVE)
-        assert codes == want_codes, keys
-        for g, w, code in zip(got, want, codes):
-            assert code or bytes(g.best) + bytes(g.cost) == bytes(w.best) + bytes(w.cost), keys
+        assert codes == want_codes == [M.ENOFEASIBLE if h.gb_bytes < 6 else M.OK] * len(keys), keys      # (the smallest mapping takes three words)
+        for g, w in zip(got, want):
+            assert bytes(g.best) + bytes(g.cost) == bytes(w.best) + bytes(w.cost), keys
 
 
 def test_a_batch_of_small_problems():

@@ -14,7 +14,7 @@ H = dict(pe_rows=4, pe_cols=3, n_arrays=1, rf_bytes=24, gb_bytes=4000, e_dram=20
 # tilings: 1, 36, 64, 81 (a chunk and 17), 128 (two), 192, 225, 192
 @pytest.mark.parametrize("I, K, L, J, mode", [(1, 1, 1, 1, 0), (4, 8, 4, 1, 0), (8, 8, 2, 2, 0), (36, 1, 36, 1, 1), (8, 8, 8, 2, 0), (2, 128, 32, 2, 0),
                                               (16, 4, 16, 4, 0), (12, 6, 2, 6, 1)])
-@pytest.mark.parametrize("gb", [300, 4000, 1 << 40])
+@pytest.mark.parametrize("gb", [4, 300, 4000, 1 << 40])       # 4: two words, which no mapping fits
 def test_chunks_against_the_oracle(I, K, L, J, mode, gb):
     import torch
     assert torch.cuda.is_available(), "GPU tests need a GPU"
@@ -24,6 +24,9 @@ def test_chunks_against_the_oracle(I, K, L, J, mode, gb):
     rc, idx, cost, _, _ = O.search_all(O.workload(c), O.hw(h))
     for keys in ([0], [1], [2], [3], [0, 1], [1, 3]):
         if rc:
+            results, codes = M.mmee_chain_search_many([(c, h, o) for o in keys], M.SEARCH_EXHAUSTIVE)
+            assert rc == M.ENOFEASIBLE and codes == [rc] * len(keys), keys
+            assert all(r.cost.valid == 0 and r.best.idx == 2**64 - 1 and r.cost.energy_pj == r.cost.latency_cycles == float("inf") for r in results), keys
             continue
         for o, got in zip(keys, M.mmee_chain_search_multi(c, h, keys, M.SEARCH_EXHAUSTIVE)):
             assert got.best.idx == idx[o], (keys, o)

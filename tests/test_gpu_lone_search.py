@@ -15,7 +15,7 @@ HW = dict(pe_rows=24, pe_cols=9, n_arrays=1, rf_bytes=200, gb_bytes=30000, e_dra
 # tilings: 1, 36, 64 (a chunk), 81, 8100 (127 chunks, the last of 36), 8192 (128), 8640 (135), 16384 (256), 32768 (512), 33280 (520)
 @pytest.mark.parametrize("I, K, L, J", [(1, 1, 1, 1), (4, 8, 4, 1), (8, 8, 2, 2), (36, 1, 36, 1), (36, 48, 48, 36), (120, 24, 24, 24), (60, 60, 60, 16),
                                         (120, 24, 120, 24), (120, 120, 120, 24), (120, 120, 4096, 48)])
-@pytest.mark.parametrize("hw", [dict(), dict(gb_bytes=1 << 40, e_dram=171.3), dict(gb_bytes=24), dict(gb_bytes=8),
+@pytest.mark.parametrize("hw", [dict(), dict(gb_bytes=1 << 40, e_dram=171.3), dict(gb_bytes=24), dict(gb_bytes=8), dict(gb_bytes=4), dict(gb_bytes=0),
                                 dict(e_dram=0.0, e_gb=0.0, e_rf=0.0, e_mac=0.0, dram_bw=0.0, gb_bw=0.0)])
 def test_one_problem(I, K, L, J, hw):
     import torch
@@ -26,9 +26,9 @@ def test_one_problem(I, K, L, J, hw):
         want, codes = M.mmee_chain_search_many([(c, h, o) for o in keys], M.SEARCH_EXHAUSTIVE)
         for _ in range(2):
             got, got_codes = M.mmee_chain_search_many([(c, h, o) for o in keys], M.SEARCH_PRUNED)
-            assert got_codes == codes, keys
-            for g, w, code in zip(got, want, codes):
-                assert code or bytes(g.best) + bytes(g.cost) == bytes(w.best) + bytes(w.cost), keys
+            assert got_codes == codes == [M.ENOFEASIBLE if h.gb_bytes < 6 else M.OK] * len(keys), keys      # (the smallest mapping takes three words)
+            for g, w in zip(got, want):
+                assert bytes(g.best) + bytes(g.cost) == bytes(w.best) + bytes(w.cost), keys
 
 
 def test_calls_without_allocation_in_turn_with_others():

@@ -59,8 +59,12 @@ def test_noalloc_every_key_and_row_set(M):
 
 def test_noalloc_infeasible_and_too_big(M):
     cfg = CONFIGS["tiny"]
-    got = run_noalloc(M, cfg["workload"], dict(cfg["hw"], gb_bytes=4), M.OBJ_LATENCY, M.SEARCH_PRUNED)
-    assert got.cost.valid == 0
+    for gb in (0, 4):                                        # no and two words: the smallest mapping takes three
+        for flags in (M.SEARCH_PRUNED, M.SEARCH_EXHAUSTIVE):
+            for obj in range(4):
+                got = run_noalloc(M, cfg["workload"], dict(cfg["hw"], gb_bytes=gb), obj, flags)
+                assert got.cost.valid == 0 and got.best.idx == 2**64 - 1, (gb, flags, obj)
+                assert got.cost.energy_pj == got.cost.latency_cycles == float("inf"), (gb, flags, obj)
     # 240 * 240 tilings: beyond the fixed scratch, refused before anything is enqueued
     w = dict(B=1, H=1, N=720720, d=1, word_bytes=2, tiling_mode=1, c_softmax=10)
     with pytest.raises(M.MmeeError) as e:
