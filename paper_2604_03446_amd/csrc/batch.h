@@ -95,8 +95,8 @@ __device__ __forceinline__ void batch_tables(const BatchArgs &a, const BatchProb
 // The least traffic (B*H * Eq. (7)) of piece PIECE's rows that fit, for the tiling whose table column is `col`; +inf: none does.
 // Straight-line code: the entries' places are immediate offsets of the LDS reads.  In a loop every row waited for its
 // offsets (a scalar load) and then for its entries, 330 cycles a row, more than half of a chunk's time, whatever the
-// number of reads (1050 instead of 2160 per tiling in a loop gained 2 %).  Kernels, us, loop -> here: 1600 chunks, energy
-// 48 -> 35, energy and latency 71 -> 59; 20736 chunks 356 -> 239 and 452 -> 331.  Rows come in runs with common entries of D, E and C (rows.h); a row compares its entries of A and B with what
+// number of reads (1050 instead of 2160 per tiling in a loop gained 2 %).  Kernels, us, loop -> this, with the fold of then: 1600 chunks, energy
+// 48 -> 35, energy and latency 71 -> 59 (with the fold as it is 27 and 47); 20736 chunks 356 -> 239 and 452 -> 331.  Rows come in runs with common entries of D, E and C (rows.h); a row compares its entries of A and B with what
 // the run leaves of the capacity: Eq. (1), (2), (4), whole numbers, so exact in any order.
 template <uint32_t SPLIT, int RUN, int ROW, int... I>
 __device__ __forceinline__ void run_least(const char *col, double cap, double &least, std::integer_sequence<int, I...>)
@@ -166,7 +166,7 @@ __global__ __launch_bounds__(BATCH_THREADS, 4) void k_search_batch(BatchArgs a)
     const double inf = pos_inf();
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // (0.8 us less of a block with one chunk, 7 us)  So are the rows that a position may be recovered from asked for.
+    // the arguments' lines and the rows that a position may be recovered from, all asked for at the start (0.8 us of a one-chunk block's 7)
     if (wave == BATCH_WAVES - 1) ask_for_arguments<BatchArgs>(lane);
     static_assert(KEPT_ALL <= BATCH_THREADS, "a thread per row");
     if (threadIdx.x < KEPT_ALL) {
@@ -378,6 +378,11 @@ __global__ __launch_bounds__(BATCH_THREADS, 4) void k_search_batch(BatchArgs a)
             // Only minima were kept; the position is recovered where it can matter, which is long: by the waves that hold the lowest value
             // the block has met so far in the lowest class of candidates -- they meet for it, once for the value and once for the class
             // (1600 chunks, two keys: 57 us from the first block to the last record, now 45).
+            // What only a recovered position reads, the nine combinations' constants, the compiler stores to scratch once an item where two keys,
+            // the pair or the product are held: 25, 20 and 10 registers at most.  Formed again instead, for the one combination or for
+            // all nine at either meeting, it costs more than it saves wherever a block has several items (us a call as it is / one / nine:
+            // 40 shapes, 5568 chunks, energy and latency 158 / 164 / 168, energy, where nothing is stored, 124 / 130 / 132; 1600 chunks, energy and
+            // latency 53.2 / 54.1 / 55.3) and saves up to 5 % where it has one (484 chunks 31.2 / 30.9 / 29.5).
             double own_p[N_OBJ], own_s[N_OBJ];
             uint32_t own_c[N_OBJ], own_code[N_OBJ];
 #pragma unroll

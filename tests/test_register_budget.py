@@ -1,6 +1,7 @@
-"""What the compiler made of k_search_dense's registers, read from the metadata of the library that is built here: at most
-128 for two blocks per CU, and the row loop's values held in them.  A variant that keeps one double too many per p_D
-value spills 8 to 15 registers, and the shortest launches get a quarter slower."""
+"""What the compiler made of the searches' registers, read from the metadata of the library that is built here: at most 128 for two
+blocks per CU.  k_search_dense holds the row loop's values in them: a variant that keeps one double too many per p_D
+value spills 8 to 15, and the shortest launches get a quarter slower.  k_search_batch holds everything with one scalar key other than the
+product; with the others it stores, once an item, what only a recovered position reads."""
 import os
 import re
 import struct
@@ -35,3 +36,14 @@ def test_spills_of_the_dense_kernel():
         regrouped, both = kind == 1, keys != 2 and keys != 1 or bounded or capped
         # one key that needs the energy or the time alone, or a regrouped one: none; constants in order cost a few
         assert k[".vgpr_spill_count"] <= (0 if regrouped or not both else 5), (name, k[".vgpr_spill_count"])
+
+
+@pytest.mark.skipif(not os.path.exists(LIB), reason="the library is not built")
+def test_spills_of_the_batched_kernel():
+    batch = {n: k for n, k in kernels(LIB).items() if "k_search_batch" in n}
+    assert len(batch) == 15
+    for name, k in batch.items():
+        keys = int(re.search(r"k_search_batchILi(\d+)E", name).group(1))
+        assert k[".vgpr_count"] <= 128 and 2 * k[".group_segment_fixed_size"] <= 160 << 10, name
+        # energy, latency: none; both: the nine combinations' constants, 18 doubles, at most; (latency, energy), product: fewer
+        assert k[".vgpr_spill_count"] <= {1: 0, 2: 0, 3: 25, 4: 20, 8: 10}[keys], (name, k[".vgpr_spill_count"])
