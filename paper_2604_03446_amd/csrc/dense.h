@@ -16,8 +16,9 @@
 //
 // Lanes.  A chunk is 64 neighbours in an order of the tilings of its own: k's divisors fastest, then j's, l's, i's.  In attention
 // and in feed-forward layers i and l are the long extents, so the footprints of neighbours differ least, and a row fits all
-// of a wave or nothing of it more often than in index order (12544 tilings of 8192 x 128, buffer 8 MiB: 72 % of the wave-rows
-// run, 97 % of these full, against 83 and 46 % in index order; 10692 tilings of 2048 x 768 x 3072 x 768, 1 MiB: 11.7 % against 13.6 %).
+// of a wave or nothing of it more often than in index order (counted over the whole space: 12544 tilings of 8192 x 128, buffer 8 MiB,
+// 62.7 % of the wave-rows run, 92 % of these full, against 72.1 and 48 % in index order; 10692 tilings of 2048 x 768 x 3072 x 768,
+// 1 MiB, 10.9 %, 40 % of these full, against 12.1 and 10 %).
 //
 // Tables.  Single operands' terms are 41 values a tiling, the nine combinations' constants 40: a block forms them for its
 // chunk straight from the divisor lists, in LDS, and nothing per tiling is in memory.  (Sums of pairs, 123 values,

@@ -1178,13 +1178,11 @@ void pruned_slices(const std::vector<PrunedEntry> &entries, std::vector<uint32_t
 // Sharing from four problems a group on whatever their size cost up to 208 % (64 problems of one chunk, energy: 118
 // us, 68 in batches), never sharing up to 270 % (64 problems of 324 chunks, energy: 475 us, 126 shared).  A pass of its
 // own costs 33 us a problem of one chunk and 105 us at 324 chunks (energy, latency and energy-delay product).
-// These figures and the constants are of the kernels of the fit.  Since then a round of k_search_batch takes 6 to 8 us instead
-// of 9 to 11 where every chunk has a block to itself (at most 256 chunks in a launch run the same rows as then), a block of
-// k_search_pruned 62 us instead of 88.  Both ways of 815 calls with the kernels as they are (2 to 640 problems on 1 to 40 shapes of 1
-// to 324 chunks): with a group of four problems or more the choice costs 1.2 % over the better way on average and 10 % or more in
-// 22 of 549 calls (32 problems on each of two shapes of 3 and 7 chunks, energy-delay product: 86 us in batches, 163 shared).  Of
-// the 266 calls without such a group, which stay in batches whatever the estimates say (none_large), 108 would be 10 % or more
-// faster shared (three problems on each of four shapes of 25 to 31 chunks, energy: 101 us, 44 shared).
+// These figures and the constants are of the kernels of the fit.  Both ways of 600 calls with the kernels as they are (2 to 640 problems on 1 to
+// 16 shapes of 1 to 324 chunks): with a group of four problems or more the choice costs 1.6 % over the better way on average and 10 %
+// or more in 19 of 413 calls (32 problems on one shape of 105 chunks, 16 capacities, latency: 103 us in batches, 146 shared).  Of the 187 calls
+// without such a group, which stay in batches whatever the estimates say (none_large), 74 would be 10 % or more faster shared (three
+// problems on each of eight shapes of 28 to 100 chunks, energy and latency: 82 us, 58 shared).
 void keep_shared(const std::vector<PrunedEntry> &entries, const std::vector<uint32_t> &order, std::vector<PrunedSlice> &slices)
 {
     struct Batches {                         // chunks, and kinds of kernel: each is a launch of its own
