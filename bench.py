@@ -49,10 +49,10 @@ HBM_PEAK_GBS = 8000.0
 # HBM bytes per launch from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (summaries under profiles/), scaled by
 # what the same counters read for a 1 GiB device-to-device copy (x2.0 and x1.0).  Valid only for the kernel
 # sources they were taken with: any change to the sources turns "traffic" into null.
-COUNTERS_TAKEN_WITH = "62b4c2a21c8e8038271abb25dba0c916065628315d1264d5d1100765c2fd9c23"
+COUNTERS_TAKEN_WITH = "58963f86fde51bcd20c8c58c1d65d171aee06e66700844b44cf740abc76eca08"
 TRAFFIC = {"k_search_dense_long": (2 * 265.0 + 161.0) * 1024.0,      # FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0, KiB per dispatch
            "k_search_dense_bert": (2 * 258.0 + 196.0) * 1024.0,
-           "k_eval_batch": (2 * 19957.0 + 4195190.0) * 1024.0}
+           "k_eval_batch": (2 * 19966.0 + 4195062.0) * 1024.0}
 TRAFFIC_SOURCE = {"k_search_dense_long": "profiles/k_search_dense_long.md", "k_search_dense_bert": "profiles/k_search_dense_bert.md",
                   "k_eval_batch": "profiles/k_eval_batch_bert.md"}
 
